@@ -109,6 +109,9 @@ constexpr int gP2 = gP1 + 4 * kH * 4; // [4][k][2] dW3, db2 per entry tile
 constexpr int gAct = gP2 + 4 * kH * 2;  // [8] ints: tile of the screened group has an entry inside
 constexpr int gEnd = gAct + 8;
 constexpr int kGroup = kGT / kTE;     // tiles screened together, one per wave
+__host__ __device__ inline int64_t tile_groups(int64_t total) {
+  return (total + kTE * kGroup - 1) / (kTE * kGroup);
+}
 // then doubles: per entry r, dL/dw, d - theta, theta; per neuron the fp64
 // sums dW1 (3), db1, db2, dW3; dB3
 constexpr int dR = 0, dG = kTE, dDM = 2 * kTE, dTH = 3 * kTE, dRow = 4 * kTE,
@@ -180,19 +183,26 @@ __device__ __noinline__ bool tile_entry(float* L, double* Ld, int e, int64_t ent
   return inside;
 }
 
-// Screening of the group of kGroup tiles from tile t0: thread tid takes
-// entry t0 kTE + tid (wave w = tile t0 + w) and the wave's ballot records
-// whether its tile has an entry inside the window.  Without a Jacobi target
+// Screening of the group of kGroup tiles gr, gr + ngroups, gr + 2 ngroups,
+// ...: wave w takes tile gr + w ngroups, one entry per lane, and its ballot
+// records whether the tile has an entry inside the window.  The tiles of a
+// group lie far apart because the entries inside the window are often
+// neighbours (a diagonal that rises along the matrix): with groups of
+// neighbouring tiles, n = 2e5 and 8 columns left the 650 active tiles of
+// 25000 to 81 of 256 workgroups, eight in series each (k_mlp_apply 189 us,
+// k_mlp_grad 424 us); apart, no workgroup has more than three (138 us,
+// 301 us).  Without a Jacobi target
 // (J == nullptr) that is all; with one, the entries of tiles with none
 // inside take the guarded Jacobi step there (the learned step with c = 0).
 // The caller syncs before reading the flags.
 template <typename T>
-__device__ __forceinline__ void screen_group(float* L, int64_t t0, int64_t total, int nact,
+__device__ __forceinline__ void screen_group(float* L, int64_t gr, int64_t ngroups, int64_t total,
+                                             int nact,
                                              const double* __restrict__ diag,
                                              const double* __restrict__ rho,
                                              const double* __restrict__ theta, T* __restrict__ J,
                                              int64_t ld) {
-  const int64_t ent = t0 * kTE + threadIdx.x;
+  const int64_t ent = (gr + (int64_t)(threadIdx.x >> 6) * ngroups) * kTE + (threadIdx.x & 63);
   const bool valid = ent < total;
   int64_t row = 0;
   int col = 0;
@@ -288,12 +298,12 @@ __global__ __launch_bounds__(kGT) void k_mlp_apply(T* __restrict__ R, int64_t ld
   const double s = *sptr;
   const int tid = threadIdx.x;
   const int64_t total = n * nact;
-  const int64_t ntiles = (total + kTE - 1) / kTE;
-  for (int64_t t0 = (int64_t)blockIdx.x * kGroup; t0 < ntiles; t0 += (int64_t)gridDim.x * kGroup) {
+  const int64_t ngroups = tile_groups(total);
+  for (int64_t gr = blockIdx.x; gr < ngroups; gr += gridDim.x) {
     __syncthreads();  // previous group's flag reads done
     // the net only matters inside the window: tiles without such entries
     // take the Jacobi step here and skip it
-    screen_group(L, t0, total, nact, diag, rho, theta, R, ld);
+    screen_group(L, gr, ngroups, total, nact, diag, rho, theta, R, ld);
     __syncthreads();
     for (int u = 0; u < kGroup; ++u) {
       if (reinterpret_cast<const int*>(L + gAct)[u] == 0) continue;  // uniform in the workgroup
@@ -301,7 +311,7 @@ __global__ __launch_bounds__(kGT) void k_mlp_apply(T* __restrict__ R, int64_t ld
       int lid = tid;
       asm volatile("" : "+v"(lid));
       const int w = lid >> 6, c = lid & 15, g = (lid >> 4) & 3;
-      const int64_t ent = (t0 + u) * kTE + tid;
+      const int64_t ent = (gr + u * ngroups) * kTE + tid;
       bool inside = false;
       __syncthreads();  // weights loaded / previous tile's LDS reads done
       if (tid < kTE)
@@ -360,20 +370,20 @@ __global__ __launch_bounds__(kGT) void k_mlp_grad(const double* __restrict__ R,
   for (int idx = tid; idx < 6 * kH + 2; idx += kGT) Ld[dRow + idx] = 0.0;
   const double s = *sptr;
   const int64_t total = n * nact;
-  const int64_t ntiles = (total + kTE - 1) / kTE;
+  const int64_t ngroups = tile_groups(total);
   double aW2[8][4];  // dW2[k = 16 w + 4 g + r][j = 16 t + c]
 #pragma unroll
   for (int t = 0; t < 8; ++t)
 #pragma unroll
     for (int r = 0; r < 4; ++r) aW2[t][r] = 0.0;
-  for (int64_t t0 = (int64_t)blockIdx.x * kGroup; t0 < ntiles; t0 += (int64_t)gridDim.x * kGroup) {
+  for (int64_t gr = blockIdx.x; gr < ngroups; gr += gridDim.x) {
     __syncthreads();  // previous group's flag reads done
     // entries outside the window have dL/dy = 0: tiles without any inside are skipped
-    screen_group<double>(L, t0, total, nact, diag, rho, theta, nullptr, 0);
+    screen_group<double>(L, gr, ngroups, total, nact, diag, rho, theta, nullptr, 0);
     __syncthreads();
     for (int u = 0; u < kGroup; ++u) {
       if (reinterpret_cast<const int*>(L + gAct)[u] == 0) continue;  // uniform in the workgroup
-      const int64_t tile = t0 + u;
+      const int64_t tile = gr + u * ngroups;
       // the lane indices are re-derived per tile, opaque to the compiler: the
       // swizzled LDS addresses built from them are recomputed inside the loop
       // instead of being hoisted into (and spilled from) registers
@@ -661,20 +671,21 @@ __global__ __launch_bounds__(256, 2) void k_mlp_apply_bf16(T* __restrict__ R, in
   // the super tiles (kSE entries) that k_mlp_screen flagged as holding
   // entries inside the window, each taken as kSE / E tiles
   constexpr int kSE = kMlpSuper, kTS = kSE / E;
-  // wave w takes super tiles w, w + nw, w + 2 nw, ...: their flags are read
-  // 64 at a time (one per lane) and the flagged ones processed in order
-  const int64_t nst = (total + kSE - 1) / kSE;
+  // wave w takes tiles w, w + nw, w + 2 nw, ...: the flags of their super
+  // tiles are read 64 at a time (one per lane) and the flagged ones processed
+  // in order.  Neighbouring tiles go to different waves because flagged super
+  // tiles are often neighbours too: at n = 2e5 with 12 columns a whole super
+  // tile per wave left 250 of 2048 waves with all the work, eight tiles in
+  // series (50 us; one tile at a time 32 us).
   const int64_t gw = (int64_t)blockIdx.x * 4 + wave, nw = (int64_t)gridDim.x * 4;
-  for (int64_t jb = 0; gw + jb * nw < nst; jb += 64) {
+  for (int64_t jb = 0; gw + jb * nw < nwt; jb += 64) {
     const int64_t mine = gw + (jb + lane) * nw;
-    uint64_t pend = __ballot(mine < nst && tflags[mine] != 0);
+    uint64_t pend = __ballot(mine < nwt && tflags[mine / kTS] != 0);
     while (pend != 0) {
       const int bit = __builtin_ctzll(pend);
       pend &= pend - 1;
-      const int64_t st = gw + (jb + bit) * nw;
-      for (int u = 0; u < kTS; ++u) {
-        const int64_t wt = st * kTS + u;
-        if (wt >= nwt) break;
+      {
+        const int64_t wt = gw + (jb + bit) * nw;
         // keep the weight reads inside the loop (LDS re-reads are cheap; holding
         // every fragment in registers for the whole kernel would cap occupancy)
         asm volatile("" ::: "memory");
@@ -788,12 +799,29 @@ __global__ __launch_bounds__(256, 2) void k_mlp_apply_bf16(T* __restrict__ R, in
   }
 }
 
-__global__ void k_grad_reduce(const double* __restrict__ part, int nblk, double* __restrict__ g) {
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= kMlpParams) return;
+// Sum of the workgroup partials per parameter, in a fixed order: a workgroup
+// takes kRedP parameters, thread (slice, parameter) adds the partials
+// b = slice, slice + 8, ... in order, then the slices are added in order.
+// (One thread per parameter walked its 256 partials in one chain on 68
+// workgroups: 65 us for 35 MB, now 9.5 us.)
+constexpr int kRedP = 32;
+__global__ __launch_bounds__(256) void k_grad_reduce(const double* __restrict__ part, int nblk,
+                                                     double* __restrict__ g) {
+  __shared__ double red[8][kRedP];
+  const int p = threadIdx.x & (kRedP - 1), sl = threadIdx.x / kRedP;
+  const int idx = blockIdx.x * kRedP + p;
   double s = 0.0;
-  for (int b = 0; b < nblk; ++b) s += part[(size_t)b * kMlpParams + idx];
-  g[idx] = s;
+  if (idx < kMlpParams) {
+#pragma unroll 8
+    for (int b = sl; b < nblk; b += 8) s += part[(size_t)b * kMlpParams + idx];
+  }
+  red[sl][p] = s;
+  __syncthreads();
+  if (sl == 0 && idx < kMlpParams) {
+    double t = red[0][p];
+    for (int k = 1; k < 8; ++k) t += red[k][p];
+    g[idx] = t;
+  }
 }
 
 __global__ void k_adam(float* __restrict__ w, float* __restrict__ m, float* __restrict__ v,
@@ -871,8 +899,7 @@ inline int cdiv64(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 
 // workgroups of the fp32 tile kernels: one per group of kGroup tiles, at most kMlpBlocks
 int mlp_grid(int64_t total) {
-  const int64_t groups = (total + kTE * kGroup - 1) / (kTE * kGroup);
-  return (int)std::min<int64_t>(groups, kMlpBlocks);
+  return (int)std::min<int64_t>(tile_groups(total), kMlpBlocks);
 }
 
 }  // namespace
@@ -956,7 +983,7 @@ hipError_t mlp_grad(const double* R, const double* G, int64_t ld, int nact, int6
   if (grid > 0)
     hipLaunchKernelGGL(k_mlp_grad, dim3(grid), dim3(kGT), kTileBytes, st, R, G, ld, nact, n,
                        theta, diag, rho, s, w, part);
-  hipLaunchKernelGGL(k_grad_reduce, dim3(cdiv64(kMlpParams, 256)), dim3(256), 0, st, part, grid,
+  hipLaunchKernelGGL(k_grad_reduce, dim3(cdiv64(kMlpParams, kRedP)), dim3(256), 0, st, part, grid,
                      grad);
   return hipGetLastError();
 }
