@@ -207,13 +207,12 @@ hipError_t gen_lt_inv(const double* L, int p, double* out, hipStream_t s);
 hipError_t vec_max_abs(const double* x, int64_t len, double* part, double* out, hipStream_t s);
 
 // ---- tridiagonal preconditioner (k_tri.hip) ------------------------------
-constexpr int kTriMaxChunks = 1024;
-// Chunks of the partition method for order n (balanced, >= 64 rows each).
-int tri_chunks(int64_t n);
+constexpr int kTriMaxChunks = 1024;  // groups of rows whose interfaces bnd and xb hold
 // In place: R[:, 0:nact] (ld) <- T_j^-1 R[:, j], T_j = tridiag(e, t, e) with
 // t_i = max(|d_i - theta_j|, off_i + delta_j).  e: n values (e[n-1] = 0),
 // off_i = |e_{i-1}| + |e_i|; bnd: 6 kTriMaxChunks nact doubles, xb: 2
-// kTriMaxChunks nact doubles; scr: n nact doubles.
+// kTriMaxChunks nact doubles; scr: n nact doubles (used for n beyond
+// 256 kTriMaxChunks).
 hipError_t tri_apply_f64(double* R, int64_t ld, int nact, int64_t n, const double* theta,
                          const double* d, const double* e, const double* off, double* bnd,
                          double* xb, double* scr, hipStream_t s);

@@ -7,265 +7,385 @@
 // symmetric and strictly diagonally dominant with a positive diagonal, so
 // elimination without pivoting is stable.
 //
-// Partition method over P balanced chunks [s_c, e_c) of at least 64 rows:
-//   k_tri_bound   thread (c, j): an LU sweep down and a UL sweep up over the
-//                 chunk give its first and last unknowns as affine functions
-//                 of the two unknowns just outside it,
-//                   x_i = y_i + v_i x_{s-1} + w_i x_e   (i = s, e - 1);
-//   k_tri_reduced workgroup j: the 2P boundary unknowns b_c = (x_s, x_{e-1})
-//                 form a block tridiagonal system with 2 x 2 blocks, solved
-//                 by block Thomas in LDS;
-//   k_tri_final   thread (c, j): the chunk's own system with the neighbours'
-//                 boundary values on the right-hand side, by Thomas (the
-//                 forward factors kept in `scr`, n x nact fp64, the forward
-//                 right-hand side in R itself).
-// Every sum and factor is fp64; in the fp32 phase R is read and written in
-// fp32.
+// Partition method.  A run of rows is described by its interface, its first
+// and last unknowns as affine functions of the two just outside it,
+//   x_first = ys + vs x_left + ws x_right,  x_last = ye + ve x_left + we x_right,
+// and the interfaces of two neighbouring runs give the one of both (Iface,
+// merge).  A thread takes a chunk of L rows of one column, a workgroup a group
+// of 256 / CW neighbouring chunks:
+//   k_tri_rows<false>  a UL and an LU sweep over the chunk give its interface;
+//                      the chunks' are merged to the group's (across lanes,
+//                      then across the waves through LDS);
+//   k_tri_top          workgroup j: the groups' interfaces are merged up a tree
+//                      in LDS, the values beside each group come down again;
+//   k_tri_rows<true>   the same sweeps, with the factors kept in registers;
+//                      the values beside the group come down the same merges
+//                      to each chunk, which is then solved in registers.
+// Every sum and factor is fp64, whatever R holds.
+//
+// R is read twice and written once (n = 1e6, 16 columns: 384 MB, part of the
+// second read from the last-level cache): 47 + 10 + 67 us there, bound by the
+// rows' loads and the sweeps behind them, which overlap only across the two to
+// four workgroups of a CU.  With 1024 chunks of 977 rows the sweeps were 16 k
+// serial chains of divisions over strided rows, R passed memory five times and
+// one thread per column ran through the 1024 chunks: 400 + 210 + 420 us.
 #include <algorithm>
 
 #include "internal.h"
 
 namespace lobpcg {
 
-__device__ __forceinline__ void chunk_bounds(int64_t n, int P, int c, int64_t* s, int64_t* e) {
-  *s = (int64_t)c * n / P;
-  *e = (int64_t)(c + 1) * n / P;
+namespace {
+
+typedef double dd2 __attribute__((ext_vector_type(2)));
+
+struct Iface {
+  double ys, vs, ws, ye, ve, we;
+};
+
+// The unknowns a (last of the left run) and b (first of the right run) at the
+// seam of two runs, as functions of the unknowns outside both.
+struct Seam {
+  double a0, al, ar, b0, bl, br;
+};
+
+// 1 / q to 1 ulp: the hardware estimate and two Newton steps
+__device__ __forceinline__ double rcp2(double q) {
+  double r = __builtin_amdgcn_rcp(q);
+  r = fma(r, fma(-q, r, 1.0), r);
+  return fma(r, fma(-q, r, 1.0), r);
 }
 
-__device__ __forceinline__ double tri_diag(double d, double th, double off, double delta) {
-  return fmax(fabs(d - th), off + delta);
+// A, B: neighbouring runs; returns the interface of both
+__device__ __forceinline__ Iface merge(const Iface& A, const Iface& B, Seam& s) {
+  const double k = rcp2(fma(-A.we, B.vs, 1.0));
+  s.a0 = fma(A.we, B.ys, A.ye) * k;
+  s.al = A.ve * k;
+  s.ar = A.we * B.ws * k;
+  s.b0 = fma(B.vs, s.a0, B.ys);
+  s.bl = B.vs * s.al;
+  s.br = fma(B.vs, s.ar, B.ws);
+  Iface o;
+  o.ys = fma(A.ws, s.b0, A.ys);
+  o.vs = fma(A.ws, s.bl, A.vs);
+  o.ws = A.ws * s.br;
+  o.ye = fma(B.ve, s.a0, B.ye);
+  o.ve = B.ve * s.al;
+  o.we = fma(B.ve, s.ar, B.we);
+  return o;
 }
 
-// Operands of row i for column j, loaded kU rows ahead of the dependent
-// recurrences (every sweep is latency-bound on its divisions; the loads are
-// not).
-constexpr int kU = 8;
+// the values (left, right) outside a pair of runs become those outside one of
+// them: the right run's when `right`, else the left one's
+__device__ __forceinline__ void descend(const Seam& s, bool right, double& xl, double& xr) {
+  const double a = fma(s.ar, xr, fma(s.al, xl, s.a0));
+  const double b = fma(s.br, xr, fma(s.bl, xl, s.b0));
+  if (right) xl = a;
+  else xr = b;
+}
 
-// bnd[(c * nact + j) * 6 + {0..5}] = y_s, v_s, w_s, y_e, v_e, w_e
-template <typename T>
-__global__ __launch_bounds__(256) void k_tri_bound(const T* __restrict__ R, int64_t ld, int nact,
-                                                   int64_t n, int P, const double* __restrict__ theta,
-                                                   const double* __restrict__ d,
-                                                   const double* __restrict__ e,
-                                                   const double* __restrict__ off,
-                                                   double* __restrict__ bnd) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= P * nact) return;
-  const int c = t / nact, j = t - c * nact;
-  int64_t s, en;
-  chunk_bounds(n, P, c, &s, &en);
-  const double th = theta[j];
+// the lower and the upper lane's value of the pair (lane, lane ^ M)
+template <int M>
+__device__ __forceinline__ void lane_pair(double v, bool upper, double& lo, double& hi) {
+  if constexpr (M == 16 || M == 32) {
+    const auto l = (M == 16) ? __builtin_amdgcn_permlane16_swap(__double2loint(v), __double2loint(v), false, false)
+                             : __builtin_amdgcn_permlane32_swap(__double2loint(v), __double2loint(v), false, false);
+    const auto h = (M == 16) ? __builtin_amdgcn_permlane16_swap(__double2hiint(v), __double2hiint(v), false, false)
+                             : __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v), false, false);
+    lo = __hiloint2double(h[0], l[0]);
+    hi = __hiloint2double(h[1], l[1]);
+  } else {
+    const double o = __shfl_xor(v, M);
+    lo = upper ? o : v;
+    hi = upper ? v : o;
+  }
+}
+template <int M>
+__device__ __forceinline__ Iface merge_lanes(const Iface& f, bool upper, Seam& s) {
+  Iface A, B;
+  lane_pair<M>(f.ys, upper, A.ys, B.ys);
+  lane_pair<M>(f.vs, upper, A.vs, B.vs);
+  lane_pair<M>(f.ws, upper, A.ws, B.ws);
+  lane_pair<M>(f.ye, upper, A.ye, B.ye);
+  lane_pair<M>(f.ve, upper, A.ve, B.ve);
+  lane_pair<M>(f.we, upper, A.we, B.we);
+  return merge(A, B, s);
+}
+
+// L rows per chunk, CW columns side by side (nact of them real).  Rows past n
+// continue the system by uncoupled rows with r = 0.
+template <typename T, int L, int CW, bool SOLVE>
+__global__ __launch_bounds__(256, SOLVE ? 2 : 4) void k_tri_rows(T* R, int64_t ld, int nact, int64_t n,
+                                                  const double* __restrict__ theta,
+                                                  const double* __restrict__ d,
+                                                  const double* __restrict__ e,
+                                                  const double* __restrict__ off,
+                                                  double* __restrict__ bnd,
+                                                  const double* __restrict__ xb) {
+  constexpr int NQ = 256 / CW;  // chunks per group
+  constexpr int LP = L + 1;
+  __shared__ dd2 sdo[NQ * LP];      // (d, off) of row u of chunk q at q LP + u (a stride off the banks)
+  __shared__ double se[NQ * LP];    // the coupling of that row to the one above; u = L: below the last
+  __shared__ Iface wf[4][CW];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int j = blockIdx.y * CW + (tid & (CW - 1)), q = tid / CW;
+  const int64_t g = blockIdx.x, r0 = g * (NQ * L);
+  const bool live = j < nact;
+  const int64_t row = r0 + (int64_t)q * L;
+  T* Rj = R + row * ld + (live ? j : 0);
+  double x[L];
+#pragma unroll
+  for (int u = 0; u < L; ++u) x[u] = (live && row + u < n) ? (double)Rj[u * ld] : 0.0;
+  const double th = live ? theta[j] : 0.0;
   const double delta = kPrecondGuard * fmax(1.0, fabs(th));
-  const double a_s = (s > 0) ? e[s - 1] : 0.0;  // coupling to x_{s-1}
-  const double c_e = e[en - 1];                 // coupling to x_e (e[n-1] = 0)
-  // LU sweep down: last-row values
-  double cp = 0.0, ry = 0.0, rv = 0.0, den = 1.0;
-  for (int64_t i0 = s; i0 < en; i0 += kU) {
-    double tt[kU], ea[kU], ec[kU], rr[kU];
-#pragma unroll
-    for (int u = 0; u < kU; ++u) {
-      const int64_t i = min(i0 + u, en - 1);
-      tt[u] = tri_diag(d[i], th, off[i], delta);
-      ea[u] = (i > s) ? e[i - 1] : 0.0;
-      ec[u] = e[i];
-      rr[u] = (double)R[i * ld + j];
-    }
-#pragma unroll
-    for (int u = 0; u < kU; ++u) {
-      if (i0 + u >= en) break;
-      den = tt[u] - ea[u] * cp;
-      const double inv = 1.0 / den;
-      ry = (rr[u] - ea[u] * ry) * inv;
-      rv = ((i0 + u == s ? -a_s : 0.0) - ea[u] * rv) * inv;
-      cp = ec[u] * inv;
-    }
+  for (int i = tid; i < NQ * L; i += 256) {
+    const int64_t r = r0 + i;
+    const int qq = i / L, at = qq * LP + (i - qq * L);
+    sdo[at] = (r < n) ? dd2{d[r], off[r]} : dd2{0.0, 1.0};
+    const double ei = (r > 0 && r <= n) ? e[r - 1] : 0.0;  // (e[n - 1] = 0)
+    se[at] = ei;
+    if (i == qq * L && qq > 0) se[qq * LP - 1] = ei;
   }
-  const double y_e = ry, v_e = rv, w_e = -c_e / den;
-  // UL sweep up: first-row values
-  double ap = 0.0, sy = 0.0, sw = 0.0;
-  den = 1.0;
-  for (int64_t i0 = en - 1; i0 >= s; i0 -= kU) {
-    double tt[kU], ea[kU], ec[kU], rr[kU];
-#pragma unroll
-    for (int u = 0; u < kU; ++u) {
-      const int64_t i = max(i0 - u, s);
-      tt[u] = tri_diag(d[i], th, off[i], delta);
-      ea[u] = (i > 0) ? e[i - 1] : 0.0;
-      ec[u] = (i < en - 1) ? e[i] : 0.0;
-      rr[u] = (double)R[i * ld + j];
-    }
-#pragma unroll
-    for (int u = 0; u < kU; ++u) {
-      if (i0 - u < s) break;
-      den = tt[u] - ec[u] * ap;
-      const double inv = 1.0 / den;
-      sy = (rr[u] - ec[u] * sy) * inv;
-      sw = ((i0 - u == en - 1 ? -c_e : 0.0) - ec[u] * sw) * inv;
-      ap = ea[u] * inv;
-    }
-  }
-  const double y_s = sy, v_s = -a_s / den, w_s = sw;
-  double* o = bnd + (int64_t)t * 6;
-  o[0] = y_s;
-  o[1] = v_s;
-  o[2] = w_s;
-  o[3] = y_e;
-  o[4] = v_e;
-  o[5] = w_e;
-}
-
-// Block Thomas on b_c = (f_c, l_c):
-//   b_c - Lo_c b_{c-1} - Up_c b_{c+1} = y_c,
-//   Lo_c = [[0, v_s], [0, v_e]],  Up_c = [[w_s, 0], [w_e, 0]].
-// One workgroup per column: the column's boundary data are staged in LDS,
-// one thread runs the sequential elimination there, and the solution b_c is
-// written to xb[(c * nact + j) * 2 + {0, 1}].
-__global__ __launch_bounds__(256) void k_tri_reduced(int nact, int P, const double* __restrict__ bnd,
-                                                     double* __restrict__ xb) {
-  extern __shared__ double lds[];  // P * 6 boundary data, then P * 4 factors
-  const int j = blockIdx.x;
-  double* q = lds;
-  double* f = lds + (int64_t)P * 6;
-  for (int idx = threadIdx.x; idx < P * 6; idx += blockDim.x) {
-    const int c = idx / 6, k = idx - c * 6;
-    q[idx] = bnd[((int64_t)c * nact + j) * 6 + k];
+  if (tid == 0) {
+    const int64_t r = r0 + NQ * L;
+    se[NQ * LP - 1] = (r <= n) ? e[r - 1] : 0.0;
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    // G_{c-1} = [[G0, 0], [G1, 0]] (its right column is always 0), g_{c-1}
-    double G0 = 0.0, G1 = 0.0, g0 = 0.0, g1 = 0.0;
-    for (int c = 0; c < P; ++c) {
-      const double* b = q + c * 6;
-      const double ys = b[0], vs = b[1], ws = b[2], ye = b[3], ve = b[4], we = b[5];
-      // S = I - Lo G_{c-1} = [[1 - vs G1, 0], [-ve G1, 1]]
-      const double S00 = 1.0 - vs * G1;
-      const double S10 = -ve * G1;
-      const double i00 = 1.0 / S00;
-      // rhs = y + Lo g_{c-1}
-      const double r0 = ys + vs * g1, r1 = ye + ve * g1;
-      // S^-1 = [[i00, 0], [-S10 i00, 1]]
-      G0 = i00 * ws;
-      G1 = -S10 * i00 * ws + we;
-      g0 = i00 * r0;
-      g1 = -S10 * i00 * r0 + r1;
-      double* o = f + c * 4;
-      o[0] = G0;
-      o[1] = G1;
-      o[2] = g0;
-      o[3] = g1;
+  const dd2* cdo = sdo + q * LP;
+  const double* ce = se + q * LP;
+  const double a_s = ce[0], c_e = ce[L];
+  auto diag = [&](int u) {
+    const dd2 t = cdo[u];
+    return fmax(fabs(t[0] - th), t[1] + delta);
+  };
+  Iface f;
+  {
+    // UL sweep up: the first row
+    double ap = 0.0, sy = 0.0, sw = 0.0, inv = 1.0;
+#pragma unroll
+    for (int u = L - 1; u >= 0; --u) {
+      const double ec = (u == L - 1) ? 0.0 : ce[u + 1];
+      inv = rcp2(fma(-ec, ap, diag(u)));
+      sy = fma(-ec, sy, x[u]) * inv;
+      sw = ((u == L - 1) ? -c_e : -ec * sw) * inv;
+      ap = ce[u] * inv;
     }
-    // back substitution: b_c = g_c + G_c b_{c+1} (b_P = 0); G_c b = G f_{c+1}
-    double bf = 0.0;
-    for (int c = P - 1; c >= 0; --c) {
-      double* o = f + c * 4;
-      const double n0 = o[2] + o[0] * bf;
-      const double n1 = o[3] + o[1] * bf;
-      o[2] = n0;
-      o[3] = n1;
-      bf = n0;
-    }
+    f.ys = sy;
+    f.vs = -a_s * inv;
+    f.ws = sw;
   }
+  // (the diagonal and the couplings are read again: kept in registers they
+  // would cost two of four waves per SIMD)
+  asm volatile("" ::: "memory");
+  double iv[SOLVE ? L : 1];
+  {
+    // LU sweep down: the last row; SOLVE keeps the pivots' reciprocals and
+    // leaves the forward right-hand side in x
+    double cp = 0.0, ry = 0.0, rv = 0.0, inv = 1.0;
+#pragma unroll
+    for (int u = 0; u < L; ++u) {
+      const double ea = (u == 0) ? 0.0 : ce[u];
+      inv = rcp2(fma(-ea, cp, diag(u)));
+      ry = fma(-ea, ry, x[u]) * inv;
+      rv = ((u == 0) ? -a_s : -ea * rv) * inv;
+      cp = ce[u + 1] * inv;
+      if (SOLVE) {
+        iv[u] = inv;
+        x[u] = ry;
+      }
+    }
+    f.ye = ry;
+    f.ve = rv;
+    f.we = -c_e * inv;
+  }
+  // merge the wave's chunks, then the waves'
+  Seam s4, s8, s16, s32, w01, w23, top;
+  if constexpr (CW <= 4) f = merge_lanes<4>(f, (lane & 4) != 0, s4);
+  if constexpr (CW <= 8) f = merge_lanes<8>(f, (lane & 8) != 0, s8);
+  f = merge_lanes<16>(f, (lane & 16) != 0, s16);
+  f = merge_lanes<32>(f, (lane & 32) != 0, s32);
+  if (lane < CW) wf[wave][lane] = f;
   __syncthreads();
-  for (int c = threadIdx.x; c < P; c += blockDim.x) {
-    xb[((int64_t)c * nact + j) * 2 + 0] = f[c * 4 + 2];
-    xb[((int64_t)c * nact + j) * 2 + 1] = f[c * 4 + 3];
+  const int c = tid & (CW - 1);
+  const Iface f01 = merge(wf[0][c], wf[1][c], w01), f23 = merge(wf[2][c], wf[3][c], w23);
+  f = merge(f01, f23, top);
+  if constexpr (!SOLVE) {
+    if (tid < CW && live) {
+      // one run of groups per column and coefficient, as k_tri_top reads them
+      const int64_t P = gridDim.x;
+      double* o = bnd + (int64_t)j * 6 * P + g;
+      o[0] = f.ys;
+      o[P] = f.vs;
+      o[2 * P] = f.ws;
+      o[3 * P] = f.ye;
+      o[4 * P] = f.ve;
+      o[5 * P] = f.we;
+    }
+  } else {
+    // down again to the values beside this chunk
+    const double* xj = xb + (int64_t)j * 2 * gridDim.x + g;
+    double xl = live ? xj[0] : 0.0;
+    double xr = live ? xj[gridDim.x] : 0.0;
+    descend(top, wave >= 2, xl, xr);
+    if (wave >= 2) descend(w23, wave == 3, xl, xr);
+    else descend(w01, wave == 1, xl, xr);
+    descend(s32, (lane & 32) != 0, xl, xr);
+    descend(s16, (lane & 16) != 0, xl, xr);
+    if constexpr (CW <= 8) descend(s8, (lane & 8) != 0, xl, xr);
+    if constexpr (CW <= 4) descend(s4, (lane & 4) != 0, xl, xr);
+    // forward right-hand side with the left neighbour, then back
+    double t = xl;
+#pragma unroll
+    for (int u = 0; u < L; ++u) {
+      t *= -ce[u] * iv[u];
+      x[u] += t;
+    }
+    double y = xr;
+#pragma unroll
+    for (int u = L - 1; u >= 0; --u) {
+      y = fma(-ce[u + 1] * iv[u], y, x[u]);
+      x[u] = y;
+    }
+#pragma unroll
+    for (int u = 0; u < L; ++u)
+      if (live && row + u < n) Rj[u * ld] = (T)x[u];
   }
 }
 
-template <typename T>
-__global__ __launch_bounds__(256) void k_tri_final(T* __restrict__ R, int64_t ld, int nact, int64_t n,
-                                                   int P, const double* __restrict__ theta,
-                                                   const double* __restrict__ d,
-                                                   const double* __restrict__ e,
-                                                   const double* __restrict__ off,
-                                                   const double* __restrict__ xb,
-                                                   double* __restrict__ scr) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= P * nact) return;
-  const int c = t / nact, j = t - c * nact;
-  int64_t s, en;
-  chunk_bounds(n, P, c, &s, &en);
-  const double th = theta[j];
-  const double delta = kPrecondGuard * fmax(1.0, fabs(th));
-  // neighbours' boundary values: x_{s-1} = l_{c-1}, x_e = f_{c+1}
-  const double xl = (c > 0) ? xb[((int64_t)(c - 1) * nact + j) * 2 + 1] : 0.0;
-  const double xf = (c < P - 1) ? xb[((int64_t)(c + 1) * nact + j) * 2 + 0] : 0.0;
-  const double a_s = (s > 0) ? e[s - 1] : 0.0;
-  const double c_e = e[en - 1];
-  double cp = 0.0, rp = 0.0;
-  for (int64_t i0 = s; i0 < en; i0 += kU) {
-    double tt[kU], ea[kU], ec[kU], rr[kU];
-#pragma unroll
-    for (int u = 0; u < kU; ++u) {
-      const int64_t i = min(i0 + u, en - 1);
-      tt[u] = tri_diag(d[i], th, off[i], delta);
-      ea[u] = (i > s) ? e[i - 1] : 0.0;
-      ec[u] = e[i];
-      rr[u] = (double)R[i * ld + j];
-    }
-#pragma unroll
-    for (int u = 0; u < kU; ++u) {
-      const int64_t i = i0 + u;
-      if (i >= en) break;
-      const double den = tt[u] - ea[u] * cp;
-      const double inv = 1.0 / den;
-      double r = rr[u];
-      if (i == s) r -= a_s * xl;
-      if (i == en - 1) r -= c_e * xf;
-      rp = (r - ea[u] * rp) * inv;
-      cp = ec[u] * inv;
-      scr[i * nact + j] = cp;
-      R[i * ld + j] = (T)rp;  // (in the fp32 phase at the blocks' precision)
-    }
+// One workgroup per column: P groups' interfaces (bnd) -> the values left and
+// right of each group (xb).  Thread t takes `per` neighbouring groups (one up
+// to 1024 of them), merged in order; the threads' interfaces go up a binary
+// tree in LDS (level of node i in [NP, 2 NP) the leaves, i / 2 its parent) and
+// the outside values down it.
+constexpr int kTopThreads = 1024;
+__global__ __launch_bounds__(kTopThreads) void k_tri_top(int64_t P, int per, int NP,
+                                                         double* __restrict__ bnd,
+                                                         double* __restrict__ xb) {
+  extern __shared__ __attribute__((aligned(16))) char top_smem[];
+  Iface* node = reinterpret_cast<Iface*>(top_smem);  // 2 NP (index 0 unused)
+  dd2* out = reinterpret_cast<dd2*>(node + 2 * NP);  // (left, right) of each node
+  const int j = blockIdx.x, t = threadIdx.x;
+  const int64_t g0 = (int64_t)t * per, g1 = min(P, g0 + per);
+  bnd += (int64_t)j * 6 * P;
+  xb += (int64_t)j * 2 * P;
+  auto load = [&](int64_t g) {
+    return Iface{bnd[g], bnd[P + g], bnd[2 * P + g], bnd[3 * P + g], bnd[4 * P + g], bnd[5 * P + g]};
+  };
+  // the thread's run; the last-row part of each prefix replaces the group's own
+  Iface f{0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+  if (g0 < g1) f = load(g0);
+  for (int64_t g = g0 + 1; g < g1; ++g) {
+    Seam s;
+    f = merge(f, load(g), s);
+    bnd[3 * P + g] = f.ye;
+    bnd[4 * P + g] = f.ve;
+    bnd[5 * P + g] = f.we;
   }
-  double x = 0.0;
-  for (int64_t i0 = en - 1; i0 >= s; i0 -= kU) {
-    double rr[kU], cc[kU];
-#pragma unroll
-    for (int u = 0; u < kU; ++u) {
-      const int64_t i = max(i0 - u, s);
-      rr[u] = (double)R[i * ld + j];
-      cc[u] = scr[i * nact + j];
+  if (t < NP) node[NP + t] = f;
+  __syncthreads();
+  for (int w = NP >> 1; w >= 1; w >>= 1) {
+    if (t < w) {
+      Seam s;
+      node[w + t] = merge(node[2 * (w + t)], node[2 * (w + t) + 1], s);
     }
-#pragma unroll
-    for (int u = 0; u < kU; ++u) {
-      const int64_t i = i0 - u;
-      if (i < s) break;
-      x = (i == en - 1) ? rr[u] : rr[u] - cc[u] * x;
-      R[i * ld + j] = (T)x;
+    __syncthreads();
+  }
+  if (t == 0) out[1] = dd2{0.0, 0.0};
+  __syncthreads();
+  for (int w = 1; w < NP; w <<= 1) {
+    if (t < w) {
+      const int i = w + t;
+      Seam s;
+      merge(node[2 * i], node[2 * i + 1], s);
+      const dd2 o = out[i];
+      double l0 = o[0], r0 = o[1], l1 = o[0], r1 = o[1];
+      descend(s, false, l0, r0);
+      descend(s, true, l1, r1);
+      out[2 * i] = dd2{l0, r0};
+      out[2 * i + 1] = dd2{l1, r1};
     }
+    __syncthreads();
+  }
+  if (g0 >= g1) return;
+  // back through the thread's run: group g's left value is the last unknown of
+  // the prefix before it, whose right value is group g's first unknown
+  const dd2 o = out[NP + t];
+  double right = o[1];
+  for (int64_t g = g1 - 1; g >= g0; --g) {
+    double left = o[0], first = 0.0;
+    if (g > g0) {
+      const double ys = bnd[g], vs = bnd[P + g], ws = bnd[2 * P + g];  // own first row
+      const double ye = bnd[3 * P + g - 1], ve = bnd[4 * P + g - 1], we = bnd[5 * P + g - 1];  // prefix's last
+      const double pa = fma(ve, o[0], ye);     // last of the prefix without `first`
+      const double fb = fma(ws, right, ys);    // first of g without `left`
+      left = fma(we, fb, pa) * rcp2(fma(-we, vs, 1.0));
+      first = fma(vs, left, fb);
+    }
+    xb[g] = left;
+    xb[P + g] = right;
+    right = first;
   }
 }
 
-int tri_chunks(int64_t n) { return (int)std::max<int64_t>(1, std::min<int64_t>(kTriMaxChunks, n / 64)); }
+constexpr int kTriNarrow = 16, kTriWide = 32;  // rows per chunk
 
-template <typename T>
-static hipError_t tri_apply_any(T* R, int64_t ld, int nact, int64_t n, const double* theta,
-                                const double* d, const double* e, const double* off,
-                                double* bnd, double* xb, double* scr, hipStream_t s) {
-  if (n < 1 || nact < 1 || nact > 64 || ld < nact) return hipErrorInvalidValue;
-  const int P = tri_chunks(n);
-  const int threads = P * nact;
-  const int grid = (threads + 255) / 256;
-  hipLaunchKernelGGL((k_tri_bound<T>), dim3(grid), dim3(256), 0, s, R, ld, nact, n, P, theta, d, e,
-                     off, bnd);
+template <typename T, int L, int CW>
+hipError_t tri_launch(T* R, int64_t ld, int nact, int64_t n, const double* theta, const double* d,
+                      const double* e, const double* off, double* bnd, double* xb, hipStream_t s) {
+  const int64_t P = (n + (256 / CW) * L - 1) / ((256 / CW) * L);
+  const dim3 grid((unsigned)P, (unsigned)((nact + CW - 1) / CW));
+  hipLaunchKernelGGL((k_tri_rows<T, L, CW, false>), grid, dim3(256), 0, s, R, ld, nact, n, theta, d, e, off, bnd,
+                     xb);
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;
   static bool attr = false;
   if (!attr) {
-    (void)hipFuncSetAttribute((const void*)k_tri_reduced, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              kTriMaxChunks * 10 * (int)sizeof(double));
-    (void)hipGetLastError();
+    err = hipFuncSetAttribute(reinterpret_cast<const void*>(k_tri_top), hipFuncAttributeMaxDynamicSharedMemorySize,
+                              2 * kTopThreads * (int)(sizeof(Iface) + sizeof(dd2)));
+    if (err != hipSuccess) return err;
     attr = true;
   }
-  hipLaunchKernelGGL(k_tri_reduced, dim3(nact), dim3(256), (size_t)P * 10 * sizeof(double), s, nact, P,
-                     bnd, xb);
+  const int per = (int)((P + kTopThreads - 1) / kTopThreads);
+  int NP = 1;
+  while (NP * (int64_t)per < P) NP <<= 1;
+  hipLaunchKernelGGL(k_tri_top, dim3(nact), dim3(std::max(64, NP)), 2 * NP * (sizeof(Iface) + sizeof(dd2)), s, P,
+                     per, NP, bnd, xb);
   err = hipGetLastError();
   if (err != hipSuccess) return err;
-  hipLaunchKernelGGL((k_tri_final<T>), dim3(grid), dim3(256), 0, s, R, ld, nact, n, P, theta, d, e,
-                     off, xb, scr);
+  hipLaunchKernelGGL((k_tri_rows<T, L, CW, true>), grid, dim3(256), 0, s, R, ld, nact, n, theta, d, e, off, bnd,
+                     xb);
   return hipGetLastError();
 }
+
+// Chunks of 32 rows where they fill the chip (two waves per SIMD), of 16 below
+// that: half the length of every chain.  Columns in blocks of 16, 8 or 4.
+template <typename T, int CW>
+hipError_t tri_rows(T* R, int64_t ld, int nact, int64_t n, const double* theta, const double* d,
+                    const double* e, const double* off, double* bnd, double* xb, hipStream_t s) {
+  const int64_t threads = n / kTriWide * ((nact + CW - 1) / CW * CW);
+  return threads >= 2 * 1024 * 64
+             ? tri_launch<T, kTriWide, CW>(R, ld, nact, n, theta, d, e, off, bnd, xb, s)
+             : tri_launch<T, kTriNarrow, CW>(R, ld, nact, n, theta, d, e, off, bnd, xb, s);
+}
+
+template <typename T>
+hipError_t tri_apply_any(T* R, int64_t ld, int nact, int64_t n, const double* theta, const double* d,
+                         const double* e, const double* off, double* bnd, double* xb, double* scr,
+                         hipStream_t s) {
+  if (n < 1 || nact < 1 || nact > 64 || ld < nact) return hipErrorInvalidValue;
+  // the interfaces of more groups than bnd and xb hold go to scr (n nact
+  // doubles against 8 nact per group of at least 256 rows)
+  if (n > (int64_t)kTriMaxChunks * 256) {
+    bnd = scr;
+    xb = scr + n / 256 * 6 * nact + 6 * nact;
+  }
+  if (nact <= 4) return tri_rows<T, 4>(R, ld, nact, n, theta, d, e, off, bnd, xb, s);
+  if (nact <= 8) return tri_rows<T, 8>(R, ld, nact, n, theta, d, e, off, bnd, xb, s);
+  return tri_rows<T, 16>(R, ld, nact, n, theta, d, e, off, bnd, xb, s);
+}
+
+}  // namespace
 
 hipError_t tri_apply_f64(double* R, int64_t ld, int nact, int64_t n, const double* theta,
                          const double* d, const double* e, const double* off, double* bnd,
