@@ -10,8 +10,6 @@
 //   * the controller of ortho(W; Y) on n-vectors (Alg. 2 inside Alg. 3): it
 //     reads the overlap G = [Y W]^T W of the current W and emits the small
 //     coefficient matrix that the streaming kernel applies next.
-#include <type_traits>
-
 #include "internal.h"
 
 namespace lobpcg {
@@ -29,9 +27,6 @@ __device__ __forceinline__ uint64_t sm64(uint64_t x) {
   return z ^ (z >> 31);
 }
 
-// index of the wave in its workgroup, in a scalar register
-__device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
-
 // LDS writes of one wave visible to the same wave's later reads
 __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -44,138 +39,92 @@ __device__ __forceinline__ double readlane_f64(double v, int l) {
                           __builtin_amdgcn_readlane(__double2loint(v), l));
 }
 
-template <int CTRL>
-__device__ __forceinline__ double dpp_f64(double v) {
-  return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xF, 0xF, true),
-                          __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xF, 0xF, true));
-}
-// the 64-bit DPP move (row_newbcast is the one control it takes)
-extern "C" __device__ long lobpcg_update_dpp_i64(long old, long src, int ctrl, int row_mask, int bank_mask,
-                                                 bool bound_ctrl) __asm("llvm.amdgcn.update.dpp.i64");
-// lane L of each row of 16 to the whole row
-template <int L>
-__device__ __forceinline__ double row_bcast(double v) {
-  const long x = __double_as_longlong(v);
-  return __longlong_as_double(lobpcg_update_dpp_i64(x, x, 0x150 + L, 0xF, 0xF, true));
-}
-// f(integral constant I) for I = B .. E-1
-template <int B, int E, class F>
-__device__ __forceinline__ void static_for(F&& f) {
-  if constexpr (B < E) {
-    f(std::integral_constant<int, B>{});
-    static_for<B + 1, E>(f);
-  }
-}
-// Sum over the 16 lanes of a row, the same bits in every lane (swap
-// neighbours, swap pairs, mirror 8, mirror 16; each step adds the same two
-// operands on both partners).
-__device__ __forceinline__ double row_sum(double v) {
-  v += dpp_f64<0xB1>(v);   // quad_perm [1, 0, 3, 2]
-  v += dpp_f64<0x4E>(v);   // quad_perm [2, 3, 0, 1]
-  v += dpp_f64<0x141>(v);  // row_half_mirror
-  v += dpp_f64<0x140>(v);  // row_mirror
-  return v;
-}
-__device__ __forceinline__ double row_max(double v) {
-  v = fmax(v, dpp_f64<0xB1>(v));
-  v = fmax(v, dpp_f64<0x4E>(v));
-  v = fmax(v, dpp_f64<0x141>(v));
-  return fmax(v, dpp_f64<0x140>(v));
-}
-// (v of this lane's row or of the row beside it in the pair) for N = 16, of
-// the wave's lower and upper half for N = 32; the same in all lanes concerned
-template <int N>
-__device__ __forceinline__ void lane_pair(double v, double& a, double& b) {
-  if constexpr (N == 16) {
-    const auto l = __builtin_amdgcn_permlane16_swap(__double2loint(v), __double2loint(v), false, false);
-    const auto h = __builtin_amdgcn_permlane16_swap(__double2hiint(v), __double2hiint(v), false, false);
-    a = __hiloint2double(h[0], l[0]);
-    b = __hiloint2double(h[1], l[1]);
-  } else {
-    const auto l = __builtin_amdgcn_permlane32_swap(__double2loint(v), __double2loint(v), false, false);
-    const auto h = __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v), false, false);
-    a = __hiloint2double(h[0], l[0]);
-    b = __hiloint2double(h[1], l[1]);
-  }
-}
-// Sum (maximum) over the 64 lanes (all active), the same bits in every lane
-__device__ __forceinline__ double wave_sum(double v) {
-  double a, b;
-  lane_pair<16>(row_sum(v), a, b);
-  lane_pair<32>(a + b, a, b);
-  return a + b;
-}
-__device__ __forceinline__ double wave_max(double v) {
-  double a, b;
-  lane_pair<16>(row_max(v), a, b);
-  lane_pair<32>(fmax(a, b), a, b);
-  return fmax(a, b);
-}
-
-// 1 / q and 1 / sqrt(x) to 1 ulp: the hardware estimate (2^-23 or better)
-// and two Newton steps.  q, x finite and not 0, x > 0.
-__device__ __forceinline__ double rcp2(double q) {
-  double r = __builtin_amdgcn_rcp(q);
-  r = fma(r, fma(-q, r, 1.0), r);
-  return fma(r, fma(-q, r, 1.0), r);
-}
-__device__ __forceinline__ double rsq2(double x) {
-  double y = __builtin_amdgcn_rsq(x);
-  y = fma(0.5 * y, fma(-x * y, y, 1.0), y);
-  return fma(0.5 * y, fma(-x * y, y, 1.0), y);
-}
-
-// Cholesky of a 16 x 16 matrix by one wave, each row of 16 lanes with a copy
-// of its own: lane l holds matrix row l % 16 in g (g[c] read for c <= row).
-// An n x n matrix (n < 16) comes padded with the identity.  The next pivot
-// is a lane broadcast, a reciprocal square root and one update away from the
-// last, which is the chain that bounds it: 1.5 us with the broadcasts as DPP
-// moves, 8.6 us with a rounded root and division per column and lane shuffles
-// through LDS.  On return g holds L and inv the reciprocals of its diagonal.
-// False (uniform) when a pivot was not > 0 or not finite.
-__device__ __forceinline__ bool chol16_rows(double (&g)[16], int n, double (&inv)[16]) {
-  const int row = threadIdx.x & 15;
-  bool ok = true;
-  auto column = [&](auto K) {
-    constexpr int k = K;
-    const double piv = row_bcast<k>(g[k]);
-    ok = ok && piv > 0.0 && piv < INFINITY;
-    const double y = rsq2(piv);
-    inv[k] = y;
-    const double lk = ((row == k) ? piv : g[k]) * y;
-    g[k] = lk;
-    const double nlk = -lk;
-    static_for<k + 1, 16>([&](auto C) { g[C] = fma(row_bcast<C>(lk), nlk, g[C]); });
-  };
-  static_for<0, 16>([&](auto K) { inv[K] = 1.0; });
-  static_for<0, 4>(column);
-  if (n > 4) static_for<4, 8>(column);
-  if (n > 8) static_for<8, 16>(column);
-  return __builtin_amdgcn_readfirstlane(ok) != 0;
-}
-
-// Rows of X (p x n, n <= 16) times L^-T, thread i taking row i, with L and
-// inv as chol16_rows left them in this thread's row of 16 lanes
-__device__ __forceinline__ void trsm16_rows(double* X, int ldx, int p, int n, const double (&g)[16],
-                                            const double (&inv)[16]) {
-  const int i = threadIdx.x;
-  double z[16];
+// Cholesky of an n x n symmetric matrix (n <= 16) held by one wave in
+// registers: lane l keeps column c = l & 15, rows r = (l >> 4) + 4 t
+// (t = 0..3), in g[t]; only r >= c is read, and rows or columns from n to 15
+// are those of the identity.  Right-looking, column by column: the pivot is
+// read from its lane, column k of L is formed in its four lanes and handed
+// to the others by lane shuffles, then the trailing entries are updated.
+// Every entry takes the same operations in the same order as the LDS
+// factorizations: G[r][k] / l_kk (KDIV) or G[r][k] * (1 / l_kk), and
+// G[r][c] - L[r][k] L[c][k] as one fused multiply-add.  On return g holds L
+// (diagonal included).  False, uniform over the wave, when a pivot is not
+// > 0 (or, with CHECKINF, not finite); linv (LDS, may be null) receives
+// 1 / l_kk when !KDIV.
+template <bool KDIV, bool CHECKINF>
+__device__ __forceinline__ bool reg_chol16(double (&g)[4], int n, double* linv) {
+  const int l = threadIdx.x & 63, c = l & 15, rb = l >> 4;
+  for (int k = 0; k < n; ++k) {
+    // register k >> 2 of lane k + 16 (k & 3) (a select: no indexed registers)
+    const int tk = k >> 2;
+    const double gk = (tk == 0) ? g[0] : (tk == 1) ? g[1] : (tk == 2) ? g[2] : g[3];
+    const double gkk = readlane_f64(gk, k + 16 * (k & 3));
+    if (!(gkk > 0.0)) return false;
+    if (CHECKINF && !(gkk < INFINITY)) return false;
+    const double lkk = sqrt(gkk);
+    const double inv = KDIV ? 0.0 : 1.0 / lkk;
+    if (c == k) {
 #pragma unroll
-  for (int c = 0; c < 16; ++c) z[c] = (c < n && i < p) ? X[i * ldx + c] : 0.0;
-  auto column = [&](auto C) {
-    constexpr int c = C;
-    z[c] *= inv[c];
-    const double nz = -z[c];
-    static_for<c + 1, 16>([&](auto K) { z[K] = fma(row_bcast<K>(g[c]), nz, z[K]); });
-  };
-  static_for<0, 4>(column);
-  if (n > 4) static_for<4, 8>(column);
-  if (n > 8) static_for<8, 16>(column);
-  if (i < p) {
+      for (int t = 0; t < 4; ++t) {
+        const int r = rb + 4 * t;
+        if (r > k) g[t] = KDIV ? g[t] / lkk : g[t] * inv;
+        else if (r == k) g[t] = lkk;
+      }
+    }
+    if (!KDIV && linv != nullptr && l == 0) linv[k] = inv;
+    // lr[t] = L[rb + 4t][k] (lane k + 16 rb, register t); lc[t] from lane
+    // k + 16 (c & 3): L[c][k] is its register c >> 2
+    double lr[4], lc[4];
 #pragma unroll
-    for (int c = 0; c < 16; ++c)
-      if (c < n) X[i * ldx + c] = z[c];
+    for (int t = 0; t < 4; ++t) {
+      lr[t] = __shfl(g[t], k + 16 * rb);
+      lc[t] = __shfl(g[t], k + 16 * (c & 3));
+    }
+    const int tc = c >> 2;
+    const double lck = (tc == 0) ? lc[0] : (tc == 1) ? lc[1] : (tc == 2) ? lc[2] : lc[3];
+    if (c > k) {
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        if (rb + 4 * t >= c) g[t] = fma(-lr[t], lck, g[t]);
+    }
   }
+  return true;
+}
+
+// One wave (all 64 lanes): L = chol(S + shift I) for the n x n (n <= 16)
+// matrix S in LDS (lower triangle read), written to L in LDS (lower
+// triangle; the strict upper one zeroed when ZUP).  wave_chol16_lds is the
+// out-of-line form, so that the large single-workgroup kernels keep their
+// own register budgets.  Returns false (uniform) on a pivot that is not > 0
+// (or, CHECKINF, not finite).
+template <bool KDIV, bool CHECKINF, bool ZUP>
+__device__ __forceinline__ bool wave_chol16_body(const double* S, int lds_, int n, double shift,
+                                                 double* L, int ldl, double* linv) {
+  const int l = threadIdx.x & 63, c = l & 15, rb = l >> 4;
+  double g[4];
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    const int r = rb + 4 * t;
+    g[t] = (r < n && c < n) ? ((r >= c) ? S[r * lds_ + c] + (r == c ? shift : 0.0) : 0.0)
+                            : (r == c ? 1.0 : 0.0);
+  }
+  const bool ok = reg_chol16<KDIV, CHECKINF>(g, n, linv);
+  if (ok || ZUP) {
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const int r = rb + 4 * t;
+      if (r < n && c < n) {
+        if (r >= c) L[r * ldl + c] = g[t];
+        else if (ZUP) L[r * ldl + c] = 0.0;
+      }
+    }
+  }
+  return ok;
+}
+template <bool KDIV, bool CHECKINF, bool ZUP>
+__device__ __noinline__ bool wave_chol16_lds(const double* S, int lds_, int n, double shift, double* L,
+                                             int ldl, double* linv) {
+  return wave_chol16_body<KDIV, CHECKINF, ZUP>(S, lds_, n, shift, L, ldl, linv);
 }
 
 // ---------------------------------------------------------------------------
@@ -207,52 +156,72 @@ __device__ __forceinline__ double blk_reduce_sum_ordered(double v, double* scrat
   return r;
 }
 
-// scale columns of X (n x q) to unit norm, 16 lanes per column; exact-zero
-// columns are replaced by SplitMix64 columns (entry i of column j:
-// splitmix64(seed + j n + i)).
-__device__ __forceinline__ void blk_normalize(double* X, int ldx, int n, int q, int* zeros) {
-  const int l = threadIdx.x & 15;
-  for (int j = threadIdx.x >> 4; j < q; j += blockDim.x >> 4) {
+// C (p x q) = A^T B, A: n x p, B: n x q
+__device__ __forceinline__ void blk_gemm_tn(const double* A, int lda, const double* B, int ldb, int n, int p,
+                            int q, double* C, int ldc) {
+  for (int idx = threadIdx.x; idx < p * q; idx += blockDim.x) {
+    const int i = idx / q, j = idx - i * q;
     double s = 0.0;
-    for (int r = l; r < n; r += 16) s = fma(X[r * ldx + j], X[r * ldx + j], s);
-    s = row_sum(s);
-    if (s == 0.0) {  // uniform over the 16 lanes
-      for (int r = l; r < n; r += 16) {
-        const uint64_t z = sm64(kZeroColumnSeed + (uint64_t)j * (uint64_t)n + (uint64_t)r);
-        const double x = (double)(z >> 11) * 0x1.0p-53 - 0.5;
-        X[r * ldx + j] = x;
-        s = fma(x, x, s);
-      }
-      s = row_sum(s);
-      if (l == 0) atomicAdd(zeros, 1);
-    }
-    const double inv = rsq2(s);
-    for (int r = l; r < n; r += 16) X[r * ldx + j] *= inv;
+    for (int r = 0; r < n; ++r) s += A[r * lda + i] * B[r * ldb + j];
+    C[i * ldc + j] = s;
   }
   __syncthreads();
 }
 
-// Cholesky L L^T = M + shift I (lower, n x n; the strict upper part of L is
-// zeroed); returns true on success.  Breaks down when a pivot is not > 0 (NaN
-// included), like LAPACK potrf.  Every thread calls it and M must be complete
-// on entry.  Wave 0 alone factors (REG and n <= 16: in registers, else column
-// by column in LDS with wave-level syncs) while the other waves wait at the
-// closing barriers: two workgroup barriers per factorization.
-template <bool REG = true>
+// X (n x q) -= Y (n x p) C (p x q)
+__device__ __forceinline__ void blk_sub_mm(double* X, int ldx, const double* Y, int ldy, const double* C, int ldc,
+                           int n, int p, int q) {
+  for (int idx = threadIdx.x; idx < n * q; idx += blockDim.x) {
+    const int r = idx / q, j = idx - r * q;
+    double s = 0.0;
+    for (int k = 0; k < p; ++k) s += Y[r * ldy + k] * C[k * ldc + j];
+    X[r * ldx + j] -= s;
+  }
+  __syncthreads();
+}
+
+// scale columns of X (n x q) to unit norm; exact-zero columns are replaced
+// by SplitMix64 columns (entry i of column j: splitmix64(seed + j n + i)).
+__device__ __forceinline__ void blk_normalize(double* X, int ldx, int n, int q, double* tmp, int* zeros) {
+  for (int j = threadIdx.x; j < q; j += blockDim.x) {
+    double s = 0.0;
+    for (int r = 0; r < n; ++r) s += X[r * ldx + j] * X[r * ldx + j];
+    if (s == 0.0) {
+      for (int r = 0; r < n; ++r) {
+        const uint64_t z = sm64(kZeroColumnSeed + (uint64_t)j * (uint64_t)n + (uint64_t)r);
+        X[r * ldx + j] = (double)(z >> 11) * 0x1.0p-53 - 0.5;
+      }
+      s = 0.0;
+      for (int r = 0; r < n; ++r) s += X[r * ldx + j] * X[r * ldx + j];
+      atomicAdd(zeros, 1);
+    }
+    tmp[j] = sqrt(s);
+  }
+  __syncthreads();
+  for (int idx = threadIdx.x; idx < n * q; idx += blockDim.x) {
+    const int j = idx % q;
+    X[idx / q * ldx + j] /= tmp[j];
+  }
+  __syncthreads();
+}
+
+// Cholesky L L^T = M + shift I (lower, n x n); returns true on success.
+// Breaks down when a pivot is not > 0 (NaN included), like LAPACK potrf.
+// Every thread calls it and M must be complete on entry.  Wave 0 alone
+// factors (REG != 0 and n <= 16: in registers, by an out-of-line call in
+// the Rayleigh-Ritz kernel, whose register budget is full, inline in the
+// ortho controller; otherwise column by column in LDS with wave-level
+// syncs) while the other
+// waves wait at the closing barriers: two workgroup barriers per
+// factorization.  Each entry takes the same operations in the same order as
+// a column-parallel factorization by the whole workgroup.
+// REG: 0 column by column in LDS, 1 registers (out of line), 2 registers (inline)
+template <int REG = 1>
 __device__ __forceinline__ bool blk_chol(const double* M, int ldm, int n, double shift, double* L, int ldl,
                          int* flag) {
-  if (REG && threadIdx.x < 64 && n <= 16) {
-    const int r = threadIdx.x & 15;
-    double g[16], inv[16];
-#pragma unroll
-    for (int c = 0; c < 16; ++c)
-      g[c] = (r < n && c <= r) ? M[r * ldm + c] + (r == c ? shift : 0.0) : (r == c ? 1.0 : 0.0);
-    const bool ok = chol16_rows(g, n, inv);
-    if ((int)threadIdx.x < n) {
-#pragma unroll
-      for (int c = 0; c < 16; ++c)
-        if (c < n) L[r * ldl + c] = (c <= r) ? g[c] : 0.0;
-    }
+  if (REG != 0 && threadIdx.x < 64 && n <= 16) {
+    const bool ok = (REG == 1) ? wave_chol16_lds<true, false, true>(M, ldm, n, shift, L, ldl, nullptr)
+                               : wave_chol16_body<true, false, true>(M, ldm, n, shift, L, ldl, nullptr);
     if (threadIdx.x == 0) *flag = ok ? 0 : 1;
   } else if (threadIdx.x < 64) {
     const int l = threadIdx.x;
@@ -293,9 +262,9 @@ struct ShiftCount {
 
 // Sec. 3.2 / Alg. 2: plain Cholesky, then shifts alpha*eps*||X||_F with
 // ||X||_F = sqrt(trace M), alpha = 100, x10 per retry.
-template <bool REG = true>
+template <int REG = 1>
 __device__ __forceinline__ bool blk_shifted_chol(const double* M, int ldm, int n, double* L, int ldl, int* flag,
-                                 ShiftCount* c, int retries = kShiftRetries) {
+                                 ShiftCount* c, double* scratch, int retries = kShiftRetries) {
   if (threadIdx.x == 0) c->factorizations++;
   if (blk_chol<REG>(M, ldm, n, 0.0, L, ldl, flag)) return true;
   if (threadIdx.x == 0) c->failed++;
@@ -354,10 +323,8 @@ __device__ __forceinline__ void blk_trsm_rt(double* X, int ldx, int n, int q, co
 // J^T A J, so no double buffer is needed), and V's column pairs likewise.
 // A rotation is skipped when |a_pq| <= 2^-53 sqrt(|a_pp a_qq|) or
 // |a_pq| <= 2^-60 ||A||_F; the sweep loop stops after a sweep without any
-// rotation.  Returns the number of sweeps.
+// rotation.  Returns the number of sweeps.  Must run with blockDim.x == 1024.
 
-// NT: threads of the workgroup.
-template <int NT>
 __device__ __forceinline__ int blk_jacobi(double* A, int lda, double* V, int ldv, int n, double* cs, int* pr,
                           int* rot_flag, double* scratch) {
   for (int idx = threadIdx.x; idx < n * n; idx += blockDim.x) {
@@ -378,6 +345,7 @@ __device__ __forceinline__ int blk_jacobi(double* A, int lda, double* V, int ldv
   double* ss = cs + 64;       // sin per pair
   double* tt = cs + 128;      // tan per pair
   int sweep = 0;
+  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
   for (; sweep < kJacobiMaxSweeps; ++sweep) {
     if (threadIdx.x == 0) *rot_flag = 0;
     __syncthreads();
@@ -418,13 +386,10 @@ __device__ __forceinline__ int blk_jacobi(double* A, int lda, double* V, int ldv
         tt[k] = tn;
       }
       __syncthreads();
-      // Phase 2: item (ty, tx) of a 32 x 32 grid owns the 2x2 blocks (P, Q)
-      // for P in {ty, ty+32}, Q in {tx, tx+32} with P <= Q, and V's column
-      // pair Q on the rows ty, ty+32, ty+64; every load of an item is issued
-      // before its arithmetic.  The items of a round are independent.
-#pragma unroll 1
-      for (int it = 0; it < 1024 / NT; ++it) {
-      const int tx = threadIdx.x & 31, ty = (threadIdx.x >> 5) + it * (NT / 32);
+      // Phase 2 (needs blockDim == 1024: a 32 x 32 thread grid).  Thread
+      // (ty, tx) owns the 2x2 blocks (P, Q) for P in {ty, ty+32}, Q in
+      // {tx, tx+32} with P <= Q, and V's column pair Q on the rows ty,
+      // ty+32, ty+64; every load of an item is issued before its arithmetic.
 #pragma unroll
       for (int hq = 0; hq < 2; ++hq) {
         const int Q = tx + 32 * hq;
@@ -496,7 +461,6 @@ __device__ __forceinline__ int blk_jacobi(double* A, int lda, double* V, int ldv
           }
         }
       }
-      }
       __syncthreads();
     }
     const int any = *rot_flag;
@@ -534,20 +498,45 @@ __device__ __forceinline__ void blk_sort_evals(const double* A, int lda, int n, 
   __syncthreads();
 }
 
-// Workspace of the Jacobi sweeps besides A and V
-struct JacobiLds {
-  double cs[3 * 64];
-  double scratch[16];
-  int pr[2 * 64];
-  int perm[128];
-  int flags[8];
+// LDS layout shared by the eig-based kernels
+struct EigLds {
+  double* A;  // p x (p+1)
+  double* V;  // p x (p+1)
+  double* cs;
+  int* pr;
+  int* perm;
+  double* scratch;
+  int* flags;
 };
 
-// sym(a) into A (stride lda), scaled by ds[i] ds[j] from both sides
-__device__ __forceinline__ void load_sym(const double* a, int p, const double* ds, double* A, int lda) {
+// The second area holds V during the Jacobi sweeps and, in k_small_rr, the
+// R^p orthonormalisation work arrays afterwards (X p x na, C m x na, M, L and
+// an SVQB workspace), hence its size max(p (p+1), 2 p m + 3 m^2 + 2 m).
+__host__ __device__ inline int eig_area2(int p, int m) {
+  const int a = p * (p + 1), b = 2 * p * m + 3 * m * m + 2 * m;
+  return a > b ? a : b;
+}
+__device__ __forceinline__ EigLds eig_lds(double* smem, int p, int m) {
+  EigLds L;
+  const int ld = p + 1;
+  L.A = smem;
+  L.V = L.A + p * ld;
+  L.cs = L.V + eig_area2(p, m);   // 3 * 64
+  L.scratch = L.cs + 3 * 64;      // 16
+  L.pr = (int*)(L.scratch + 16);  // 2 * 64
+  L.perm = L.pr + 2 * 64;         // 128
+  L.flags = L.perm + 128;         // 8
+  return L;
+}
+static size_t eig_lds_bytes(int p, int m) {
+  return sizeof(double) * (size_t)(p * (p + 1) + eig_area2(p, m) + 3 * 64 + 16) +
+         sizeof(int) * (2 * 64 + 128 + 8);
+}
+
+__device__ __forceinline__ void load_sym(const double* a, int p, double* A, int lda) {
   for (int idx = threadIdx.x; idx < p * p; idx += blockDim.x) {
     const int i = idx / p, j = idx - i * p;
-    A[i * lda + j] = 0.5 * (a[i * p + j] + a[j * p + i]) * (ds[i] * ds[j]);
+    A[i * lda + j] = 0.5 * (a[i * p + j] + a[j * p + i]);
   }
   __syncthreads();
 }
@@ -555,713 +544,570 @@ __device__ __forceinline__ void load_sym(const double* a, int p, const double* d
 // ---------------------------------------------------------------------------
 // Lowest nev eigenpairs of a symmetric p x p matrix by the tridiagonal
 // route (the Rayleigh-Ritz solve of Alg. 1; the paper calls LAPACK for it,
-// Sec. 3.1), by one workgroup of four waves:
-//   1. Householder reduction A = Q T Q^T: reflector k,
+// Sec. 3.1).  Jacobi needs p - 1 dependent rounds per sweep, each a chain
+// of square roots and divisions followed by a full-matrix update; this path
+// has one short chain per reflector and per Sturm count instead:
+//   1. Householder reduction A = Q T Q^T by the workgroup: reflector k,
 //      H_k = I - beta_k v_k v_k^T, maps column k below the diagonal to
-//      alpha_k e_{k+1} (Q = H_0 H_1 ... H_{p-2}, the last one I);
-//   2. the nev lowest eigenvalues of T by multisection on Sturm counts,
+//      alpha_k e_{k+1} (v_k kept in that column, Q = H_0 H_1 ... H_{p-3});
+//   2. the nev lowest eigenvalues of T by multisection on Sturm counts
+//      (counts of negative pivots of T - x I with LAPACK's pivmin guard),
 //      G points per eigenvalue and round;
 //   3. their vectors by block inverse iteration: a solve with the
 //      partial-pivoting LU of T - lambda_j I from a SplitMix64 start
 //      (pivots below eps ||T|| raised to eps ||T||, one thread per vector),
 //      Cholesky-QR of the nev vectors, a second solve;
-//   4. back-transformation u = Q z, 16 lanes per vector;
+//   4. back-transformation u = Q z, one wave per vector;
 //   5. Cholesky-QR, twice, of the nev vectors.
 // Inverse iteration returns the vectors of a cluster of close or repeated
 // eigenvalues as independent mixtures of the cluster's eigenvectors, which
 // drift towards each other with further solves; orthonormalising them in
 // ascending order between and after the solves keeps them an orthonormal
-// eigenbasis of the cluster.  Cholesky-QR goes by panels of 16 columns, each
-// made orthogonal to the ones before it first.
-// What bounds it is the latency of dependent fp64 steps, not their number,
-// so every phase is laid out for a short chain: the matrix of phase 1 and
-// the factors of phase 5 stay in registers, four waves make a barrier cheap
-// (16 waves bring it no more arithmetic worth having, and leave each 128
-// registers), every function is inlined (a call would turn its LDS accesses
-// into flat ones and its uniform arguments into vector registers), reciprocals and square roots are the hardware's estimate with
-// two Newton steps (1 ulp; a correctly rounded division is about twice as
-// many dependent operations), small products run on the fp64 MFMA.
-// Returns false when a Cholesky-QR breaks down; the callers then reload A
-// and run Jacobi.
+// eigenbasis of the cluster (residuals and orthogonality ~1e-15 ||A|| on
+// repeated and 1e-14-separated eigenvalues, where three plain solves
+// followed by Cholesky-QR lose two digits).
+// Returns false when a Cholesky-QR breaks down (A is destroyed); the
+// callers then reload A and run Jacobi.
 
 constexpr int kEigLdsBytes = 152 * 1024;  // dynamic LDS of the eigensolver kernels
-constexpr int kEigThreads = 256;
+constexpr int kMsPoints = 32;              // multisection points per eigenvalue
 
-typedef double dd2 __attribute__((ext_vector_type(2)));
 
-// LDS layout of the tridiagonal path, in doubles.  `work` is where a caller
-// may lay its own data over everything but Z and ev once the vectors are
-// done.  The reduction's vectors and the LU of the inverse iteration share
-// `lu`.  Z and the LU have rows for p rounded up to 8.
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xF, 0xF, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xF, 0xF, false);
+  return __hiloint2double(hi, lo);
+}
+// Sum over the 64 lanes (all active), the same bits in every lane: within
+// each row of 16 by DPP (swap neighbours, swap pairs, mirror 8, mirror 16;
+// each step adds the same two operands on both partners), then the four row
+// sums in a fixed order.
+__device__ __forceinline__ double wave_sum(double v) {
+  v += dpp_f64<0xB1>(v);   // quad_perm [1, 0, 3, 2]
+  v += dpp_f64<0x4E>(v);   // quad_perm [2, 3, 0, 1]
+  v += dpp_f64<0x141>(v);  // row_half_mirror
+  v += dpp_f64<0x140>(v);  // row_mirror
+  return (readlane_f64(v, 0) + readlane_f64(v, 16)) + (readlane_f64(v, 32) + readlane_f64(v, 48));
+}
+
+// LDS layout after the p x (p+1) A area, in doubles
 struct TriLayout {
   int ldz, nb;
-  int Z, ev, d, e, beta, work, de, vref, orth, lu, total;
+  int d, e, inve, e2, beta, vv, ww, ev, linv, G, Z, ws, sw, total;
 };
-constexpr int kTrans = 16 * 17;  // one wave's 16 x 16 transpose
-constexpr int kRedScratch = 128 + 4 * 128;
-// reflectors: rows of 64 up to p = 64 (zeros in front and behind), packed above
-__host__ __device__ inline int ref_doubles(int p) { return p <= 64 ? 64 * p : p * (p - 1) / 2; }
 __host__ __device__ inline TriLayout tri_layout(int p, int nev) {
   TriLayout t;
-  const int p8 = (p + 7) & ~7;
-  t.ldz = nev | 1;
+  t.ldz = nev + 1;
   int o = 0;
-  t.Z = o; o += p8 * t.ldz;
-  t.ev = o; o += nev;
-  t.d = o; o += p8 + 1;
-  t.e = o; o += p8 + 1;
+  t.d = o; o += p;
+  t.e = o; o += p;
+  t.inve = o; o += p;
+  t.e2 = o; o += p;
   t.beta = o; o += p;
-  o += o & 1;
-  t.work = o;
-  t.de = o; o += 2 * (p + 16);
-  t.vref = o; o += ref_doubles(p);
-  t.orth = o; o += 4 * kTrans + (nev > 16 ? (nev - 1) / 16 * 16 * 17 : 0);
-  t.lu = o;
-  const int avail = kEigLdsBytes / 8 - o;
-  int nb = avail / (3 * p8);  // U0^-1, U1, multipliers
+  t.vv = o; o += p;
+  t.ww = o; o += p;
+  t.ev = o; o += nev;
+  t.linv = o; o += nev;
+  t.G = o; o += nev * (nev + 1);
+  t.Z = o; o += p * t.ldz;
+  t.ws = o;
+  const int avail = kEigLdsBytes / 8 - p * (p + 1) - o;
+  const int per = 4 * p + (p + 7) / 8 + 1;  // U0^-1, U1, U2, multipliers + pivot flags
+  int nb = avail / per;
   if (nb > nev) nb = nev;
   t.nb = nb;
-  const int lu = 3 * p8 * nb;
-  t.total = o + (lu > kRedScratch ? lu : kRedScratch);
+  if (nb < 1) {
+    t.sw = o;
+    t.total = o;
+    return t;
+  }
+  o += 4 * p * nb;
+  t.sw = o;
+  o += (p * nb + 7) / 8;
+  t.total = o;
   return t;
 }
-// the path runs for every p the kernels take, also with all vectors wanted
-static_assert(kEigLdsBytes / 8 > 96 * 97 + 4 * 98 + 2 * 112 + 96 * 95 / 2 + 4 * kTrans + 80 * 17 + kRedScratch &&
-                  kEigLdsBytes / 8 > 64 * 65 + 4 * 66 + 2 * 80 + 64 * 64 + 4 * kTrans + 48 * 17 + kRedScratch,
-              "LDS of the largest eigensolves");
 
-// offset of reflector k (its entries k+1 .. p-1) in the packed store
-__device__ __forceinline__ int ref_off(int p, int k) { return k * (p - 1) - k * (k - 1) / 2; }
-
-// Householder reduction of sym(a) scaled by ds from both sides.  Lane l of
-// wave w keeps, in registers, rows l (and l + 64: H = 2) of the columns
-// c = w (mod 4), slot by slot; every four steps each wave takes its next slot
-// out as `cur`, the pivot of one of those steps, and moves the rest down.
-// Per step the pivot's wave forms the reflector (one wave sum, a reciprocal
-// square root, a reciprocal) and hands it out through LDS (barrier); every
-// wave takes its columns' part of A v and exchanges the parts (barrier); each
-// then has p = beta A v, K = beta / 2 p^T v and w = p - K v in all its lanes
-// and updates A -= v w^T + w v^T.  The v and w of its own columns a wave reads
-// from its lanes (a broadcast from LDS costs a whole wave's worth of its
-// return path, four waves' worth per step).  Rows above the pivot only see
-// reflections and are not read any more; a zero reflector (beta = 0) changes
-// nothing.  One wave per SIMD, so the instruction count of a step is its time:
-// two barriers and about 2100 cycles, where the trailing matrix in LDS under 16 waves took
-// three barriers and 3500 (p = 48: 67 us, now 42).
-template <int H, int NJ>
-__device__ __forceinline__ void reg_tridiag(const double* __restrict__ a, int p, const double* ds, double* d,
-                                            double* e, double* beta, double* vref, double* scr) {
-  double* vlin = scr;         // 64 H (H = 2; else the reflector's row of vref)
-  double* part = vlin + 128;  // [wave][128]
-  const int lane = threadIdx.x & 63, wave = wave_id();
-  if (H == 2 && threadIdx.x < 128) vlin[threadIdx.x] = 0.0;
-  double A[H][NJ], cur[H];
+// Householder reduction by the whole workgroup, three barriers per step:
+// wave 0 forms reflector k from row k (= column k, the trailing block is
+// kept symmetric); each wave takes rows i of p = beta A v, its lanes
+// splitting the row; every thread then updates trailing entries with
+// w = p - K v, K = beta/2 p^T v (formed by every wave in the same order).
+__device__ void blk_tridiag(double* A, int lda, int p, double* d, double* e, double* beta, double* vv,
+                            double* pp) {
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, nw = blockDim.x >> 6;
+  for (int k = 0; k + 2 < p; ++k) {
+    const int k1 = k + 1, s = p - k1;
+    if (wave == 0) {
+      double x[2];
+      double tail = 0.0;
 #pragma unroll
-  for (int h = 0; h < H; ++h)
+      for (int h = 0; h < 2; ++h) {
+        const int i = lane + 64 * h;
+        x[h] = (i > k && i < p) ? A[k * lda + i] : 0.0;
+        if (i > k1) tail += x[h] * x[h];
+      }
+      const double x1 = A[k * lda + k1];
+      tail = wave_sum(tail);
+      double alpha = x1, b = 0.0;
+      if (tail > 0.0) {
+        const double nrm = sqrt(x1 * x1 + tail);
+        alpha = (x1 >= 0.0) ? -nrm : nrm;
+        b = 1.0 / (nrm * (nrm + fabs(x1)));  // 2 / v^T v for v = x - alpha e_1
+      }
 #pragma unroll
-    for (int jj = 0; jj < NJ; ++jj) {
-      const int i = lane + 64 * h, c = 4 * jj + wave;
-      A[h][jj] = (i < p && c < p) ? 0.5 * (a[i * p + c] + a[c * p + i]) * (ds[i] * ds[c]) : 0.0;
+      for (int h = 0; h < 2; ++h) {
+        const int i = lane + 64 * h;
+        if (i > k && i < p) {
+          const double v = (b != 0.0 && i == k1) ? x1 - alpha : x[h];
+          A[i * lda + k] = v;  // reflector k, kept for the back-transformation
+          vv[i] = v;
+        }
+      }
+      if (lane == 0) {
+        d[k] = A[k * lda + k];
+        e[k] = alpha;
+        beta[k] = b;
+      }
     }
-  __syncthreads();
-  const int nslot = (p + 3) >> 2;
-  // lane c of x[] (c uniform); 0 past the lanes, where a chunk's last slots
-  // may lie with one row per lane and more than 52 of them (their columns are
-  // empty and stay so)
-  auto at = [](const double (&x)[H], int c) {
-    if (H == 1 && 4 * NJ > 52 && c > 63) return 0.0;
-    return (H == 1 || c < 64) ? readlane_f64(x[0], c & 63) : readlane_f64(x[H - 1], c & 63);
-  };
-  for (int o = 0; o < nslot; ++o) {
+    __syncthreads();
+    const double b = beta[k];
+    if (b == 0.0) continue;  // H_k = I (uniform)
+    for (int i = k1 + wave; i < p; i += nw) {
+      double acc = 0.0;
 #pragma unroll
-    for (int h = 0; h < H; ++h) {
-      cur[h] = A[h][0];
-#pragma unroll
-      for (int jj = 0; jj + 1 < NJ; ++jj) A[h][jj] = A[h][jj + 1];
-      A[h][NJ - 1] = 0.0;
+      for (int h = 0; h < 2; ++h) {
+        const int j = k1 + lane + 64 * h;
+        if (j < p) acc += A[i * lda + j] * vv[j];
+      }
+      acc = wave_sum(acc);
+      if (lane == 0) pp[i] = b * acc;
     }
-    const int nrem = nslot - 1 - o;  // slots behind cur
-    for (int w4 = 0; w4 < 4; ++w4) {
-      const int k = 4 * o + w4, k1 = k + 1;
-      if (k1 >= p) {
-        if (k < p && wave == w4) {
-          // the last column: its diagonal entry
+    __syncthreads();
+    double kp = 0.0;
 #pragma unroll
-          for (int h = 0; h < H; ++h)
-            if (lane + 64 * h == k) d[k] = cur[h];
-        }
-        break;
-      }
-      if (wave == w4) {
-        double tail = 0.0;
-#pragma unroll
-        for (int h = 0; h < H; ++h) {
-          const double t = (lane + 64 * h > k1) ? cur[h] : 0.0;
-          tail = fma(t, t, tail);
-        }
-        const double x0 = at(cur, k), x1 = at(cur, k1);
-        tail = wave_sum(tail);
-        double alpha = x1, b = 0.0;
-        if (tail > 0.0) {
-          const double s2 = fma(x1, x1, tail);
-          const double y = rsq2(s2);
-          double nrm = s2 * y;
-          nrm = fma(0.5 * y, fma(-nrm, nrm, s2), nrm);
-          alpha = (x1 >= 0.0) ? -nrm : nrm;
-          b = rcp2(nrm * (nrm + fabs(x1)));  // 2 / v^T v for v = x - alpha e_1
-        }
-        const double v1 = x1 - alpha;
-#pragma unroll
-        for (int h = 0; h < H; ++h) {
-          const int i = lane + 64 * h;
-          const double v = (i > k1) ? cur[h] : ((i == k1) ? v1 : 0.0);
-          if (H == 1) {
-            vref[64 * k + i] = v;
-          } else if (i < p) {
-            vlin[i] = v;
-            if (i > k) vref[ref_off(p, k) + i - k1] = v;
-          }
-        }
-        if (lane == 0) {
-          d[k] = x0;
-          e[k] = alpha;
-          beta[k] = b;
-        }
-      }
-      __syncthreads();
-      // the part of A v that this wave's columns give
-      const double b = beta[k];
-      const double* vrow = (H == 1) ? vref + 64 * k : vlin;
-      double vi[H], vj[NJ], acc[H][2];
-#pragma unroll
-      for (int h = 0; h < H; ++h) vi[h] = vrow[lane + 64 * h];
-      const int c0 = 4 * o + wave;  // cur's column; slot jj holds c0 + 4 (jj + 1)
-      const double vc = at(vi, c0);
-#pragma unroll
-      for (int h = 0; h < H; ++h) {
-        acc[h][0] = cur[h] * vc;
-        acc[h][1] = 0.0;
-      }
-#pragma unroll
-      for (int c4 = 0; c4 < NJ; c4 += 4)
-        if (c4 < nrem) {
-#pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            vj[c4 + u] = at(vi, c0 + 4 * (c4 + u + 1));
-#pragma unroll
-            for (int h = 0; h < H; ++h) acc[h][u & 1] = fma(A[h][c4 + u], vj[c4 + u], acc[h][u & 1]);
-          }
-        }
-#pragma unroll
-      for (int h = 0; h < H; ++h) part[wave * 128 + lane + 64 * h] = acc[h][0] + acc[h][1];
-      __syncthreads();
-      double wi[H], kp = 0.0;
-#pragma unroll
-      for (int h = 0; h < H; ++h) {
-        const double* q = part + lane + 64 * h;
-        wi[h] = b * ((q[0] + q[128]) + (q[256] + q[384]));
-        kp = fma(wi[h], vi[h], kp);
-      }
-      const double nK = -0.5 * b * wave_sum(kp);
-#pragma unroll
-      for (int h = 0; h < H; ++h) wi[h] = fma(nK, vi[h], wi[h]);
-      const double wc = at(wi, c0);
-#pragma unroll
-      for (int h = 0; h < H; ++h) cur[h] = fma(-wi[h], vc, fma(-vi[h], wc, cur[h]));
-#pragma unroll
-      for (int c4 = 0; c4 < NJ; c4 += 4)
-        if (c4 < nrem) {
-#pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            const double wj = at(wi, c0 + 4 * (c4 + u + 1));
-#pragma unroll
-            for (int h = 0; h < H; ++h)
-              A[h][c4 + u] = fma(-wi[h], vj[c4 + u], fma(-vi[h], wj, A[h][c4 + u]));
-          }
-        }
+    for (int h = 0; h < 2; ++h) {
+      const int i = k1 + lane + 64 * h;
+      if (i < p) kp += pp[i] * vv[i];
     }
+    const double K = 0.5 * b * wave_sum(kp);
+    for (int idx = tid; idx < s * s; idx += blockDim.x) {
+      const int jj = idx / s, ii = idx - jj * s;
+      const int j = k1 + jj, i = k1 + ii;
+      const double vj = vv[j], vi = vv[i];
+      const double wi = pp[i] - K * vi, wj = pp[j] - K * vj;
+      A[j * lda + i] -= vj * wi + wj * vi;
+    }
+    __syncthreads();
+  }
+  if (tid == 0) {
+    if (p >= 2) {
+      d[p - 2] = A[(p - 2) * lda + p - 2];
+      e[p - 2] = A[(p - 1) * lda + p - 2];
+    }
+    d[p - 1] = A[(p - 1) * lda + p - 1];
   }
   __syncthreads();
 }
 
-// Sturm count of T - x I: the number of sign changes in p_0 = 1,
-// p_1 = d_0 - x, p_{i+1} = (d_i - x) p_i - e_{i-1}^2 p_{i-1} (the leading
-// minors), one fused multiply-add per dependent step where the pivots'
-// quotient form has a reciprocal and two.  de[i] = (d_i, e_{i-1}^2) for ||T||
-// in [1, 2), with e^2 raised to 2^-120 (a change of T below its rounding): a
-// zero minor is then followed by a nonzero one of the other sign, one sign
-// change whichever sign the zero carries.  A step multiplies the pair by at
-// most 2^4 and at least about 2^-60; a power of two brings it back to 1 every
-// 8 steps.  de is padded with steps that change no sign, and the operands of
-// the next eight steps are loaded ahead.
-__device__ __forceinline__ int sturm_count(const dd2* __restrict__ de, int p, double x) {
-  const dd2 t0 = de[0];
-  double p0 = 1.0, p1 = t0[0] - x;
-  uint32_t c = (uint32_t)__double2hiint(p1) >> 31;
-  dd2 t[8];
-#pragma unroll
-  for (int u = 0; u < 8; ++u) {
-    t[u] = de[1 + u];
-    asm("" : "+v"(t[u]));  // (else the compiler folds the two loads into one at the loop's top)
-  }
-  for (int i = 1; i < p; i += 8) {
-    dd2 tn[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) tn[u] = de[i + 8 + u];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const double pn = fma(t[u][0] - x, p1, -(t[u][1] * p0));
-      c += (uint32_t)(__double2hiint(pn) ^ __double2hiint(p1)) >> 31;
-      p0 = p1;
-      p1 = pn;
-    }
-    const int ex = __builtin_amdgcn_frexp_exp(fmax(fabs(p0), fabs(p1)));
-    p0 = __builtin_amdgcn_ldexp(p0, -ex);
-    p1 = __builtin_amdgcn_ldexp(p1, -ex);
-#pragma unroll
-    for (int u = 0; u < 8; ++u) t[u] = tn[u];
-  }
-  return (int)c;
+// 1 / q to ~1 ulp: the hardware reciprocal and one Newton step (the Sturm
+// count only needs each step to a few ulps, Kahan's backward-error argument)
+__device__ __forceinline__ double rcp_nr(double q) {
+  const double r = __builtin_amdgcn_rcp(q);
+  return fma(r, fma(-q, r, 1.0), r);
 }
 
-// Eigenvalues 0 .. nev-1 (ascending) of T into ev, G lanes to each: the
-// largest power of two (64 at most) with one point per thread.  More points
-// per thread shorten the search by less than they add to the count loop,
-// which one wave per SIMD runs at its instruction rate.  Every thread calls
-// it.
-__device__ __forceinline__ void blk_multisection(const dd2* de, int p, int nev, double gl, double gu, double tnorm,
-                                                 double* ev) {
-  int G = 64;
-  while (G > 1 && G * nev > kEigThreads) G >>= 1;
+// number of eigenvalues of T below x (negative pivots of T - x I)
+__device__ __forceinline__ int sturm_count(const double* d, const double* e2, int p, double x,
+                                           double pivmin) {
+  double q = d[0] - x;
+  int c = 0;
+  if (q <= pivmin) {
+    ++c;
+    q = fmin(q, -pivmin);
+  }
+#pragma unroll 4
+  for (int i = 1; i < p; ++i) {
+    q = (d[i] - x) - e2[i - 1] * rcp_nr(q);
+    if (q <= pivmin) {
+      ++c;
+      q = fmin(q, -pivmin);
+    }
+  }
+  return c;
+}
+
+// eigenvalues 0 .. nev-1 (ascending) of T into ev; every thread calls it
+__device__ void blk_multisection(const double* d, const double* e2, int p, int nev, double gl, double gu,
+                                 double tnorm, double pivmin, double* ev) {
+  int G = kMsPoints;
+  while (G > 1 && G * nev > (int)blockDim.x) G >>= 1;
+  const int t = threadIdx.x & (G - 1);
+  const int gi = threadIdx.x / G, ngroups = blockDim.x / G;
   const int lane = threadIdx.x & 63;
-  const int t = lane & (G - 1), gi = (int)threadIdx.x / G;
   const uint64_t gmask = (G == 64) ? ~0ull : (((1ull << G) - 1ull) << (lane & ~(G - 1)));
-  const double inv = 1.0 / (double)(G + 1), tp = (double)(t + 1);
-  for (int j0 = 0; j0 < nev; j0 += kEigThreads / G) {
-    const int j = j0 + gi;
-    bool act = j < nev;
+  for (int j = gi; j < nev; j += ngroups) {
     double lo = gl, hi = gu;
     for (int round = 0; round < 256; ++round) {
       const double w = hi - lo;
-      act = act && !(w <= 2.0 * kEps * fmax(fabs(lo), fabs(hi)) || w <= kEps * tnorm);
-      if (__ballot(act) == 0) break;
-      const double h = w * inv;
-      const int c = sturm_count(de, p, fma(tp, h, lo));
+      if (w <= 2.0 * kEps * fmax(fabs(lo), fabs(hi)) || w <= kEps * tnorm) break;
+      const double h = w / (double)(G + 1);
+      const double x = lo + (double)(t + 1) * h;
+      const int c = sturm_count(d, e2, p, x, pivmin);
       const int k = __popcll(__ballot(c <= j) & gmask);
-      const double nlo = (k > 0) ? fma((double)k, h, lo) : lo;
-      const double nhi = (k < G) ? fma((double)(k + 1), h, lo) : hi;
-      act = act && !(nlo == lo && nhi == hi);
-      if (act) {
-        lo = nlo;
-        hi = nhi;
-      }
+      const double nlo = (k > 0) ? lo + (double)k * h : lo;
+      const double nhi = (k < G) ? lo + (double)(k + 1) * h : hi;
+      if (nlo == lo && nhi == hi) break;
+      lo = nlo;
+      hi = nhi;
     }
-    if (t == 0 && j < nev) ev[j] = lo + 0.5 * (hi - lo);
+    if (t == 0) ev[j] = lo + 0.5 * (hi - lo);
   }
 }
 
-// One inverse-iteration solve of (T - lam I) z = Z[:, j], thread t of nb.
-// FACTOR builds the LU (partial pivoting by selects, so that lanes that swap
-// and lanes that do not take the same steps) and keeps U0^-1, U1 and the
-// multipliers in LDS, the swaps as bits in sw0, sw1: U2 is e_{i+1} after a
-// swap, 0 otherwise.  Rows p .. p8-1 continue T by the identity (d = lam + 1,
-// e = 0; zero in Z), so that the rows go by eights without a branch, their
-// operands loaded ahead of the dependent chain.
-template <bool FACTOR>
-__device__ __forceinline__ void tri_invit_solve(const double* __restrict__ d, const double* __restrict__ e, int p,
-                                                double lam, double tol, double* __restrict__ Z, int ldz, int j,
-                                                double* __restrict__ U0, double* __restrict__ U1,
-                                                double* __restrict__ LM, int nb, uint64_t& sw0, uint64_t& sw1) {
-  const int p8 = (p + 7) & ~7;
+// one inverse-iteration solve of (T - lam I) z = Z[:, j] for the vectors
+// j = j0 + t, t < nb (thread t); factor = true builds the LU, else reuses it.
+// The loads of the next step are issued before the current step's stores.
+__device__ void tri_invit_solve(const double* __restrict__ d, const double* __restrict__ e,
+                                const double* __restrict__ inve, int p, double lam, double tol, double* Z,
+                                int ldz, int j, double* ws, uint8_t* sw, int nb, int t, bool factor) {
+  double* U0 = ws;
+  double* U1 = ws + p * nb;
+  double* U2 = ws + 2 * p * nb;
+  double* LM = ws + 3 * p * nb;
   double y = Z[j];
-  double c0 = d[0] - lam, c1 = e[0];
-  if (FACTOR) sw0 = sw1 = 0;
-  for (int i0 = 0; i0 < p8; i0 += 8) {
-    // step i eliminates row i + 1; the last chunk's last step meets row p8,
-    // which is again one of the identity
-    double bz[8], dn[8], en[9], lm[8];
-    const bool lastc = i0 + 8 == p8;
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int i = i0 + u;
-      if (u < 7) bz[u] = Z[(i + 1) * ldz + j];
-      else bz[u] = lastc ? 0.0 : Z[(i + 1) * ldz + j];
-      if (FACTOR) {
-        dn[u] = (i + 1 < p) ? d[i + 1] - lam : 1.0;
-        en[u] = e[i];
+  double bnx = (p > 1) ? Z[ldz + j] : 0.0;
+  if (factor) {
+    double c0 = d[0] - lam, c1 = (p > 1) ? e[0] : 0.0;
+    for (int i = 0; i + 1 < p; ++i) {
+      const double ei = e[i];
+      const double dn = d[i + 1] - lam;
+      const double en = (i + 2 < p) ? e[i + 1] : 0.0;
+      const double ie = inve[i];
+      const double bn = bnx;
+      if (i + 2 < p) bnx = Z[(i + 2) * ldz + j];
+      if (fabs(c0) >= fabs(ei)) {
+        if (fabs(c0) < tol) c0 = (c0 < 0.0) ? -tol : tol;
+        const double li = ei / c0;
+        U0[i * nb + t] = 1.0 / c0;
+        U1[i * nb + t] = c1;
+        U2[i * nb + t] = 0.0;
+        LM[i * nb + t] = li;
+        sw[i * nb + t] = 0;
+        Z[i * ldz + j] = y;
+        y = bn - li * y;
+        c0 = dn - li * c1;
+        c1 = en;
       } else {
-        lm[u] = LM[i * nb];
+        const double li = c0 * ie;
+        U0[i * nb + t] = ie;
+        U1[i * nb + t] = dn;
+        U2[i * nb + t] = en;
+        LM[i * nb + t] = li;
+        sw[i * nb + t] = 1;
+        Z[i * ldz + j] = bn;
+        y = y - li * bn;
+        const double nc0 = c1 - li * dn;
+        c1 = -li * en;
+        c0 = nc0;
       }
     }
-    if (FACTOR) en[8] = e[i0 + 8];
-    uint32_t m = 0;
-    if (!FACTOR) m = (uint32_t)(((i0 < 64) ? sw0 : sw1) >> (i0 & 63));
-    double zo[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      bool s;
-      double li;
-      if (FACTOR) {
-        const double ei = en[u];
-        s = fabs(c0) < fabs(ei);
-        double piv = s ? ei : c0;
-        piv = (fabs(piv) < tol) ? copysign(tol, piv) : piv;
-        const double r = rcp2(piv);
-        li = (s ? c0 : ei) * r;
-        const double u1 = s ? dn[u] : c1;
-        U0[(i0 + u) * nb] = r;
-        U1[(i0 + u) * nb] = u1;
-        LM[(i0 + u) * nb] = li;
-        m |= s ? (1u << u) : 0u;
-        c0 = fma(-li, u1, s ? c1 : dn[u]);
-        c1 = s ? -li * en[u + 1] : en[u + 1];
-      } else {
-        s = (m >> u) & 1;
-        li = lm[u];
+    if (fabs(c0) < tol) c0 = (c0 < 0.0) ? -tol : tol;
+    U0[(p - 1) * nb + t] = 1.0 / c0;
+    U1[(p - 1) * nb + t] = 0.0;
+    U2[(p - 1) * nb + t] = 0.0;
+  } else {
+    double lmx = LM[t];
+    uint8_t swx = sw[t];
+    for (int i = 0; i + 1 < p; ++i) {
+      const double bn = bnx, li = lmx;
+      const uint8_t si = swx;
+      if (i + 2 < p) bnx = Z[(i + 2) * ldz + j];
+      if (i + 1 < p) {
+        lmx = LM[(i + 1) * nb + t];
+        swx = sw[(i + 1) * nb + t];
       }
-      const double zi = s ? bz[u] : y;
-      zo[u] = zi;
-      y = fma(-li, zi, s ? y : bz[u]);
+      if (si == 0) {
+        Z[i * ldz + j] = y;
+        y = bn - li * y;
+      } else {
+        Z[i * ldz + j] = bn;
+        y = y - li * bn;
+      }
     }
-    if (FACTOR) {
-      if (i0 < 64) sw0 |= (uint64_t)m << i0;
-      else sw1 |= (uint64_t)m << (i0 - 64);
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) Z[(i0 + u) * ldz + j] = zo[u];
   }
-  // (the scale of z is left to the Cholesky-QR)
-  double z1 = 0.0, z2 = 0.0;
-  for (int i0 = p8 - 8; i0 >= 0; i0 -= 8) {
-    double zr[8], u0[8], u1[8], u2[8];
-    const uint32_t m = (uint32_t)(((i0 < 64) ? sw0 : sw1) >> (i0 & 63));
-#pragma unroll
-    for (int u = 7; u >= 0; --u) {
-      const int i = i0 + u;
-      zr[u] = Z[i * ldz + j];
-      u0[u] = U0[i * nb];
-      u1[u] = U1[i * nb];
-      u2[u] = ((m >> u) & 1) ? e[i + 1] : 0.0;
+  Z[(p - 1) * ldz + j] = y;
+  double z1 = 0.0, z2 = 0.0, zmax = 0.0;
+  double zx = Z[(p - 1) * ldz + j], u0x = U0[(p - 1) * nb + t], u1x = U1[(p - 1) * nb + t],
+         u2x = U2[(p - 1) * nb + t];
+  for (int i = p - 1; i >= 0; --i) {
+    const double zr = zx, u0 = u0x, u1 = u1x, u2 = u2x;
+    if (i > 0) {
+      zx = Z[(i - 1) * ldz + j];
+      u0x = U0[(i - 1) * nb + t];
+      u1x = U1[(i - 1) * nb + t];
+      u2x = U2[(i - 1) * nb + t];
     }
-#pragma unroll
-    for (int u = 7; u >= 0; --u) {
-      const double zi = fma(-u1[u], z1, fma(-u2[u], z2, zr[u])) * u0[u];
-      zr[u] = zi;
-      z2 = z1;
-      z1 = zi;
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) Z[(i0 + u) * ldz + j] = zr[u];
+    const double zi = (zr - u1 * z1 - u2 * z2) * u0;
+    Z[i * ldz + j] = zi;
+    zmax = fmax(zmax, fabs(zi));
+    z2 = z1;
+    z1 = zi;
   }
+  const double sc = (zmax > 0.0 && zmax < INFINITY) ? 1.0 / zmax : 1.0;
+#pragma unroll 4
+  for (int i = 0; i < p; ++i) Z[i * ldz + j] *= sc;
 }
 
-// ---- small products on the fp64 MFMA 16x16x4 -------------------------------
-// Lane l holds A[l % 16][l / 16] and B[l / 16][l % 16]; accumulator register
-// r is row 4 r + l / 16, column l % 16.
-__device__ __forceinline__ d4 mma64(double a, double b, d4 c) {
-  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-}
-// One 16 x 16 tile of A^T B (A: K x m, B: K x n), by one wave
-__device__ __forceinline__ d4 tile_tn(const double* A, int lda, int i0, int m, const double* B, int ldb, int j0,
-                                      int n, int K) {
-  const int g = (threadIdx.x & 63) >> 4, r = threadIdx.x & 15;
-  const bool vi = i0 + r < m, vj = j0 + r < n;
-  d4 acc = {0.0, 0.0, 0.0, 0.0};
-  for (int k0 = 0; k0 < K; k0 += 16) {
-    double av[4], bv[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int k = k0 + 4 * u + g;
-      av[u] = (vi && k < K) ? A[k * lda + i0 + r] : 0.0;
-      bv[u] = (vj && k < K) ? B[k * ldb + j0 + r] : 0.0;
+// G (lower, n x n, stride ldg) <- Z^T Z for Z (p x n, stride ldz), every
+// thread; ends with a barrier
+__device__ void blk_gram_lower(const double* Z, int ldz, int p, int n, double* G, int ldg) {
+  for (int idx = threadIdx.x; idx < n * n; idx += blockDim.x) {
+    const int r = idx / n, c = idx - r * n;
+    if (c > r) continue;
+    double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
+    int i = 0;
+    for (; i + 4 <= p; i += 4) {
+      s0 += Z[i * ldz + r] * Z[i * ldz + c];
+      s1 += Z[(i + 1) * ldz + r] * Z[(i + 1) * ldz + c];
+      s2 += Z[(i + 2) * ldz + r] * Z[(i + 2) * ldz + c];
+      s3 += Z[(i + 3) * ldz + r] * Z[(i + 3) * ldz + c];
     }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) acc = mma64(av[u], bv[u], acc);
-  }
-  return acc;
-}
-// C (m x n) = A^T B by the workgroup's waves; ends with a barrier
-__device__ __forceinline__ void blk_gemm_tn(const double* A, int lda, const double* B, int ldb, int K, int m,
-                                            int n, double* C, int ldc) {
-  const int lane = threadIdx.x & 63, g = lane >> 4, r = lane & 15;
-  const int tm = (m + 15) >> 4, tn = (n + 15) >> 4;
-  for (int t = wave_id(); t < tm * tn; t += blockDim.x >> 6) {
-    const int i0 = 16 * (tn == 1 ? t : t / tn), j0 = tn == 1 ? 0 : 16 * (t % tn);
-    const d4 acc = tile_tn(A, lda, i0, m, B, ldb, j0, n, K);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int i = i0 + 4 * q + g;
-      if (i < m && j0 + r < n) C[i * ldc + j0 + r] = acc[q];
-    }
-  }
-  __syncthreads();
-}
-// X (n x q) -= Y (n x K) C (K x q) by the workgroup's waves; ends with a barrier
-__device__ __forceinline__ void blk_sub_mm(double* X, int ldx, const double* Y, int ldy, const double* C, int ldc,
-                                           int n, int K, int q) {
-  const int lane = threadIdx.x & 63, g = lane >> 4, r = lane & 15;
-  const int tm = (n + 15) >> 4, tn = (q + 15) >> 4;
-  for (int t = wave_id(); t < tm * tn; t += blockDim.x >> 6) {
-    const int i0 = 16 * (tn == 1 ? t : t / tn), j0 = tn == 1 ? 0 : 16 * (t % tn);
-    d4 acc = {0.0, 0.0, 0.0, 0.0};
-    for (int k0 = 0; k0 < K; k0 += 16) {
-      double av[4], bv[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int k = k0 + 4 * u + g;
-        av[u] = (i0 + r < n && k < K) ? Y[(i0 + r) * ldy + k] : 0.0;
-        bv[u] = (j0 + r < q && k < K) ? C[k * ldc + j0 + r] : 0.0;
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) acc = mma64(av[u], bv[u], acc);
-    }
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const int i = i0 + 4 * c + g;
-      if (i < n && j0 + r < q) X[i * ldx + j0 + r] -= acc[c];
-    }
+    for (; i < p; ++i) s0 += Z[i * ldz + r] * Z[i * ldz + c];
+    G[r * ldg + c] = (s0 + s1) + (s2 + s3);
   }
   __syncthreads();
 }
 
-// Row l % 16 of the Gram P^T P (p x n, n <= 16), padded with the identity, in
-// every lane of the wave; tr: the wave's transpose area.
-__device__ __forceinline__ void gram16_rows(const double* P, int ldp, int p, int n, double* tr, double (&g)[16]) {
-  const int lane = threadIdx.x & 63, gq = lane >> 4, r = lane & 15;
-  const d4 acc = tile_tn(P, ldp, 0, n, P, ldp, 0, n, p);
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int i = 4 * q + gq;
-    tr[i * 17 + r] = (i == r && i >= n) ? 1.0 : acc[q];
-  }
+// Z <- Z L^-T with L L^T = G (the Gram Z^T Z from blk_gram_lower), by one
+// wave; G is overwritten by L (n <= 16: factored in registers by
+// reg_chol16).  False when a pivot is not > 0.
+template <int NR>
+__device__ bool wave_cholqr(double* Z, int ldz, int p, int n, double* G, int ldg, double* linv) {
+  const int l = threadIdx.x & 63;
   wave_sync();
+  if (n <= 16) {
+    if (!wave_chol16_lds<false, true, false>(G, ldg, n, 0.0, G, ldg, linv)) return false;
+    wave_sync();
+  } else {
+    for (int k = 0; k < n; ++k) {
+      const double gkk = G[k * ldg + k];
+      if (!(gkk > 0.0) || !(gkk < INFINITY)) return false;
+      const double lkk = sqrt(gkk), inv = 1.0 / lkk;
 #pragma unroll
-  for (int c = 0; c < 16; ++c) g[c] = tr[r * 17 + c];
-  wave_sync();
-}
-
-// Z (p x n, stride ldz) <- orthonormal columns: by panels of 16, each made
-// orthogonal to the panels before it, then Cholesky-QR.  Every wave forms the
-// panel's Gram and factor itself (the same bits), so that the only barriers
-// are around the writes of Z.  scr: tri_layout's `orth`.  False (uniform) on
-// breakdown.  Every thread calls it; ends with a barrier.
-__device__ __forceinline__ bool blk_cholqr(double* Z, int ldz, int p, int n, double* scr) {
-  double* tr = scr + wave_id() * kTrans;
-  double* C = scr + 4 * kTrans;
-  for (int j0 = 0; j0 < n; j0 += 16) {
-    const int nb = min(16, n - j0);
-    double* P = Z + j0;
-    if (j0 > 0) {
-      blk_gemm_tn(Z, ldz, P, ldz, p, j0, nb, C, 17);
-      blk_sub_mm(P, ldz, Z, ldz, C, 17, p, j0, nb);
+      for (int h = 0; h < NR; ++h) {
+        const int r = l + 64 * h;
+        if (r > k && r < n) G[r * ldg + k] *= inv;
+      }
+      if (l == 0) {
+        G[k * ldg + k] = lkk;
+        linv[k] = inv;
+      }
+      wave_sync();
+      // trailing update, lane c owning column c: G[r][c] -= L[r][k] L[c][k], r >= c > k
+#pragma unroll
+      for (int h = 0; h < NR; ++h) {
+        const int c = l + 64 * h;
+        if (c > k && c < n) {
+          const double lck = G[c * ldg + k];
+          for (int r0 = c; r0 < n; r0 += 4) {
+            double lk[4], gc[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+              const int r = min(r0 + u, n - 1);
+              lk[u] = G[r * ldg + k];
+              gc[u] = G[r * ldg + c];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+              if (r0 + u < n) G[(r0 + u) * ldg + c] = gc[u] - lk[u] * lck;
+          }
+        }
+      }
+      wave_sync();
     }
-    double g[16], inv[16];
-    gram16_rows(P, ldz, p, nb, tr, g);
-    const bool ok = chol16_rows(g, nb, inv);
-    __syncthreads();  // every wave has read the panel
-    if (!ok) return false;
-    trsm16_rows(P, ldz, p, nb, g, inv);
-    __syncthreads();
   }
+#pragma unroll
+  for (int h = 0; h < NR; ++h) {
+    const int i = l + 64 * h;
+    if (i < p) {
+      for (int jj = 0; jj < n; ++jj) {
+        double s0 = Z[i * ldz + jj], s1 = 0.0;
+        int k = 0;
+        for (; k + 2 <= jj; k += 2) {
+          s0 -= Z[i * ldz + k] * G[jj * ldg + k];
+          s1 -= Z[i * ldz + k + 1] * G[jj * ldg + k + 1];
+        }
+        if (k < jj) s0 -= Z[i * ldz + k] * G[jj * ldg + k];
+        Z[i * ldz + jj] = (s0 + s1) * linv[jj];
+      }
+    }
+  }
+  wave_sync();
   return true;
 }
 
-// u = H_0 H_1 ... H_{p-2} z for the columns of Z: 16 lanes per vector, NT
-// rows per lane, four vectors per wave; reflector k - 1 is loaded while
-// reflector k is applied (PACK: from the packed store)
-template <int NT, bool PACK>
-__device__ __forceinline__ void blk_backtransform(double* Z, int ldz, int p, int nev, const double* vref,
-                                                  const double* beta) {
-  const int lane = threadIdx.x & 63, s = lane & 15;
-  for (int jb = 0; jb < nev; jb += 16) {
-    const int j = jb + 4 * wave_id() + (lane >> 4);
-    double z[NT];
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      const int i = s + 16 * t;
-      z[t] = (i < p && j < nev) ? Z[i * ldz + j] : 0.0;
-    }
-    double v[NT], b = 0.0;
-    auto load = [&](int k) {
-      b = beta[k];  // 0 for H_k = I
-#pragma unroll
-      for (int t = 0; t < NT; ++t) {
-        const int i = s + 16 * t;
-        if (PACK) v[t] = (i > k && i < p) ? vref[ref_off(p, k) - (k + 1) + i] : 0.0;
-        else v[t] = vref[64 * k + i];
-      }
-    };
-    if (p >= 2) load(p - 2);
-    for (int k = p - 2; k >= 0; --k) {
-      double vk[NT], dot = 0.0;
-      const double nb = -b;
-#pragma unroll
-      for (int t = 0; t < NT; ++t) {
-        vk[t] = v[t];
-        dot = fma(vk[t], z[t], dot);
-      }
-      if (k > 0) load(k - 1);
-      const double c = nb * row_sum(dot);
-#pragma unroll
-      for (int t = 0; t < NT; ++t) z[t] = fma(c, vk[t], z[t]);
-    }
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      const int i = s + 16 * t;
-      if (i < p && j < nev) Z[i * ldz + j] = z[t];
-    }
-  }
-  __syncthreads();
-}
-
-// The whole path (1-5) on a (device, p x p) scaled by ds (LDS) from both
-// sides; base: LDS laid out by tri_layout(p, nev), whose ev and Z receive the
-// result.  Every thread of a kEigThreads workgroup calls it; the return value
-// is uniform.
-__device__ __forceinline__ bool blk_tri_eigh(const double* __restrict__ a, int p, int nev, const double* ds, double* base,
-                             const TriLayout& L) {
+// The whole path (1-5).  A: p x lda in LDS (destroyed); base: the area after
+// A laid out by tri_layout(p, nev), whose ev and Z receive the result.  Every
+// thread calls it; the return value is uniform.
+__device__ bool blk_tri_eigh(double* A, int lda, int p, int nev, double* base, const TriLayout& L,
+                             int* flag) {
   double* d = base + L.d;
   double* e = base + L.e;
+  double* inve = base + L.inve;
+  double* e2 = base + L.e2;
   double* beta = base + L.beta;
-  double* vref = base + L.vref;
   double* ev = base + L.ev;
   double* Z = base + L.Z;
-  dd2* de = reinterpret_cast<dd2*>(base + L.de);
   const int ldz = L.ldz;
-  const int lane = threadIdx.x & 63;
-  if (p <= 48) reg_tridiag<1, 12>(a, p, ds, d, e, beta, vref, base + L.lu);
-  else if (p <= 64) reg_tridiag<1, 16>(a, p, ds, d, e, beta, vref, base + L.lu);
-  else reg_tridiag<2, 24>(a, p, ds, d, e, beta, vref, base + L.lu);
-  // Gershgorin interval and ||T||, by every wave
-  double gl = -INFINITY, gu = -INFINITY;  // (gl holds -min)
-  bool bad = false;
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int i = lane + 64 * h;
-    if (i < p) {
-      const double r = ((i > 0) ? fabs(e[i - 1]) : 0.0) + ((i + 1 < p) ? fabs(e[i]) : 0.0);
-      gl = fmax(gl, r - d[i]);
-      gu = fmax(gu, d[i] + r);
-      bad |= !(fabs(d[i]) + r < INFINITY);
-    }
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  blk_tridiag(A, lda, p, d, e, beta, base + L.vv, base + L.ww);
+  // Gershgorin interval, ||T||, pivmin (every thread, same order)
+  double gl = INFINITY, gu = -INFINITY, emax2 = 0.0;
+  for (int i = 0; i < p; ++i) {
+    const double r = ((i > 0) ? fabs(e[i - 1]) : 0.0) + ((i + 1 < p) ? fabs(e[i]) : 0.0);
+    gl = fmin(gl, d[i] - r);
+    gu = fmax(gu, d[i] + r);
+    if (i + 1 < p) emax2 = fmax(emax2, e[i] * e[i]);
   }
-  if (__ballot(bad) != 0) return false;
-  gl = -wave_max(gl);
-  gu = wave_max(gu);
-  double tnorm = fmax(fabs(gl), fabs(gu));
+  const double tnorm = fmax(fabs(gl), fabs(gu));
+  if (!(tnorm < INFINITY)) return false;
   if (tnorm == 0.0) {  // the zero matrix
-    for (int idx = threadIdx.x; idx < p * nev; idx += kEigThreads) {
+    for (int idx = threadIdx.x; idx < p * nev; idx += blockDim.x) {
       const int i = idx / nev, j = idx - i * nev;
       Z[i * ldz + j] = (i == j) ? 1.0 : 0.0;
     }
-    for (int j = threadIdx.x; j < nev; j += kEigThreads) ev[j] = 0.0;
+    for (int j = threadIdx.x; j < nev; j += blockDim.x) ev[j] = 0.0;
     __syncthreads();
     return true;
   }
-  // T scaled by a power of two to ||T|| in [1, 2)
-  const int ex = 1 - __builtin_amdgcn_frexp_exp(tnorm);
-  tnorm = __builtin_amdgcn_ldexp(tnorm, ex);
-  gl = __builtin_amdgcn_ldexp(gl, ex);
-  gu = __builtin_amdgcn_ldexp(gu, ex);
+  const double pivmin = 0x1.0p-1022 * fmax(1.0, emax2);
   const double tol = kEps * tnorm;
-  const double widen = 2.1 * (kEps * tnorm * p);
+  const double widen = 2.1 * (kEps * tnorm * p + 2.0 * pivmin);
   gl -= widen;
   gu += widen;
-  const int p8 = (p + 7) & ~7;
-  __syncthreads();  // the bounds are read
-  {
-    const int i = threadIdx.x;
-    double di = 0.0, ei = 0.0, em = 0.0;
-    if (i < p) {
-      di = __builtin_amdgcn_ldexp(d[i], ex);
-      ei = (i + 1 < p) ? __builtin_amdgcn_ldexp(e[i], ex) : 0.0;
-      em = (i > 0) ? __builtin_amdgcn_ldexp(e[i - 1], ex) : 0.0;
-    }
-    __syncthreads();
-    if (i < p) d[i] = di;
-    if (i <= p8) e[i] = ei;
-    // past the end: |d - x| > 1 with the sign of + and no coupling
-    if (i < p + 16) de[i] = (i < p) ? dd2{di, fmax(em * em, 0x1.0p-120)} : dd2{4.0, 0x1.0p-120};
+  for (int i = threadIdx.x; i + 1 < p; i += blockDim.x) {
+    e2[i] = e[i] * e[i];
+    const double piv = (fabs(e[i]) < tol) ? ((e[i] < 0.0) ? -tol : tol) : e[i];
+    inve[i] = (e[i] == 0.0) ? 0.0 : 1.0 / piv;
   }
+  __syncthreads();
+  blk_multisection(d, e2, p, nev, gl, gu, tnorm, pivmin, ev);
   // start vectors
-  for (int idx = threadIdx.x; idx < p8 * nev; idx += kEigThreads) {
+  for (int idx = threadIdx.x; idx < p * nev; idx += blockDim.x) {
     const int i = idx / nev, j = idx - i * nev;
-    if (i >= p) {
-      Z[i * ldz + j] = 0.0;
-      continue;
-    }
     const uint64_t z = sm64(kZeroColumnSeed ^ (0x5EEDull << 32) ^ ((uint64_t)j * (uint64_t)p + (uint64_t)i));
     Z[i * ldz + j] = (double)(z >> 11) * 0x1.0p-52 - 1.0;
   }
   __syncthreads();
-  blk_multisection(de, p, nev, gl, gu, tnorm, ev);
-  __syncthreads();
-  // two solves with a Cholesky-QR between them (block inverse iteration;
-  // with several batches the LU is rebuilt for the second solve), the
-  // back-transformation, then Cholesky-QR twice.  One pass leaves the vectors
-  // orthonormal to a few units of rounding when the Gram is well conditioned,
-  // yet the second pass is kept: the P coefficients are the small differences
-  // u_x - E, and dropping it whenever the columns' cosines were below 1e-3
-  // doubled the iterations of a dense generalized solve (n = 2000, 4 pairs:
-  // 51 against 25, the lowest pair lagging).
+  // two solves with a Cholesky-QR between them (block inverse iteration);
+  // with several batches the LU is rebuilt for the second solve
   const int nb = L.nb;
-  double* lu = base + L.lu;
-  uint64_t sw0 = 0, sw1 = 0;
-  for (int stage = 0; stage < 3; ++stage) {
-    if (stage < 2) {
-      for (int j0 = 0; j0 < nev; j0 += nb) {
-        const int t = threadIdx.x, j = j0 + t;
-        if (t < nb && j < nev) {
-          double *u0 = lu + t, *u1 = u0 + p8 * nb, *lm = u1 + p8 * nb;
-          if (stage == 0 || nb < nev) tri_invit_solve<true>(d, e, p, ev[j], tol, Z, ldz, j, u0, u1, lm, nb, sw0, sw1);
-          else tri_invit_solve<false>(d, e, p, ev[j], tol, Z, ldz, j, u0, u1, lm, nb, sw0, sw1);
-        }
-        __syncthreads();
+  for (int it = 0; it < 2; ++it) {
+    for (int j0 = 0; j0 < nev; j0 += nb) {
+      const int t = threadIdx.x;
+      if (t < nb && j0 + t < nev) {
+        const int j = j0 + t;
+        tri_invit_solve(d, e, inve, p, ev[j], tol, Z, ldz, j, base + L.ws,
+                        reinterpret_cast<uint8_t*>(base + L.sw), nb, t, it == 0 || nb < nev);
       }
+      __syncthreads();
     }
-    if (stage == 1) {
-      if (p <= 48) blk_backtransform<3, false>(Z, ldz, p, nev, vref, beta);
-      else if (p <= 64) blk_backtransform<4, false>(Z, ldz, p, nev, vref, beta);
-      else blk_backtransform<6, true>(Z, ldz, p, nev, vref, beta);
-      for (int j = threadIdx.x; j < nev; j += kEigThreads) ev[j] = __builtin_amdgcn_ldexp(ev[j], -ex);
+    if (it == 0) {
+      blk_gram_lower(Z, ldz, p, nev, base + L.G, nev + 1);
+      if (wave == 0) {
+        const bool ok = (p <= 64) ? wave_cholqr<1>(Z, ldz, p, nev, base + L.G, nev + 1, base + L.linv)
+                                  : wave_cholqr<2>(Z, ldz, p, nev, base + L.G, nev + 1, base + L.linv);
+        if (lane == 0) *flag = ok ? 1 : 0;
+      }
+      __syncthreads();
+      const bool ok = *flag != 0;
+      __syncthreads();
+      if (!ok) return false;
     }
-    if (!blk_cholqr(Z, ldz, p, nev, base + L.orth)) return false;
+  }
+  // u = H_0 H_1 ... H_{p-3} z, one wave per vector
+  const int nw = blockDim.x >> 6;
+  for (int j = wave; j < nev; j += nw) {
+    double z[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int i = lane + 64 * h;
+      z[h] = (i < p) ? Z[i * ldz + j] : 0.0;
+    }
+#pragma unroll 2
+    for (int k = p - 3; k >= 0; --k) {
+      const double b = beta[k];  // 0 for H_k = I: then s = 0
+      double v[2];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int i = lane + 64 * h;
+        v[h] = (i > k && i < p) ? A[i * lda + k] : 0.0;
+      }
+      const double s = b * wave_sum(v[0] * z[0] + v[1] * z[1]);
+      z[0] -= s * v[0];
+      z[1] -= s * v[1];
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int i = lane + 64 * h;
+      if (i < p) Z[i * ldz + j] = z[h];
+    }
+  }
+  __syncthreads();
+  // Cholesky-QR twice, with the A area as Gram scratch.  One pass leaves
+  // the vectors orthonormal to a few units of rounding when the Gram is
+  // well conditioned, yet the second pass is kept: the P coefficients are
+  // the small differences u_x - E, and dropping it whenever the columns'
+  // cosines were below 1e-3 doubled the iterations of a dense generalized
+  // solve (n = 2000, 4 pairs: 51 against 25, the lowest pair lagging).
+  for (int pass = 0; pass < 2; ++pass) {
+    blk_gram_lower(Z, ldz, p, nev, A, lda);
+    if (wave == 0) {
+      const bool ok = (p <= 64) ? wave_cholqr<1>(Z, ldz, p, nev, A, lda, base + L.linv)
+                                : wave_cholqr<2>(Z, ldz, p, nev, A, lda, base + L.linv);
+      if (lane == 0) *flag = ok ? 1 : 0;
+    }
+    __syncthreads();
+    const bool ok = *flag != 0;
+    __syncthreads();
+    if (!ok) return false;
   }
   return true;
 }
 
-__global__ __launch_bounds__(kEigThreads) void k_small_eigh(const double* __restrict__ a, int p,
-                                                            double* __restrict__ evals,
-                                                            double* __restrict__ evecs, int* sweeps) {
-  extern __shared__ __attribute__((aligned(16))) double smem[];
-  __shared__ JacobiLds J;
-  __shared__ double ds[kMaxP];
-  for (int i = threadIdx.x; i < p; i += kEigThreads) ds[i] = 1.0;
-  __syncthreads();
-  const TriLayout T = tri_layout(p, p);
-  if (blk_tri_eigh(a, p, p, ds, smem, T)) {
-    for (int idx = threadIdx.x; idx < p * p; idx += kEigThreads) {
-      const int i = idx / p, j = idx - i * p;
-      const double sg = (smem[T.Z + j * T.ldz + j] < 0.0) ? -1.0 : 1.0;
-      evecs[i * p + j] = sg * smem[T.Z + i * T.ldz + j];
-    }
-    for (int j = threadIdx.x; j < p; j += kEigThreads) evals[j] = smem[T.ev + j];
-    if (threadIdx.x == 0 && sweeps != nullptr) *sweeps = 0;
-    return;
-  }
-  __syncthreads();
+__global__ __launch_bounds__(1024) void k_small_eigh(const double* __restrict__ a, int p,
+                                                    double* __restrict__ evals,
+                                                    double* __restrict__ evecs, int* sweeps) {
+  extern __shared__ double smem[];
+  __shared__ int tflag;
   const int ld = p + 1;
-  double* A = smem;
-  double* V = smem + p * ld;
-  load_sym(a, p, ds, A, ld);
-  const int sw = blk_jacobi<kEigThreads>(A, ld, V, ld, p, J.cs, J.pr, J.flags, J.scratch);
-  blk_sort_evals(A, ld, p, J.perm);
-  for (int idx = threadIdx.x; idx < p * p; idx += kEigThreads) {
-    const int i = idx / p, j = idx - i * p;
-    const double sg = (V[j * ld + J.perm[j]] < 0.0) ? -1.0 : 1.0;
-    evecs[i * p + j] = sg * V[i * ld + J.perm[j]];
+  const TriLayout T = tri_layout(p, p);
+  if (T.nb >= 1) {
+    load_sym(a, p, smem, ld);
+    double* base = smem + p * ld;
+    if (blk_tri_eigh(smem, ld, p, p, base, T, &tflag)) {
+      for (int idx = threadIdx.x; idx < p * p; idx += blockDim.x) {
+        const int i = idx / p, j = idx - i * p;
+        const double sg = (base[T.Z + j * T.ldz + j] < 0.0) ? -1.0 : 1.0;
+        evecs[i * p + j] = sg * base[T.Z + i * T.ldz + j];
+      }
+      for (int j = threadIdx.x; j < p; j += blockDim.x) evals[j] = base[T.ev + j];
+      if (threadIdx.x == 0 && sweeps != nullptr) *sweeps = 0;
+      return;
+    }
   }
-  for (int j = threadIdx.x; j < p; j += kEigThreads) evals[j] = A[J.perm[j] * ld + J.perm[j]];
+  EigLds L = eig_lds(smem, p, 1);
+  load_sym(a, p, L.A, ld);
+  const int sw = blk_jacobi(L.A, ld, L.V, ld, p, L.cs, L.pr, L.flags, L.scratch);
+  blk_sort_evals(L.A, ld, p, L.perm);
+  for (int idx = threadIdx.x; idx < p * p; idx += blockDim.x) {
+    const int i = idx / p, j = idx - i * p;
+    const double sg = (L.V[j * ld + L.perm[j]] < 0.0) ? -1.0 : 1.0;
+    evecs[i * p + j] = sg * L.V[i * ld + L.perm[j]];
+  }
+  for (int j = threadIdx.x; j < p; j += blockDim.x) evals[j] = L.A[L.perm[j] * ld + L.perm[j]];
   if (threadIdx.x == 0 && sweeps != nullptr) *sweeps = sw;
 }
 
@@ -1271,11 +1117,11 @@ hipError_t small_eigh(const double* a, int p, double* evals, double* evecs, int*
   static bool attr = false;
   if (!attr) {
     (void)hipFuncSetAttribute((const void*)k_small_eigh, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              kEigLdsBytes);
+                              152 * 1024);
     (void)hipGetLastError();
     attr = true;
   }
-  hipLaunchKernelGGL(k_small_eigh, dim3(1), dim3(kEigThreads), kEigLdsBytes, s, a, p, evals, evecs, sweeps);
+  hipLaunchKernelGGL(k_small_eigh, dim3(1), dim3(1024), kEigLdsBytes, s, a, p, evals, evecs, sweeps);
   return hipGetLastError();
 }
 
@@ -1283,7 +1129,6 @@ hipError_t small_eigh(const double* a, int p, double* evals, double* evecs, int*
 // SVQB (Stathopoulos-Wu) coefficient for an n x n overlap M: X <- X U S^-1/2,
 // eigenvalues clamped below eps * max.  Writes the n x n coefficient to Cf.
 // Uses Ws (2 * n * (n+1) doubles) as Jacobi workspace.
-template <int NT>
 __device__ __forceinline__ bool blk_svqb_coef(const double* M, int ldm, int n, double* Cf, int ldc, double* Ws,
                               double* cs, int* pr, int* flag, int* perm, double* scratch) {
   const int ld = n + 1;
@@ -1294,7 +1139,7 @@ __device__ __forceinline__ bool blk_svqb_coef(const double* M, int ldm, int n, d
     A[i * ld + j] = M[i * ldm + j];
   }
   __syncthreads();
-  blk_jacobi<NT>(A, ld, U, ld, n, cs, pr, flag, scratch);
+  blk_jacobi(A, ld, U, ld, n, cs, pr, flag, scratch);
   double smax = 0.0;
   for (int i = 0; i < n; ++i) smax = fmax(smax, A[i * ld + i]);
   if (!(smax > 0.0)) return false;
@@ -1312,188 +1157,138 @@ __device__ __forceinline__ bool blk_svqb_coef(const double* M, int ldm, int n, d
 // eigenvectors; optionally u_p = ortho(u_x[:, a0:m] - E[:, a0:m]; u_x) in R^p
 // by Alg. 3 / Alg. 2 (the same readings as on n-vectors).
 
-// Rayleigh-Ritz coefficients (see small_rr in internal.h).  JAC: the Jacobi
-// eigensolver (LOBPCG_OPT_RR_JACOBI), 1024 threads; else the tridiagonal
-// path on kEigThreads, with Jacobi where that breaks down.
-template <bool JAC>
-__global__ __launch_bounds__(JAC ? 1024 : kEigThreads) void k_small_rr(
-    const double* __restrict__ a, int p, int m, int a0, int want_up, double tau,
-    const OrthoState* __restrict__ pend, int woff, double* __restrict__ theta_all,
-    double* __restrict__ U, int* __restrict__ info) {
-  extern __shared__ __attribute__((aligned(16))) double smem[];
-  __shared__ JacobiLds J;
-  __shared__ double ds[kMaxP];  // column scaling of V that is still pending
-  __shared__ double sg[kMaxP];
+// sym(a) into A (stride lda), with the pending column scaling of the W block
+// (see small_rr in internal.h) applied from both sides when pend != nullptr
+__device__ void load_rr_matrix(const double* a, int p, double* A, int lda, const OrthoState* pend,
+                               int woff) {
+  load_sym(a, p, A, lda);
+  if (pend != nullptr) {
+    const int nws = pend->nw;
+    for (int idx = threadIdx.x; idx < p * p; idx += blockDim.x) {
+      const int i = idx / p, j = idx - i * p;
+      const double di = (i >= woff && i < woff + nws) ? pend->dscale[i - woff] : 1.0;
+      const double dj = (j >= woff && j < woff + nws) ? pend->dscale[j - woff] : 1.0;
+      A[i * lda + j] *= di * dj;
+    }
+    __syncthreads();
+  }
+}
+
+__global__ __launch_bounds__(1024) void k_small_rr(const double* __restrict__ a, int p, int m,
+                                                  int a0, int want_up, double tau,
+                                                  const OrthoState* __restrict__ pend, int woff,
+                                                  double* __restrict__ theta_all,
+                                                  double* __restrict__ U, int* __restrict__ info,
+                                                  int jacobi) {
+  extern __shared__ double smem[];
+  EigLds L = eig_lds(smem, p, m);
+  const int ld = p + 1;
   __shared__ ShiftCount cnt;
   __shared__ int zeros;
-  __shared__ int stalled, passes, grams, updates;
+  __shared__ int stalled, passes, grams, updates, tflag;
   if (threadIdx.x == 0) {
     cnt.factorizations = cnt.failed = cnt.shifted = cnt.svqb = 0;
     zeros = stalled = passes = grams = updates = 0;
   }
-  {
-    const bool scaled = (pend != nullptr) && pend->pending_scale;
-    const int nws = scaled ? pend->nw : 0;
-    for (int i = threadIdx.x; i < p; i += blockDim.x)
-      ds[i] = (i >= woff && i < woff + nws) ? pend->dscale[i - woff] : 1.0;
-  }
-  __syncthreads();
+  const bool scaled = (pend != nullptr) && pend->pending_scale;
+  double* Us = L.A;  // sorted eigenvectors u_x (first m columns), stride ld
   int sw = 0;
-  // sorted eigenvectors u_x (first m columns), stride ldu, and the LDS after them
-  double *Us, *work;
-  int ldu;
+  const TriLayout T = tri_layout(p, m);
   bool tri = false;
-  if constexpr (!JAC) {
-    const TriLayout T = tri_layout(p, m);
-    tri = blk_tri_eigh(a, p, m, ds, smem, T);
+  if (!jacobi && T.nb >= 1) {
+    load_rr_matrix(a, p, L.A, ld, scaled ? pend : nullptr, woff);
+    double* base = L.A + p * ld;
+    tri = blk_tri_eigh(L.A, ld, p, m, base, T, &tflag);
     if (tri) {
-      Us = smem + T.Z;
-      ldu = T.ldz;
-      work = smem + T.work;
-      for (int j = threadIdx.x; j < m; j += blockDim.x) {
-        theta_all[j] = smem[T.ev + j];
-        // orientation: u[j][j] >= 0, so that u_x - E is the small update X_new - X_old
-        sg[j] = (Us[j * ldu + j] < 0.0) ? -1.0 : 1.0;
-      }
-      __syncthreads();
+      for (int j = threadIdx.x; j < m; j += blockDim.x) theta_all[j] = base[T.ev + j];
+      // orientation: u[j][j] >= 0, so that u_x - E is the small update X_new - X_old
       for (int idx = threadIdx.x; idx < p * m; idx += blockDim.x) {
         const int i = idx / m, j = idx - i * m;
-        Us[i * ldu + j] *= sg[j];
+        const double sg = (base[T.Z + j * T.ldz + j] < 0.0) ? -1.0 : 1.0;
+        Us[i * ld + j] = sg * base[T.Z + i * T.ldz + j];
       }
       __syncthreads();
     }
   }
   if (!tri) {
-    const int ld = p + 1;
-    double* V = smem + p * ld;
-    Us = smem;
-    ldu = ld;
-    work = V;
-    __syncthreads();
-    load_sym(a, p, ds, Us, ld);
-    sw = blk_jacobi<JAC ? 1024 : kEigThreads>(Us, ld, V, ld, p, J.cs, J.pr, J.flags, J.scratch);
-    blk_sort_evals(Us, ld, p, J.perm);
-    for (int j = threadIdx.x; j < m; j += blockDim.x) theta_all[j] = Us[J.perm[j] * ld + J.perm[j]];
+    load_rr_matrix(a, p, L.A, ld, scaled ? pend : nullptr, woff);
+    sw = blk_jacobi(L.A, ld, L.V, ld, p, L.cs, L.pr, L.flags, L.scratch);
+    blk_sort_evals(L.A, ld, p, L.perm);
+    for (int j = threadIdx.x; j < m; j += blockDim.x) theta_all[j] = L.A[L.perm[j] * ld + L.perm[j]];
     __syncthreads();
     for (int idx = threadIdx.x; idx < p * p; idx += blockDim.x) {
       const int i = idx / p, j = idx - i * p;
-      const double s = (V[j * ld + J.perm[j]] < 0.0) ? -1.0 : 1.0;
-      Us[i * ld + j] = s * V[i * ld + J.perm[j]];
+      const double sg = (L.V[j * ld + L.perm[j]] < 0.0) ? -1.0 : 1.0;
+      Us[i * ld + j] = sg * L.V[i * ld + L.perm[j]];
     }
     __syncthreads();
   }
   const int na = want_up ? (m - a0) : 0;
   const int q = m + na;
-  // 16 lanes to a row of the small matrices from here on
-  const int row0 = threadIdx.x >> 4, col0 = threadIdx.x & 15, rstep = blockDim.x >> 4;
   // u_x (row scaling for a pending W scaling is applied when U is written)
-  for (int i = row0; i < p; i += rstep)
-    for (int j = col0; j < m; j += 16) U[i * q + j] = ds[i] * Us[i * ldu + j];
+  for (int idx = threadIdx.x; idx < p * m; idx += blockDim.x) {
+    const int i = idx / m, j = idx - i * m;
+    const double di = (scaled && i >= woff && i < woff + pend->nw) ? pend->dscale[i - woff] : 1.0;
+    U[i * q + j] = di * Us[i * ld + j];
+  }
   int bad = 0;
   if (na > 0) {
-    // X (p x na), C (m x na), M and its factor (na x na), SVQB workspace;
-    // odd strides, so that a column's entries lie in different banks
-    const int ldx = na | 1;
-    double* X = work;
-    double* C = X + p * ldx;
-    double* M = C + m * ldx;
-    double* Lc = M + na * ldx;
-    double* Ws = Lc + na * ldx;  // max(2 na (na + 1), p na, one transpose per wave)
+    // V area becomes: X (p x na), C (m x na), M (na x na), Lc (na x na), Li, svqb workspace
+    double* X = L.V;
+    const int ldx = na;
+    double* C = X + p * na;
+    double* M = C + m * na;
+    double* Lc = M + na * na;
+    double* Ws = Lc + na * na;
     // u~_p = u_x[:, a0:m] - E[:, a0:m]
-    for (int i = row0; i < p; i += rstep)
-      for (int j = col0; j < na; j += 16) X[i * ldx + j] = Us[i * ldu + a0 + j] - ((i == a0 + j) ? 1.0 : 0.0);
+    for (int idx = threadIdx.x; idx < p * na; idx += blockDim.x) {
+      const int i = idx / na, j = idx - i * na;
+      X[i * ldx + j] = Us[i * ld + a0 + j] - ((i == a0 + j) ? 1.0 : 0.0);
+    }
     __syncthreads();
-    blk_normalize(X, ldx, p, na, &zeros);
-    blk_gemm_tn(Us, ldu, X, ldx, p, m, na, C, ldx);  // C = u_x^T X
+    blk_normalize(X, ldx, p, na, L.cs, &zeros);
+    blk_gemm_tn(Us, ld, X, ldx, p, m, na, C, na);  // C = u_x^T X
     for (int pass = 0; pass < 4; ++pass) {
       if (threadIdx.x == 0) passes++;
-      blk_sub_mm(X, ldx, Us, ldu, C, ldx, p, m, na);
+      blk_sub_mm(X, ldx, Us, ld, C, na, p, m, na);
       // ortho(X): normalise, then Gram / check / shifted Cholesky / X L^-T
-      blk_normalize(X, ldx, p, na, &zeros);
+      blk_normalize(X, ldx, p, na, L.cs, &zeros);
       for (int it = 0; it < 6; ++it) {
+        blk_gemm_tn(X, ldx, X, ldx, p, na, na, M, na);
         if (threadIdx.x == 0) grams++;
-        bool fact;
-        if (!JAC && na <= 16) {
-          // every wave for itself (the same bits), M and its factor in registers
-          double g[16], f[16], inv[16];
-          gram16_rows(X, ldx, p, na, Ws + wave_id() * kTrans, g);
-          double dev = 0.0, diag = 0.0;
-#pragma unroll
-          for (int c = 0; c < 16; ++c) {
-            dev = fmax(dev, fabs(g[c] - (col0 == c ? 1.0 : 0.0)));
-            if (col0 == c) diag = g[c];
-            f[c] = g[c];
-          }
-          dev = row_max(dev);
-          if (__builtin_amdgcn_readfirstlane(dev <= tau)) break;
-          if (it == 5) {
-            if (threadIdx.x == 0) stalled++;
-            break;
-          }
-          // plain Cholesky, then shifts (as blk_shifted_chol)
-          if (threadIdx.x == 0) cnt.factorizations++;
-          fact = chol16_rows(f, na, inv);
-          if (!fact) {
-            if (threadIdx.x == 0) cnt.failed++;
-            const double normx = sqrt(fmax(row_sum(col0 < na ? diag : 0.0), 0.0));
-            double alpha = kShiftAlpha0;
-            for (int t = 0; t < kShiftRetries && !fact; ++t) {
-#pragma unroll
-              for (int c = 0; c < 16; ++c) f[c] = g[c] + (col0 == c ? alpha * kEps * normx : 0.0);
-              fact = chol16_rows(f, na, inv);
-              if (threadIdx.x == 0) {
-                cnt.factorizations++;
-                if (fact) cnt.shifted++;
-                else cnt.failed++;
-              }
-              alpha *= kShiftGrowth;
-            }
-          }
-          __syncthreads();  // every wave has read X
-          if (fact) {
-            trsm16_rows(X, ldx, p, na, f, inv);
-          } else if (threadIdx.x < 16 && col0 < na) {
-#pragma unroll
-            for (int c = 0; c < 16; ++c)
-              if (c < na) M[col0 * ldx + c] = g[c];
-          }
-          __syncthreads();
-        } else {
-          blk_gemm_tn(X, ldx, X, ldx, p, na, na, M, ldx);
-          double dev = 0.0;
-          for (int i = row0; i < na; i += rstep)
-            for (int j = col0; j < na; j += 16)
-              dev = fmax(dev, fabs(0.5 * (M[i * ldx + j] + M[j * ldx + i]) - (i == j ? 1.0 : 0.0)));
-          dev = blk_reduce_max(dev, J.scratch);
-          if (dev <= tau) break;
-          if (it == 5) {
-            if (threadIdx.x == 0) stalled++;
-            break;
-          }
-          // (both halves of M are read: the pair (i, j), (j, i) by one thread)
-          for (int i = row0; i < na; i += rstep)
-            for (int j = col0; j < i; j += 16) {
-              const double v = 0.5 * (M[i * ldx + j] + M[j * ldx + i]);
-              M[i * ldx + j] = v;
-              M[j * ldx + i] = v;
-            }
-          __syncthreads();
-          fact = blk_shifted_chol(M, ldx, na, Lc, ldx, J.flags, &cnt);
-          if (fact) blk_trsm_rt(X, ldx, p, na, Lc, ldx);
+        double dev = 0.0;
+        for (int idx = threadIdx.x; idx < na * na; idx += blockDim.x) {
+          const int i = idx / na, j = idx - i * na;
+          const double v = 0.5 * (M[i * na + j] + M[j * na + i]) - (i == j ? 1.0 : 0.0);
+          dev = fmax(dev, fabs(v));
         }
-        if (!fact) {
+        dev = blk_reduce_max(dev, L.scratch);
+        if (dev <= tau) break;
+        if (it == 5) {
+          if (threadIdx.x == 0) stalled++;
+          break;
+        }
+        for (int idx = threadIdx.x; idx < na * na; idx += blockDim.x) {
+          const int i = idx / na, j = idx - i * na;
+          M[idx] = 0.5 * (M[i * na + j] + M[j * na + i]);
+        }
+        __syncthreads();
+        // symmetrised copy is in place; compute Cholesky
+        if (blk_shifted_chol(M, na, na, Lc, na, L.flags, &cnt, L.scratch)) {
+          blk_trsm_rt(X, ldx, p, na, Lc, na);
+        } else {
           if (threadIdx.x == 0) cnt.svqb++;
-          if (!blk_svqb_coef<JAC ? 1024 : kEigThreads>(M, ldx, na, Lc, ldx, Ws, J.cs, J.pr, J.flags, J.perm, J.scratch)) {
+          if (!blk_svqb_coef(M, na, na, Lc, na, Ws, L.cs, L.pr, L.flags, L.perm, L.scratch)) {
             bad = 1;
             break;
           }
           // X <- X Cf (Cf in Lc), through the Ws area as a copy of X
-          for (int idx = threadIdx.x; idx < p * na; idx += blockDim.x) Ws[idx] = X[idx / na * ldx + idx % na];
+          for (int idx = threadIdx.x; idx < p * na; idx += blockDim.x) Ws[idx] = X[idx];
           __syncthreads();
           for (int idx = threadIdx.x; idx < p * na; idx += blockDim.x) {
             const int r = idx / na, j = idx - r * na;
             double acc = 0.0;
-            for (int k = 0; k < na; ++k) acc += Ws[r * na + k] * Lc[k * ldx + j];
+            for (int k = 0; k < na; ++k) acc += Ws[r * na + k] * Lc[k * na + j];
             X[r * ldx + j] = acc;
           }
           __syncthreads();
@@ -1501,16 +1296,18 @@ __global__ __launch_bounds__(JAC ? 1024 : kEigThreads) void k_small_rr(
         if (threadIdx.x == 0) updates++;
       }
       if (bad) break;
-      blk_gemm_tn(Us, ldu, X, ldx, p, m, na, C, ldx);
+      blk_gemm_tn(Us, ld, X, ldx, p, m, na, C, na);
       double cm = 0.0;
-      for (int i = row0; i < m; i += rstep)
-        for (int j = col0; j < na; j += 16) cm = fmax(cm, fabs(C[i * ldx + j]));
-      cm = blk_reduce_max(cm, J.scratch);
+      for (int idx = threadIdx.x; idx < m * na; idx += blockDim.x) cm = fmax(cm, fabs(C[idx]));
+      cm = blk_reduce_max(cm, L.scratch);
       if (cm <= tau) break;
       if (pass == 3 && threadIdx.x == 0) stalled++;
     }
-    for (int i = row0; i < p; i += rstep)
-      for (int j = col0; j < na; j += 16) U[i * q + m + j] = ds[i] * X[i * ldx + j];
+    for (int idx = threadIdx.x; idx < p * na; idx += blockDim.x) {
+      const int i = idx / na, j = idx - i * na;
+      const double di = (scaled && i >= woff && i < woff + pend->nw) ? pend->dscale[i - woff] : 1.0;
+      U[i * q + m + j] = di * X[i * ldx + j];
+    }
   }
   if (threadIdx.x == 0) {
     info[0] = sw;
@@ -1524,40 +1321,25 @@ __global__ __launch_bounds__(JAC ? 1024 : kEigThreads) void k_small_rr(
     info[8] = stalled;
     info[9] = cnt.svqb;
     info[10] = zeros;
-    info[11] = (tri || JAC) ? 0 : 1;  // Jacobi fallback of the eigensolve
+    info[11] = (tri || jacobi) ? 0 : 1;  // Jacobi fallback of the eigensolve
   }
-}
-
-// u~_p's arrays (k_small_rr's carve-up) behind u_x: p x (p + 1) of it after
-// Jacobi, less on the tridiagonal path
-static_assert(kMaxP * (kMaxP + 1) + kMaxP * (kMaxBlock | 1) + 3 * kMaxBlock * (kMaxBlock | 1) + kMaxP * kMaxBlock <=
-                      kEigLdsBytes / 8 &&
-                  kMaxP >= 2 * (kMaxBlock + 1) - 1,
-              "LDS of the largest Rayleigh-Ritz call");
-
-template <bool JAC>
-static hipError_t small_rr_launch(const double* a, int p, int m, int a0, int want_up, double tau,
-                                  const OrthoState* pend, int woff, double* theta_all, double* U, int* info,
-                                  hipStream_t s) {
-  static bool attr = false;
-  if (!attr) {
-    // dynamic + static LDS must stay within the 160 KB of a workgroup
-    (void)hipFuncSetAttribute((const void*)k_small_rr<JAC>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              kEigLdsBytes);
-    (void)hipGetLastError();
-    attr = true;
-  }
-  hipLaunchKernelGGL(k_small_rr<JAC>, dim3(1), dim3(JAC ? 1024 : kEigThreads), kEigLdsBytes, s, a, p, m, a0,
-                     want_up, tau, pend, woff, theta_all, U, info);
-  return hipGetLastError();
 }
 
 hipError_t small_rr(const double* a, int p, int m, int a0, int want_up, double tau,
                     const OrthoState* pend, int woff, double* theta_all, double* U, int* info,
                     int jacobi, hipStream_t s) {
-  if (p < 1 || p > kMaxP || m < 1 || m > p || m > kMaxBlock || a0 < 0 || a0 > m) return hipErrorInvalidValue;
-  return jacobi ? small_rr_launch<true>(a, p, m, a0, want_up, tau, pend, woff, theta_all, U, info, s)
-                : small_rr_launch<false>(a, p, m, a0, want_up, tau, pend, woff, theta_all, U, info, s);
+  if (p < 1 || p > kMaxP || m < 1 || m > p || a0 < 0 || a0 > m) return hipErrorInvalidValue;
+  static bool attr = false;
+  if (!attr) {
+    // dynamic + static LDS must stay within the 160 KB of a workgroup
+    (void)hipFuncSetAttribute((const void*)k_small_rr, hipFuncAttributeMaxDynamicSharedMemorySize,
+                              152 * 1024);
+    (void)hipGetLastError();
+    attr = true;
+  }
+  hipLaunchKernelGGL(k_small_rr, dim3(1), dim3(1024), kEigLdsBytes, s, a, p, m, a0, want_up, tau,
+                     pend, woff, theta_all, U, info, jacobi);
+  return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
@@ -1567,6 +1349,7 @@ __global__ __launch_bounds__(256) void k_small_chol(const double* __restrict__ M
                                                     double* __restrict__ Lout, int* info) {
   __shared__ double Ms[64 * 65];
   __shared__ double Ls[64 * 65];
+  __shared__ double scratch[16];
   __shared__ int flag;
   __shared__ ShiftCount cnt;
   if (threadIdx.x == 0) cnt.factorizations = cnt.failed = cnt.shifted = cnt.svqb = 0;
@@ -1575,7 +1358,7 @@ __global__ __launch_bounds__(256) void k_small_chol(const double* __restrict__ M
     Ms[i * 65 + j] = 0.5 * (M[i * p + j] + M[j * p + i]);
   }
   __syncthreads();
-  const bool ok = blk_shifted_chol<false>(Ms, 65, p, Ls, 65, &flag, &cnt);
+  const bool ok = blk_shifted_chol<0>(Ms, 65, p, Ls, 65, &flag, &cnt, scratch);
   for (int idx = threadIdx.x; idx < p * p; idx += blockDim.x) {
     const int i = idx / p, j = idx - i * p;
     Lout[idx] = ok ? Ls[i * 65 + j] : 0.0;
@@ -1772,7 +1555,7 @@ __global__ __launch_bounds__(1024) void k_ortho_ctl(const double* __restrict__ G
     have_scale = (phase == kPhBegin);
   } else {
     // shifted Cholesky of M (= M' in BEGIN)
-    const bool ok = blk_shifted_chol(Ms, ldm, nw, Ls, ldm, &flag, &cnt, st.shift_retries);
+    const bool ok = blk_shifted_chol<2>(Ms, ldm, nw, Ls, ldm, &flag, &cnt, scratch, st.shift_retries);
     if (ok) {
       blk_tri_inv(Ls, ldm, nw, Li, ldm);
       // coef W part: D L^-T, i.e. coef[ny+i][j] = D_i Linv[j][i]
@@ -1808,7 +1591,7 @@ __global__ __launch_bounds__(1024) void k_ortho_ctl(const double* __restrict__ G
       return;
     } else {
       if (threadIdx.x == 0) cnt.svqb++;
-      const bool sv = blk_svqb_coef<1024>(Ms, ldm, nw, Li, ldm, Ws, cs, pr, &flag, perm, scratch);
+      const bool sv = blk_svqb_coef(Ms, ldm, nw, Li, ldm, Ws, cs, pr, &flag, perm, scratch);
       if (!sv) {
         if (threadIdx.x == 0) {
           st.error = kOrthoErrFailed;
