@@ -21,6 +21,7 @@ SOURCES = [
     "k_gen.hip",
     "k_kron.hip",
     "k_small.hip",
+    "k_eigh.hip",
     "k_mlp.hip",
     "k_learn.hip",
     "solver.cpp",

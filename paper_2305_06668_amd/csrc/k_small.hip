@@ -1,8 +1,7 @@
 // Small dense fp64 linear algebra of the LOBPCG step, one workgroup each,
 // everything resident in LDS (gfx950: 160 KB per workgroup):
-//   * cyclic Jacobi eigensolver in parallel (round-robin) order for the
-//     p x p Rayleigh-Ritz matrix, p <= 96 (Alg. 1, "solve a u = lambda u";
-//     the paper calls LAPACK dsyev, Sec. 3.1);
+//   * the eigensolve of the p x p Rayleigh-Ritz matrix, p <= 96 (Alg. 1,
+//     "solve a u = lambda u"; the paper calls LAPACK dsyev, Sec. 3.1);
 //   * shifted Cholesky of an overlap matrix (Sec. 3.2: retry with
 //     alpha * eps * ||X|| added to the diagonal, alpha = 100, 1000, ...);
 //   * the implicit P coefficients u_p = ortho(u_x[:, act] - E[:, act]; u_x)
@@ -10,34 +9,13 @@
 //   * the controller of ortho(W; Y) on n-vectors (Alg. 2 inside Alg. 3): it
 //     reads the overlap G = [Y W]^T W of the current W and emits the small
 //     coefficient matrix that the streaming kernel applies next.
-#include "internal.h"
+#include "small.h"
 
 namespace lobpcg {
 
-constexpr double kEps = 0x1.0p-52;  // double precision machine epsilon
 constexpr double kShiftAlpha0 = 100.0;
 constexpr double kShiftGrowth = 10.0;
 constexpr int kShiftRetries = 20;
-constexpr int kJacobiMaxSweeps = 40;
-
-__device__ __forceinline__ uint64_t sm64(uint64_t x) {
-  uint64_t z = x + 0x9E3779B97F4A7C15ull;
-  z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
-  z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
-  return z ^ (z >> 31);
-}
-
-// LDS writes of one wave visible to the same wave's later reads
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-__device__ __forceinline__ double readlane_f64(double v, int l) {
-  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
-                          __builtin_amdgcn_readlane(__double2loint(v), l));
-}
 
 // Cholesky of an n x n symmetric matrix (n <= 16) held by one wave in
 // registers: lane l keeps column c = l & 15, rows r = (l >> 4) + 4 t
@@ -129,32 +107,6 @@ __device__ __noinline__ bool wave_chol16_lds(const double* S, int lds_, int n, d
 
 // ---------------------------------------------------------------------------
 // block-wide helpers (every thread of the block calls them)
-
-__device__ __forceinline__ double blk_reduce_max(double v, double* scratch) {
-  // scratch: blockDim.x / 64 doubles
-  for (int off = 32; off >= 1; off >>= 1) v = fmax(v, __shfl_xor(v, off));
-  const int w = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) scratch[w] = v;
-  __syncthreads();
-  double r = scratch[0];
-  for (int i = 1; i < nw; ++i) r = fmax(r, scratch[i]);
-  __syncthreads();
-  return r;
-}
-
-__device__ __forceinline__ double blk_reduce_sum_ordered(double v, double* scratch) {
-  // deterministic: each wave reduces by a fixed xor tree, waves in order
-  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off);
-  const int w = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) scratch[w] = v;
-  __syncthreads();
-  double r = scratch[0];
-  for (int i = 1; i < nw; ++i) r += scratch[i];
-  __syncthreads();
-  return r;
-}
 
 // C (p x q) = A^T B, A: n x p, B: n x q
 __device__ __forceinline__ void blk_gemm_tn(const double* A, int lda, const double* B, int ldb, int n, int p,
@@ -312,192 +264,6 @@ __device__ __forceinline__ void blk_trsm_rt(double* X, int ldx, int n, int q, co
   __syncthreads();
 }
 
-// ---------------------------------------------------------------------------
-// Parallel cyclic Jacobi on the symmetric n x n matrix A (LDS, stride lda),
-// accumulating V (stride ldv, initialised here to I).  Round-robin pairing:
-// in round r the pairs are {pp-1, r} and {(r+k) mod (pp-1), (r-k) mod (pp-1)}
-// for k = 1 .. pp/2-1, with pp = n rounded up to even (index n is a dummy).
-// Two phases per round: (1) one thread per pair computes its rotation from
-// the current 2x2 block; (2) every 2x2 block {i0,i1} x {j0,j1} of two pairs
-// is rotated in place from both sides by one thread (it is closed under
-// J^T A J, so no double buffer is needed), and V's column pairs likewise.
-// A rotation is skipped when |a_pq| <= 2^-53 sqrt(|a_pp a_qq|) or
-// |a_pq| <= 2^-60 ||A||_F; the sweep loop stops after a sweep without any
-// rotation.  Returns the number of sweeps.  Must run with blockDim.x == 1024.
-
-__device__ __forceinline__ int blk_jacobi(double* A, int lda, double* V, int ldv, int n, double* cs, int* pr,
-                          int* rot_flag, double* scratch) {
-  for (int idx = threadIdx.x; idx < n * n; idx += blockDim.x) {
-    const int i = idx / n, j = idx - i * n;
-    V[i * ldv + j] = (i == j) ? 1.0 : 0.0;
-  }
-  double fro = 0.0;
-  for (int idx = threadIdx.x; idx < n * n; idx += blockDim.x) {
-    const double v = A[(idx / n) * lda + idx % n];
-    fro += v * v;
-  }
-  fro = sqrt(blk_reduce_sum_ordered(fro, scratch));
-  const double abs_tol = 0x1.0p-60 * fro;
-  if (n < 2) return 0;
-  const int pp = n + (n & 1);
-  const int npairs = pp / 2;
-  double* cc = cs;            // cos per pair
-  double* ss = cs + 64;       // sin per pair
-  double* tt = cs + 128;      // tan per pair
-  int sweep = 0;
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-  for (; sweep < kJacobiMaxSweeps; ++sweep) {
-    if (threadIdx.x == 0) *rot_flag = 0;
-    __syncthreads();
-    for (int r = 0; r < pp - 1; ++r) {
-      for (int k = threadIdx.x; k < npairs; k += blockDim.x) {
-        int i, j;
-        if (k == 0) {
-          i = pp - 1;
-          j = r;
-        } else {
-          i = r + k;
-          if (i >= pp - 1) i -= pp - 1;
-          j = r - k;
-          if (j < 0) j += pp - 1;
-        }
-        if (i > j) {
-          const int t = i;
-          i = j;
-          j = t;
-        }
-        double c = 1.0, sn = 0.0, tn = 0.0;
-        if (j < n) {
-          const double apq = A[i * lda + j];
-          const double app = A[i * lda + i], aqq = A[j * lda + j];
-          if (fabs(apq) > 0x1.0p-53 * sqrt(fabs(app * aqq)) && fabs(apq) > abs_tol) {
-            const double tau = (aqq - app) / (2.0 * apq);
-            tn = (tau >= 0.0) ? 1.0 / (tau + sqrt(1.0 + tau * tau))
-                              : -1.0 / (-tau + sqrt(1.0 + tau * tau));
-            c = 1.0 / sqrt(1.0 + tn * tn);
-            sn = tn * c;
-            *rot_flag = 1;
-          }
-        }
-        pr[2 * k] = i;
-        pr[2 * k + 1] = j;
-        cc[k] = c;
-        ss[k] = sn;
-        tt[k] = tn;
-      }
-      __syncthreads();
-      // Phase 2 (needs blockDim == 1024: a 32 x 32 thread grid).  Thread
-      // (ty, tx) owns the 2x2 blocks (P, Q) for P in {ty, ty+32}, Q in
-      // {tx, tx+32} with P <= Q, and V's column pair Q on the rows ty,
-      // ty+32, ty+64; every load of an item is issued before its arithmetic.
-#pragma unroll
-      for (int hq = 0; hq < 2; ++hq) {
-        const int Q = tx + 32 * hq;
-        if (Q >= npairs) continue;
-        const double cQ = cc[Q], sQ = ss[Q], tQ = tt[Q];
-        const int j0 = pr[2 * Q], j1 = pr[2 * Q + 1];
-        const bool vj1 = j1 < n;
-#pragma unroll
-        for (int hp = 0; hp < 2; ++hp) {
-          const int P = ty + 32 * hp;
-          if (P >= npairs || P > Q) continue;
-          if (P == Q) {
-            if (sQ == 0.0) continue;  // skipped or dummy pair
-            const double a01 = A[j0 * lda + j1];
-            const double a00 = A[j0 * lda + j0], a11 = A[j1 * lda + j1];
-            A[j0 * lda + j0] = a00 - tQ * a01;
-            A[j1 * lda + j1] = a11 + tQ * a01;
-            A[j0 * lda + j1] = 0.0;
-            A[j1 * lda + j0] = 0.0;
-            continue;
-          }
-          const double cP = cc[P], sP = ss[P];
-          if (sP == 0.0 && sQ == 0.0) continue;
-          const int i0 = pr[2 * P], i1 = pr[2 * P + 1];
-          const bool vi1 = i1 < n;
-          const double b00 = A[i0 * lda + j0];
-          const double b01 = vj1 ? A[i0 * lda + j1] : 0.0;
-          const double b10 = vi1 ? A[i1 * lda + j0] : 0.0;
-          const double b11 = (vi1 && vj1) ? A[i1 * lda + j1] : 0.0;
-          // rows (J^T A): i0' = c i0 - s i1, i1' = s i0 + c i1
-          const double t00 = cP * b00 - sP * b10, t01 = cP * b01 - sP * b11;
-          const double t10 = sP * b00 + cP * b10, t11 = sP * b01 + cP * b11;
-          // columns (A J): j0' = c j0 - s j1, j1' = s j0 + c j1
-          const double n00 = cQ * t00 - sQ * t01, n01 = sQ * t00 + cQ * t01;
-          const double n10 = cQ * t10 - sQ * t11, n11 = sQ * t10 + cQ * t11;
-          A[i0 * lda + j0] = n00;
-          A[j0 * lda + i0] = n00;
-          if (vj1) {
-            A[i0 * lda + j1] = n01;
-            A[j1 * lda + i0] = n01;
-          }
-          if (vi1) {
-            A[i1 * lda + j0] = n10;
-            A[j0 * lda + i1] = n10;
-          }
-          if (vi1 && vj1) {
-            A[i1 * lda + j1] = n11;
-            A[j1 * lda + i1] = n11;
-          }
-        }
-        if (sQ != 0.0) {
-          // rows ty, ty + 32, ty + 64 (clamped reads, guarded writes)
-          const int r0 = ty, r1 = ty + 32, r2 = ty + 64;
-          const int q1 = (r1 < n) ? r1 : r0, q2 = (r2 < n) ? r2 : r0;
-          const double a0 = V[r0 * ldv + j0], b0 = V[r0 * ldv + j1];
-          const double a1 = V[q1 * ldv + j0], b1 = V[q1 * ldv + j1];
-          const double a2 = V[q2 * ldv + j0], b2 = V[q2 * ldv + j1];
-          if (r0 < n) {
-            V[r0 * ldv + j0] = cQ * a0 - sQ * b0;
-            V[r0 * ldv + j1] = sQ * a0 + cQ * b0;
-          }
-          if (r1 < n) {
-            V[r1 * ldv + j0] = cQ * a1 - sQ * b1;
-            V[r1 * ldv + j1] = sQ * a1 + cQ * b1;
-          }
-          if (r2 < n) {
-            V[r2 * ldv + j0] = cQ * a2 - sQ * b2;
-            V[r2 * ldv + j1] = sQ * a2 + cQ * b2;
-          }
-        }
-      }
-      __syncthreads();
-    }
-    const int any = *rot_flag;
-    __syncthreads();
-    if (!any) break;
-    // stop without a confirming sweep when no pair would rotate any more
-    if (threadIdx.x == 0) *rot_flag = 0;
-    __syncthreads();
-    for (int idx = threadIdx.x; idx < n * n; idx += blockDim.x) {
-      const int i = idx / n, j = idx - i * n;
-      if (j <= i) continue;
-      const double apq = A[i * lda + j];
-      if (fabs(apq) > 0x1.0p-53 * sqrt(fabs(A[i * lda + i] * A[j * lda + j])) && fabs(apq) > abs_tol)
-        *rot_flag = 1;
-    }
-    __syncthreads();
-    const int more = *rot_flag;
-    __syncthreads();
-    if (!more) break;
-  }
-  return sweep + 1;
-}
-
-// evals ascending (ties by index) -> perm[rank] = index
-__device__ __forceinline__ void blk_sort_evals(const double* A, int lda, int n, int* perm) {
-  for (int i = threadIdx.x; i < n; i += blockDim.x) {
-    const double li = A[i * lda + i];
-    int rank = 0;
-    for (int j = 0; j < n; ++j) {
-      const double lj = A[j * lda + j];
-      if (lj < li || (lj == li && j < i)) ++rank;
-    }
-    perm[rank] = i;
-  }
-  __syncthreads();
-}
-
 // LDS layout shared by the eig-based kernels
 struct EigLds {
   double* A;  // p x (p+1)
@@ -569,27 +335,8 @@ __device__ __forceinline__ void load_sym(const double* a, int p, double* A, int 
 // Returns false when a Cholesky-QR breaks down (A is destroyed); the
 // callers then reload A and run Jacobi.
 
-constexpr int kEigLdsBytes = 152 * 1024;  // dynamic LDS of the eigensolver kernels
 constexpr int kMsPoints = 32;              // multisection points per eigenvalue
 
-
-template <int CTRL>
-__device__ __forceinline__ double dpp_f64(double v) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xF, 0xF, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xF, 0xF, false);
-  return __hiloint2double(hi, lo);
-}
-// Sum over the 64 lanes (all active), the same bits in every lane: within
-// each row of 16 by DPP (swap neighbours, swap pairs, mirror 8, mirror 16;
-// each step adds the same two operands on both partners), then the four row
-// sums in a fixed order.
-__device__ __forceinline__ double wave_sum(double v) {
-  v += dpp_f64<0xB1>(v);   // quad_perm [1, 0, 3, 2]
-  v += dpp_f64<0x4E>(v);   // quad_perm [2, 3, 0, 1]
-  v += dpp_f64<0x141>(v);  // row_half_mirror
-  v += dpp_f64<0x140>(v);  // row_mirror
-  return (readlane_f64(v, 0) + readlane_f64(v, 16)) + (readlane_f64(v, 32) + readlane_f64(v, 48));
-}
 
 // LDS layout after the p x (p+1) A area, in doubles
 struct TriLayout {
@@ -1077,54 +824,6 @@ __device__ bool blk_tri_eigh(double* A, int lda, int p, int nev, double* base, c
   return true;
 }
 
-__global__ __launch_bounds__(1024) void k_small_eigh(const double* __restrict__ a, int p,
-                                                    double* __restrict__ evals,
-                                                    double* __restrict__ evecs, int* sweeps) {
-  extern __shared__ double smem[];
-  __shared__ int tflag;
-  const int ld = p + 1;
-  const TriLayout T = tri_layout(p, p);
-  if (T.nb >= 1) {
-    load_sym(a, p, smem, ld);
-    double* base = smem + p * ld;
-    if (blk_tri_eigh(smem, ld, p, p, base, T, &tflag)) {
-      for (int idx = threadIdx.x; idx < p * p; idx += blockDim.x) {
-        const int i = idx / p, j = idx - i * p;
-        const double sg = (base[T.Z + j * T.ldz + j] < 0.0) ? -1.0 : 1.0;
-        evecs[i * p + j] = sg * base[T.Z + i * T.ldz + j];
-      }
-      for (int j = threadIdx.x; j < p; j += blockDim.x) evals[j] = base[T.ev + j];
-      if (threadIdx.x == 0 && sweeps != nullptr) *sweeps = 0;
-      return;
-    }
-  }
-  EigLds L = eig_lds(smem, p, 1);
-  load_sym(a, p, L.A, ld);
-  const int sw = blk_jacobi(L.A, ld, L.V, ld, p, L.cs, L.pr, L.flags, L.scratch);
-  blk_sort_evals(L.A, ld, p, L.perm);
-  for (int idx = threadIdx.x; idx < p * p; idx += blockDim.x) {
-    const int i = idx / p, j = idx - i * p;
-    const double sg = (L.V[j * ld + L.perm[j]] < 0.0) ? -1.0 : 1.0;
-    evecs[i * p + j] = sg * L.V[i * ld + L.perm[j]];
-  }
-  for (int j = threadIdx.x; j < p; j += blockDim.x) evals[j] = L.A[L.perm[j] * ld + L.perm[j]];
-  if (threadIdx.x == 0 && sweeps != nullptr) *sweeps = sw;
-}
-
-hipError_t small_eigh(const double* a, int p, double* evals, double* evecs, int* sweeps,
-                      hipStream_t s) {
-  if (p < 1 || p > kMaxP) return hipErrorInvalidValue;
-  static bool attr = false;
-  if (!attr) {
-    (void)hipFuncSetAttribute((const void*)k_small_eigh, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              152 * 1024);
-    (void)hipGetLastError();
-    attr = true;
-  }
-  hipLaunchKernelGGL(k_small_eigh, dim3(1), dim3(1024), kEigLdsBytes, s, a, p, evals, evecs, sweeps);
-  return hipGetLastError();
-}
-
 // ---------------------------------------------------------------------------
 // SVQB (Stathopoulos-Wu) coefficient for an n x n overlap M: X <- X U S^-1/2,
 // eigenvalues clamped below eps * max.  Writes the n x n coefficient to Cf.
@@ -1139,7 +838,7 @@ __device__ __forceinline__ bool blk_svqb_coef(const double* M, int ldm, int n, d
     A[i * ld + j] = M[i * ldm + j];
   }
   __syncthreads();
-  blk_jacobi(A, ld, U, ld, n, cs, pr, flag, scratch);
+  blk_jacobi<1024>(A, ld, U, ld, n, cs, pr, flag, scratch);
   double smax = 0.0;
   for (int i = 0; i < n; ++i) smax = fmax(smax, A[i * ld + i]);
   if (!(smax > 0.0)) return false;
@@ -1212,7 +911,7 @@ __global__ __launch_bounds__(1024) void k_small_rr(const double* __restrict__ a,
   }
   if (!tri) {
     load_rr_matrix(a, p, L.A, ld, scaled ? pend : nullptr, woff);
-    sw = blk_jacobi(L.A, ld, L.V, ld, p, L.cs, L.pr, L.flags, L.scratch);
+    sw = blk_jacobi<1024>(L.A, ld, L.V, ld, p, L.cs, L.pr, L.flags, L.scratch);
     blk_sort_evals(L.A, ld, p, L.perm);
     for (int j = threadIdx.x; j < m; j += blockDim.x) theta_all[j] = L.A[L.perm[j] * ld + L.perm[j]];
     __syncthreads();
