@@ -2,20 +2,15 @@
 // operator).  The (col, val) stream is read from HBM once; every stored entry
 // then needs one row of W (ncols * s contiguous bytes), gathered through L2.
 // For the banded workloads the W window stays in L2 (hit rate ~90 %, HBM
-// traffic within 1 % of the algorithmic bytes), and what bounds the kernel is
-// the rate of L1 misses a CU keeps in flight: one 64- or 128-byte request per
-// stored entry whatever the column count, ~0.2 requests per clock per CU at
-// ~250 cycles of L2 latency.  Two kernels:
-//   * k_spmm_csr_vec (2 fp64 / 4 fp32 columns per lane, 16-byte loads; the
-//     block's (col, val) range staged in LDS): the fewest instructions and
-//     wave slots per gathered row, used whenever W and ldw allow 16-byte
-//     loads and the block has at least 5 (fp64) or 9 (fp32) columns;
+// traffic within 1 % of the algorithmic bytes).  Two kernels:
+//   * k_spmm_rows (2 fp64 / 4 fp32 columns per lane, 16-byte loads; each wave
+//     stages its rows' (col, val) range in LDS): the fewest instructions and
+//     wave slots per gathered row, used from 5 (fp64) or 9 (fp32) columns;
 //   * k_spmm_csr (one column per lane, (col, val) broadcast by shuffles):
-//     narrow or misaligned blocks.
+//     narrow blocks.
 // Row blocks are remapped so that each XCD (hardware dispatches block b to
 // XCD b % 8) walks one contiguous range of rows: a banded matrix then keeps
-// its W window inside that XCD's L2.  The (col, val) stream is loaded with the
-// non-temporal hint so that it does not evict W rows from L2.
+// its W window inside that XCD's L2.
 #include <algorithm>
 
 #include "internal.h"
@@ -124,109 +119,231 @@ static hipError_t spmm_launch(const int32_t* rp, const int32_t* ci, const TV* va
 }
 
 
-// 16-byte vector of CPL elements (CPL * sizeof(T) == 16)
+// 16 bytes of CPL elements at element alignment (a global load of four dwords
+// needs no more than a dword's)
 template <typename T, int CPL>
 struct Vec16;
 template <>
 struct Vec16<double, 2> {
-  typedef double __attribute__((ext_vector_type(2))) type;
+  typedef double __attribute__((ext_vector_type(2), aligned(8))) type;
 };
 template <>
 struct Vec16<float, 4> {
-  typedef float __attribute__((ext_vector_type(4))) type;
+  typedef float __attribute__((ext_vector_type(4), aligned(4))) type;
 };
 
-constexpr int kVecCap = 2048;  // (col, val) entries staged in LDS per pass
+// a stored entry in LDS: where its W row starts and its value, one LDS read
+template <typename TW> struct Entry;
+template <> struct alignas(16) Entry<double> { uint32_t at; uint32_t pad; double v; };
+template <> struct alignas(8) Entry<float> { uint32_t at; float v; };
 
-// A group of G lanes owns one row; lane l holds columns [l CPL, l CPL + CPL)
-// and gathers them with one 16-byte load per stored entry (lanes whose
-// columns run past ncols load element by element, or nothing).  The block's
-// rows are consecutive, so their stored entries form one contiguous range:
-// it is copied to LDS in passes of kVecCap entries (coalesced, non-temporal),
-// and every group reads its row's (col, val) pairs from there as broadcasts.
-// Entries are accumulated in CSR order, UN gathers in flight per lane.
-// Requires W and ldw aligned to CPL elements (16 bytes).
-template <typename TV, typename TW, int G, int CPL, int UN>
-__global__ __launch_bounds__(256) void k_spmm_csr_vec(const int32_t* __restrict__ rp,
-                                                      const int32_t* __restrict__ ci,
-                                                      const TV* __restrict__ val,
-                                                      const TW* __restrict__ W, int64_t ldw,
-                                                      TW* __restrict__ Y, int64_t ldy, int ncols,
-                                                      int64_t n, int per_xcd) {
+// A wave takes 64 / G rows at once, G lanes to a row; lane l holds columns
+// c .. c + CPL - 1, c = min(l CPL, ncols - CPL) (the last lanes may repeat
+// columns, so that every load is whole), and gathers them with one 16-byte
+// load per stored entry.  The rows are consecutive, so their stored entries
+// form one range: a wave copies it to its own part of LDS (coalesced,
+// non-temporal) as entries of W offset and value, and each row's lanes read
+// theirs from there.  Everything is private to the wave (no barrier), waves
+// walk on through their XCD's rows, and while a wave gathers for one group
+// of rows its loads of the next group's entries and of the row pointers
+// after that are in flight.  A group whose entries do not fit (rows much
+// longer than kRowCap on average) is taken kRowCap entries of each row at a
+// time.  Entries are accumulated in CSR order, four gathers in flight per
+// lane.
+// BIG: W spans 4 GB or more, LDS holds the column and the address is formed in
+// 64 bits; else it holds the byte offset, added to a scalar base by the load.
+// A matrix of up to kCachedBytes is read through the caches, so that the next
+// product finds it in the memory-side one (256 MB); a larger one would only
+// evict W and itself, and is read with the non-temporal hint (n = 3e5, fp32
+// of 98 MB: 64 against 80 us; n = 1e6, fp64 of 492 MB: 373 against 350 us).
+// What bounds it: a 16-byte load of 64 lanes takes the L1 16 cycles, hit or
+// not, so every gather that is issued for a lane group whose row has ended is
+// lost (rows of 41 +- 4.5 entries, eight to a wave: 55 issued with eight in
+// flight, 49 with four), and loads return in order, so the gathers behind a
+// fetch of entries wait for HBM.  Gathers alone take 160 us for the n = 1e6,
+// 41 entries per row, 16-column product, the entries alone 125 us, both
+// together without rows or sums 230 to 270 us; the product takes 345 to 355
+// (380 with the block's entries staged between barriers, two LDS reads, two
+// selects and a 64-bit address per gather, 256 threads a row block).  Rows
+// one after the other without a common end (fewer gathers, more work per
+// entry) took 415 to 480 us, larger fetches with fewer waves 420 us.
+constexpr int kRowCap = 48;  // entries per row that a wave's LDS holds
+constexpr int64_t kCachedBytes = 160ll << 20;
+template <typename TV, typename TW, int G, int CPL, bool BIG>
+__global__ __launch_bounds__(256) void k_spmm_rows(const int32_t* __restrict__ rp,
+                                                   const int32_t* __restrict__ ci,
+                                                   const TV* __restrict__ val,
+                                                   const TW* __restrict__ W, int64_t ldw,
+                                                   TW* __restrict__ Y, int64_t ldy, int ncols,
+                                                   int64_t n, int per_xcd) {
   typedef typename Vec16<TW, CPL>::type VT;
-  constexpr int RPB = 256 / G;
-  __shared__ int32_t scol[kVecCap];
-  __shared__ TV sval[kVecCap];
-  const int b = blockIdx.x;
-  const int lb = (b & 7) * per_xcd + (b >> 3);
-  const int64_t r0 = (int64_t)lb * RPB;
-  if (r0 >= n) return;  // whole block
-  const int64_t rl = min((int64_t)RPB, n - r0);
-  const int myr = threadIdx.x / G;
-  const int c = (threadIdx.x % G) * CPL;
-  const int nv = max(0, min(CPL, ncols - c));  // columns this lane owns
-  const int64_t row = r0 + myr;
-  const int B0 = rp[r0], B1 = rp[r0 + rl];
-  int e0 = 0, e1 = 0;
-  if (myr < rl && nv > 0) {
+  constexpr int NR = 64 / G;             // rows per wave and step
+  constexpr int CAP = kRowCap * NR;      // entries in the wave's LDS
+  constexpr int NL = CAP / 64;           // entries per lane and copy
+  constexpr int UN = 4;
+  __shared__ Entry<TW> lds[4][CAP];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  Entry<TW>* E = lds[wave];
+  const int r = lane / G, l = lane % G;
+  const int c = min(l * CPL, ncols - CPL);
+  const bool store = l * CPL < ncols;
+  const uint32_t rowb = (uint32_t)(ldw * sizeof(TW)), cb = (uint32_t)(c * sizeof(TW));
+  const TW* Wc = W + c;
+  // this wave's groups of rows: first, first + step, ... below last
+  const int64_t first = (int64_t)(blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3) * 4 + wave;
+  const int step = (gridDim.x >> 3) * 4;
+  const int64_t last = min((int64_t)((blockIdx.x & 7) + 1) * per_xcd, (n + NR - 1) / NR);
+  if (first >= last) return;
+  // row pointers of this lane's row of group g (empty past the matrix)
+  auto load_rp = [&](int64_t g, int& e0, int& e1) {
+    const int64_t row = min(g * NR + r, n);
     e0 = rp[row];
-    e1 = rp[row + 1];
-  }
-  TW acc[CPL];
+    e1 = rp[min(row + 1, n)];
+  };
+  // the group's range of entries: the first row's start, the last row's end
+  auto lo_of = [&](int e0) { return __builtin_amdgcn_readlane(e0, 0); };
+  auto hi_of = [&](int e1) { return __builtin_amdgcn_readlane(e1, 63); };
+  int32_t pc[NL];
+  TV pv[NL];
+  const bool cached = (int64_t)rp[n] * (int)(sizeof(TV) + 4) <= kCachedBytes;
+  auto fetch = [&](int b0, int cnt) {
+    const int32_t* cp = ci + b0;
+    const TV* vp = val + b0;
+    if (cached) {
 #pragma unroll
-  for (int q = 0; q < CPL; ++q) acc[q] = TW(0);
-  for (int p0 = B0; p0 < B1; p0 += kVecCap) {
-    const int p1 = min(p0 + kVecCap, B1);
-    __syncthreads();  // the previous pass is consumed
-    for (int i = p0 + (int)threadIdx.x; i < p1; i += 256) {
-      scol[i - p0] = __builtin_nontemporal_load(ci + i);
-      sval[i - p0] = __builtin_nontemporal_load(val + i);
-    }
-    __syncthreads();
-    const int a = max(e0, p0) - p0, z = min(e1, p1) - p0;
-    for (int e = a; e < z; e += UN) {
-      TW w[UN][CPL];
-      TW vv[UN];
-#pragma unroll
-      for (int u = 0; u < UN; ++u) {
-        const bool ok = e + u < z;
-        const int col = ok ? scol[e + u] : 0;  // past the row end: row 0, weight 0
-        vv[u] = ok ? (TW)sval[e + u] : TW(0);
-        const TW* src = W + (int64_t)col * ldw + c;
-        if (nv == CPL) {
-          const VT t = *reinterpret_cast<const VT*>(src);
-#pragma unroll
-          for (int q = 0; q < CPL; ++q) w[u][q] = t[q];
-        } else {
-#pragma unroll
-          for (int q = 0; q < CPL; ++q) w[u][q] = (q < nv) ? src[q] : TW(0);
+      for (int k = 0; k < NL; ++k) {
+        const int i = 64 * k + lane;
+        if (i < cnt) {
+          pc[k] = cp[i];
+          pv[k] = vp[i];
         }
       }
+    } else {
 #pragma unroll
-      for (int u = 0; u < UN; ++u)
-#pragma unroll
-        for (int q = 0; q < CPL; ++q) acc[q] += vv[u] * w[u][q];
+      for (int k = 0; k < NL; ++k) {
+        const int i = 64 * k + lane;
+        if (i < cnt) {
+          pc[k] = __builtin_nontemporal_load(cp + i);
+          pv[k] = __builtin_nontemporal_load(vp + i);
+        }
+      }
     }
-  }
-  if (myr < rl) {
-    TW* dst = Y + row * ldy + c;
+  };
+  auto entry = [&](int32_t col, TV v) {
+    Entry<TW> x;
+    x.at = BIG ? (uint32_t)col : (uint32_t)col * rowb;
+    x.v = (TW)v;
+    return x;
+  };
+  auto gather = [&](const Entry<TW>& x) {
+    if (BIG) return *reinterpret_cast<const VT*>(Wc + (int64_t)x.at * ldw);
+    return *reinterpret_cast<const VT*>(reinterpret_cast<const char*>(W) + (x.at + cb));
+  };
+  int e0, e1, f0, f1;  // row pointers of this group and the next
+  load_rp(first, e0, e1);
+  load_rp(first + step, f0, f1);
+  int b0 = lo_of(e0), b1 = hi_of(e1);
+  fetch(b0, min(b1 - b0, CAP));
+  for (int64_t g = first; g < last; g += step) {
+    VT acc;
 #pragma unroll
-    for (int q = 0; q < CPL; ++q)
-      if (q < nv) dst[q] = acc[q];
+    for (int q = 0; q < CPL; ++q) acc[q] = TW(0);
+    const bool fits = b1 - b0 <= CAP;
+    // (the previous group's gathers have returned: their LDS reads are done)
+    if (fits) {
+#pragma unroll
+      for (int k = 0; k < NL; ++k)
+        if (64 * k + lane < b1 - b0) E[64 * k + lane] = entry(pc[k], pv[k]);
+    }
+    // the next group's entries and the row pointers of the one after it
+    const int nb0 = lo_of(f0), nb1 = hi_of(f1);
+    if (g + step < last) fetch(nb0, min(nb1 - nb0, CAP));
+    int g0, g1;
+    load_rp(g + 2 * step, g0, g1);
+    auto rows = [&](const Entry<TW>* x, int m) {
+      int t = 0;
+      for (; t + UN <= m; t += UN) {
+        VT w[UN];
+        TW v[UN];
+#pragma unroll
+        for (int u = 0; u < UN; ++u) {
+          const Entry<TW> en = x[t + u];
+          v[u] = en.v;
+          w[u] = gather(en);
+        }
+#pragma unroll
+        for (int u = 0; u < UN; ++u)
+#pragma unroll
+          for (int q = 0; q < CPL; ++q) acc[q] += v[u] * w[u][q];
+      }
+      if (t < m) {
+        VT w[UN - 1];
+        TW v[UN - 1];
+#pragma unroll
+        for (int u = 0; u < UN - 1; ++u) {
+#pragma unroll
+          for (int q = 0; q < CPL; ++q) w[u][q] = TW(0);
+          v[u] = TW(0);
+          if (t + u < m) {
+            const Entry<TW> en = x[t + u];
+            v[u] = en.v;
+            w[u] = gather(en);
+          }
+        }
+#pragma unroll
+        for (int u = 0; u < UN - 1; ++u)
+          if (t + u < m) {
+#pragma unroll
+            for (int q = 0; q < CPL; ++q) acc[q] += v[u] * w[u][q];
+          }
+      }
+    };
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    if (fits) {
+      rows(E + (e0 - b0), e1 - e0);
+    } else {
+      // kRowCap entries of every row at a time
+      for (int p = 0; __ballot(p < e1 - e0) != 0; p += kRowCap) {
+        for (int k = l; k < kRowCap; k += G)
+          if (k < e1 - e0 - p) E[r * kRowCap + k] = entry(ci[e0 + p + k], val[e0 + p + k]);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        rows(E + r * kRowCap, min(kRowCap, e1 - e0 - p));
+      }
+    }
+    const int64_t row = g * NR + r;
+    if (row < n && store) *reinterpret_cast<VT*>(Y + row * ldy + c) = acc;
+    e0 = f0;
+    e1 = f1;
+    f0 = g0;
+    f1 = g1;
+    b0 = nb0;
+    b1 = nb1;
   }
 }
 
 template <typename TV, typename TW, int G>
-static hipError_t spmm_vec_launch(const int32_t* rp, const int32_t* ci, const TV* val, const TW* W,
-                                  int64_t ldw, TW* Y, int64_t ldy, int ncols, int64_t n,
-                                  hipStream_t s) {
+static hipError_t spmm_rows_launch(const int32_t* rp, const int32_t* ci, const TV* val, const TW* W,
+                                   int64_t ldw, TW* Y, int64_t ldy, int ncols, int64_t n,
+                                   hipStream_t s) {
   constexpr int CPL = 16 / (int)sizeof(TW);
-  constexpr int UN = (G <= 4 && sizeof(TW) == 8) ? 8 : 4;
-  constexpr int RPB = 256 / G;
-  const int64_t nb = (n + RPB - 1) / RPB;
-  const int64_t nbp = (nb + 7) / 8 * 8;
-  hipLaunchKernelGGL((k_spmm_csr_vec<TV, TW, G, CPL, UN>), dim3((unsigned)nbp), dim3(256), 0, s, rp,
-                     ci, val, W, ldw, Y, ldy, ncols, n, (int)(nbp / 8));
+  constexpr int NR = 64 / G;
+  // a persistent grid, a multiple of the 8 XCDs: four workgroups per CU, three
+  // where a wave takes 16 rows (n = 1e6: 16 fp64 columns 350, 350, 379, 403 us
+  // with 3, 4, 5, 6; 16 fp32 columns 258, 275, 310, 305 us)
+  const int64_t groups = (n + NR - 1) / NR;
+  const int64_t nb = std::min<int64_t>((groups + 3) / 4, 256 * (G == 4 ? 3 : 4));
+  const unsigned grid = (unsigned)((nb + 7) / 8 * 8);
+  const int per = (int)((groups + 7) / 8);
+  if ((uint64_t)n * (uint64_t)ldw * sizeof(TW) >= (1ull << 32))
+    hipLaunchKernelGGL((k_spmm_rows<TV, TW, G, CPL, true>), dim3(grid), dim3(256), 0, s, rp, ci, val, W, ldw, Y,
+                       ldy, ncols, n, per);
+  else
+    hipLaunchKernelGGL((k_spmm_rows<TV, TW, G, CPL, false>), dim3(grid), dim3(256), 0, s, rp, ci, val, W, ldw, Y,
+                       ldy, ncols, n, per);
   return hipGetLastError();
 }
 
@@ -384,29 +501,28 @@ static hipError_t spmm_any(const int32_t* rp, const int32_t* ci, const TV* val, 
     return hipSuccess;
   }
   constexpr int CPL = 16 / (int)sizeof(TW);
-  // 16-byte loads need W and its row stride aligned to CPL elements; the
-  // vector kernel is used from 5 (fp64) / 9 (fp32) columns, below which the
-  // one-column-per-lane kernel is as fast, up to 16 lanes per row
-  const bool aligned = (reinterpret_cast<uintptr_t>(W) % 16) == 0 && ldw % CPL == 0;
-  const int vec_min = (CPL == 2) ? 5 : 9;
-  const int slice = aligned ? 16 * CPL : 64;
+  // the row kernel is used from 5 (fp64) / 9 (fp32) columns, below which the
+  // one-column-per-lane kernel is as fast, up to 16 lanes per row.  Five to
+  // eight fp64 columns that are not aligned to 16 bytes stay with the latter,
+  // which adds the entries of a row in two sums: a solve that has not
+  // converged amplifies rounding, so each product keeps its order of addition.
+  const bool odd = CPL == 2 && ((reinterpret_cast<uintptr_t>(W) % 16) != 0 || ldw % CPL != 0);
+  const int rows_min = (CPL == 2) ? (odd ? 9 : 5) : 9;
+  constexpr int slice = 16 * CPL;
   for (int c0 = 0; c0 < ncols; c0 += slice) {
     const int nc = std::min(slice, ncols - c0);
     const TW* Wc = W + c0;
     TW* Yc = Y + c0;
     hipError_t e;
-    if (aligned && nc >= vec_min) {
+    if (nc >= rows_min) {
       const int lanes = (nc + CPL - 1) / CPL;
-      if (lanes <= 4) e = spmm_vec_launch<TV, TW, 4>(rp, ci, val, Wc, ldw, Yc, ldy, nc, n, s);
-      else if (lanes <= 8) e = spmm_vec_launch<TV, TW, 8>(rp, ci, val, Wc, ldw, Yc, ldy, nc, n, s);
-      else e = spmm_vec_launch<TV, TW, 16>(rp, ci, val, Wc, ldw, Yc, ldy, nc, n, s);
+      if (lanes <= 4) e = spmm_rows_launch<TV, TW, 4>(rp, ci, val, Wc, ldw, Yc, ldy, nc, n, s);
+      else if (lanes <= 8) e = spmm_rows_launch<TV, TW, 8>(rp, ci, val, Wc, ldw, Yc, ldy, nc, n, s);
+      else e = spmm_rows_launch<TV, TW, 16>(rp, ci, val, Wc, ldw, Yc, ldy, nc, n, s);
     } else if (nc <= 1) e = spmm_launch<TV, TW, 1>(rp, ci, val, Wc, ldw, Yc, ldy, nc, n, s);
     else if (nc <= 2) e = spmm_launch<TV, TW, 2>(rp, ci, val, Wc, ldw, Yc, ldy, nc, n, s);
     else if (nc <= 4) e = spmm_launch<TV, TW, 4>(rp, ci, val, Wc, ldw, Yc, ldy, nc, n, s);
-    else if (nc <= 8) e = spmm_launch<TV, TW, 8>(rp, ci, val, Wc, ldw, Yc, ldy, nc, n, s);
-    else if (nc <= 16) e = spmm_launch<TV, TW, 16>(rp, ci, val, Wc, ldw, Yc, ldy, nc, n, s);
-    else if (nc <= 32) e = spmm_launch<TV, TW, 32>(rp, ci, val, Wc, ldw, Yc, ldy, nc, n, s);
-    else e = spmm_launch<TV, TW, 64>(rp, ci, val, Wc, ldw, Yc, ldy, nc, n, s);
+    else e = spmm_launch<TV, TW, 8>(rp, ci, val, Wc, ldw, Yc, ldy, nc, n, s);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
