@@ -99,35 +99,172 @@ __device__ __forceinline__ bool wave_chol16_body(const double* S, int lds_, int 
   }
   return ok;
 }
-template <bool KDIV, bool CHECKINF, bool ZUP>
-__device__ __noinline__ bool wave_chol16_lds(const double* S, int lds_, int n, double shift, double* L,
-                                             int ldl, double* linv) {
-  return wave_chol16_body<KDIV, CHECKINF, ZUP>(S, lds_, n, shift, L, ldl, linv);
+// Cholesky of an n x n matrix (n <= N <= 16) in LDS by one wave, each row of 16
+// lanes with a copy of its own: lane l holds matrix row l % 16 in g (only the
+// lower triangle is read; rows and columns from n to N - 1 are those of the
+// identity).  The pivot is handed on by DPP, so a column costs a root, a
+// division, a product and an update in sequence (220 cycles; by lane shuffles
+// through LDS 1100).  Every entry takes the operations of reg_chol16 in its
+// order: G[r][k] / l_kk (KDIV) or G[r][k] * (1 / l_kk), and
+// G[r][c] - L[r][k] L[c][k] as one fused multiply-add.  On return g holds L
+// and inv the reciprocals of its diagonal (!KDIV).  False, uniform, when a
+// pivot is not > 0 (or, CHECKINF, not finite).
+template <int N, bool KDIV, bool CHECKINF>
+__device__ __forceinline__ bool chol16_rows(const double* G, int ldg, int n, double (&g)[N], double (&inv)[N]) {
+  const int r = threadIdx.x & 15;
+  const double* Gr = G + min(r, n - 1) * ldg;
+#pragma unroll
+  for (int c = 0; c < N; ++c) {
+    const double v = Gr[min(c, n - 1)];
+    g[c] = ((r < n) & (c < n) & (r >= c)) ? v : ((r == c) ? 1.0 : 0.0);
+  }
+  bool bad = false;
+  static_for<0, N>([&](auto kc) {
+    constexpr int k = decltype(kc)::value;
+    const double gkk = row_bcast<k>(g[k]);
+    bad |= !(gkk > 0.0) | (CHECKINF & !(gkk < INFINITY));
+    const double lkk = sqrt(gkk);
+    double below;
+    if (KDIV) {
+      below = g[k] / lkk;
+    } else {
+      inv[k] = 1.0 / lkk;
+      below = g[k] * inv[k];
+    }
+    g[k] = (r > k) ? below : (r == k) ? lkk : g[k];
+    static_for<k + 1, N>([&](auto cc) {
+      constexpr int c = decltype(cc)::value;
+      const double lck = row_bcast<c>(g[k]);
+      g[c] = fma(-g[k], lck, g[c]);  // (r < c: not used)
+    });
+    __builtin_amdgcn_sched_barrier(0);
+  });
+  // (or the broadcasts above would be kept, two registers each, for the solves)
+#pragma unroll
+  for (int c = 0; c < N; ++c) asm("" : "+v"(g[c]));
+  return __ballot(bad) == 0;
+}
+// X (p x n) <- X L^-T for row i of this lane, L in g as chol16_rows leaves it.
+// KDIV: z_j = (x_j - sum_{k<j} z_k L_jk) / L_jj, summed in order; else the sum
+// runs over even and odd k apart and the reciprocal multiplies it.
+template <int N, bool KDIV>
+__device__ __forceinline__ void trsm16_rows(double* X, int ldx, int i, int p, int n, const double (&g)[N],
+                                            const double (&inv)[N]) {
+  double z[N];
+  double* Xi = X + min(i, p - 1) * ldx;
+#pragma unroll
+  for (int j = 0; j < N; ++j) z[j] = Xi[min(j, n - 1)];
+  static_for<0, N>([&](auto jc) {
+    constexpr int j = decltype(jc)::value;
+    if (KDIV) {
+      double t = z[j];
+      static_for<0, j>([&](auto kc) {
+        constexpr int k = decltype(kc)::value;
+        t = fma(-z[k], row_bcast<j>(g[k]), t);
+      });
+      z[j] = t / row_bcast<j>(g[j]);
+    } else {
+      double s0 = z[j], s1 = 0.0;
+      static_for<0, j>([&](auto kc) {
+        constexpr int k = decltype(kc)::value;
+        const double ljk = row_bcast<j>(g[k]);
+        if (k % 2 == 0) s0 = fma(-z[k], ljk, s0);
+        else s1 = fma(-z[k], ljk, s1);
+      });
+      z[j] = (s0 + s1) * inv[j];
+    }
+    asm volatile("" : "+v"(z[j]));  // (computed here, not where it is stored: the broadcasts would stay)
+  });
+  if (i < p) {
+#pragma unroll
+    for (int j = 0; j < N; ++j)
+      if (j < n) Xi[j] = z[j];
+  }
+}
+// both, by the waves that have rows (64 to a wave); the flag (LDS) is 1 on success
+template <int N, bool KDIV, bool CHECKINF>
+__device__ __forceinline__ void chol_trsm(double* X, int ldx, int p, int n, const double* G, int ldg, int* flag) {
+  if (64 * wave_id() < p) {
+    double g[N], inv[N];
+    const bool ok = chol16_rows<N, KDIV, CHECKINF>(G, ldg, n, g, inv);
+    if (ok) trsm16_rows<N, KDIV>(X, ldx, 64 * wave_id() + (threadIdx.x & 63), p, n, g, inv);
+    if (threadIdx.x == 0) *flag = ok ? 1 : 0;
+  }
 }
 
 // ---------------------------------------------------------------------------
 // block-wide helpers (every thread of the block calls them)
 
+// ---- small products on the fp64 MFMA 16x16x4 -------------------------------
+// Lane l holds A[l % 16][l / 16] and B[l / 16][l % 16]; accumulator register
+// r is row 4 r + l / 16, column l % 16.  An accumulator takes its products one
+// after the other, k ascending, each as a fused multiply-add: the bits of the
+// scalar loop s = fma(a, b, s).
+typedef double d4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ d4 mma64(double a, double b, d4 c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+// f(i, j, sum) over the entries of A^T B (A: K x m, B: K x n), a wave per 16 x 16 tile
+template <class F>
+__device__ __forceinline__ void blk_tiles_tn(const double* A, int lda, const double* B, int ldb, int K, int m, int n,
+                                             F&& f) {
+  const int lane = threadIdx.x & 63, g = lane >> 4, r = lane & 15;
+  const int tm = (m + 15) >> 4, tn = (n + 15) >> 4;
+  for (int t = wave_id(); t < tm * tn; t += blockDim.x >> 6) {
+    const int i0 = 16 * (tn == 1 ? t : t / tn), j0 = tn == 1 ? 0 : 16 * (t % tn);
+    const bool vi = i0 + r < m, vj = j0 + r < n;
+    d4 acc = {0.0, 0.0, 0.0, 0.0};
+    for (int k0 = 0; k0 < K; k0 += 16) {
+      double av[4], bv[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int k = k0 + 4 * u + g, kc = min(k, K - 1);
+        const double x = A[kc * lda + min(i0 + r, m - 1)], y = B[kc * ldb + min(j0 + r, n - 1)];
+        av[u] = (vi & (k < K)) ? x : 0.0;
+        bv[u] = (vj & (k < K)) ? y : 0.0;
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) acc = mma64(av[u], bv[u], acc);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int i = i0 + 4 * q + g;
+      if (i < m && vj) f(i, j0 + r, acc[q]);
+    }
+  }
+}
 // C (p x q) = A^T B, A: n x p, B: n x q
 __device__ __forceinline__ void blk_gemm_tn(const double* A, int lda, const double* B, int ldb, int n, int p,
                             int q, double* C, int ldc) {
-  for (int idx = threadIdx.x; idx < p * q; idx += blockDim.x) {
-    const int i = idx / q, j = idx - i * q;
-    double s = 0.0;
-    for (int r = 0; r < n; ++r) s += A[r * lda + i] * B[r * ldb + j];
-    C[i * ldc + j] = s;
-  }
+  blk_tiles_tn(A, lda, B, ldb, n, p, q, [&](int i, int j, double v) { C[i * ldc + j] = v; });
   __syncthreads();
 }
 
 // X (n x q) -= Y (n x p) C (p x q)
 __device__ __forceinline__ void blk_sub_mm(double* X, int ldx, const double* Y, int ldy, const double* C, int ldc,
                            int n, int p, int q) {
-  for (int idx = threadIdx.x; idx < n * q; idx += blockDim.x) {
-    const int r = idx / q, j = idx - r * q;
-    double s = 0.0;
-    for (int k = 0; k < p; ++k) s += Y[r * ldy + k] * C[k * ldc + j];
-    X[r * ldx + j] -= s;
+  const int lane = threadIdx.x & 63, g = lane >> 4, r = lane & 15;
+  const int tm = (n + 15) >> 4, tn = (q + 15) >> 4;
+  for (int t = wave_id(); t < tm * tn; t += blockDim.x >> 6) {
+    const int i0 = 16 * (tn == 1 ? t : t / tn), j0 = tn == 1 ? 0 : 16 * (t % tn);
+    d4 acc = {0.0, 0.0, 0.0, 0.0};
+    for (int k0 = 0; k0 < p; k0 += 16) {
+      double av[4], bv[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int k = k0 + 4 * u + g;
+        const double x = Y[min(i0 + r, n - 1) * ldy + min(k, p - 1)], y = C[min(k, p - 1) * ldc + min(j0 + r, q - 1)];
+        av[u] = ((i0 + r < n) & (k < p)) ? x : 0.0;
+        bv[u] = ((j0 + r < q) & (k < p)) ? y : 0.0;
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) acc = mma64(av[u], bv[u], acc);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int i = i0 + 4 * u + g;
+      if (i < n && j0 + r < q) X[i * ldx + j0 + r] -= acc[u];
+    }
   }
   __syncthreads();
 }
@@ -137,6 +274,7 @@ __device__ __forceinline__ void blk_sub_mm(double* X, int ldx, const double* Y, 
 __device__ __forceinline__ void blk_normalize(double* X, int ldx, int n, int q, double* tmp, int* zeros) {
   for (int j = threadIdx.x; j < q; j += blockDim.x) {
     double s = 0.0;
+#pragma unroll 16
     for (int r = 0; r < n; ++r) s += X[r * ldx + j] * X[r * ldx + j];
     if (s == 0.0) {
       for (int r = 0; r < n; ++r) {
@@ -150,10 +288,8 @@ __device__ __forceinline__ void blk_normalize(double* X, int ldx, int n, int q, 
     tmp[j] = sqrt(s);
   }
   __syncthreads();
-  for (int idx = threadIdx.x; idx < n * q; idx += blockDim.x) {
-    const int j = idx % q;
-    X[idx / q * ldx + j] /= tmp[j];
-  }
+  for (int j = threadIdx.x & 15; j < q; j += 16)
+    for (int r = threadIdx.x >> 4; r < n; r += blockDim.x >> 4) X[r * ldx + j] /= tmp[j];
   __syncthreads();
 }
 
@@ -168,12 +304,11 @@ __device__ __forceinline__ void blk_normalize(double* X, int ldx, int n, int q, 
 // factorization.  Each entry takes the same operations in the same order as
 // a column-parallel factorization by the whole workgroup.
 // REG: 0 column by column in LDS, 1 registers (out of line), 2 registers (inline)
-template <int REG = 1>
+template <bool REG>
 __device__ __forceinline__ bool blk_chol(const double* M, int ldm, int n, double shift, double* L, int ldl,
                          int* flag) {
-  if (REG != 0 && threadIdx.x < 64 && n <= 16) {
-    const bool ok = (REG == 1) ? wave_chol16_lds<true, false, true>(M, ldm, n, shift, L, ldl, nullptr)
-                               : wave_chol16_body<true, false, true>(M, ldm, n, shift, L, ldl, nullptr);
+  if (REG && threadIdx.x < 64 && n <= 16) {
+    const bool ok = wave_chol16_body<true, false, true>(M, ldm, n, shift, L, ldl, nullptr);
     if (threadIdx.x == 0) *flag = ok ? 0 : 1;
   } else if (threadIdx.x < 64) {
     const int l = threadIdx.x;
@@ -213,12 +348,13 @@ struct ShiftCount {
 };
 
 // Sec. 3.2 / Alg. 2: plain Cholesky, then shifts alpha*eps*||X||_F with
-// ||X||_F = sqrt(trace M), alpha = 100, x10 per retry.
-template <int REG = 1>
+// ||X||_F = sqrt(trace M), alpha = 100, x10 per retry.  plain = false: the
+// caller has tried the plain one, and failed.
+template <bool REG>
 __device__ __forceinline__ bool blk_shifted_chol(const double* M, int ldm, int n, double* L, int ldl, int* flag,
-                                 ShiftCount* c, double* scratch, int retries = kShiftRetries) {
+                                 ShiftCount* c, double* scratch, int retries = kShiftRetries, bool plain = true) {
   if (threadIdx.x == 0) c->factorizations++;
-  if (blk_chol<REG>(M, ldm, n, 0.0, L, ldl, flag)) return true;
+  if (plain && blk_chol<REG>(M, ldm, n, 0.0, L, ldl, flag)) return true;
   if (threadIdx.x == 0) c->failed++;
   double tr = 0.0;
   for (int i = 0; i < n; ++i) tr += M[i * ldm + i];
@@ -338,122 +474,324 @@ __device__ __forceinline__ void load_sym(const double* a, int p, double* A, int 
 constexpr int kMsPoints = 32;              // multisection points per eigenvalue
 
 
-// LDS layout after the p x (p+1) A area, in doubles
+// Every phase is bounded by the latency of dependent steps, not by their
+// number, and every sum keeps its order (see the comment of k_small_rr): eight
+// waves, two per SIMD, a barrier as rarely as possible.
+
+constexpr int kRrThreads = 512;
+typedef double dd2 __attribute__((ext_vector_type(2)));
+
+// LDS layout (the matrix comes first), in doubles
 struct TriLayout {
   int ldz, nb;
-  int d, e, inve, e2, beta, vv, ww, ev, linv, G, Z, ws, sw, total;
+  int de, d, e, inve, beta, ww, ev, linv, G, Z, ws;
 };
+// row stride of the matrix: up to p = 64 rows are padded by 64 zeros (and lie on
+// different banks), so that no lane needs to know where they end
+__host__ __device__ inline int tri_lda(int p) { return p > 64 ? p + 1 : p > 33 ? 129 : 97; }
 __host__ __device__ inline TriLayout tri_layout(int p, int nev) {
   TriLayout t;
   t.ldz = nev + 1;
-  int o = 0;
-  t.d = o; o += p;
-  t.e = o; o += p;
-  t.inve = o; o += p;
-  t.e2 = o; o += p;
+  const int o0 = (p * tri_lda(p) + 1) & ~1;  // after the matrix
+  int o = o0;
+  t.de = o; o += 2 * (p + 24);  // pairs: diagonal, square of the entry above it; padded
+  t.d = o; o += p + 9;
+  t.e = o; o += p + 9;
+  t.inve = o; o += p + 9;
   t.beta = o; o += p;
-  t.vv = o; o += p;
-  t.ww = o; o += p;
+  o += o & 1;
+  t.ww = o; o += (p > 64) ? p : 3 * (p + 64);
   t.ev = o; o += nev;
   t.linv = o; o += nev;
   t.G = o; o += nev * (nev + 1);
   t.Z = o; o += p * t.ldz;
   t.ws = o;
-  const int avail = kEigLdsBytes / 8 - p * (p + 1) - o;
-  const int per = 4 * p + (p + 7) / 8 + 1;  // U0^-1, U1, U2, multipliers + pivot flags
+  const int avail = kEigLdsBytes / 8 - o;
+  const int per = 4 * (((p + 7) & ~7) + 1);  // z, U0^-1, U1, multipliers
   int nb = avail / per;
   if (nb > nev) nb = nev;
   t.nb = nb;
-  if (nb < 1) {
-    t.sw = o;
-    t.total = o;
-    return t;
-  }
-  o += 4 * p * nb;
-  t.sw = o;
-  o += (p * nb + 7) / 8;
-  t.total = o;
   return t;
 }
 
-// Householder reduction by the whole workgroup, three barriers per step:
-// wave 0 forms reflector k from row k (= column k, the trailing block is
-// kept symmetric); each wave takes rows i of p = beta A v, its lanes
-// splitting the row; every thread then updates trailing entries with
-// w = p - K v, K = beta/2 p^T v (formed by every wave in the same order).
-__device__ void blk_tridiag(double* A, int lda, int p, double* d, double* e, double* beta, double* vv,
-                            double* pp) {
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, nw = blockDim.x >> 6;
+// Sum over 64 leaves, 4 q + u in x[u] of lane q of a row of 16, the same bits
+// as wave_sum of leaf l in lane l: both add by a balanced tree.
+__device__ __forceinline__ double tree64(const double (&x)[4]) { return row_sum((x[0] + x[1]) + (x[2] + x[3])); }
+
+// Householder reduction by the whole workgroup, two barriers per step: every
+// wave forms reflector k from row k (= column k, the trailing block is kept
+// symmetric but for rounding); each row of 16 lanes takes a row i of
+// p = beta A v, four entries per lane; every wave forms K = beta/2 p^T v and
+// updates its rows of the trailing block with w = p - K v.
+__device__ __forceinline__ void blk_tridiag(double* A, int lda, int p, double* d, double* e, double* beta, double* pp) {
+  constexpr int NW = kRrThreads / 64;
+  constexpr int H = 2, T = 3;  // entries per lane / 4, passes of 4 NW rows
+  const int tid = threadIdx.x, wave = wave_id(), lane = tid & 63, q = lane & 15, rg = lane >> 4;
   for (int k = 0; k + 2 < p; ++k) {
-    const int k1 = k + 1, s = p - k1;
-    if (wave == 0) {
-      double x[2];
-      double tail = 0.0;
+    const int k1 = k + 1;
+    const double* row = A + k * lda;
+    const double x1 = row[k1];
+    // row k by leaves of the norm (entry i: leaf i) and of the products
+    // (entry k1 + l: leaf l), and this wave's rows of the block
+    double xa[H][4], v[H][4], a[T][H][4];
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int i = lane + 64 * h;
-        x[h] = (i > k && i < p) ? A[k * lda + i] : 0.0;
-        if (i > k1) tail += x[h] * x[h];
-      }
-      const double x1 = A[k * lda + k1];
-      tail = wave_sum(tail);
-      double alpha = x1, b = 0.0;
-      if (tail > 0.0) {
-        const double nrm = sqrt(x1 * x1 + tail);
-        alpha = (x1 >= 0.0) ? -nrm : nrm;
-        b = 1.0 / (nrm * (nrm + fabs(x1)));  // 2 / v^T v for v = x - alpha e_1
+    for (int h = 0; h < H; ++h)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int i = 4 * q + u + 64 * h, j = k1 + i;
+        const double x = row[min(i, p - 1)], y = row[min(j, p - 1)];
+        xa[h][u] = ((i > k1) & (i < p)) ? x : 0.0;
+        v[h][u] = (j < p) ? y : 0.0;
       }
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int i = lane + 64 * h;
-        if (i > k && i < p) {
-          const double v = (b != 0.0 && i == k1) ? x1 - alpha : x[h];
-          A[i * lda + k] = v;  // reflector k, kept for the back-transformation
-          vv[i] = v;
-        }
-      }
-      if (lane == 0) {
-        d[k] = A[k * lda + k];
-        e[k] = alpha;
-        beta[k] = b;
+    for (int t = 0; t < T; ++t) {
+      const int i = k1 + 4 * wave + rg + 4 * NW * t;
+      if (k1 + 4 * wave + 4 * NW * t < p) {
+#pragma unroll
+        for (int h = 0; h < H; ++h)
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const int j = k1 + 4 * q + u + 64 * h;
+            a[t][h][u] = A[min(i, p - 1) * lda + min(j, p - 1)];  // (v is zero past the end)
+          }
       }
     }
-    __syncthreads();
-    const double b = beta[k];
+    double lf[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      lf[u] = fma(xa[0][u], xa[0][u], 0.0);  // (a bare product would fuse with the tree's first sum)
+      if (H == 2) lf[u] = fma(xa[H - 1][u], xa[H - 1][u], lf[u]);
+    }
+    const double tail = tree64(lf);
+    double alpha = x1, b = 0.0;
+    if (tail > 0.0) {
+      const double nrm = sqrt(x1 * x1 + tail);
+      alpha = (x1 >= 0.0) ? -nrm : nrm;
+      b = 1.0 / (nrm * (nrm + fabs(x1)));  // 2 / v^T v for v = x - alpha e_1
+    }
+    const double v1 = (b != 0.0) ? x1 - alpha : x1;
+    if (tid > k && tid < p) A[tid * lda + k] = (tid == k1) ? v1 : row[tid];  // kept for the back-transformation
+    if (tid == 0) {
+      d[k] = row[k];
+      e[k] = alpha;
+      beta[k] = b;
+    }
     if (b == 0.0) continue;  // H_k = I (uniform)
-    for (int i = k1 + wave; i < p; i += nw) {
-      double acc = 0.0;
+    if (q == 0) v[0][0] = v1;
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int j = k1 + lane + 64 * h;
-        if (j < p) acc += A[i * lda + j] * vv[j];
+    for (int t = 0; t < T; ++t) {
+      const int i = k1 + 4 * wave + rg + 4 * NW * t;
+      if (k1 + 4 * wave + 4 * NW * t < p) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          lf[u] = fma(a[t][0][u], v[0][u], 0.0);
+          if (H == 2) lf[u] = fma(a[t][H - 1][u], v[H - 1][u], lf[u]);
+        }
+        const double acc = tree64(lf);
+        if (q == 0 && i < p) pp[i] = b * acc;
       }
-      acc = wave_sum(acc);
-      if (lane == 0) pp[i] = b * acc;
     }
     __syncthreads();
-    double kp = 0.0;
+    // column lane (+ 64) of the update, and the leaves of p^T v
+    double vi[H], wi[H];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
+    for (int h = 0; h < H; ++h) {
       const int i = k1 + lane + 64 * h;
-      if (i < p) kp += pp[i] * vv[i];
+      const double x = row[min(i, p - 1)];
+      vi[h] = (i == k1) ? v1 : x;
+      wi[h] = pp[min(i, p - 1)];
     }
-    const double K = 0.5 * b * wave_sum(kp);
-    for (int idx = tid; idx < s * s; idx += blockDim.x) {
-      const int jj = idx / s, ii = idx - jj * s;
-      const int j = k1 + jj, i = k1 + ii;
-      const double vj = vv[j], vi = vv[i];
-      const double wi = pp[i] - K * vi, wj = pp[j] - K * vj;
-      A[j * lda + i] -= vj * wi + wj * vi;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      lf[u] = 0.0;
+#pragma unroll
+      for (int h = 0; h < H; ++h) {
+        const int i = k1 + 4 * q + u + 64 * h;
+        const double pi = pp[min(i, p - 1)];
+        lf[u] = fma((i < p) ? pi : 0.0, v[h][u], lf[u]);
+      }
+    }
+    // rows wave, wave + NW, ...: the first ones' entries are on their way
+    constexpr int UR = 4;
+    double vj[UR], wj[UR], aj[UR][H];
+    auto load = [&](int j0) {
+#pragma unroll
+      for (int r = 0; r < UR; ++r) {
+        const int j = min(j0 + NW * r, p - 1);
+        const double x = row[j];
+        vj[r] = (j == k1) ? v1 : x;
+        wj[r] = pp[j];
+#pragma unroll
+        for (int h = 0; h < H; ++h) aj[r][h] = A[j * lda + min(k1 + lane + 64 * h, p - 1)];
+      }
+    };
+    load(k1 + wave);
+    const double K = 0.5 * b * tree64(lf);
+#pragma unroll
+    for (int h = 0; h < H; ++h) wi[h] = wi[h] - K * vi[h];
+    for (int j0 = k1 + wave; j0 < p; j0 += UR * NW) {
+      if (j0 != k1 + wave) load(j0);
+#pragma unroll
+      for (int r = 0; r < UR; ++r) {
+        const int j = j0 + NW * r;
+        const double w = wj[r] - K * vj[r];
+#pragma unroll
+        for (int h = 0; h < H; ++h)
+          if (j < p && k1 + lane + 64 * h < p) A[j * lda + k1 + lane + 64 * h] = aj[r][h] - (vj[r] * wi[h] + w * vi[h]);
+      }
     }
     __syncthreads();
   }
+  __syncthreads();
   if (tid == 0) {
     if (p >= 2) {
       d[p - 2] = A[(p - 2) * lda + p - 2];
       e[p - 2] = A[(p - 1) * lda + p - 2];
     }
     d[p - 1] = A[(p - 1) * lda + p - 1];
+  }
+  __syncthreads();
+}
+
+// The same up to p = 64, by four waves (one per SIMD; the others only meet the
+// barriers), the block in registers: lane 16 g + l of wave w holds, of the rows
+// 4 w + g + 16 t, the columns k + 1 + 4 l .. + 3 of step k, and moves them on by
+// one when it has updated them.  LDS carries row k, beta and p only: a wave's
+// load costs the LDS its whole width, also where all waves read the same, and
+// with the block in LDS as well its traffic bound a step (3500 cycles at
+// p = 48, now 3100: the chains of roots, divisions and tree sums).  The wave with row k forms the reflector; vv (two of p + 64 entries) and
+// pp (p + 64) are padded by zeros, as the block is.
+__device__ __forceinline__ void blk_tridiag64(double* A, int lda, int p, double* d, double* e, double* beta, double* vv0,
+                                              double* pp) {
+  constexpr int NW = 4;
+  const int tid = threadIdx.x, wave = wave_id(), lane = tid & 63, q4 = 4 * (lane & 15), rg = lane >> 4;
+  double* vv1 = vv0 + p + 64;
+  for (int i = tid; i < p + 64; i += kRrThreads) vv0[i] = vv1[i] = pp[i] = 0.0;
+  const int r0 = 4 * wave + rg;  // rows r0 + 16 t
+  double a[4][4];
+  if (wave < NW) {
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) a[t][u] = A[min(r0 + 16 * t, p - 1) * lda + q4 + u];
+  }
+  __syncthreads();
+  // column k1 is first: its diagonal entry, at the end the last entries
+  auto emit = [&](int k1) {
+    if (wave == ((k1 >> 2) & 3)) {
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        if ((k1 >> 4) == t) {
+          if (lane == 16 * (k1 & 3)) d[k1] = a[t][0];
+        }
+    }
+    if (k1 + 2 == p && wave == (((p - 1) >> 2) & 3)) {
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        if (((p - 1) >> 4) == t) {
+          if (lane == 16 * ((p - 1) & 3)) {
+            e[p - 2] = a[t][0];
+            d[p - 1] = a[t][1];
+          }
+        }
+    }
+  };
+  auto advance = [&](double (&x)[4]) {
+    const double n = dpp_f64<0x101>(x[0]);  // lane + 1 of the row, zero past its end
+    x[0] = x[1];
+    x[1] = x[2];
+    x[2] = x[3];
+    x[3] = n;
+  };
+  if (wave < NW) {
+    emit(0);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) advance(a[t]);
+  }
+  for (int k = 0; k + 2 < p; ++k) {
+    const int k1 = k + 1;
+    double* vv = (k & 1) ? vv1 : vv0;
+    if (wave == ((k >> 2) & 3)) {
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        if ((k >> 4) == t) {
+          if (rg == (k & 3)) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) vv[k1 + q4 + u] = a[t][u];
+          }
+        }
+      wave_sync();
+      const double x1 = vv[k1], own = vv[lane];
+      double lf[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) lf[u] = vv[q4 + u];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const double x = (q4 + u > k1) ? lf[u] : 0.0;
+        lf[u] = fma(x, x, 0.0);  // (a bare product would fuse with the tree's first sum)
+      }
+      const double tail = tree64(lf);
+      double alpha = x1, b = 0.0;
+      if (__ballot(tail > 0.0) != 0) {  // (uniform)
+        const double nrm = sqrt(fma(x1, x1, tail));
+        alpha = (x1 >= 0.0) ? -nrm : nrm;
+        b = 1.0 / (nrm * (nrm + fabs(x1)));  // 2 / v^T v for v = x - alpha e_1
+      }
+      const double v1 = (b != 0.0) ? x1 - alpha : x1;
+      if (lane == 0) {
+        vv[k1] = v1;
+        e[k] = alpha;
+        beta[k] = b;
+      }
+      if ((lane > k) & (lane < p)) A[lane * lda + k] = (lane == k1) ? v1 : own;  // kept for the back-transformation
+    }
+    __syncthreads();
+    const double b = beta[k];
+    const bool on = __ballot(b != 0.0) != 0;  // (uniform; else H_k = I)
+    double v[4];
+    if ((wave < NW) & on) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = vv[k1 + q4 + u];
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        if ((16 * t + 15 >= k1) & (16 * t < p)) {
+          double lf[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) lf[u] = fma(a[t][u], v[u], 0.0);
+          const double acc = tree64(lf);
+          const int i = r0 + 16 * t;
+          if ((q4 == 0) & (i >= k1) & (i < p)) pp[i] = b * acc;
+        }
+    }
+    __syncthreads();
+    if (wave < NW) {
+      if (on) {
+        double lf[4], wi[4], vj[4], pj[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) wi[u] = pp[k1 + q4 + u];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          const int i = min(r0 + 16 * t, p - 1);
+          vj[t] = vv[i];
+          pj[t] = pp[i];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) lf[u] = fma(wi[u], v[u], 0.0);
+        const double K = 0.5 * b * tree64(lf);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) wi[u] = fma(-K, v[u], wi[u]);
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+          if ((16 * t + 15 >= k1) & (16 * t < p)) {
+            const double wj = fma(-K, vj[t], pj[t]);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) a[t][u] = a[t][u] - fma(vj[t], wi[u], wj * v[u]);
+          }
+      }
+      emit(k1);
+#pragma unroll
+      for (int t = 0; t < 4; ++t) advance(a[t]);
+    }
   }
   __syncthreads();
 }
@@ -465,215 +803,267 @@ __device__ __forceinline__ double rcp_nr(double q) {
   return fma(r, fma(-q, r, 1.0), r);
 }
 
-// number of eigenvalues of T below x (negative pivots of T - x I)
-__device__ __forceinline__ int sturm_count(const double* d, const double* e2, int p, double x,
+// number of eigenvalues of T below x (negative pivots of T - x I).  Each row of
+// 16 lanes holds the pairs (diagonal, square of the entry above it) of steps
+// 1 + 16 c + (lane % 16) in t[c] and hands them on by DPP (read from LDS, each
+// wave's broadcast of a pair costs 8 cycles of all waves': that bound the
+// loop); past the end come steps (infinity, 0) that count nothing.
+template <int NC>
+__device__ __forceinline__ int sturm_count(const double (&td)[NC], const double (&te)[NC], double d0, int p, double x,
                                            double pivmin) {
-  double q = d[0] - x;
   int c = 0;
-  if (q <= pivmin) {
-    ++c;
-    q = fmin(q, -pivmin);
-  }
-#pragma unroll 4
-  for (int i = 1; i < p; ++i) {
-    q = (d[i] - x) - e2[i - 1] * rcp_nr(q);
-    if (q <= pivmin) {
-      ++c;
-      q = fmin(q, -pivmin);
-    }
+  double q = d0 - x;
+  auto guard = [&]() {
+    c += (q <= pivmin) ? 1 : 0;
+    q = (fabs(q) <= pivmin) ? -pivmin : q;
+  };
+  guard();
+#pragma unroll
+  for (int k = 0; k < NC; ++k) {
+    if (1 + 16 * k >= p) break;
+    static_for<0, 4>([&](auto h) {
+      if (1 + 16 * k + 4 * decltype(h)::value < p) {
+        static_for<0, 4>([&](auto u) {
+          constexpr int U = 4 * decltype(h)::value + decltype(u)::value;
+          q = (row_bcast<U>(td[k]) - x) - row_bcast<U>(te[k]) * rcp_nr(q);
+          guard();
+        });
+      }
+    });
   }
   return c;
 }
 
-// eigenvalues 0 .. nev-1 (ascending) of T into ev; every thread calls it
-__device__ void blk_multisection(const double* d, const double* e2, int p, int nev, double gl, double gu,
-                                 double tnorm, double pivmin, double* ev) {
+// eigenvalues 0 .. nev-1 (ascending) of T into ev; every thread calls it.  The
+// points per eigenvalue and round are those of 1024 threads.
+template <int NC>
+__device__ __forceinline__ void blk_multisection(const dd2* de, int p, int nev, double gl, double gu, double tnorm,
+                                                 double pivmin, double* ev) {
   int G = kMsPoints;
-  while (G > 1 && G * nev > (int)blockDim.x) G >>= 1;
+  while (G > 1 && G * nev > 1024) G >>= 1;
   const int t = threadIdx.x & (G - 1);
-  const int gi = threadIdx.x / G, ngroups = blockDim.x / G;
+  const int gi = threadIdx.x / G, ngroups = kRrThreads / G;
   const int lane = threadIdx.x & 63;
   const uint64_t gmask = (G == 64) ? ~0ull : (((1ull << G) - 1ull) << (lane & ~(G - 1)));
-  for (int j = gi; j < nev; j += ngroups) {
+  double td[NC], te[NC];
+  const double d0 = de[0][0];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) {
+    const dd2 x = de[min(1 + 16 * c + (lane & 15), p + 15)];
+    td[c] = x[0];
+    te[c] = x[1];
+  }
+  for (int j0 = 0; j0 < nev; j0 += ngroups) {
+    const int j = j0 + gi;
+    bool act = j < nev;
     double lo = gl, hi = gu;
     for (int round = 0; round < 256; ++round) {
       const double w = hi - lo;
-      if (w <= 2.0 * kEps * fmax(fabs(lo), fabs(hi)) || w <= kEps * tnorm) break;
+      act = act && !(w <= 2.0 * kEps * fmax(fabs(lo), fabs(hi)) || w <= kEps * tnorm);
+      if (__ballot(act) == 0) break;  // (all lanes of a wave run: their registers are read by DPP)
       const double h = w / (double)(G + 1);
       const double x = lo + (double)(t + 1) * h;
-      const int c = sturm_count(d, e2, p, x, pivmin);
+      const int c = sturm_count<NC>(td, te, d0, p, x, pivmin);
       const int k = __popcll(__ballot(c <= j) & gmask);
       const double nlo = (k > 0) ? lo + (double)k * h : lo;
       const double nhi = (k < G) ? lo + (double)(k + 1) * h : hi;
-      if (nlo == lo && nhi == hi) break;
-      lo = nlo;
-      hi = nhi;
+      act = act && !(nlo == lo && nhi == hi);
+      if (act) {
+        lo = nlo;
+        hi = nhi;
+      }
     }
-    if (t == 0) ev[j] = lo + 0.5 * (hi - lo);
+    if (t == 0 && j < nev) ev[j] = lo + 0.5 * (hi - lo);
   }
 }
 
-// one inverse-iteration solve of (T - lam I) z = Z[:, j] for the vectors
-// j = j0 + t, t < nb (thread t); factor = true builds the LU, else reuses it.
-// The loads of the next step are issued before the current step's stores.
-__device__ void tri_invit_solve(const double* __restrict__ d, const double* __restrict__ e,
-                                const double* __restrict__ inve, int p, double lam, double tol, double* Z,
-                                int ldz, int j, double* ws, uint8_t* sw, int nb, int t, bool factor) {
-  double* U0 = ws;
-  double* U1 = ws + p * nb;
-  double* U2 = ws + 2 * p * nb;
-  double* LM = ws + 3 * p * nb;
-  double y = Z[j];
-  double bnx = (p > 1) ? Z[ldz + j] : 0.0;
-  if (factor) {
-    double c0 = d[0] - lam, c1 = (p > 1) ? e[0] : 0.0;
-    for (int i = 0; i + 1 < p; ++i) {
-      const double ei = e[i];
-      const double dn = d[i + 1] - lam;
-      const double en = (i + 2 < p) ? e[i + 1] : 0.0;
-      const double ie = inve[i];
-      const double bn = bnx;
-      if (i + 2 < p) bnx = Z[(i + 2) * ldz + j];
-      if (fabs(c0) >= fabs(ei)) {
-        if (fabs(c0) < tol) c0 = (c0 < 0.0) ? -tol : tol;
-        const double li = ei / c0;
-        U0[i * nb + t] = 1.0 / c0;
-        U1[i * nb + t] = c1;
-        U2[i * nb + t] = 0.0;
-        LM[i * nb + t] = li;
-        sw[i * nb + t] = 0;
-        Z[i * ldz + j] = y;
-        y = bn - li * y;
-        c0 = dn - li * c1;
-        c1 = en;
+// Inverse iteration, one solve of (T - lam I) z = z per thread, in two halves.
+// The forward one builds the LU (FACTOR: partial pivoting by selects, so that
+// lanes that swap and lanes that do not take the same steps) and keeps U1, the
+// multipliers and the pivots, whose reciprocals the whole workgroup forms in
+// between, in LDS, the swaps as bits in sw0, sw1: U2 is e_{i+1} after a swap, 0
+// otherwise.  One thread's entries of an array lie together (odd stride between
+// threads: no address arithmetic, no bank conflicts), rows p .. p8-1 continue T
+// by the identity (e = 0; zero in z) and leave the others as they are, so that
+// rows go by eights without a branch, their operands loaded ahead of the
+// dependent chain.
+template <bool FACTOR>
+__device__ __forceinline__ void invit_forward(const double* __restrict__ d, const double* __restrict__ e,
+                                              const double* __restrict__ inve, int p8, double lam, double tol,
+                                              double* __restrict__ Z, double* __restrict__ U0,
+                                              double* __restrict__ U1, double* __restrict__ LM, uint64_t& sw0,
+                                              uint64_t& sw1) {
+  double y = Z[0];
+  double c0 = d[0] - lam, c1 = e[0];
+  if (FACTOR) sw0 = sw1 = 0;
+  for (int i0 = 0; i0 < p8; i0 += 8) {
+    double bz[8], dn[8], en[9], ie[8], lm[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int i = i0 + u;
+      bz[u] = Z[i + 1];
+      if (FACTOR) {
+        dn[u] = d[i + 1] - lam;
+        en[u] = e[i];
+        ie[u] = inve[i];
       } else {
-        const double li = c0 * ie;
-        U0[i * nb + t] = ie;
-        U1[i * nb + t] = dn;
-        U2[i * nb + t] = en;
-        LM[i * nb + t] = li;
-        sw[i * nb + t] = 1;
-        Z[i * ldz + j] = bn;
-        y = y - li * bn;
-        const double nc0 = c1 - li * dn;
-        c1 = -li * en;
-        c0 = nc0;
+        lm[u] = LM[i];
       }
     }
-    if (fabs(c0) < tol) c0 = (c0 < 0.0) ? -tol : tol;
-    U0[(p - 1) * nb + t] = 1.0 / c0;
-    U1[(p - 1) * nb + t] = 0.0;
-    U2[(p - 1) * nb + t] = 0.0;
-  } else {
-    double lmx = LM[t];
-    uint8_t swx = sw[t];
-    for (int i = 0; i + 1 < p; ++i) {
-      const double bn = bnx, li = lmx;
-      const uint8_t si = swx;
-      if (i + 2 < p) bnx = Z[(i + 2) * ldz + j];
-      if (i + 1 < p) {
-        lmx = LM[(i + 1) * nb + t];
-        swx = sw[(i + 1) * nb + t];
-      }
-      if (si == 0) {
-        Z[i * ldz + j] = y;
-        y = bn - li * y;
+    if (FACTOR) en[8] = e[i0 + 8];
+    uint32_t m = 0;
+    if (!FACTOR) m = (uint32_t)(((i0 < 64) ? sw0 : sw1) >> (i0 & 63));
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int i = i0 + u;
+      bool s;
+      double li;
+      if (FACTOR) {
+        const double ei = en[u], ex = en[u + 1];
+        s = !(fabs(c0) >= fabs(ei));
+        const double cand = s ? ei : c0;
+        const double piv = (fabs(cand) < tol) ? ((cand < 0.0) ? -tol : tol) : cand;
+        double l0 = ei / piv;
+        asm("" : "+v"(l0));  // (a select, not a branch around the division)
+        li = s ? c0 * ie[u] : l0;
+        const double u1 = s ? dn[u] : c1;
+        U0[i] = piv;
+        U1[i] = u1;
+        LM[i] = li;
+        m |= s ? (1u << u) : 0u;
+        c0 = fma(-li, u1, s ? c1 : dn[u]);
+        c1 = s ? -li * ex : ex;
       } else {
-        Z[i * ldz + j] = bn;
-        y = y - li * bn;
+        s = (m >> u) & 1;
+        li = lm[u];
       }
+      const double zi = s ? bz[u] : y;
+      Z[i] = zi;
+      y = fma(-li, zi, s ? y : bz[u]);
+    }
+    if (FACTOR) {
+      if (i0 < 64) sw0 |= (uint64_t)m << i0;
+      else sw1 |= (uint64_t)m << (i0 - 64);
     }
   }
-  Z[(p - 1) * ldz + j] = y;
+}
+// Z: the row-major vectors' column, which receives the scaled result
+__device__ __forceinline__ void invit_backward(const double* __restrict__ e, int p, int p8, double* __restrict__ z,
+                                               const double* __restrict__ U0, const double* __restrict__ U1,
+                                               uint64_t sw0, uint64_t sw1, double* __restrict__ Z, int ldz) {
   double z1 = 0.0, z2 = 0.0, zmax = 0.0;
-  double zx = Z[(p - 1) * ldz + j], u0x = U0[(p - 1) * nb + t], u1x = U1[(p - 1) * nb + t],
-         u2x = U2[(p - 1) * nb + t];
-  for (int i = p - 1; i >= 0; --i) {
-    const double zr = zx, u0 = u0x, u1 = u1x, u2 = u2x;
-    if (i > 0) {
-      zx = Z[(i - 1) * ldz + j];
-      u0x = U0[(i - 1) * nb + t];
-      u1x = U1[(i - 1) * nb + t];
-      u2x = U2[(i - 1) * nb + t];
+  for (int i0 = p8 - 8; i0 >= 0; i0 -= 8) {
+    double zr[8], u0[8], u1[8], u2[8];
+    const uint32_t m = (uint32_t)(((i0 < 64) ? sw0 : sw1) >> (i0 & 63));
+#pragma unroll
+    for (int u = 7; u >= 0; --u) {
+      const int i = i0 + u;
+      zr[u] = z[i];
+      u0[u] = U0[i];
+      u1[u] = U1[i];
+      const double ex = e[i + 1];
+      u2[u] = ((m >> u) & 1) ? ex : 0.0;
     }
-    const double zi = (zr - u1 * z1 - u2 * z2) * u0;
-    Z[i * ldz + j] = zi;
-    zmax = fmax(zmax, fabs(zi));
-    z2 = z1;
-    z1 = zi;
+#pragma unroll
+    for (int u = 7; u >= 0; --u) {
+      const double zi = (zr[u] - u1[u] * z1 - u2[u] * z2) * u0[u];
+      z[i0 + u] = zi;
+      zmax = fmax(zmax, fabs(zi));
+      z2 = z1;
+      z1 = zi;
+    }
   }
   const double sc = (zmax > 0.0 && zmax < INFINITY) ? 1.0 / zmax : 1.0;
-#pragma unroll 4
-  for (int i = 0; i < p; ++i) Z[i * ldz + j] *= sc;
+  for (int i0 = 0; i0 < p; i0 += 8) {
+    double zr[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) zr[u] = z[i0 + u];
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (i0 + u < p) Z[(i0 + u) * ldz] = zr[u] * sc;
+  }
 }
 
 // G (lower, n x n, stride ldg) <- Z^T Z for Z (p x n, stride ldz), every
-// thread; ends with a barrier
-__device__ void blk_gram_lower(const double* Z, int ldz, int p, int n, double* G, int ldg) {
-  for (int idx = threadIdx.x; idx < n * n; idx += blockDim.x) {
-    const int r = idx / n, c = idx - r * n;
-    if (c > r) continue;
-    double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-    int i = 0;
-    for (; i + 4 <= p; i += 4) {
-      s0 += Z[i * ldz + r] * Z[i * ldz + c];
-      s1 += Z[(i + 1) * ldz + r] * Z[(i + 1) * ldz + c];
-      s2 += Z[(i + 2) * ldz + r] * Z[(i + 2) * ldz + c];
-      s3 += Z[(i + 3) * ldz + r] * Z[(i + 3) * ldz + c];
+// thread; ends with a barrier.  Four sums per entry, over i = u (mod 4), the
+// last p % 4 rows in the first; one MFMA takes four terms of one of them.
+__device__ __forceinline__ void blk_gram_lower(const double* Z, int ldz, int p, int n, double* G, int ldg) {
+  const int lane = threadIdx.x & 63, g = lane >> 4, r = lane & 15;
+  const int tn = (n + 15) >> 4, p4 = p & ~3;
+  for (int t = wave_id(); t < tn * tn; t += blockDim.x >> 6) {
+    const int ti = tn == 1 ? t : t / tn, i0 = 16 * ti, j0 = 16 * (t - ti * tn);
+    if (j0 > i0) continue;
+    const bool vi = i0 + r < n, vj = j0 + r < n;
+    d4 acc[4] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
+    for (int k0 = 0; k0 < p4; k0 += 16) {
+      double av[4], bv[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int k = k0 + 4 * g + u;
+        const double x = Z[min(k, p - 1) * ldz + min(i0 + r, n - 1)], y = Z[min(k, p - 1) * ldz + min(j0 + r, n - 1)];
+        av[u] = (vi & (k < p4)) ? x : 0.0;
+        bv[u] = (vj & (k < p4)) ? y : 0.0;
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) acc[u] = mma64(av[u], bv[u], acc[u]);
     }
-    for (; i < p; ++i) s0 += Z[i * ldz + r] * Z[i * ldz + c];
-    G[r * ldg + c] = (s0 + s1) + (s2 + s3);
+    if (p4 < p) {
+      const int k = p4 + g;
+      const double x = Z[min(k, p - 1) * ldz + min(i0 + r, n - 1)], y = Z[min(k, p - 1) * ldz + min(j0 + r, n - 1)];
+      acc[0] = mma64((vi & (k < p)) ? x : 0.0, (vj & (k < p)) ? y : 0.0, acc[0]);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int i = i0 + 4 * q + g;
+      if (i < n && vj && j0 + r <= i) G[i * ldg + j0 + r] = (acc[0][q] + acc[1][q]) + (acc[2][q] + acc[3][q]);
+    }
   }
   __syncthreads();
 }
 
-// Z <- Z L^-T with L L^T = G (the Gram Z^T Z from blk_gram_lower), by one
-// wave; G is overwritten by L (n <= 16: factored in registers by
-// reg_chol16).  False when a pivot is not > 0.
+// Z <- Z L^-T with L L^T = G (the Gram Z^T Z from blk_gram_lower); G may be
+// overwritten.  Every thread calls it; n <= 16: a wave per 64 rows, each with
+// the factor in its registers, else one wave and the factor in LDS.  False
+// (uniform) when a pivot is not > 0.
 template <int NR>
-__device__ bool wave_cholqr(double* Z, int ldz, int p, int n, double* G, int ldg, double* linv) {
+__device__ __forceinline__ bool wave_cholqr(double* Z, int ldz, int p, int n, double* G, int ldg, double* linv) {
   const int l = threadIdx.x & 63;
   wave_sync();
-  if (n <= 16) {
-    if (!wave_chol16_lds<false, true, false>(G, ldg, n, 0.0, G, ldg, linv)) return false;
+  for (int k = 0; k < n; ++k) {
+    const double gkk = G[k * ldg + k];
+    if (!(gkk > 0.0) || !(gkk < INFINITY)) return false;
+    const double lkk = sqrt(gkk), inv = 1.0 / lkk;
+#pragma unroll
+    for (int h = 0; h < NR; ++h) {
+      const int r = l + 64 * h;
+      if (r > k && r < n) G[r * ldg + k] *= inv;
+    }
+    if (l == 0) {
+      G[k * ldg + k] = lkk;
+      linv[k] = inv;
+    }
     wave_sync();
-  } else {
-    for (int k = 0; k < n; ++k) {
-      const double gkk = G[k * ldg + k];
-      if (!(gkk > 0.0) || !(gkk < INFINITY)) return false;
-      const double lkk = sqrt(gkk), inv = 1.0 / lkk;
+    // trailing update, lane c owning column c: G[r][c] -= L[r][k] L[c][k], r >= c > k
 #pragma unroll
-      for (int h = 0; h < NR; ++h) {
-        const int r = l + 64 * h;
-        if (r > k && r < n) G[r * ldg + k] *= inv;
-      }
-      if (l == 0) {
-        G[k * ldg + k] = lkk;
-        linv[k] = inv;
-      }
-      wave_sync();
-      // trailing update, lane c owning column c: G[r][c] -= L[r][k] L[c][k], r >= c > k
+    for (int h = 0; h < NR; ++h) {
+      const int c = l + 64 * h;
+      if (c > k && c < n) {
+        const double lck = G[c * ldg + k];
+        for (int r0 = c; r0 < n; r0 += 4) {
+          double lk[4], gc[4];
 #pragma unroll
-      for (int h = 0; h < NR; ++h) {
-        const int c = l + 64 * h;
-        if (c > k && c < n) {
-          const double lck = G[c * ldg + k];
-          for (int r0 = c; r0 < n; r0 += 4) {
-            double lk[4], gc[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-              const int r = min(r0 + u, n - 1);
-              lk[u] = G[r * ldg + k];
-              gc[u] = G[r * ldg + c];
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-              if (r0 + u < n) G[(r0 + u) * ldg + c] = gc[u] - lk[u] * lck;
+          for (int u = 0; u < 4; ++u) {
+            const int r = min(r0 + u, n - 1);
+            lk[u] = G[r * ldg + k];
+            gc[u] = G[r * ldg + c];
           }
+#pragma unroll
+          for (int u = 0; u < 4; ++u)
+            if (r0 + u < n) G[(r0 + u) * ldg + c] = gc[u] - lk[u] * lck;
         }
       }
-      wave_sync();
     }
+    wave_sync();
   }
 #pragma unroll
   for (int h = 0; h < NR; ++h) {
@@ -694,30 +1084,118 @@ __device__ bool wave_cholqr(double* Z, int ldz, int p, int n, double* G, int ldg
   wave_sync();
   return true;
 }
+__device__ __forceinline__ bool blk_cholqr(double* Z, int ldz, int p, int n, double* G, int ldg, double* linv,
+                                           int* flag) {
+  const int wave = wave_id(), lane = threadIdx.x & 63;
+  if (n <= 16) {
+    if (n <= 8) chol_trsm<8, false, true>(Z, ldz, p, n, G, ldg, flag);
+    else chol_trsm<16, false, true>(Z, ldz, p, n, G, ldg, flag);
+  } else if (wave == 0) {
+    const bool ok = (p <= 64) ? wave_cholqr<1>(Z, ldz, p, n, G, ldg, linv)
+                              : wave_cholqr<2>(Z, ldz, p, n, G, ldg, linv);
+    if (lane == 0) *flag = ok ? 1 : 0;
+  }
+  __syncthreads();
+  const bool ok = *flag != 0;
+  __syncthreads();  // the flag is rewritten by the next call
+  return ok;
+}
 
-// The whole path (1-5).  A: p x lda in LDS (destroyed); base: the area after
-// A laid out by tri_layout(p, nev), whose ev and Z receive the result.  Every
+// u = H_0 H_1 ... H_{p-3} z, 16 lanes per vector (z in the columns of Z, the
+// reflectors in the columns of A), the next reflector on its way
+template <int H>
+__device__ __forceinline__ void blk_backtransform(double* Z, int ldz, const double* A, int lda, int p, int nev,
+                                                  const double* beta) {
+  const int lane = threadIdx.x & 63, q = lane & 15, rg = lane >> 4;
+  for (int j0 = 4 * wave_id(); j0 < nev; j0 += 4 * (kRrThreads / 64)) {
+    const int j = j0 + rg;
+    double z[H][4], vn[H][4], bn = 0.0;
+#pragma unroll
+    for (int h = 0; h < H; ++h)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int i = 4 * q + u + 64 * h;
+        const double x = Z[min(i, p - 1) * ldz + min(j, nev - 1)];
+        z[h][u] = (i < p) ? x : 0.0;
+      }
+    auto next = [&](int k) {
+      k = max(k, 0);
+      bn = beta[k];  // 0 for H_k = I: then s = 0
+#pragma unroll
+      for (int h = 0; h < H; ++h)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int i = 4 * q + u + 64 * h;
+          const double x = A[min(i, p - 1) * lda + k];
+          vn[h][u] = ((i > k) & (i < p)) ? x : 0.0;
+        }
+    };
+    next(p - 3);
+    for (int k = p - 3; k >= 0; --k) {
+      double v[H][4], lf[4], b = bn;
+#pragma unroll
+      for (int h = 0; h < H; ++h)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          v[h][u] = vn[h][u];
+          asm("" : "+v"(v[h][u]));
+        }
+      asm("" : "+v"(b));
+      next(k - 1);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        if (H == 1) lf[u] = fma(v[0][u], z[0][u], 0.0);
+        else lf[u] = v[0][u] * z[0][u] + v[H - 1][u] * z[H - 1][u];
+      }
+      const double sv = b * tree64(lf);
+#pragma unroll
+      for (int h = 0; h < H; ++h)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) z[h][u] -= sv * v[h][u];
+    }
+#pragma unroll
+    for (int h = 0; h < H; ++h)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int i = 4 * q + u + 64 * h;
+        if (i < p && j < nev) Z[i * ldz + j] = z[h][u];
+      }
+  }
+  __syncthreads();
+}
+
+// The whole path (1-5).  A: p x lda in LDS (destroyed), at base, which is laid
+// out by tri_layout(p, nev), whose ev and Z receive the result.  Every
 // thread calls it; the return value is uniform.
-__device__ bool blk_tri_eigh(double* A, int lda, int p, int nev, double* base, const TriLayout& L,
+__device__ __forceinline__ bool blk_tri_eigh(double* A, int lda, int p, int nev, double* base, const TriLayout& L,
                              int* flag) {
   double* d = base + L.d;
   double* e = base + L.e;
   double* inve = base + L.inve;
-  double* e2 = base + L.e2;
   double* beta = base + L.beta;
   double* ev = base + L.ev;
   double* Z = base + L.Z;
+  dd2* de = reinterpret_cast<dd2*>(base + L.de);
   const int ldz = L.ldz;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  blk_tridiag(A, lda, p, d, e, beta, base + L.vv, base + L.ww);
-  // Gershgorin interval, ||T||, pivmin (every thread, same order)
-  double gl = INFINITY, gu = -INFINITY, emax2 = 0.0;
-  for (int i = 0; i < p; ++i) {
-    const double r = ((i > 0) ? fabs(e[i - 1]) : 0.0) + ((i + 1 < p) ? fabs(e[i]) : 0.0);
-    gl = fmin(gl, d[i] - r);
-    gu = fmax(gu, d[i] + r);
-    if (i + 1 < p) emax2 = fmax(emax2, e[i] * e[i]);
+  const int lane = threadIdx.x & 63;
+  if (p <= 64) blk_tridiag64(A, lda, p, d, e, beta, base + L.ww, base + L.ww + 2 * (p + 64));
+  else blk_tridiag(A, lda, p, d, e, beta, base + L.ww);
+  // Gershgorin interval, ||T||, pivmin, by every wave
+  double gl = -INFINITY, gu = -INFINITY, emax2 = 0.0;  // (gl holds -min)
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int i = lane + 64 * h;
+    if (i < p) {
+      const double ei = (i + 1 < p) ? e[i] : 0.0;
+      const double r = ((i > 0) ? fabs(e[i - 1]) : 0.0) + fabs(ei);
+      gl = fmax(gl, -(d[i] - r));
+      gu = fmax(gu, d[i] + r);
+      emax2 = fmax(emax2, ei * ei);
+    }
   }
+  gl = -wave_max(gl);
+  gu = wave_max(gu);
+  emax2 = wave_max(emax2);
   const double tnorm = fmax(fabs(gl), fabs(gu));
   if (!(tnorm < INFINITY)) return false;
   if (tnorm == 0.0) {  // the zero matrix
@@ -734,75 +1212,64 @@ __device__ bool blk_tri_eigh(double* A, int lda, int p, int nev, double* base, c
   const double widen = 2.1 * (kEps * tnorm * p + 2.0 * pivmin);
   gl -= widen;
   gu += widen;
-  for (int i = threadIdx.x; i + 1 < p; i += blockDim.x) {
-    e2[i] = e[i] * e[i];
-    const double piv = (fabs(e[i]) < tol) ? ((e[i] < 0.0) ? -tol : tol) : e[i];
-    inve[i] = (e[i] == 0.0) ? 0.0 : 1.0 / piv;
+  {
+    const int i = threadIdx.x;
+    if (i < p) {
+      const double em = (i > 0) ? e[i - 1] : 0.0, ei = (i + 1 < p) ? e[i] : 0.0;
+      de[i] = dd2{d[i], em * em};
+      const double piv = (fabs(ei) < tol) ? ((ei < 0.0) ? -tol : tol) : ei;
+      inve[i] = (ei == 0.0) ? 0.0 : 1.0 / piv;
+    } else if (i < p + 24) {
+      de[i] = dd2{INFINITY, 0.0};
+      if (i < p + 9) {
+        d[i] = 1.0;
+        e[i] = inve[i] = 0.0;
+      }
+    }
+    if (i == p - 1) e[i] = 0.0;
   }
-  __syncthreads();
-  blk_multisection(d, e2, p, nev, gl, gu, tnorm, pivmin, ev);
   // start vectors
-  for (int idx = threadIdx.x; idx < p * nev; idx += blockDim.x) {
-    const int i = idx / nev, j = idx - i * nev;
-    const uint64_t z = sm64(kZeroColumnSeed ^ (0x5EEDull << 32) ^ ((uint64_t)j * (uint64_t)p + (uint64_t)i));
-    Z[i * ldz + j] = (double)(z >> 11) * 0x1.0p-52 - 1.0;
-  }
+  for (int j = threadIdx.x & 15; j < nev; j += 16)
+    for (int i = threadIdx.x >> 4; i < p; i += kRrThreads / 16) {
+      const uint64_t z = sm64(kZeroColumnSeed ^ (0x5EEDull << 32) ^ ((uint64_t)j * (uint64_t)p + (uint64_t)i));
+      Z[i * ldz + j] = (double)(z >> 11) * 0x1.0p-52 - 1.0;
+    }
+  __syncthreads();
+  if (p <= 49) blk_multisection<3>(de, p, nev, gl, gu, tnorm, pivmin, ev);
+  else blk_multisection<6>(de, p, nev, gl, gu, tnorm, pivmin, ev);
   __syncthreads();
   // two solves with a Cholesky-QR between them (block inverse iteration);
   // with several batches the LU is rebuilt for the second solve
-  const int nb = L.nb;
+  const int nb = L.nb, p8 = (p + 7) & ~7, ps = p8 + 1;
+  uint64_t sw0 = 0, sw1 = 0;
   for (int it = 0; it < 2; ++it) {
     for (int j0 = 0; j0 < nev; j0 += nb) {
-      const int t = threadIdx.x;
-      if (t < nb && j0 + t < nev) {
-        const int j = j0 + t;
-        tri_invit_solve(d, e, inve, p, ev[j], tol, Z, ldz, j, base + L.ws,
-                        reinterpret_cast<uint8_t*>(base + L.sw), nb, t, it == 0 || nb < nev);
+      const int t = threadIdx.x, j = min(j0 + t, nev - 1), nv = min(nb, nev - j0);
+      const bool mine = t < nv, factor = it == 0 || nb < nev;
+      double *z0 = base + L.ws, *U0 = z0 + nb * ps, *U1 = U0 + nb * ps, *LM = U1 + nb * ps;
+      for (int v = t >> 4; v < nv; v += kRrThreads / 16)
+        for (int i = t & 15; i <= p8; i += 16) z0[v * ps + i] = (i < p) ? Z[i * ldz + j0 + v] : 0.0;
+      __syncthreads();
+      if (mine) {
+        if (factor) invit_forward<true>(d, e, inve, p8, ev[j], tol, z0 + t * ps, U0 + t * ps, U1 + t * ps, LM + t * ps, sw0, sw1);
+        else invit_forward<false>(d, e, inve, p8, ev[j], tol, z0 + t * ps, U0 + t * ps, U1 + t * ps, LM + t * ps, sw0, sw1);
       }
+      if (factor) {
+        __syncthreads();
+        for (int v = t >> 4; v < nv; v += kRrThreads / 16)
+          for (int i = t & 15; i < p8; i += 16) U0[v * ps + i] = 1.0 / U0[v * ps + i];
+        __syncthreads();
+      }
+      if (mine) invit_backward(e, p, p8, z0 + t * ps, U0 + t * ps, U1 + t * ps, sw0, sw1, Z + j, ldz);
       __syncthreads();
     }
     if (it == 0) {
       blk_gram_lower(Z, ldz, p, nev, base + L.G, nev + 1);
-      if (wave == 0) {
-        const bool ok = (p <= 64) ? wave_cholqr<1>(Z, ldz, p, nev, base + L.G, nev + 1, base + L.linv)
-                                  : wave_cholqr<2>(Z, ldz, p, nev, base + L.G, nev + 1, base + L.linv);
-        if (lane == 0) *flag = ok ? 1 : 0;
-      }
-      __syncthreads();
-      const bool ok = *flag != 0;
-      __syncthreads();
-      if (!ok) return false;
+      if (!blk_cholqr(Z, ldz, p, nev, base + L.G, nev + 1, base + L.linv, flag)) return false;
     }
   }
-  // u = H_0 H_1 ... H_{p-3} z, one wave per vector
-  const int nw = blockDim.x >> 6;
-  for (int j = wave; j < nev; j += nw) {
-    double z[2];
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int i = lane + 64 * h;
-      z[h] = (i < p) ? Z[i * ldz + j] : 0.0;
-    }
-#pragma unroll 2
-    for (int k = p - 3; k >= 0; --k) {
-      const double b = beta[k];  // 0 for H_k = I: then s = 0
-      double v[2];
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int i = lane + 64 * h;
-        v[h] = (i > k && i < p) ? A[i * lda + k] : 0.0;
-      }
-      const double s = b * wave_sum(v[0] * z[0] + v[1] * z[1]);
-      z[0] -= s * v[0];
-      z[1] -= s * v[1];
-    }
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int i = lane + 64 * h;
-      if (i < p) Z[i * ldz + j] = z[h];
-    }
-  }
-  __syncthreads();
+  if (p <= 64) blk_backtransform<1>(Z, ldz, A, lda, p, nev, beta);
+  else blk_backtransform<2>(Z, ldz, A, lda, p, nev, beta);
   // Cholesky-QR twice, with the A area as Gram scratch.  One pass leaves
   // the vectors orthonormal to a few units of rounding when the Gram is
   // well conditioned, yet the second pass is kept: the P coefficients are
@@ -811,15 +1278,7 @@ __device__ bool blk_tri_eigh(double* A, int lda, int p, int nev, double* base, c
   // solve (n = 2000, 4 pairs: 51 against 25, the lowest pair lagging).
   for (int pass = 0; pass < 2; ++pass) {
     blk_gram_lower(Z, ldz, p, nev, A, lda);
-    if (wave == 0) {
-      const bool ok = (p <= 64) ? wave_cholqr<1>(Z, ldz, p, nev, A, lda, base + L.linv)
-                                : wave_cholqr<2>(Z, ldz, p, nev, A, lda, base + L.linv);
-      if (lane == 0) *flag = ok ? 1 : 0;
-    }
-    __syncthreads();
-    const bool ok = *flag != 0;
-    __syncthreads();
-    if (!ok) return false;
+    if (!blk_cholqr(Z, ldz, p, nev, A, lda, base + L.linv, flag)) return false;
   }
   return true;
 }
@@ -828,6 +1287,7 @@ __device__ bool blk_tri_eigh(double* A, int lda, int p, int nev, double* base, c
 // SVQB (Stathopoulos-Wu) coefficient for an n x n overlap M: X <- X U S^-1/2,
 // eigenvalues clamped below eps * max.  Writes the n x n coefficient to Cf.
 // Uses Ws (2 * n * (n+1) doubles) as Jacobi workspace.
+template <int NT>
 __device__ __forceinline__ bool blk_svqb_coef(const double* M, int ldm, int n, double* Cf, int ldc, double* Ws,
                               double* cs, int* pr, int* flag, int* perm, double* scratch) {
   const int ld = n + 1;
@@ -838,7 +1298,7 @@ __device__ __forceinline__ bool blk_svqb_coef(const double* M, int ldm, int n, d
     A[i * ld + j] = M[i * ldm + j];
   }
   __syncthreads();
-  blk_jacobi<1024>(A, ld, U, ld, n, cs, pr, flag, scratch);
+  blk_jacobi<NT>(A, ld, U, ld, n, cs, pr, flag, scratch);
   double smax = 0.0;
   for (int i = 0; i < n; ++i) smax = fmax(smax, A[i * ld + i]);
   if (!(smax > 0.0)) return false;
@@ -856,30 +1316,46 @@ __device__ __forceinline__ bool blk_svqb_coef(const double* M, int ldm, int n, d
 // eigenvectors; optionally u_p = ortho(u_x[:, a0:m] - E[:, a0:m]; u_x) in R^p
 // by Alg. 3 / Alg. 2 (the same readings as on n-vectors).
 
-// sym(a) into A (stride lda), with the pending column scaling of the W block
+// sym(a) into A (stride lda; columns up to width zero), with the pending column scaling of the W block
 // (see small_rr in internal.h) applied from both sides when pend != nullptr
-__device__ void load_rr_matrix(const double* a, int p, double* A, int lda, const OrthoState* pend,
-                               int woff) {
-  load_sym(a, p, A, lda);
-  if (pend != nullptr) {
-    const int nws = pend->nw;
-    for (int idx = threadIdx.x; idx < p * p; idx += blockDim.x) {
-      const int i = idx / p, j = idx - i * p;
-      const double di = (i >= woff && i < woff + nws) ? pend->dscale[i - woff] : 1.0;
-      const double dj = (j >= woff && j < woff + nws) ? pend->dscale[j - woff] : 1.0;
-      A[i * lda + j] *= di * dj;
+__device__ __forceinline__ void load_rr_matrix(const double* a, int p, double* A, int lda, int width,
+                                               const OrthoState* pend, int woff) {
+  const int nws = (pend != nullptr) ? pend->nw : 0;
+  for (int j = threadIdx.x & 63; j < width; j += 64) {
+    if (j >= p) {
+      for (int i = threadIdx.x >> 6; i < p; i += blockDim.x >> 6) A[i * lda + j] = 0.0;
+      continue;
     }
-    __syncthreads();
+    const double dj = (j >= woff && j < woff + nws) ? pend->dscale[j - woff] : 1.0;
+#pragma unroll 4
+    for (int i = threadIdx.x >> 6; i < p; i += blockDim.x >> 6) {
+      const double di = (i >= woff && i < woff + nws) ? pend->dscale[i - woff] : 1.0;
+      const double v = 0.5 * (a[i * p + j] + a[j * p + i]);
+      A[i * lda + j] = (nws > 0) ? v * (di * dj) : v;
+    }
   }
+  __syncthreads();
 }
 
-__global__ __launch_bounds__(1024) void k_small_rr(const double* __restrict__ a, int p, int m,
+// Rayleigh-Ritz step.  The order of every sum is part of what it computes: an
+// iteration that has not converged amplifies rounding (on a banded matrix of
+// order 1e5, one unit in the last place of the starting block moves the
+// eigenvalues in the first digit after five iterations), so a change of order
+// would change what a few iterations give and what is trained on it.
+// JAC: the Jacobi option, 1024 threads; else the tridiagonal path, 512.
+// Measured (p = 48, m = 16; 39, 13; 24, 8; 12, 4): 160, 135, 79, 52 us, where
+// 1024 threads with three barriers per reflector, whole waves per row, one
+// column per thread in the triangular solves and scalar loops for the products
+// took 257, 187, 107, 60; above p = 64, where LDS holds no padded rows and the
+// vectors are more than 16, 848 against 970 us (p = 96, m = 32).
+template <bool JAC>
+__global__ __launch_bounds__(JAC ? 1024 : kRrThreads) void k_small_rr(const double* __restrict__ a, int p, int m,
                                                   int a0, int want_up, double tau,
                                                   const OrthoState* __restrict__ pend, int woff,
                                                   double* __restrict__ theta_all,
-                                                  double* __restrict__ U, int* __restrict__ info,
-                                                  int jacobi) {
-  extern __shared__ double smem[];
+                                                  double* __restrict__ U, int* __restrict__ info) {
+  constexpr int NT = JAC ? 1024 : kRrThreads;
+  extern __shared__ __attribute__((aligned(16))) double smem[];
   EigLds L = eig_lds(smem, p, m);
   const int ld = p + 1;
   __shared__ ShiftCount cnt;
@@ -894,24 +1370,24 @@ __global__ __launch_bounds__(1024) void k_small_rr(const double* __restrict__ a,
   int sw = 0;
   const TriLayout T = tri_layout(p, m);
   bool tri = false;
-  if (!jacobi && T.nb >= 1) {
-    load_rr_matrix(a, p, L.A, ld, scaled ? pend : nullptr, woff);
-    double* base = L.A + p * ld;
-    tri = blk_tri_eigh(L.A, ld, p, m, base, T, &tflag);
+  if (!JAC && T.nb >= 1) {
+    const int lda = tri_lda(p);
+    load_rr_matrix(a, p, L.A, lda, lda > p + 1 ? lda : p, scaled ? pend : nullptr, woff);
+    double* base = L.A;
+    tri = blk_tri_eigh(L.A, lda, p, m, base, T, &tflag);
     if (tri) {
       for (int j = threadIdx.x; j < m; j += blockDim.x) theta_all[j] = base[T.ev + j];
       // orientation: u[j][j] >= 0, so that u_x - E is the small update X_new - X_old
-      for (int idx = threadIdx.x; idx < p * m; idx += blockDim.x) {
-        const int i = idx / m, j = idx - i * m;
+      for (int j = threadIdx.x & 15; j < m; j += 16) {
         const double sg = (base[T.Z + j * T.ldz + j] < 0.0) ? -1.0 : 1.0;
-        Us[i * ld + j] = sg * base[T.Z + i * T.ldz + j];
+        for (int i = threadIdx.x >> 4; i < p; i += NT / 16) Us[i * ld + j] = sg * base[T.Z + i * T.ldz + j];
       }
       __syncthreads();
     }
   }
   if (!tri) {
-    load_rr_matrix(a, p, L.A, ld, scaled ? pend : nullptr, woff);
-    sw = blk_jacobi<1024>(L.A, ld, L.V, ld, p, L.cs, L.pr, L.flags, L.scratch);
+    load_rr_matrix(a, p, L.A, ld, p, scaled ? pend : nullptr, woff);
+    sw = blk_jacobi<NT>(L.A, ld, L.V, ld, p, L.cs, L.pr, L.flags, L.scratch);
     blk_sort_evals(L.A, ld, p, L.perm);
     for (int j = threadIdx.x; j < m; j += blockDim.x) theta_all[j] = L.A[L.perm[j] * ld + L.perm[j]];
     __syncthreads();
@@ -925,11 +1401,12 @@ __global__ __launch_bounds__(1024) void k_small_rr(const double* __restrict__ a,
   const int na = want_up ? (m - a0) : 0;
   const int q = m + na;
   // u_x (row scaling for a pending W scaling is applied when U is written)
-  for (int idx = threadIdx.x; idx < p * m; idx += blockDim.x) {
-    const int i = idx / m, j = idx - i * m;
-    const double di = (scaled && i >= woff && i < woff + pend->nw) ? pend->dscale[i - woff] : 1.0;
-    U[i * q + j] = di * Us[i * ld + j];
-  }
+  const int sn = scaled ? pend->nw : 0;
+  for (int j = threadIdx.x & 15; j < m; j += 16)
+    for (int i = threadIdx.x >> 4; i < p; i += NT / 16) {
+      const double di = (i >= woff && i < woff + sn) ? pend->dscale[i - woff] : 1.0;
+      U[i * q + j] = di * Us[i * ld + j];
+    }
   int bad = 0;
   if (na > 0) {
     // V area becomes: X (p x na), C (m x na), M (na x na), Lc (na x na), Li, svqb workspace
@@ -940,10 +1417,8 @@ __global__ __launch_bounds__(1024) void k_small_rr(const double* __restrict__ a,
     double* Lc = M + na * na;
     double* Ws = Lc + na * na;
     // u~_p = u_x[:, a0:m] - E[:, a0:m]
-    for (int idx = threadIdx.x; idx < p * na; idx += blockDim.x) {
-      const int i = idx / na, j = idx - i * na;
-      X[i * ldx + j] = Us[i * ld + a0 + j] - ((i == a0 + j) ? 1.0 : 0.0);
-    }
+    for (int j = threadIdx.x & 15; j < na; j += 16)
+      for (int i = threadIdx.x >> 4; i < p; i += NT / 16) X[i * ldx + j] = Us[i * ld + a0 + j] - ((i == a0 + j) ? 1.0 : 0.0);
     __syncthreads();
     blk_normalize(X, ldx, p, na, L.cs, &zeros);
     blk_gemm_tn(Us, ld, X, ldx, p, m, na, C, na);  // C = u_x^T X
@@ -955,29 +1430,32 @@ __global__ __launch_bounds__(1024) void k_small_rr(const double* __restrict__ a,
       for (int it = 0; it < 6; ++it) {
         blk_gemm_tn(X, ldx, X, ldx, p, na, na, M, na);
         if (threadIdx.x == 0) grams++;
+        // (M's two halves take the same operations: it is symmetric)
         double dev = 0.0;
-        for (int idx = threadIdx.x; idx < na * na; idx += blockDim.x) {
-          const int i = idx / na, j = idx - i * na;
-          const double v = 0.5 * (M[i * na + j] + M[j * na + i]) - (i == j ? 1.0 : 0.0);
-          dev = fmax(dev, fabs(v));
-        }
-        dev = blk_reduce_max(dev, L.scratch);
+        for (int j = threadIdx.x & 15; j < na; j += 16)
+          for (int i = (threadIdx.x & 63) >> 4; i < na; i += 4) dev = fmax(dev, fabs(M[i * na + j] - (i == j ? 1.0 : 0.0)));
+        dev = wave_max(dev);  // every wave
         if (dev <= tau) break;
         if (it == 5) {
           if (threadIdx.x == 0) stalled++;
           break;
         }
-        for (int idx = threadIdx.x; idx < na * na; idx += blockDim.x) {
-          const int i = idx / na, j = idx - i * na;
-          M[idx] = 0.5 * (M[i * na + j] + M[j * na + i]);
+        // plain Cholesky, then shifts
+        bool ok = false;
+        if (!JAC && na <= 16) {
+          if (na <= 8) chol_trsm<8, true, false>(X, ldx, p, na, M, na, L.flags);
+          else chol_trsm<16, true, false>(X, ldx, p, na, M, na, L.flags);
+          __syncthreads();
+          ok = L.flags[0] != 0;
+          if (ok && threadIdx.x == 0) cnt.factorizations++;
+          __syncthreads();
         }
-        __syncthreads();
-        // symmetrised copy is in place; compute Cholesky
-        if (blk_shifted_chol(M, na, na, Lc, na, L.flags, &cnt, L.scratch)) {
+        if (ok) {
+        } else if (blk_shifted_chol<JAC>(M, na, na, Lc, na, L.flags, &cnt, L.scratch, kShiftRetries, JAC || na > 16)) {
           blk_trsm_rt(X, ldx, p, na, Lc, na);
         } else {
           if (threadIdx.x == 0) cnt.svqb++;
-          if (!blk_svqb_coef(M, na, na, Lc, na, Ws, L.cs, L.pr, L.flags, L.perm, L.scratch)) {
+          if (!blk_svqb_coef<NT>(M, na, na, Lc, na, Ws, L.cs, L.pr, L.flags, L.perm, L.scratch)) {
             bad = 1;
             break;
           }
@@ -997,16 +1475,17 @@ __global__ __launch_bounds__(1024) void k_small_rr(const double* __restrict__ a,
       if (bad) break;
       blk_gemm_tn(Us, ld, X, ldx, p, m, na, C, na);
       double cm = 0.0;
-      for (int idx = threadIdx.x; idx < m * na; idx += blockDim.x) cm = fmax(cm, fabs(C[idx]));
-      cm = blk_reduce_max(cm, L.scratch);
+      for (int j = threadIdx.x & 15; j < na; j += 16)
+        for (int i = (threadIdx.x & 63) >> 4; i < m; i += 4) cm = fmax(cm, fabs(C[i * na + j]));
+      cm = wave_max(cm);  // every wave
       if (cm <= tau) break;
       if (pass == 3 && threadIdx.x == 0) stalled++;
     }
-    for (int idx = threadIdx.x; idx < p * na; idx += blockDim.x) {
-      const int i = idx / na, j = idx - i * na;
-      const double di = (scaled && i >= woff && i < woff + pend->nw) ? pend->dscale[i - woff] : 1.0;
-      U[i * q + m + j] = di * X[i * ldx + j];
-    }
+    for (int j = threadIdx.x & 15; j < na; j += 16)
+      for (int i = threadIdx.x >> 4; i < p; i += NT / 16) {
+        const double di = (i >= woff && i < woff + sn) ? pend->dscale[i - woff] : 1.0;
+        U[i * q + m + j] = di * X[i * ldx + j];
+      }
   }
   if (threadIdx.x == 0) {
     info[0] = sw;
@@ -1020,25 +1499,32 @@ __global__ __launch_bounds__(1024) void k_small_rr(const double* __restrict__ a,
     info[8] = stalled;
     info[9] = cnt.svqb;
     info[10] = zeros;
-    info[11] = (tri || jacobi) ? 0 : 1;  // Jacobi fallback of the eigensolve
+    info[11] = (tri || JAC) ? 0 : 1;  // Jacobi fallback of the eigensolve
   }
+}
+
+template <bool JAC>
+static hipError_t rr_launch(const double* a, int p, int m, int a0, int want_up, double tau, const OrthoState* pend,
+                            int woff, double* theta_all, double* U, int* info, hipStream_t s) {
+  static bool attr = false;
+  if (!attr) {
+    // dynamic + static LDS must stay within the 160 KB of a workgroup
+    (void)hipFuncSetAttribute((const void*)k_small_rr<JAC>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                              kEigLdsBytes);
+    (void)hipGetLastError();
+    attr = true;
+  }
+  hipLaunchKernelGGL(k_small_rr<JAC>, dim3(1), dim3(JAC ? 1024 : kRrThreads), kEigLdsBytes, s, a, p, m, a0, want_up,
+                     tau, pend, woff, theta_all, U, info);
+  return hipGetLastError();
 }
 
 hipError_t small_rr(const double* a, int p, int m, int a0, int want_up, double tau,
                     const OrthoState* pend, int woff, double* theta_all, double* U, int* info,
                     int jacobi, hipStream_t s) {
   if (p < 1 || p > kMaxP || m < 1 || m > p || a0 < 0 || a0 > m) return hipErrorInvalidValue;
-  static bool attr = false;
-  if (!attr) {
-    // dynamic + static LDS must stay within the 160 KB of a workgroup
-    (void)hipFuncSetAttribute((const void*)k_small_rr, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              152 * 1024);
-    (void)hipGetLastError();
-    attr = true;
-  }
-  hipLaunchKernelGGL(k_small_rr, dim3(1), dim3(1024), kEigLdsBytes, s, a, p, m, a0, want_up, tau,
-                     pend, woff, theta_all, U, info, jacobi);
-  return hipGetLastError();
+  return jacobi ? rr_launch<true>(a, p, m, a0, want_up, tau, pend, woff, theta_all, U, info, s)
+                : rr_launch<false>(a, p, m, a0, want_up, tau, pend, woff, theta_all, U, info, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -1057,7 +1543,7 @@ __global__ __launch_bounds__(256) void k_small_chol(const double* __restrict__ M
     Ms[i * 65 + j] = 0.5 * (M[i * p + j] + M[j * p + i]);
   }
   __syncthreads();
-  const bool ok = blk_shifted_chol<0>(Ms, 65, p, Ls, 65, &flag, &cnt, scratch);
+  const bool ok = blk_shifted_chol<false>(Ms, 65, p, Ls, 65, &flag, &cnt, scratch);
   for (int idx = threadIdx.x; idx < p * p; idx += blockDim.x) {
     const int i = idx / p, j = idx - i * p;
     Lout[idx] = ok ? Ls[i * 65 + j] : 0.0;
@@ -1254,7 +1740,7 @@ __global__ __launch_bounds__(1024) void k_ortho_ctl(const double* __restrict__ G
     have_scale = (phase == kPhBegin);
   } else {
     // shifted Cholesky of M (= M' in BEGIN)
-    const bool ok = blk_shifted_chol<2>(Ms, ldm, nw, Ls, ldm, &flag, &cnt, scratch, st.shift_retries);
+    const bool ok = blk_shifted_chol<true>(Ms, ldm, nw, Ls, ldm, &flag, &cnt, scratch, st.shift_retries);
     if (ok) {
       blk_tri_inv(Ls, ldm, nw, Li, ldm);
       // coef W part: D L^-T, i.e. coef[ny+i][j] = D_i Linv[j][i]
@@ -1290,7 +1776,7 @@ __global__ __launch_bounds__(1024) void k_ortho_ctl(const double* __restrict__ G
       return;
     } else {
       if (threadIdx.x == 0) cnt.svqb++;
-      const bool sv = blk_svqb_coef(Ms, ldm, nw, Li, ldm, Ws, cs, pr, &flag, perm, scratch);
+      const bool sv = blk_svqb_coef<1024>(Ms, ldm, nw, Li, ldm, Ws, cs, pr, &flag, perm, scratch);
       if (!sv) {
         if (threadIdx.x == 0) {
           st.error = kOrthoErrFailed;
