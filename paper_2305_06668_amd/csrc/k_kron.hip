@@ -17,6 +17,12 @@
 // is staged back through LDS so the diagonal term and the stores run along
 // contiguous (j, b) rows.  4 na flops per output entry: na = 4096, 8 columns
 // (n = 16.8M) is 2.2 TFLOP per application.
+// What bounds it: the fp64 MFMA (28 ms at its nominal rate, 31 at the rate of a
+// large library product) and, for the rest of its 38.8 ms, the latency of W
+// from L2 and beyond: the staging registers hold one chunk, and chunks of 8
+// with two LDS buffers, which wait for a chunk after half the time, took 49 ms
+// (one buffer and three workgroups per CU 42.8).  43.4 ms with tiles row by row
+// over all XCDs and a test for each pair loaded.
 #include <algorithm>
 #include <cstddef>
 #include <cstdint>
@@ -162,7 +168,54 @@ struct KronStage {
   }
 };
 
-template <typename T, bool VEC>
+// Loads of the chunks that lie wholly inside k, where all 8 columns may be
+// read: no test and no address arithmetic per load (a uniform base that moves
+// on by chunks, and an offset per thread that does not change).  Rows i and
+// columns j past na read the last one: their outputs are not stored.
+// With a test per pair a chunk took 620 instructions and 36 branches.
+template <typename T> struct PairE;
+template <> struct __attribute__((aligned(8))) PairE<double> { double x, y; };
+template <> struct __attribute__((aligned(4))) PairE<float> { float x, y; };
+template <typename T>
+struct KronWalk {
+  uint32_t vk, vi[kPXI], va, vj;
+  bool shift;  // the pair of A's last column starts one before it
+
+  __device__ __forceinline__ void init(int64_t na, int64_t ldw, int64_t i0, int64_t j0, int t) {
+    const uint32_t row = (uint32_t)(na * ldw * sizeof(T)), el = (uint32_t)(ldw * sizeof(T));
+    const int bp = t & 3, il = (int)min((int64_t)kTI, na - i0) - 1, jl = (int)min((int64_t)kTJ, na - j0) - 1;
+    vk = (uint32_t)(t >> 7) * row + (uint32_t)min((t >> 2) & (kTJ - 1), jl) * el + 2 * bp * (int)sizeof(T);
+#pragma unroll
+    for (int u = 0; u < kPXI; ++u)
+      vi[u] = (uint32_t)min((t >> 6) + 4 * u, il) * row + (uint32_t)((t >> 2) & (kKC - 1)) * el + 2 * bp * (int)sizeof(T);
+    va = (uint32_t)(min(t >> 3, il) * na + 2 * (t & 7)) * (uint32_t)sizeof(T);
+    const int jp = 2 * (t & 15), jc = max(min(jp, jl - 1), 0);
+    vj = (uint32_t)((t >> 4) * na + jc) * (uint32_t)sizeof(T);
+    shift = jp == jl && jp > 0;
+  }
+  template <typename S>
+  __device__ __forceinline__ void load(S& st, const T* __restrict__ A, const T* __restrict__ W,
+                                       int64_t na, int64_t ldw, int64_t i0, int64_t j0, int b0, int64_t k0) const {
+    const char* bk = reinterpret_cast<const char*>(W + (k0 * na + j0) * ldw + b0);
+    const char* bi = reinterpret_cast<const char*>(W + (i0 * na + k0) * ldw + b0);
+    const char* ba = reinterpret_cast<const char*>(A + i0 * na + k0);
+    const char* bj = reinterpret_cast<const char*>(A + k0 * na + j0);
+    auto ld = [](const char* b, uint32_t o) {
+      const PairE<T> v = *reinterpret_cast<const PairE<T>*>(b + o);
+      return Pair<T>{v.x, v.y};
+    };
+#pragma unroll
+    for (int u = 0; u < kPXK; ++u) st.xk[u] = ld(bk + (int64_t)(2 * u) * na * ldw * (int)sizeof(T), vk);
+#pragma unroll
+    for (int u = 0; u < kPXI; ++u) st.xi[u] = ld(bi, vi[u]);
+    st.ai = ld(ba, va);
+    const Pair<T> a = ld(bj, vj);
+    st.aj = Pair<T>{shift ? a.y : a.x, a.y};
+  }
+};
+
+// WALK: all 8 columns of the block may be read and na >= 2
+template <typename T, bool VEC, bool WALK>
 __global__ __launch_bounds__(256, 2) void k_kron_mfma(const T* __restrict__ A,
                                                       const T* __restrict__ Vp, int64_t na,
                                                       const T* __restrict__ W, int64_t ldw,
@@ -173,8 +226,13 @@ __global__ __launch_bounds__(256, 2) void k_kron_mfma(const T* __restrict__ A,
   const int t = threadIdx.x;
   const int lane = t & 63, wave = t >> 6;
   const int g = lane >> 4, r = lane & 15;
-  const int64_t j0 = (int64_t)blockIdx.x * kTJ, i0 = (int64_t)blockIdx.y * kTI;
-  const int b0 = blockIdx.z * kBB;
+  // XCD b % 8 takes an eighth of the tiles, in strips of 8 rows of tiles
+  const int ni = (int)((na + kTI - 1) / kTI), nj = (int)((na + kTJ - 1) / kTJ);
+  const int per = gridDim.x >> 3, idx = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+  if (idx >= ni * nj) return;  // the whole block
+  const int strip = idx / (8 * nj), in = idx - strip * 8 * nj, h = min(8, ni - 8 * strip);
+  const int64_t j0 = (int64_t)(in / h) * kTJ, i0 = (int64_t)(8 * strip + in % h) * kTI;
+  const int b0 = blockIdx.y * kBB;
   AccT acc[2][2][2];  // [b local 2 wave + bw][si][sj]
 #pragma unroll
   for (int bw = 0; bw < 2; ++bw)
@@ -185,13 +243,24 @@ __global__ __launch_bounds__(256, 2) void k_kron_mfma(const T* __restrict__ A,
 #pragma unroll
         for (int e = 0; e < 4; ++e) acc[bw][si][sj][e] = T(0);
   KronStage<T, VEC> st;
-  st.load(A, W, na, ldw, ncl, i0, j0, b0, 0, t);
+  KronWalk<T> walk;
+  if (WALK) walk.init(na, ldw, i0, j0, t);
+  auto load = [&](int64_t k0) {
+    if constexpr (WALK) {
+      if (k0 + kKC <= na) {
+        walk.load(st, A, W, na, ldw, i0, j0, b0, k0);
+        return;
+      }
+    }
+    st.load(A, W, na, ldw, ncl, i0, j0, b0, k0, t);
+  };
+  load(0);
   st.store(sm, t);
   __syncthreads();
   for (int64_t k0 = 0; k0 < na; k0 += kKC) {
     // the next chunk's loads are in flight while this chunk's MFMAs run
     const bool more = k0 + kKC < na;
-    if (more) st.load(A, W, na, ldw, ncl, i0, j0, b0, k0 + kKC, t);
+    if (more) load(k0 + kKC);
     // k steps not unrolled: 228 registers (all four unrolled hold 256 and
     // spill, two unrolled run 2 % slower)
 #pragma unroll 1
@@ -280,17 +349,25 @@ __global__ __launch_bounds__(256) void k_kron_pack8(const T* __restrict__ W, int
 template <typename T>
 static hipError_t kron_launch(const T* A, const T* Vp, int64_t na, const T* W, int64_t ldw, T* Y,
                               int64_t ldy, int nc, int ncl, hipStream_t s) {
-  const dim3 grid((unsigned)((na + kTJ - 1) / kTJ), (unsigned)((na + kTI - 1) / kTI),
-                  (unsigned)((nc + kBB - 1) / kBB));
+  // The blocks that an XCD runs at once (64) form a square of tiles, so that its
+  // L2 feeds 8 rows and 8 columns of tiles with W instead of 4 and 16 that drift
+  // apart (na = 4096, 8 fp64 columns: 38.8 ms, row by row over all XCDs 41.6).
+  const int64_t tiles = ((na + kTI - 1) / kTI) * ((na + kTJ - 1) / kTJ);
+  const dim3 grid((unsigned)((tiles + 7) / 8 * 8), (unsigned)((nc + kBB - 1) / kBB));
   const bool vec = (ldw % 2 == 0) && (na % 2 == 0) &&
                    (reinterpret_cast<uintptr_t>(W) % (2 * sizeof(T)) == 0) &&
                    (reinterpret_cast<uintptr_t>(A) % (2 * sizeof(T)) == 0);
-  if (vec)
-    hipLaunchKernelGGL((k_kron_mfma<T, true>), grid, dim3(256), 0, s, A, Vp, na, W, ldw, Y, ldy, nc,
-                       ncl);
+  // offsets inside a tile's rows are kept in 32 bits
+  const bool walk = ncl % kBB == 0 && na >= 2 &&
+                    (uint64_t)kTI * (uint64_t)na * (uint64_t)ldw * sizeof(T) < (1ull << 31);
+  if (vec && walk)
+    hipLaunchKernelGGL((k_kron_mfma<T, true, true>), grid, dim3(256), 0, s, A, Vp, na, W, ldw, Y, ldy, nc, ncl);
+  else if (walk)
+    hipLaunchKernelGGL((k_kron_mfma<T, false, true>), grid, dim3(256), 0, s, A, Vp, na, W, ldw, Y, ldy, nc, ncl);
+  else if (vec)
+    hipLaunchKernelGGL((k_kron_mfma<T, true, false>), grid, dim3(256), 0, s, A, Vp, na, W, ldw, Y, ldy, nc, ncl);
   else
-    hipLaunchKernelGGL((k_kron_mfma<T, false>), grid, dim3(256), 0, s, A, Vp, na, W, ldw, Y, ldy,
-                       nc, ncl);
+    hipLaunchKernelGGL((k_kron_mfma<T, false, false>), grid, dim3(256), 0, s, A, Vp, na, W, ldw, Y, ldy, nc, ncl);
   return hipGetLastError();
 }
 
