@@ -28,7 +28,7 @@ enum OpKind { kOpNone = 0, kOpCsr = 1, kOpDense = 2, kOpKron = 3 };
 
 struct Layout {
   size_t V[2], AV[2], diag, rho, ltiles, part, small, total;
-  size_t kpack = 0;  // dense / Kronecker operator: n x 8 packed copy of a W block
+  size_t kpack = 0;  // Kronecker operator: n x 8 packed copy of a W block
   size_t cwin = 0;   // CSR operator: column window per block of the banded path (+ a flag)
   size_t dscr = 0;   // block Davidson: n x m scratch for the explicit product A X
   // tridiagonal preconditioner: off-diagonal, row off-sums, forward factors,

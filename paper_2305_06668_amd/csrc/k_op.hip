@@ -3,8 +3,7 @@
 // Sec. 3.1, so the operator is an input, not part of the method).
 //
 //   * CSR SpMM: in k_spmm.hip.
-//   * dense: HBM-bound on A; a wave owns R rows, lanes stride the columns,
-//     and the ncols partial sums are reduced across the wave at the end.
+//   * dense: HBM-bound on A, which is read once for up to 16 columns.
 #include "internal.h"
 
 namespace lobpcg {
@@ -12,9 +11,152 @@ namespace lobpcg {
 static inline int cdiv(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 
 // ---------------------------------------------------------------------------
-// dense: Y (n x ncols) = A (n x n, lda) W (n x ncols), R rows per wave,
-// up to MC columns per launch.
+// dense: Y (n x ncols) = A (n x n, lda) W (n x ncols), up to 16 columns per
+// launch, on the MFMA 16x16x4.
+//
+// A workgroup owns RT tiles of 16 rows; its NW waves take chunks of 32 columns
+// of A in turn and add up their tiles through LDS at the end, in a fixed order.
+// A chunk's products go to NA accumulators, which are added in a tree and then
+// to the wave's sums: no chain of additions is longer than with the sums over
+// the lanes of a wave per row that this kernel replaced (n / 64 terms and six
+// levels), and the error is no larger (n = 2000, 5999, 20000 fp64, relative:
+// 2.0e-16, 2.8e-16, 4.5e-16 where it was 2.2e-16, 3.5e-16, 6.1e-16; with one
+// accumulator throughout 3.9e-16 at n = 2000).
+// A load takes 16 bytes per lane: row lane % 16, VE adjacent columns for each
+// of the four k of an MFMA (lane / 16), 64 bytes of a row; the W operand of
+// lane (g, c) is W[k][c] of the same k, columns past ncols being copies of the
+// last one that are not stored.  The next chunk is loaded while the current
+// one is multiplied.  Loads need element alignment only.
+// What bounds it: the read of A, once for up to 16 columns (n = 2e4 fp64: 630
+// us = 5.1 TB/s, where a plain sum reads 6.0; 8 columns at a time by scalar
+// products, eight rows per wave: 664 us for 8, 1330 for 16); at small n the
+// latency of a wave's few chunks (n = 2000, 13 columns: 14 us; 70 before, as
+// 63 workgroups and a packing pass for each 8 columns).  Chunks of 64 columns,
+// a contiguous range per wave and the non-temporal hint were all slower (the
+// hint 790 against 656 us, and A of up to 256 MB is read again from the
+// memory-side cache).
+typedef double __attribute__((ext_vector_type(2), aligned(8))) v2d_u;
+typedef float __attribute__((ext_vector_type(4), aligned(4))) v4f_u;
+template <typename T> struct DenseTypes;
+template <> struct DenseTypes<double> { typedef d4 Acc; typedef v2d_u Vec; };
+template <> struct DenseTypes<float> { typedef f4 Acc; typedef v4f_u Vec; };
+__device__ __forceinline__ d4 dmma(double a, double b, d4 c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ f4 dmma(float a, float b, f4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
 
+// v[0] + ... by halves (N a power of two)
+template <typename T, int N>
+__device__ __forceinline__ T tree_sum(T (&v)[N]) {
+#pragma unroll
+  for (int h = N / 2; h >= 1; h /= 2)
+#pragma unroll
+    for (int q = 0; q < h; ++q) v[q] += v[q + h];
+  return v[0];
+}
+
+template <typename T, int RT, int NW, int NA>
+__global__ __launch_bounds__(64 * NW) void k_dense_mfma(const T* __restrict__ A, int64_t lda,
+                                                        const T* __restrict__ W, int64_t ldw,
+                                                        T* __restrict__ Y, int64_t ldy, int ncols,
+                                                        int64_t n) {
+  typedef typename DenseTypes<T>::Acc Acc;
+  typedef typename DenseTypes<T>::Vec Vec;
+  constexpr int VE = 16 / (int)sizeof(T);  // columns of A per load and lane
+  constexpr int KC = 32;                   // columns of A per chunk
+  constexpr int NI = KC / (4 * VE);        // loads per row tile and chunk
+  __shared__ T part[NW][RT * 16][17];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int g = lane >> 4, r = lane & 15;
+  const int64_t r0 = (int64_t)blockIdx.x * (16 * RT);
+  const T* ap[RT];
+#pragma unroll
+  for (int t = 0; t < RT; ++t) ap[t] = A + min(r0 + 16 * t + r, n - 1) * lda + VE * g;
+  const T* wp = W + min(r, ncols - 1) + (int64_t)(VE * g) * ldw;
+  Acc sum[RT];
+#pragma unroll
+  for (int t = 0; t < RT; ++t)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) sum[t][e] = T(0);
+  struct Chunk {
+    Vec a[RT][NI];
+    T w[NI][VE];
+  };
+  auto load = [&](Chunk& c, int64_t k0) {
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+      for (int i = 0; i < NI; ++i) c.a[t][i] = *reinterpret_cast<const Vec*>(ap[t] + k0 + 4 * VE * i);
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+      for (int e = 0; e < VE; ++e) c.w[i][e] = wp[(k0 + 4 * VE * i + e) * ldw];
+  };
+  auto mul = [&](const Chunk& c) {
+    Acc acc[NA][RT];
+#pragma unroll
+    for (int q = 0; q < NI * VE; ++q)
+#pragma unroll
+      for (int t = 0; t < RT; ++t)
+        acc[q % NA][t] = dmma(c.a[t][q / VE][q % VE], c.w[q / VE][q % VE], q < NA ? Acc{} : acc[q % NA][t]);
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        T v[NA];
+#pragma unroll
+        for (int q = 0; q < NA; ++q) v[q] = acc[q][t][e];
+        sum[t][e] += tree_sum(v);
+      }
+  };
+  const int64_t nfull = n & ~(int64_t)(KC - 1);
+  constexpr int64_t step = KC * NW;
+  int64_t k = KC * wave;
+  Chunk c0, c1;
+  if (k < nfull) load(c0, k);
+  while (k < nfull) {
+    if (k + step < nfull) load(c1, k + step);
+    mul(c0);
+    k += step;
+    if (k >= nfull) break;
+    if (k + step < nfull) load(c0, k + step);
+    mul(c1);
+    k += step;
+  }
+  if (k == nfull && nfull < n) {  // the wave whose chunk is the last, partial one
+    Chunk c;
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+      for (int e = 0; e < VE; ++e) {
+        const int64_t kk = nfull + 4 * VE * i + e;
+        const bool in = kk + VE * g < n;
+        c.w[i][e] = in ? wp[kk * ldw] : T(0);
+#pragma unroll
+        for (int t = 0; t < RT; ++t) c.a[t][i][e] = in ? ap[t][kk] : T(0);
+      }
+    mul(c);
+  }
+  // accumulator register e of lane (g, c): row 4 e + g (fp64), 4 g + e (fp32)
+#pragma unroll
+  for (int t = 0; t < RT; ++t)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) part[wave][16 * t + (sizeof(T) == 8 ? 4 * e + g : 4 * g + e)][r] = sum[t][e];
+  __syncthreads();
+  for (int q = threadIdx.x; q < RT * 256; q += 64 * NW) {
+    const int i = q >> 4, j = q & 15;
+    T v[NW];
+#pragma unroll
+    for (int w = 0; w < NW; ++w) v[w] = part[w][i][j];
+    const T y = tree_sum(v);
+    if (r0 + i < n && j < ncols) Y[(r0 + i) * ldy + j] = y;
+  }
+}
+
+// At most MC columns by scalar products: a wave owns R rows, lanes stride their
+// columns, and the sums are reduced across the wave at the end.
 template <typename T, int R, int MC>
 __global__ __launch_bounds__(256) void k_dense(const T* __restrict__ A, int64_t lda,
                                                const T* __restrict__ W, int64_t ldw,
@@ -62,201 +204,32 @@ __global__ __launch_bounds__(256) void k_dense(const T* __restrict__ A, int64_t 
   }
 }
 
-// Vector form for aligned operands: a wave owns R = 8 rows; lanes take
-// VE = 16 / sizeof(T) adjacent columns per step (one 16-byte load per row),
-// so each W row fetched (as 16-byte vectors, from L2) serves 8 rows of A,
-// and the ncols x R sums are reduced across the wave once at the end, one
-// output value per lane.  Fewer rows per wave re-read W more often (4 rows:
-// half the rate); splitting a row group's columns over 2 or 4 waves, with a
-// reduction through LDS, ran 30-45 % slower.  Walking A by column strips
-// instead (A symmetric, Y = A^T W, lanes owning output rows, W rows shared
-// through LDS) ran at 0.3 TB/s: every step moves to another row of A.
-// Sharing each chunk of W rows among a workgroup's 4 waves through LDS
-// (double-buffered, one barrier per 512 columns) ran 15 % slower: the W
-// re-reads from L2 are not what bounds this kernel.  With 8 fp64 columns
-// the 64 accumulators leave room for one wave per SIMD, so A is prefetched
-// a step ahead and read with the non-temporal hint (737 -> 661 us at
-// n = 2e4 in isolation).
-template <typename T>
-struct alignas(16) DVec {
-  T v[16 / sizeof(T)];
-};
-// the same 16 bytes as a vector type (what the non-temporal load takes)
-template <typename T>
-struct NtVec;
-template <>
-struct NtVec<double> {
-  typedef double __attribute__((ext_vector_type(2))) type;
-};
-template <>
-struct NtVec<float> {
-  typedef float __attribute__((ext_vector_type(4))) type;
-};
-
-template <typename T, int R, int MC, bool FULLW>
-__global__ __launch_bounds__(256) void k_dense_vec(const T* __restrict__ A, int64_t lda,
-                                                   const T* __restrict__ W, int64_t ldw,
-                                                   T* __restrict__ Y, int64_t ldy, int ncols,
-                                                   int64_t n) {
-  constexpr int VE = 16 / sizeof(T);
-  constexpr int WV = MC / VE;  // 16-byte vectors per W row
-  static_assert(MC % VE == 0 && R * MC <= 64, "tile shape");
-  typedef DVec<T> V;
-  const int lane = threadIdx.x & 63;
-  const int64_t r0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * R;
-  if (r0 >= n) return;
-  T acc[R][MC];
-#pragma unroll
-  for (int r = 0; r < R; ++r)
-#pragma unroll
-    for (int j = 0; j < MC; ++j) acc[r][j] = T(0);
-  const T* arow[R];
-#pragma unroll
-  for (int r = 0; r < R; ++r) arow[r] = A + min(r0 + r, n - 1) * lda;
-  constexpr int64_t kStep = 64 * VE;
-  const int64_t nfull = (n / kStep) * kStep;
-  // A is read once: non-temporal loads keep it from evicting W from L2, and
-  // the next step's A vectors are loaded before this step's products (one
-  // step in flight ahead; fully unrolled steps ran 3 % slower)
-  typedef typename NtVec<T>::type VN;
-  auto load_a = [&](int64_t c, V* dst) {
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const VN t = __builtin_nontemporal_load(reinterpret_cast<const VN*>(arow[r] + c));
-#pragma unroll
-      for (int u = 0; u < VE; ++u) dst[r].v[u] = t[u];
-    }
-  };
-  // (prefetch only where occupancy is one wave per SIMD anyway: fp64 with 8
-  // columns; elsewhere its registers would cost a wave)
-  constexpr bool PF = sizeof(T) == 8 && MC == 8;
-  V anext[PF ? R : 1];
-  if (PF && nfull > 0) load_a(lane * VE, anext);
-#pragma unroll 1
-  for (int64_t c0 = 0; c0 < nfull; c0 += kStep) {
-    const int64_t c = c0 + lane * VE;
-    V a[R];
-    if constexpr (PF) {
-#pragma unroll
-      for (int r = 0; r < R; ++r) a[r] = anext[r];
-      if (c0 + kStep < nfull) load_a(c + kStep, anext);
-    } else {
-      load_a(c, a);
-    }
-    // W rows as 16-byte vectors; a vector that would reach past column
-    // ncols (the block may be a column slice of a wider buffer) is read value
-    // by value
-    V w[VE][WV];
-#pragma unroll
-    for (int e = 0; e < VE; ++e)
-#pragma unroll
-      for (int q = 0; q < WV; ++q) {
-        const T* src = W + (c + e) * ldw + q * VE;
-        if (FULLW || (q + 1) * VE <= ncols) {
-          w[e][q] = *reinterpret_cast<const V*>(src);
-        } else {
-#pragma unroll
-          for (int u = 0; u < VE; ++u) w[e][q].v[u] = (q * VE + u < ncols) ? src[u] : T(0);
-        }
-      }
-#pragma unroll
-    for (int r = 0; r < R; ++r)
-#pragma unroll
-      for (int e = 0; e < VE; ++e)
-#pragma unroll
-        for (int j = 0; j < MC; ++j) acc[r][j] += a[r].v[e] * w[e][j / VE].v[j % VE];
-  }
-  // ragged tail (fewer than 64 VE columns): value by value
-  for (int64_t c = nfull + lane; c < n; c += 64) {
-    T w[MC];
-#pragma unroll
-    for (int j = 0; j < MC; ++j) w[j] = (j < ncols) ? W[c * ldw + j] : T(0);
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const T a = arow[r][c];
-#pragma unroll
-      for (int j = 0; j < MC; ++j) acc[r][j] += a * w[j];
-    }
-  }
-  T mine = T(0);
-#pragma unroll
-  for (int r = 0; r < R; ++r)
-#pragma unroll
-    for (int j = 0; j < MC; ++j) {
-      T v = acc[r][j];
-#pragma unroll
-      for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off);
-      if (lane == r * MC + j) mine = v;
-    }
-  const int r = lane / MC, j = lane % MC;
-  if (r < R && r0 + r < n && j < ncols) Y[(r0 + r) * ldy + j] = mine;
-}
-
 template <typename T>
 static hipError_t dense_any(const T* A, int64_t lda, const T* W, int64_t ldw, T* Y, int64_t ldy,
-                            int ncols, int64_t n, T* pack, hipStream_t s) {
+                            int ncols, int64_t n, hipStream_t s) {
   if (n < 1 || ncols < 1) return hipErrorInvalidValue;
-  constexpr int VE = 16 / sizeof(T);
-  // a block that is not a compact 8-column one is packed (8 columns at a
-  // time, zero-padded) into `pack` first: strided rows and partial widths
-  // cost the vector kernel 25-70 % (n = 2e4: 904 / 1271 us at ld 24 with 8
-  // and 7 columns, against 737 us compact)
-  if (pack != nullptr && lda % VE == 0 && reinterpret_cast<uintptr_t>(A) % 16 == 0 &&
-      !(ldw == 8 && ncols == 8 && reinterpret_cast<uintptr_t>(W) % 16 == 0)) {
-    const int gridv = cdiv(cdiv(n, 8), 4);
-    for (int c0 = 0; c0 < ncols; c0 += 8) {
-      const int nc = std::min(8, ncols - c0);
-      hipError_t e = (sizeof(T) == 8)
-                         ? pack8_f64(reinterpret_cast<const double*>(W + c0), ldw, nc, n,
-                                     reinterpret_cast<double*>(pack), s)
-                         : pack8_f32(reinterpret_cast<const float*>(W + c0), ldw, nc, n,
-                                     reinterpret_cast<float*>(pack), s);
-      if (e != hipSuccess) return e;
-      hipLaunchKernelGGL((k_dense_vec<T, 8, 8, true>), dim3(gridv), dim3(256), 0, s, A, lda, pack,
-                         (int64_t)8, Y + c0, ldy, nc, n);
-      e = hipGetLastError();
-      if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
-  }
-  const bool vec = lda % VE == 0 && ldw % VE == 0 &&
-                   reinterpret_cast<uintptr_t>(A) % 16 == 0 &&
-                   reinterpret_cast<uintptr_t>(W) % 16 == 0;
-  if (vec) {
-    constexpr int RV = 8;
-    const int gridv = cdiv(cdiv(n, RV), 4);
-    for (int c0 = 0; c0 < ncols; c0 += 8) {
-      const int nc = std::min(8, ncols - c0);
-      // W + c0 stays 16-byte aligned (c0 is a multiple of 8); only the block's
-      // nc columns of each W row are read
-      if (nc == 8)
-        hipLaunchKernelGGL((k_dense_vec<T, RV, 8, true>), dim3(gridv), dim3(256), 0, s, A, lda,
-                           W + c0, ldw, Y + c0, ldy, nc, n);
-      else if (nc == 4)
-        hipLaunchKernelGGL((k_dense_vec<T, RV, 4, true>), dim3(gridv), dim3(256), 0, s, A, lda,
-                           W + c0, ldw, Y + c0, ldy, nc, n);
-      else if (nc < 4)
-        hipLaunchKernelGGL((k_dense_vec<T, RV, 4, false>), dim3(gridv), dim3(256), 0, s, A, lda,
-                           W + c0, ldw, Y + c0, ldy, nc, n);
-      else
-        hipLaunchKernelGGL((k_dense_vec<T, RV, 8, false>), dim3(gridv), dim3(256), 0, s, A, lda,
-                           W + c0, ldw, Y + c0, ldy, nc, n);
-      hipError_t e = hipGetLastError();
-      if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
-  }
-  constexpr int R = 4;
-  const int64_t waves = (n + R - 1) / R;
-  const int grid = cdiv(waves, 4);
-  for (int c0 = 0; c0 < ncols; c0 += 8) {
-    const int nc = std::min(8, ncols - c0);
-    if (nc <= 4)
-      hipLaunchKernelGGL((k_dense<T, R, 4>), dim3(grid), dim3(256), 0, s, A, lda, W + c0, ldw,
-                         Y + c0, ldy, nc, n);
+  // Below one tile per CU a workgroup is 8 waves (n = 3000 fp32: 10.7 us, 12.0
+  // with 4; n = 4000 fp64: 26.9 and 24.4).  From 6000 rows two tiles share the
+  // loads of W in fp64 (n = 6007: 69 us, 75 with one; 4000: 41 and 24).  Rows
+  // of doubles that are not all aligned to 16 bytes cost the MFMA kernel's
+  // loads half again their time: up to 4 columns the scalar products, which
+  // load 8 bytes per lane, are faster then (n = 9001, 1 column: 135 against
+  // 199 us, 4: 177 and 200, 8: 316 and 203; n = 777, 1 column: 9.4 and 8.9).
+  const bool odd = sizeof(T) == 8 && (lda % 2 != 0 || reinterpret_cast<uintptr_t>(A) % 16 != 0);
+  for (int c0 = 0; c0 < ncols; c0 += 16) {
+    const int nc = std::min(16, ncols - c0);
+    if (odd && nc <= 4 && n >= 16 * 256)
+      hipLaunchKernelGGL((k_dense<T, 4, 4>), dim3(cdiv(cdiv(n, 4), 4)), dim3(256), 0, s, A, lda, W + c0, ldw, Y + c0,
+                         ldy, nc, n);
+    else if (n < 16 * 256)
+      hipLaunchKernelGGL((k_dense_mfma<T, 1, 8, 8>), dim3(cdiv(n, 16)), dim3(512), 0, s, A, lda, W + c0, ldw, Y + c0,
+                         ldy, nc, n);
+    else if (sizeof(T) == 8 && n >= 6000)
+      hipLaunchKernelGGL((k_dense_mfma<T, 2, 4, 2>), dim3(cdiv(n, 32)), dim3(256), 0, s, A, lda, W + c0, ldw, Y + c0,
+                         ldy, nc, n);
     else
-      hipLaunchKernelGGL((k_dense<T, R, 8>), dim3(grid), dim3(256), 0, s, A, lda, W + c0, ldw,
-                         Y + c0, ldy, nc, n);
+      hipLaunchKernelGGL((k_dense_mfma<T, 1, 4, 4>), dim3(cdiv(n, 16)), dim3(256), 0, s, A, lda, W + c0, ldw, Y + c0,
+                         ldy, nc, n);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
@@ -264,12 +237,12 @@ static hipError_t dense_any(const T* A, int64_t lda, const T* W, int64_t ldw, T*
 }
 
 hipError_t dense_apply_f64(const double* A, int64_t lda, const double* W, int64_t ldw, double* Y,
-                           int64_t ldy, int ncols, int64_t n, double* pack, hipStream_t s) {
-  return dense_any<double>(A, lda, W, ldw, Y, ldy, ncols, n, pack, s);
+                           int64_t ldy, int ncols, int64_t n, hipStream_t s) {
+  return dense_any<double>(A, lda, W, ldw, Y, ldy, ncols, n, s);
 }
 hipError_t dense_apply_f32(const float* A, int64_t lda, const float* W, int64_t ldw, float* Y,
-                           int64_t ldy, int ncols, int64_t n, float* pack, hipStream_t s) {
-  return dense_any<float>(A, lda, W, ldw, Y, ldy, ncols, n, pack, s);
+                           int64_t ldy, int ncols, int64_t n, hipStream_t s) {
+  return dense_any<float>(A, lda, W, ldw, Y, ldy, ncols, n, s);
 }
 
 // ---------------------------------------------------------------------------

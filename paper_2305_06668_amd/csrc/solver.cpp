@@ -75,7 +75,7 @@ Layout lobpcg_ctx::plan(int m, int prec) const {
     L.tri_xb = take((size_t)kTriMaxChunks * kMaxBlock * 6 * sizeof(double));
   }
   L.ltiles = take((size_t)ltiles_cap() * sizeof(int));
-  if (op == kOpKron || op == kOpDense) L.kpack = take((size_t)n * 8 * sizeof(double));
+  if (op == kOpKron) L.kpack = take((size_t)n * 8 * sizeof(double));
   if (op == kOpCsr && slab_mode == 1)
     L.cwin = take(((size_t)(n + kSlabBlockRows - 1) / kSlabBlockRows + 1) * 8);
   const size_t gblk = (size_t)std::min<int64_t>(kGramBlocks, (n + 63) / 64) + 1;
@@ -168,8 +168,7 @@ int lobpcg_ctx::apply_op(const double* W, int64_t ldw, int nc, double* Y, int64_
   switch (op) {
     case kOpCsr: e = spmm_csr_f64(rp, ci, val, W, ldw, Y, ldy, nc, n, csr_slab_windows(), stream); break;
     case kOpDense:
-      e = dense_apply_f64(A, lda, W, ldw, Y, ldy, nc, n,
-                          (ws && lay_block > 0 && lay.kpack) ? dptr(lay.kpack) : nullptr, stream);
+      e = dense_apply_f64(A, lda, W, ldw, Y, ldy, nc, n, stream);
       break;
     case kOpKron:
       e = kronsum_apply_f64(A, Vpot, na, W, ldw, Y, ldy, nc,
@@ -190,8 +189,7 @@ int lobpcg_ctx::apply_op(const float* W, int64_t ldw, int nc, float* Y, int64_t 
   switch (op) {
     case kOpCsr: e = spmm_csr_f32(rp, ci, o32, W, ldw, Y, ldy, nc, n, csr_slab_windows(), stream); break;
     case kOpDense:
-      e = dense_apply_f32(o32, n, W, ldw, Y, ldy, nc, n,
-                          lay.kpack ? reinterpret_cast<float*>(dptr(lay.kpack)) : nullptr, stream);
+      e = dense_apply_f32(o32, n, W, ldw, Y, ldy, nc, n, stream);
       break;
     case kOpKron:
       e = kronsum_apply_f32(o32, o32 + na * na, na, W, ldw, Y, ldy, nc,
@@ -933,8 +931,7 @@ int lobpcg_ctx::apply_b(const double* W, int64_t ldw, int nc, double* Y, int64_t
   switch (bop) {
     case kOpCsr: e = spmm_csr_f64(brp, bci, bval, W, ldw, Y, ldy, nc, n, nullptr, stream); break;
     case kOpDense:
-      e = dense_apply_f64(Bd, ldb, W, ldw, Y, ldy, nc, n,
-                          (ws && lay_block > 0 && lay.kpack) ? dptr(lay.kpack) : nullptr, stream);
+      e = dense_apply_f64(Bd, ldb, W, ldw, Y, ldy, nc, n, stream);
       break;
     default: return fail(LOBPCG_ERR_BAD_STATE, "no B operator set");
   }
