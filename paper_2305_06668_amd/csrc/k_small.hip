@@ -181,7 +181,39 @@ __device__ __forceinline__ void trsm16_rows(double* X, int ldx, int i, int p, in
       if (j < n) Xi[j] = z[j];
   }
 }
-// both, by the waves that have rows (64 to a wave); the flag (LDS) is 1 on success
+// L = chol(M) and its inverse (both n x n in LDS, zero above the diagonal) by
+// one wave: lane j % 16 solves for column j of the inverse in its registers,
+// the operations and their order those of blk_tri_inv (the terms above the
+// diagonal add zeros).  A root and two divisions per column, one after the
+// other: 4.4 us for n = 16 (solving a row beside the next column of the factor
+// gains nothing).
+template <int N>
+__device__ __forceinline__ bool chol_inv16(const double* M, int ldm, int n, double* L, int ldl, double* Li, int ldi) {
+  const int r = threadIdx.x & 15;
+  double g[N], inv[N];
+  if (!chol16_rows<N, true, false>(M, ldm, n, g, inv)) return false;
+  double z[N];
+  static_for<0, N>([&](auto ic) {
+    constexpr int i = decltype(ic)::value;
+    double t = (r == i) ? 1.0 : 0.0;
+    static_for<0, i>([&](auto kc) {
+      constexpr int k = decltype(kc)::value;
+      t = fma(-row_bcast<i>(g[k]), z[k], t);
+    });
+    z[i] = t / row_bcast<i>(g[i]);
+    asm volatile("" : "+v"(z[i]));  // (computed here, not where it is stored: the broadcasts would stay)
+  });
+  if ((threadIdx.x & 63) < n) {
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+      if (i < n) {
+        L[r * ldl + i] = (i <= r) ? g[i] : 0.0;
+        Li[i * ldi + r] = z[i];
+      }
+  }
+  return true;
+}
+// factor and solve, by the waves that have rows (64 to a wave); the flag (LDS) is 1 on success
 template <int N, bool KDIV, bool CHECKINF>
 __device__ __forceinline__ void chol_trsm(double* X, int ldx, int p, int n, const double* G, int ldg, int* flag) {
   if (64 * wave_id() < p) {
@@ -1583,28 +1615,71 @@ hipError_t small_cholesky(const double* M, int p, double* L, int* info, hipStrea
 
 enum { kPhFinal = 5, kPhYCheck = 6 };
 
+// The ortho controller is one workgroup between two passes over the vectors, so
+// its latency is what counts: a chain of roots and divisions, barriers, and the
+// waits for its inputs.  Threads: the fewest that fill a block of 16 (each has
+// one entry of the overlap), so the factor has the registers it needs and a
+// reduction four waves to join.  12.1 us for a block of 16 under 32 columns
+// (18.6 with 1024 threads, where the factor spills), 4.4 of it the factor and
+// its inverse; 6.3 us (10.8 before) over the calls of a solve, many of which
+// have nothing to factor.
+constexpr int kCtlThreads = 256;
+
+// maximum of non-negative values over the workgroup, in every thread
+__device__ __forceinline__ double ctl_max(double v, double* scratch) {
+  v = wave_max(v);
+  if ((threadIdx.x & 63) == 0) scratch[threadIdx.x >> 6] = v;
+  __syncthreads();
+  v = fmax(fmax(scratch[0], scratch[1]), fmax(scratch[2], scratch[3]));
+  __syncthreads();
+  return v;
+}
+// sum over the wave, partners 32, 16, 8, 4, 2, 1 apart in turn (a value that is
+// the same 8 lanes on is the same 4 lanes on as 4 lanes back)
+__device__ __forceinline__ double wave_sum_halves(double v) {
+  double a, b;
+  lane_pair<32>(v, a, b);
+  lane_pair<16>(a + b, a, b);
+  v = a + b;
+  v += dpp_f64<0x128>(v);  // row_ror:8
+  v += dpp_f64<0x124>(v);  // row_ror:4
+  v += dpp_f64<0x4E>(v);   // quad_perm [2, 3, 0, 1]
+  v += dpp_f64<0xB1>(v);   // quad_perm [1, 0, 3, 2]
+  return v;
+}
 // Bound on ||L^-1||_2 for the n x n lower factor L (stride ldl) with its
 // inverse Li (stride ldi): 1 / (1 - e) when e = ||I - L||_F < 1/2 (Neumann
 // series), else ||Li||_F.  *e_out receives e.  Every thread gets the result.
-__device__ double blk_inv_bound(const double* L, int ldl, const double* Li, int ldi, int n,
+__device__ __forceinline__ double blk_inv_bound(const double* L, int ldl, const double* Li, int ldi, int n,
                                 double* e_out, double* scratch) {
-  double se = 0.0, si = 0.0;
-  for (int idx = threadIdx.x; idx < n * n; idx += blockDim.x) {
-    const int i = idx / n, j = idx - i * n;
-    if (j > i) continue;
-    const double d = (i == j ? 1.0 : 0.0) - L[i * ldl + j];
-    se += d * d;
-    const double v = Li[i * ldi + j];
-    si += v * v;
+  // 64 entries to a partial sum, these in order (scratch: two times 16)
+  const unsigned parts = (n * n + 63) / 64;
+  for (unsigned p = wave_id(); p < parts; p += kCtlThreads / 64) {
+    const unsigned idx = 64 * p + (threadIdx.x & 63), i = idx / unsigned(n), j = idx - i * n;
+    double de = 0.0, di = 0.0;
+    if (i < unsigned(n) && j <= i) {
+      de = (i == j ? 1.0 : 0.0) - L[i * ldl + j];
+      di = Li[i * ldi + j];
+    }
+    de = wave_sum_halves(de * de);
+    di = wave_sum_halves(di * di);
+    if ((threadIdx.x & 63) == 0) {
+      scratch[2 * p] = de;
+      scratch[2 * p + 1] = di;
+    }
   }
-  se = blk_reduce_sum_ordered(se, scratch);
-  si = blk_reduce_sum_ordered(si, scratch);
+  __syncthreads();
+  double se = scratch[0], si = scratch[1];
+  for (unsigned p = 1; p < parts; ++p) {
+    se += scratch[2 * p];
+    si += scratch[2 * p + 1];
+  }
   const double e = sqrt(se);
   *e_out = e;
   return (e < 0.5) ? 1.0 / (1.0 - e) : sqrt(si);
 }
 
-__global__ __launch_bounds__(1024) void k_ortho_ctl(const double* __restrict__ G,
+__global__ __launch_bounds__(kCtlThreads) void k_ortho_ctl(const double* __restrict__ G,
                                                    OrthoState* __restrict__ gst,
                                                    double* __restrict__ coef) {
   __shared__ OrthoState st;
@@ -1617,11 +1692,13 @@ __global__ __launch_bounds__(1024) void k_ortho_ctl(const double* __restrict__ G
   __shared__ double cs[3 * 64];
   __shared__ int pr[2 * 64];
   __shared__ int perm[64];
-  __shared__ double scratch[16];
+  __shared__ double scratch[32];
   __shared__ int flag, nonfinite, zero_mask;
   __shared__ ShiftCount cnt;
+  static_assert(sizeof(OrthoState) % 4 == 0, "copied by words");
+  if (threadIdx.x < sizeof(OrthoState) / 4)
+    reinterpret_cast<uint32_t*>(&st)[threadIdx.x] = reinterpret_cast<const uint32_t*>(gst)[threadIdx.x];
   if (threadIdx.x == 0) {
-    st = *gst;
     nonfinite = 0;
     zero_mask = 0;
     cnt.factorizations = cnt.failed = cnt.shifted = cnt.svqb = 0;
@@ -1707,9 +1784,9 @@ __global__ __launch_bounds__(1024) void k_ortho_ctl(const double* __restrict__ G
   if (phase == kPhBegin) {
     // M' = D M D, Alg. 2 check on the normalised X; the normalisation is
     // the first factor of this Alg. 2 call's growth
-    double dmax = 0.0;
-    for (int j = threadIdx.x; j < nw; j += blockDim.x) dmax = fmax(dmax, D[j]);
-    growth = blk_reduce_max(dmax, scratch);
+    // (every wave for itself)
+    const int lane = threadIdx.x & 63;
+    growth = wave_max((lane < nw) ? D[lane] : 0.0);
     for (int idx = threadIdx.x; idx < nw * nw; idx += blockDim.x) {
       const int i = idx / nw, j = idx - i * nw;
       Ms[i * ldm + j] *= D[i] * D[j];
@@ -1731,7 +1808,7 @@ __global__ __launch_bounds__(1024) void k_ortho_ctl(const double* __restrict__ G
     const int i = idx / nw, j = idx - i * nw;
     dev = fmax(dev, fabs(Ms[i * ldm + j] - (i == j ? 1.0 : 0.0)));
   }
-  dev = blk_reduce_max(dev, scratch);
+  dev = ctl_max(dev, scratch);
   const bool ortho_ok = dev <= st.tau;
   capped = !ortho_ok && st.inner >= st.max_inner;
   if (ortho_ok || capped) {
@@ -1740,9 +1817,25 @@ __global__ __launch_bounds__(1024) void k_ortho_ctl(const double* __restrict__ G
     have_scale = (phase == kPhBegin);
   } else {
     // shifted Cholesky of M (= M' in BEGIN)
-    const bool ok = blk_shifted_chol<true>(Ms, ldm, nw, Ls, ldm, &flag, &cnt, scratch, st.shift_retries);
+    bool ok = false;
+    if (nw <= 16) {  // the plain one, with its inverse
+      if (threadIdx.x < 64) {
+        const bool o = (nw <= 8) ? chol_inv16<8>(Ms, ldm, nw, Ls, ldm, Li, ldm)
+                                 : chol_inv16<16>(Ms, ldm, nw, Ls, ldm, Li, ldm);
+        if (threadIdx.x == 0) {
+          flag = o ? 1 : 0;
+          if (o) cnt.factorizations++;
+        }
+      }
+      __syncthreads();
+      ok = flag != 0;
+      __syncthreads();
+    }
+    if (!ok) {
+      ok = blk_shifted_chol<true>(Ms, ldm, nw, Ls, ldm, &flag, &cnt, scratch, st.shift_retries, nw > 16);
+      if (ok) blk_tri_inv(Ls, ldm, nw, Li, ldm);
+    }
     if (ok) {
-      blk_tri_inv(Ls, ldm, nw, Li, ldm);
       // coef W part: D L^-T, i.e. coef[ny+i][j] = D_i Linv[j][i]
       for (int idx = threadIdx.x; idx < nr * nw; idx += blockDim.x) {
         const int i = idx / nw, j = idx - i * nw;
@@ -1776,7 +1869,7 @@ __global__ __launch_bounds__(1024) void k_ortho_ctl(const double* __restrict__ G
       return;
     } else {
       if (threadIdx.x == 0) cnt.svqb++;
-      const bool sv = blk_svqb_coef<1024>(Ms, ldm, nw, Li, ldm, Ws, cs, pr, &flag, perm, scratch);
+      const bool sv = blk_svqb_coef<kCtlThreads>(Ms, ldm, nw, Li, ldm, Ws, cs, pr, &flag, perm, scratch);
       if (!sv) {
         if (threadIdx.x == 0) {
           st.error = kOrthoErrFailed;
@@ -1819,7 +1912,7 @@ __global__ __launch_bounds__(1024) void k_ortho_ctl(const double* __restrict__ G
     const int j = idx % nw;
     cm = fmax(cm, fabs(Gs[idx] * D[j]));
   }
-  cm = blk_reduce_max(cm, scratch);
+  cm = ctl_max(cm, scratch);
   if (grow_ok && threadIdx.x == 0) st.cheap_exits++;
   const bool y_ok = (ny == 0) || grow_ok || (cm <= st.tau);
   if (y_ok || st.outer >= st.max_outer) {
@@ -1911,8 +2004,7 @@ hipError_t ortho_init(OrthoState* st, int ny, int nw, double tau, int max_inner,
 }
 
 hipError_t ortho_ctl(const double* G, OrthoState* st, double* coef, hipStream_t s) {
-  // 1024 threads: the SVQB fallback runs the Jacobi sweep, which assumes them
-  hipLaunchKernelGGL(k_ortho_ctl, dim3(1), dim3(1024), 0, s, G, st, coef);
+  hipLaunchKernelGGL(k_ortho_ctl, dim3(1), dim3(kCtlThreads), 0, s, G, st, coef);
   return hipGetLastError();
 }
 
