@@ -158,7 +158,19 @@ __global__ __launch_bounds__(256, (MTI <= 3 && MTJ <= 3) ? 3 : 1) void k_gram_pa
 // Stage 2: C[o] = sum over blocks b of part[b][o], fixed order: block x owns
 // 16 consecutive outputs; thread (s, o) with s = tid / 16 sums the blocks
 // b = s, s + 16, s + 32, ... in order; the 16 slice sums are added in slice
-// order.  Loads of one b are 16 consecutive doubles (coalesced).
+// order.  Loads of one b are 16 consecutive doubles (coalesced).  A few
+// megabytes at most, so the waits bound it: every load of a thread is under way
+// before its first addition (5.5 us a call in a solve of n = 2e5 with four under
+// way, 4.5 so).
+template <int N>
+__device__ __forceinline__ double sum_batch(const double* __restrict__ p, int pq, int b, int nblk, double acc) {
+  double v[N];
+#pragma unroll
+  for (int u = 0; u < N; ++u) v[u] = p[(int64_t)min(b + 16 * u, nblk - 1) * pq];
+#pragma unroll
+  for (int u = 0; u < N; ++u) acc += (b + 16 * u < nblk) ? v[u] : 0.0;
+  return acc;
+}
 __global__ __launch_bounds__(256) void k_sum_parts(const double* __restrict__ part, int nblk,
                                                    int pq, double* __restrict__ C,
                                                    const int* __restrict__ skip) {
@@ -166,21 +178,11 @@ __global__ __launch_bounds__(256) void k_sum_parts(const double* __restrict__ pa
   __shared__ double red[16][17];
   const int o = blockIdx.x * 16 + (threadIdx.x & 15);
   const int sl = threadIdx.x >> 4;
+  const double* p = part + min(o, pq - 1);
   double acc = 0.0;
-  if (o < pq) {
-    int b = sl;
-    for (; b + 48 < nblk; b += 64) {
-      const double v0 = part[(int64_t)b * pq + o];
-      const double v1 = part[(int64_t)(b + 16) * pq + o];
-      const double v2 = part[(int64_t)(b + 32) * pq + o];
-      const double v3 = part[(int64_t)(b + 48) * pq + o];
-      acc += v0;
-      acc += v1;
-      acc += v2;
-      acc += v3;
-    }
-    for (; b < nblk; b += 16) acc += part[(int64_t)b * pq + o];
-  }
+  int b = 0;
+  for (; nblk - b > 128; b += 512) acc = sum_batch<32>(p, pq, b + sl, nblk, acc);
+  for (; b < nblk; b += 128) acc = sum_batch<8>(p, pq, b + sl, nblk, acc);
   red[sl][threadIdx.x & 15] = acc;
   __syncthreads();
   if (threadIdx.x < 16 && o < pq) {
@@ -1088,16 +1090,32 @@ __global__ __launch_bounds__(256) void k_colargmax(const double* __restrict__ X,
   }
 }
 
-__global__ void k_argmax_final(const double* __restrict__ X, int64_t ldx, int k, int nblk,
-                               int64_t* pidx, double* pval) {
-  const int c = threadIdx.x;
-  if (c >= k) return;
-  double v = pval[c];
-  int64_t i = pidx[c];
-  for (int b = 1; b < nblk; ++b)
-    if (better(pval[(int64_t)b * k + c], pidx[(int64_t)b * k + c], v, i)) {
-      v = pval[(int64_t)b * k + c];
-      i = pidx[(int64_t)b * k + c];
+// one workgroup: wave w takes the blocks w, w + 16, ... (53 us with one thread
+// for all blocks of a column, 9 so)
+__global__ __launch_bounds__(1024) void k_argmax_final(const double* __restrict__ X, int64_t ldx, int k, int nblk,
+                                                       const int64_t* __restrict__ pidx, double* pval) {
+  __shared__ double sv[16][64];
+  __shared__ int64_t si[16][64];
+  const int c = threadIdx.x & 63, w = threadIdx.x >> 6;
+  double v = -1.0;  // (below every entry)
+  int64_t i = INT64_MAX;
+  if (c < k)
+    for (int b = w; b < nblk; b += 16) {
+      const double bv = pval[(int64_t)b * k + c];
+      const int64_t bi = pidx[(int64_t)b * k + c];
+      if (better(bv, bi, v, i)) {
+        v = bv;
+        i = bi;
+      }
+    }
+  sv[w][c] = v;
+  si[w][c] = i;
+  __syncthreads();
+  if (w != 0 || c >= k) return;
+  for (int u = 1; u < 16; ++u)
+    if (better(sv[u][c], si[u][c], v, i)) {
+      v = sv[u][c];
+      i = si[u][c];
     }
   // sign of the winning entry, stored as +1 / -1 in pval[c]
   pval[c] = (X[i * ldx + c] < 0.0) ? -1.0 : 1.0;
@@ -1117,7 +1135,7 @@ hipError_t copy_signfix(const double* X, int64_t ldx, int k, int64_t n, double* 
   if (k < 1 || k > 64) return hipErrorInvalidValue;
   const int grid = (int)std::min<int64_t>(256, (n + 3) / 4);
   hipLaunchKernelGGL(k_colargmax, dim3(grid), dim3(256), 0, s, X, ldx, k, n, part_idx, part_val);
-  hipLaunchKernelGGL(k_argmax_final, dim3(1), dim3(64), 0, s, X, ldx, k, grid, part_idx, part_val);
+  hipLaunchKernelGGL(k_argmax_final, dim3(1), dim3(1024), 0, s, X, ldx, k, grid, part_idx, part_val);
   hipLaunchKernelGGL(k_copy_sign, dim3(cdiv(n * k, 256)), dim3(256), 0, s, X, ldx, k, n,
                      (const double*)part_val, out, ldout);
   return hipGetLastError();

@@ -9,6 +9,8 @@
 //   * the controller of ortho(W; Y) on n-vectors (Alg. 2 inside Alg. 3): it
 //     reads the overlap G = [Y W]^T W of the current W and emits the small
 //     coefficient matrix that the streaming kernel applies next.
+#include <cstring>
+
 #include "small.h"
 
 namespace lobpcg {
@@ -1695,7 +1697,6 @@ __global__ __launch_bounds__(kCtlThreads) void k_ortho_ctl(const double* __restr
   __shared__ double scratch[32];
   __shared__ int flag, nonfinite, zero_mask;
   __shared__ ShiftCount cnt;
-  static_assert(sizeof(OrthoState) % 4 == 0, "copied by words");
   if (threadIdx.x < sizeof(OrthoState) / 4)
     reinterpret_cast<uint32_t*>(&st)[threadIdx.x] = reinterpret_cast<const uint32_t*>(gst)[threadIdx.x];
   if (threadIdx.x == 0) {
@@ -1965,41 +1966,32 @@ __global__ __launch_bounds__(kCtlThreads) void k_ortho_ctl(const double* __restr
   }
 }
 
-__global__ void k_ortho_init(OrthoState* st, int ny, int nw, double tau, int max_inner,
-                             int max_outer, int shift_retries, int fold_scale, double cexit) {
+static_assert(sizeof(OrthoState) % 4 == 0, "copied by words");
+
+__global__ __launch_bounds__(256) void k_ortho_init(OrthoState* __restrict__ st, const OrthoState s) {
+  const uint32_t* w = reinterpret_cast<const uint32_t*>(&s);
+  for (unsigned i = threadIdx.x; i < sizeof(OrthoState) / 4; i += 256) reinterpret_cast<uint32_t*>(st)[i] = w[i];
+}
+
+hipError_t ortho_init(OrthoState* st, int ny, int nw, double tau, int max_inner, int max_outer,
+                      int shift_retries, int fold_scale, double cexit, hipStream_t stream) {
+  if (nw < 1 || nw > kMaxBlock || ny < 0 || ny + nw > kMaxP || shift_retries < 0)
+    return hipErrorInvalidValue;
   OrthoState s;
+  memset(&s, 0, sizeof(s));
   s.state = kPhStart;
-  s.done = 0;
-  s.inner = 0;
-  s.outer = 0;
-  s.w_only = 0;
-  s.error = 0;
-  s.zero_mask = 0;
-  s.grams = s.factorizations = s.failed = s.shifted = s.updates = s.stalled = s.svqb = s.passes = 0;
   s.ny = ny;
   s.nw = nw;
   s.max_inner = max_inner;
   s.max_outer = max_outer;
   s.shift_retries = shift_retries;
   s.fold_scale = fold_scale;
-  s.pending_scale = 0;
   s.cheap_exit = cexit > 0.0 ? 1 : 0;
-  s.cheap_exits = 0;
-  s.no_gram = 0;
-  s.skip_sum = 0;
   s.cexit = cexit;
   s.growth = INFINITY;
   s.tau = tau;
   for (int j = 0; j < kMaxBlock; ++j) s.dscale[j] = 1.0;
-  *st = s;
-}
-
-hipError_t ortho_init(OrthoState* st, int ny, int nw, double tau, int max_inner, int max_outer,
-                      int shift_retries, int fold_scale, double cexit, hipStream_t s) {
-  if (nw < 1 || nw > kMaxBlock || ny < 0 || ny + nw > kMaxP || shift_retries < 0)
-    return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_ortho_init, dim3(1), dim3(1), 0, s, st, ny, nw, tau, max_inner, max_outer,
-                     shift_retries, fold_scale, cexit);
+  hipLaunchKernelGGL(k_ortho_init, dim3(1), dim3(256), 0, stream, st, s);
   return hipGetLastError();
 }
 
