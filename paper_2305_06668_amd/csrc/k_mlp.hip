@@ -33,7 +33,7 @@
 #include <algorithm>
 #include <cmath>
 
-#include "internal.h"
+#include "small.h"
 
 namespace lobpcg {
 
@@ -49,10 +49,6 @@ static_assert(oB3 + 1 == kMlpParams, "parameter layout");
 // full division
 __device__ __forceinline__ float sigm(float z) { return __builtin_amdgcn_rcpf(1.0f + __expf(-z)); }
 __device__ __forceinline__ float silu(float z) { return z * sigm(z); }
-__device__ __forceinline__ float dsilu(float z) {
-  const float s = sigm(z);
-  return s * (1.0f + z * (1.0f - s));
-}
 __device__ __forceinline__ double softplus_d(double y) {
   return fmax(y, 0.0) + log1p(exp(-fabs(y)));
 }
@@ -91,6 +87,27 @@ __device__ __forceinline__ EntryOut regularise(const EntryIn& in, float y, doubl
   return o;
 }
 
+// v + (v of the lane N on, lane numbers by xor), N = 16, 32
+template <int N>
+__device__ __forceinline__ float add_pair(float v) {
+  const int x = __float_as_int(v);
+  const auto p = (N == 16) ? __builtin_amdgcn_permlane16_swap(x, x, false, false)
+                           : __builtin_amdgcn_permlane32_swap(x, x, false, false);
+  return __int_as_float(p[0]) + __int_as_float(p[1]);
+}
+template <int CTRL>
+__device__ __forceinline__ float add_dpp(float v) {
+  return v + __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xF, 0xF, true));
+}
+// sum over a row of 16 lanes, partners 8, 4, 2, 1 apart in turn (a value that
+// is the same 8 lanes on is the same 4 lanes on as 4 lanes back)
+__device__ __forceinline__ float add_row(float v) {
+  v = add_dpp<0x128>(v);   // row_ror:8
+  v = add_dpp<0x124>(v);   // row_ror:4
+  v = add_dpp<0x4E>(v);    // quad_perm [2, 3, 0, 1]
+  return add_dpp<0xB1>(v); // quad_perm [1, 0, 3, 2]
+}
+
 // ---- fp32 MFMA tile kernels (512 threads) ----
 constexpr int kGT = 512;
 constexpr int gW2 = 0;                // W2 [k][j]
@@ -106,9 +123,10 @@ constexpr int gYP = gPhi + kTE * 4;   // [2][e] layer-3 partials of the two neur
 constexpr int gDY = gYP + 2 * kTE;    // [e]
 constexpr int gP1 = gDY + kTE;        // [4][j][4] dW1 (3), db1 per entry tile
 constexpr int gP2 = gP1 + 4 * kH * 4; // [4][k][2] dW3, db2 per entry tile
-constexpr int gAct = gP2 + 4 * kH * 2;  // [8] ints: tile of the screened group has an entry inside
-constexpr int gEnd = gAct + 8;
-constexpr int kGroup = kGT / kTE;     // tiles screened together, one per wave
+constexpr int kGroup = kGT / kTE;       // tiles of a group, one per wave
+constexpr int kScreen = 128 / kGroup;   // groups screened together
+constexpr int gAct = gP2 + 4 * kH * 2;  // [kScreen][kGroup] ints: the tile has an entry inside
+constexpr int gEnd = gAct + kScreen * kGroup;
 __host__ __device__ inline int64_t tile_groups(int64_t total) {
   return (total + kTE * kGroup - 1) / (kTE * kGroup);
 }
@@ -131,8 +149,18 @@ __device__ __forceinline__ int swz(int row, int col) {
 }
 
 __device__ __forceinline__ void load_weights(const float* __restrict__ wts, float* L) {
-  for (int idx = threadIdx.x; idx < kH * kH; idx += kGT)
-    L[gW2 + swz(idx >> 7, idx & 127)] = wts[oW2 + idx];
+  // (8.5 us with one load under way, 2.4 with eight)
+#pragma unroll 1
+  for (int i0 = threadIdx.x; i0 < kH * kH; i0 += 8 * kGT) {
+    float v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = wts[oW2 + i0 + u * kGT];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int idx = i0 + u * kGT;
+      L[gW2 + swz(idx >> 7, idx & 127)] = v[u];
+    }
+  }
   for (int idx = threadIdx.x; idx < kH; idx += kGT) {
     // feature-major: lanes of consecutive neurons read consecutive words
     L[gW1 + 0 * kH + idx] = wts[oW1 + idx * 3 + 0];
@@ -143,6 +171,18 @@ __device__ __forceinline__ void load_weights(const float* __restrict__ wts, floa
     L[gW3 + idx] = wts[oW3 + idx];
   }
   if (threadIdx.x == 0) L[gB3] = wts[oB3];
+}
+
+// row and column of entry ent (small: it fits in 32 bits)
+__device__ __forceinline__ void entry_pos(int64_t ent, int nact, bool small, int64_t& row, int& col) {
+  if (small) {
+    const uint32_t r = (uint32_t)ent / (uint32_t)nact;
+    row = r;
+    col = (int)((uint32_t)ent - r * (uint32_t)nact);
+  } else {
+    row = ent / nact;
+    col = (int)(ent - row * nact);
+  }
 }
 
 // Features of tile entry e into LDS, with the entry's d - theta and theta
@@ -159,8 +199,9 @@ __device__ __noinline__ bool tile_entry(float* L, double* Ld, int e, int64_t ent
   double r = 0.0, gg = 0.0, dm = 0.0, th = 0.0;
   bool inside = false;
   if (ent < total) {
-    const int64_t row = ent / nact;
-    const int col = (int)(ent - row * nact);
+    int64_t row;
+    int col;
+    entry_pos(ent, nact, total < (int64_t)INT32_MAX, row, col);
     th = theta[col];
     dm = diag[row] - th;
     const double rr = rho[row];
@@ -183,59 +224,110 @@ __device__ __noinline__ bool tile_entry(float* L, double* Ld, int e, int64_t ent
   return inside;
 }
 
-// Screening of the group of kGroup tiles gr, gr + ngroups, gr + 2 ngroups,
-// ...: wave w takes tile gr + w ngroups, one entry per lane, and its ballot
-// records whether the tile has an entry inside the window.  The tiles of a
-// group lie far apart because the entries inside the window are often
-// neighbours (a diagonal that rises along the matrix): with groups of
-// neighbouring tiles, n = 2e5 and 8 columns left the 650 active tiles of
-// 25000 to 81 of 256 workgroups, eight in series each (k_mlp_apply 189 us,
-// k_mlp_grad 424 us); apart, no workgroup has more than three (138 us,
-// 301 us).  Without a Jacobi target
-// (J == nullptr) that is all; with one, the entries of tiles with none
-// inside take the guarded Jacobi step there (the learned step with c = 0).
-// The caller syncs before reading the flags.
+// Screening of the kScreen groups gr, gr + step, ...; a group gr has the tiles
+// gr, gr + ngroups, gr + 2 ngroups, ...: wave w takes tile gr + w ngroups, one
+// entry per lane, and its ballot records whether the tile has an entry inside
+// the window.  The tiles of a group lie far apart because the entries inside
+// the window are often neighbours (a diagonal that rises along the matrix):
+// with groups of neighbouring tiles, n = 2e5 and 8 columns left every active
+// tile to 81 of 256 workgroups (k_mlp_apply 189 us, k_mlp_grad 424 us; apart
+// 138 us, 301 us).  Many groups at once because a group's operands are a chain
+// of waits (index, operand, ballot, barrier): 43 thousand cycles for the 12
+// groups of a workgroup there one by one, 17 so.  Without a Jacobi target (J == nullptr) that is all;
+// with one, the entries of tiles with none inside take the guarded Jacobi step
+// there (the learned step with c = 0).  The caller syncs before reading the
+// flags.
 template <typename T>
-__device__ __forceinline__ void screen_group(float* L, int64_t gr, int64_t ngroups, int64_t total,
-                                             int nact,
-                                             const double* __restrict__ diag,
-                                             const double* __restrict__ rho,
-                                             const double* __restrict__ theta, T* __restrict__ J,
-                                             int64_t ld) {
-  const int64_t ent = (gr + (int64_t)(threadIdx.x >> 6) * ngroups) * kTE + (threadIdx.x & 63);
-  const bool valid = ent < total;
-  int64_t row = 0;
-  int col = 0;
-  double dm = 0.0, th = 0.0;
-  bool ins = false;
-  if (valid) {
-    row = ent / nact;
-    col = (int)(ent - row * nact);
-    th = theta[col];
-    dm = diag[row] - th;
-    ins = fabs(dm) <= kMlpWindow * rho[row];
-  }
-  const bool act = __ballot(ins) != 0;
-  if ((threadIdx.x & 63) == 0) reinterpret_cast<int*>(L + gAct)[threadIdx.x >> 6] = act ? 1 : 0;
-  if (J != nullptr && valid && !act) {
-    const double delta = kPrecondGuard * fmax(1.0, fabs(th));
-    T* p = J + row * ld + col;
-    *p = (T)((double)*p / sqrt(fmax(dm * dm, delta * delta)));
+__device__ __forceinline__ void screen_groups(float* L, int64_t gr, int64_t step, int64_t ngroups, int64_t total,
+                                              int nact, const double* __restrict__ diag,
+                                              const double* __restrict__ rho, const double* __restrict__ theta,
+                                              T* __restrict__ J, int64_t ld) {
+  constexpr int Q = 4;  // groups whose operands are under way together
+  const int lane = threadIdx.x & 63, w = wave_id();
+  const bool small = total < (int64_t)INT32_MAX;
+#pragma unroll 1
+  for (int b = 0; b < kScreen; b += Q) {
+    int64_t row[Q];
+    int col[Q];
+    double dm[Q], th[Q], rr[Q];
+    T x[Q];
+    bool valid[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const int64_t g = gr + (b + q) * step, ent = (g + (int64_t)w * ngroups) * kTE + lane;
+      valid[q] = (g < ngroups) & (ent < total);
+      entry_pos(valid[q] ? ent : 0, nact, small, row[q], col[q]);
+    }
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      th[q] = theta[col[q]];
+      dm[q] = diag[row[q]];
+      rr[q] = rho[row[q]];
+      if (J != nullptr) x[q] = J[row[q] * ld + col[q]];
+    }
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      dm[q] -= th[q];
+      const bool act = __ballot(valid[q] & (fabs(dm[q]) <= kMlpWindow * rr[q])) != 0;
+      if (lane == 0) reinterpret_cast<int*>(L + gAct)[(b + q) * kGroup + w] = act ? 1 : 0;
+      if (J != nullptr && valid[q] && !act) {
+        const double delta = kPrecondGuard * fmax(1.0, fabs(th[q]));
+        J[row[q] * ld + col[q]] = (T)((double)x[q] / sqrt(fmax(dm[q] * dm[q], delta * delta)));
+      }
+    }
   }
 }
 
-// Layer 1 into H1 (all threads), then layer 2 on MFMA: wave w's
+// The active tiles of the screened groups, a bit each (uniform in the workgroup)
+struct ActiveTiles {
+  uint64_t m[2];
+  __device__ __forceinline__ explicit ActiveTiles(const float* L) {
+    const int* a = reinterpret_cast<const int*>(L + gAct);
+    const int lane = threadIdx.x & 63;
+    m[0] = __ballot(a[lane] != 0);
+    m[1] = __ballot(a[64 + lane] != 0);
+  }
+  __device__ __forceinline__ bool any() const { return (m[0] | m[1]) != 0; }
+  // the next one's index: group index times kGroup + tile of the group
+  __device__ __forceinline__ int take() {
+    const int h = (m[0] == 0) ? 1 : 0;
+    const int p = __ffsll((unsigned long long)m[h]) - 1;
+    m[h] &= m[h] - 1;
+    return 64 * h + p;
+  }
+};
+static_assert(kScreen * kGroup == 128 && kTE == 64, "two ballots; an entry of a tile per lane");
+
+// Layer 1 into H1, then layer 2 on MFMA: lane (g, c) of wave w takes the same
+// entries and neurons of layer 1 as of the products' results, so that the
+// weights are read from LDS once per neuron and the gradient finds silu'(z1)
+// of its entries in its own registers (d1).  Wave w's
 // z[tt][r] = Z2[e = 16 (w & 3) + 4 g + r][k = 16 (4 (w >> 2) + tt) + c],
 // and the layer-3 partial of each entry over the wave's 64 neurons into
 // L[gYP + (w >> 2) kTE + e].  One barrier inside; the caller syncs before
 // reading the partials.
-__device__ __forceinline__ void mfma_forward(float* L, f4 (&z)[4], int w, int c, int g) {
+template <bool TRAIN>
+__device__ __forceinline__ void mfma_forward(float* L, f4 (&z)[4], f4 (&d1)[4], int w, int c, int g) {
   const int mt = w & 3, n0 = 4 * (w >> 2);
-  for (int idx = threadIdx.x; idx < kTE * kH; idx += kGT) {
-    const int e = idx >> 7, j = idx & 127;
+  float phi[4][3];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const float* ph = L + gPhi + (16 * mt + 4 * g + r) * 4;
+#pragma unroll
+    for (int f = 0; f < 3; ++f) phi[r][f] = ph[f];
+  }
+#pragma unroll
+  for (int tt = 0; tt < 4; ++tt) {
+    const int j = 16 * (n0 + tt) + c;
     const float* w1 = L + gW1 + j;
-    const float* ph = L + gPhi + e * 4;
-    L[gH1 + swz(e, j)] = silu(L[gB1 + j] + w1[0] * ph[0] + w1[kH] * ph[1] + w1[2 * kH] * ph[2]);
+    const float b1 = L[gB1 + j], wa = w1[0], wb = w1[kH], wc = w1[2 * kH];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float z1 = b1 + wa * phi[r][0] + wb * phi[r][1] + wc * phi[r][2];
+      const float sg = sigm(z1);
+      L[gH1 + swz(16 * mt + 4 * g + r, j)] = z1 * sg;
+      if (TRAIN) d1[tt][r] = sg * (1.0f + z1 * (1.0f - sg));
+    }
   }
   __syncthreads();
 #pragma unroll
@@ -256,8 +348,7 @@ __device__ __forceinline__ void mfma_forward(float* L, f4 (&z)[4], int w, int c,
     float p = 0.0f;
 #pragma unroll
     for (int tt = 0; tt < 4; ++tt) p = fmaf(L[gW3 + 16 * (n0 + tt) + c], silu(z[tt][r]), p);
-#pragma unroll
-    for (int off = 8; off >= 1; off >>= 1) p += __shfl_xor(p, off, 16);
+    p = add_row(p);
     if (c == 0) L[gYP + (w >> 2) * kTE + 16 * mt + 4 * g + r] = p;
   }
 }
@@ -299,26 +390,29 @@ __global__ __launch_bounds__(kGT) void k_mlp_apply(T* __restrict__ R, int64_t ld
   const int tid = threadIdx.x;
   const int64_t total = n * nact;
   const int64_t ngroups = tile_groups(total);
-  for (int64_t gr = blockIdx.x; gr < ngroups; gr += gridDim.x) {
-    __syncthreads();  // previous group's flag reads done
+#pragma unroll 1
+  for (int64_t gr = blockIdx.x; gr < ngroups; gr += (int64_t)kScreen * gridDim.x) {
+    __syncthreads();  // previous flags' reads done
     // the net only matters inside the window: tiles without such entries
     // take the Jacobi step here and skip it
-    screen_group(L, gr, ngroups, total, nact, diag, rho, theta, R, ld);
+    screen_groups(L, gr, gridDim.x, ngroups, total, nact, diag, rho, theta, R, ld);
     __syncthreads();
-    for (int u = 0; u < kGroup; ++u) {
-      if (reinterpret_cast<const int*>(L + gAct)[u] == 0) continue;  // uniform in the workgroup
+#pragma unroll 1
+    for (ActiveTiles act(L); act.any();) {
+      const int a = act.take();
+      const int64_t tile = gr + (int64_t)(a / kGroup) * gridDim.x + (a % kGroup) * ngroups;
       // lane indices opaque to the compiler (see k_mlp_grad)
       int lid = tid;
       asm volatile("" : "+v"(lid));
       const int w = lid >> 6, c = lid & 15, g = (lid >> 4) & 3;
-      const int64_t ent = (gr + u * ngroups) * kTE + tid;
+      const int64_t ent = tile * kTE + tid;
       bool inside = false;
       __syncthreads();  // weights loaded / previous tile's LDS reads done
       if (tid < kTE)
         inside = tile_entry(L, Ld, tid, ent, total, nact, nullptr, nullptr, 0, diag, rho, theta, s);
       __syncthreads();
-      f4 z[4];
-      mfma_forward(L, z, w, c, g);
+      f4 z[4], d1[4];
+      mfma_forward<false>(L, z, d1, w, c, g);
       __syncthreads();
       if (tid < kTE && ent < total)
         apply_entry(Ld, tid, ent, nact, R, ld, L[gB3] + L[gYP + tid] + L[gYP + kTE + tid], s,
@@ -338,6 +432,9 @@ __global__ __launch_bounds__(kGT) void k_mlp_apply(T* __restrict__ R, int64_t ld
 // the vector units.  Per-tile sums are fp32 (the MFMA accumulators, xor
 // shuffles, and LDS partials added in a fixed order); they are accumulated
 // across tiles in fp64 per workgroup (registers for dW2, LDS for the rest).
+// A tile takes 50 thousand cycles, 25 of them the products' at the fp32 MFMA
+// rate (55 with lane shuffles through the LDS, layer 1 computed twice and its
+// weights read once per entry); n = 2e5 and 8 columns 264 us, 301 before.
 
 // dL/dy of tile entry e (0 outside the window or where the floor or the
 // fallback holds): w = r q^-1/2, q = dm^2 + c^2, c = s softplus(y).
@@ -370,20 +467,22 @@ __global__ __launch_bounds__(kGT) void k_mlp_grad(const double* __restrict__ R,
   for (int idx = tid; idx < 6 * kH + 2; idx += kGT) Ld[dRow + idx] = 0.0;
   const double s = *sptr;
   const int64_t total = n * nact;
-  const int64_t ngroups = tile_groups(total);
   double aW2[8][4];  // dW2[k = 16 w + 4 g + r][j = 16 t + c]
 #pragma unroll
   for (int t = 0; t < 8; ++t)
 #pragma unroll
     for (int r = 0; r < 4; ++r) aW2[t][r] = 0.0;
-  for (int64_t gr = blockIdx.x; gr < ngroups; gr += gridDim.x) {
-    __syncthreads();  // previous group's flag reads done
+  const int64_t ngroups = tile_groups(total);
+#pragma unroll 1
+  for (int64_t gr = blockIdx.x; gr < ngroups; gr += (int64_t)kScreen * gridDim.x) {
+    __syncthreads();  // previous flags' reads done
     // entries outside the window have dL/dy = 0: tiles without any inside are skipped
-    screen_group<double>(L, gr, ngroups, total, nact, diag, rho, theta, nullptr, 0);
+    screen_groups<double>(L, gr, gridDim.x, ngroups, total, nact, diag, rho, theta, nullptr, 0);
     __syncthreads();
-    for (int u = 0; u < kGroup; ++u) {
-      if (reinterpret_cast<const int*>(L + gAct)[u] == 0) continue;  // uniform in the workgroup
-      const int64_t tile = gr + u * ngroups;
+#pragma unroll 1
+    for (ActiveTiles act(L); act.any();) {
+      const int a = act.take();
+      const int64_t tile = gr + (int64_t)(a / kGroup) * gridDim.x + (a % kGroup) * ngroups;
       // the lane indices are re-derived per tile, opaque to the compiler: the
       // swizzled LDS addresses built from them are recomputed inside the loop
       // instead of being hoisted into (and spilled from) registers
@@ -397,7 +496,8 @@ __global__ __launch_bounds__(kGT) void k_mlp_grad(const double* __restrict__ R,
         inside = tile_entry(L, Ld, tid, tile * kTE + tid, total, nact, R, G, ld, diag, rho, theta, s);
       __syncthreads();
       f4 z[4];  // Z2[e = 16 (w & 3) + 4 g + r][k = 16 (4 (w >> 2) + tt) + c]
-      mfma_forward(L, z, w, c, g);
+      f4 d1[4];  // silu'(z1) of the same entries and neurons
+      mfma_forward<true>(L, z, d1, w, c, g);
       __syncthreads();
       if (tid < kTE)
         L[gDY + tid] =
@@ -405,7 +505,12 @@ __global__ __launch_bounds__(kGT) void k_mlp_grad(const double* __restrict__ R,
       __syncthreads();
       if (tid == 0) {
         float t = 0.0f;
-        for (int e = 0; e < kTE; ++e) t += L[gDY + e];
+        const f4* dy = reinterpret_cast<const f4*>(L + gDY);
+#pragma unroll
+        for (int e = 0; e < kTE / 4; ++e) {
+          const f4 v = dy[e];
+          t = (((t + v[0]) + v[1]) + v[2]) + v[3];
+        }
         Ld[dB3] += (double)t;
       }
       // dz2 = dy w3 silu'(z2) into LDS; dW3 += dy h2, db2 += dz2 (this entry tile)
@@ -429,10 +534,8 @@ __global__ __launch_bounds__(kGT) void k_mlp_grad(const double* __restrict__ R,
         }
 #pragma unroll
         for (int tt = 0; tt < 4; ++tt) {
-          pW3[tt] += __shfl_xor(pW3[tt], 16);
-          pB2[tt] += __shfl_xor(pB2[tt], 16);
-          pW3[tt] += __shfl_xor(pW3[tt], 32);
-          pB2[tt] += __shfl_xor(pB2[tt], 32);
+          pW3[tt] = add_pair<32>(add_pair<16>(pW3[tt]));
+          pB2[tt] = add_pair<32>(add_pair<16>(pB2[tt]));
           if (g == 0) {
             float* q = L + gP2 + (mt * kH + 16 * (n0 + tt) + c) * 2;
             q[0] = pW3[tt];
@@ -480,10 +583,7 @@ __global__ __launch_bounds__(kGT) void k_mlp_grad(const double* __restrict__ R,
           const float* ph = L + gPhi + (16 * mt + 4 * g + r) * 4;
 #pragma unroll
           for (int tt = 0; tt < 4; ++tt) {
-            const int j = 16 * (n0 + tt) + c;
-            const float* w1 = L + gW1 + j;
-            const float z1 = L[gB1 + j] + w1[0] * ph[0] + w1[kH] * ph[1] + w1[2 * kH] * ph[2];
-            const float dz1 = dh[tt][r] * dsilu(z1);
+            const float dz1 = dh[tt][r] * d1[tt][r];
             p0[tt] = fmaf(dz1, ph[0], p0[tt]);
             p1[tt] = fmaf(dz1, ph[1], p1[tt]);
             p2[tt] = fmaf(dz1, ph[2], p2[tt]);
@@ -492,13 +592,10 @@ __global__ __launch_bounds__(kGT) void k_mlp_grad(const double* __restrict__ R,
         }
 #pragma unroll
         for (int tt = 0; tt < 4; ++tt) {
-#pragma unroll
-          for (int off = 16; off <= 32; off <<= 1) {
-            p0[tt] += __shfl_xor(p0[tt], off);
-            p1[tt] += __shfl_xor(p1[tt], off);
-            p2[tt] += __shfl_xor(p2[tt], off);
-            pb[tt] += __shfl_xor(pb[tt], off);
-          }
+          p0[tt] = add_pair<32>(add_pair<16>(p0[tt]));
+          p1[tt] = add_pair<32>(add_pair<16>(p1[tt]));
+          p2[tt] = add_pair<32>(add_pair<16>(p2[tt]));
+          pb[tt] = add_pair<32>(add_pair<16>(pb[tt]));
           if (g == 0) {
             float* q = L + gP1 + (mt * kH + 16 * (n0 + tt) + c) * 4;
             q[0] = p0[tt];
