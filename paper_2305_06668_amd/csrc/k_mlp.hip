@@ -750,8 +750,21 @@ __global__ __launch_bounds__(256, 2) void k_mlp_apply_bf16(T* __restrict__ R, in
   const int g = lane >> 4, r = lane & 15;
   for (int k = threadIdx.x; k < kH; k += blockDim.x)
     w1s[k] = make_float4(wts[oW1 + 3 * k], wts[oW1 + 3 * k + 1], wts[oW1 + 3 * k + 2], wts[oB1 + k]);
-  for (int idx = threadIdx.x; idx < kH * kH; idx += blockDim.x)
-    w2s[(idx / kH) * kBS + (idx % kH)] = (__bf16)wts[oW2 + idx];
+  // Half of a launch was this fill with one load under way at a time: n = 2e5
+  // and 12 columns 36 us (launches of a solve), 16 so.
+  constexpr int kWU = 16;
+#pragma unroll 1
+  for (int i0 = threadIdx.x; i0 < kH * kH; i0 += kWU * 256) {
+    float v[kWU];
+#pragma unroll
+    for (int u = 0; u < kWU; ++u) v[u] = wts[oW2 + i0 + u * 256];
+#pragma unroll
+    for (int u = 0; u < kWU; ++u) {
+      const int idx = i0 + u * 256;
+      w2s[(idx / kH) * kBS + (idx % kH)] = (__bf16)v[u];
+    }
+  }
+  static_assert(kH * kH % (kWU * 256) == 0, "whole batches of the 256 threads");
   float b2r[8], w3r[8];
 #pragma unroll
   for (int nt = 0; nt < 8; ++nt) {
@@ -773,7 +786,8 @@ __global__ __launch_bounds__(256, 2) void k_mlp_apply_bf16(T* __restrict__ R, in
   // in order.  Neighbouring tiles go to different waves because flagged super
   // tiles are often neighbours too: at n = 2e5 with 12 columns a whole super
   // tile per wave left 250 of 2048 waves with all the work, eight tiles in
-  // series (50 us; one tile at a time 32 us).
+  // series (50 us; one tile at a time 32 us, both with the slower fill of the
+  // weights).
   const int64_t gw = (int64_t)blockIdx.x * 4 + wave, nw = (int64_t)gridDim.x * 4;
   for (int64_t jb = 0; gw + jb * nw < nwt; jb += 64) {
     const int64_t mine = gw + (jb + lane) * nw;
@@ -793,8 +807,7 @@ __global__ __launch_bounds__(256, 2) void k_mlp_apply_bf16(T* __restrict__ R, in
         int col = 0;
         double th = 0.0, dmd = 0.0, rr = 0.0;
         if (valid) {
-          row = ent / nact;
-          col = (int)(ent - row * nact);
+          entry_pos(ent, nact, total < (int64_t)INT32_MAX, row, col);
           th = theta[col];
           dmd = diag[row] - th;
           rr = rho[row];
@@ -858,9 +871,7 @@ __global__ __launch_bounds__(256, 2) void k_mlp_apply_bf16(T* __restrict__ R, in
               for (int i = 0; i < 4; ++i)
                 y[t][i] = fmaf(w3r[nt], silu_fast(acc[t][nt][i] + b2r[nt]), y[t][i]);
     #pragma unroll
-            for (int i = 0; i < 4; ++i)
-    #pragma unroll
-              for (int off = 8; off >= 1; off >>= 1) y[t][i] += __shfl_xor(y[t][i], off, 16);
+            for (int i = 0; i < 4; ++i) y[t][i] = add_row(y[t][i]);
           }
           // entry L's y sits in segment (L % 16) / 4, slot (t = L / 16, i = L % 4)
           const int src = 16 * ((lane & 15) >> 2);
