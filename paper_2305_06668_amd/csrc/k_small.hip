@@ -464,11 +464,6 @@ __device__ __forceinline__ EigLds eig_lds(double* smem, int p, int m) {
   L.flags = L.perm + 128;         // 8
   return L;
 }
-static size_t eig_lds_bytes(int p, int m) {
-  return sizeof(double) * (size_t)(p * (p + 1) + eig_area2(p, m) + 3 * 64 + 16) +
-         sizeof(int) * (2 * 64 + 128 + 8);
-}
-
 __device__ __forceinline__ void load_sym(const double* a, int p, double* A, int lda) {
   for (int idx = threadIdx.x; idx < p * p; idx += blockDim.x) {
     const int i = idx / p, j = idx - i * p;

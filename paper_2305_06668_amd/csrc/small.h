@@ -104,20 +104,8 @@ __device__ __forceinline__ double wave_max(double v) {
 // ---------------------------------------------------------------------------
 // block-wide helpers (every thread of the block calls them)
 
-__device__ __forceinline__ double blk_reduce_max(double v, double* scratch) {
-  // scratch: blockDim.x / 64 doubles
-  for (int off = 32; off >= 1; off >>= 1) v = fmax(v, __shfl_xor(v, off));
-  const int w = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) scratch[w] = v;
-  __syncthreads();
-  double r = scratch[0];
-  for (int i = 1; i < nw; ++i) r = fmax(r, scratch[i]);
-  __syncthreads();
-  return r;
-}
-
 __device__ __forceinline__ double blk_reduce_sum_ordered(double v, double* scratch) {
+  // scratch: blockDim.x / 64 doubles
   // deterministic: each wave reduces by a fixed xor tree, waves in order
   for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off);
   const int w = threadIdx.x >> 6, nw = blockDim.x >> 6;
