@@ -49,11 +49,16 @@ struct Seam {
   double a0, al, ar, b0, bl, br;
 };
 
-// 1 / q to 1 ulp: the hardware estimate and two Newton steps
+// 1 / q (q > 0) to 1 ulp: the hardware estimate and two Newton steps; 0 for an
+// infinite pivot, as a division gives it: a row whose diagonal entry is infinite
+// is frozen at 0 and its neighbours do not couple through it.  (There the
+// estimate is 0 and stays so, as the steps' q is finite, which costs nothing
+// beside the estimate; a fix-up behind the steps is 1 % of the whole solve.)
 __device__ __forceinline__ double rcp2(double q) {
   double r = __builtin_amdgcn_rcp(q);
-  r = fma(r, fma(-q, r, 1.0), r);
-  return fma(r, fma(-q, r, 1.0), r);
+  const double f = fmin(q, 0x1.fffffffffffffp+1023);
+  r = fma(r, fma(-f, r, 1.0), r);
+  return fma(r, fma(-f, r, 1.0), r);
 }
 
 // A, B: neighbouring runs; returns the interface of both

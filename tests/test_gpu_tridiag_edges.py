@@ -78,3 +78,56 @@ def test_tridiag_apply_edges(P, n, m, ld):
         err = np.abs(W[:, j] - Wo[:, j]).max() / np.abs(Wo[:, j]).max()
         assert err <= 1e-13 * max(kap, 10.0), (j, err, kap)
     s.close()
+
+
+@pytest.mark.parametrize("where", ["inside", "ends", "seams", "alternate", "run"])
+@pytest.mark.parametrize("n,m", [(40, 3), (1025, 4), (5003, 16), (262145, 8)])
+def test_tridiag_apply_frozen_rows(P, n, m, where):
+    """Infinite entries of a diagonal that the caller gives, and an infinite
+    theta: w is 0 in these rows (in the whole column), and the rows beside
+    them are solved without the coupling.  Tolerance as above."""
+    from scipy.linalg import solve_banded
+
+    print("tridiag frozen rows", n, m, where, flush=True)
+    g = synth.rng(3 * n + m)
+    e = g.uniform(-0.5, 0.5, n - 1)
+    d = 1.0 + g.uniform(0.0, 2.0, n)
+    frozen = {
+        "inside": np.array([n // 3]),
+        "ends": np.array([0, n - 1]),
+        "seams": np.arange(15, n, 16),  # last rows of chunks, of groups
+        "alternate": np.arange(1, n, 2),
+        "run": np.arange(n // 4, n // 2),
+    }[where]
+    theta = np.sort(g.uniform(0.5, 1.5, m))
+    theta[-1] = np.inf
+    rp, ci, val = tridiag_csr(d, e)
+    du = d.copy()
+    du[frozen] = np.where(np.arange(frozen.size) % 2 == 0, np.inf, -np.inf)
+    dd = torch.from_numpy(du).cuda()
+    s = P.Solver(n)
+    s.set_operator_csr(torch.from_numpy(rp).cuda(), torch.from_numpy(ci).cuda(), torch.from_numpy(val).cuda())
+    s.set_preconditioner(P.PRECOND_TRIDIAG, dd)
+    s.ensure_workspace(m)
+    R = g.standard_normal((n, m))
+    Rd = torch.from_numpy(R).cuda()
+    P.lobpcg_tridiag_apply(s.h, Rd, torch.from_numpy(theta).cuda())
+    W = Rd.cpu().numpy()
+    off = np.zeros(n)
+    off[:-1] += np.abs(e)
+    off[1:] += np.abs(e)
+    for j in range(m - 1):
+        t = np.maximum(np.abs(d - theta[j]), off + O.PRECOND_GUARD * max(1.0, abs(theta[j])))
+        kap = float((t + off).max() / (t - off).min())
+        band = np.zeros((3, n))
+        band[0, 1:], band[1], band[2, :-1], r = e, t, e, R[:, j].copy()
+        band[1, frozen], r[frozen] = 1.0, 0.0
+        for b, k in ((0, 0), (0, 1), (2, 0), (2, -1)):  # the couplings of row i: band[0, i], [0, i + 1], [2, i], [2, i - 1]
+            at = frozen + k
+            band[b, at[(at >= 0) & (at < n)]] = 0.0
+        ref = solve_banded((1, 1), band, r)
+        assert np.all(W[frozen, j] == 0.0), (j, W[frozen, j])
+        err = np.abs(W[:, j] - ref).max() / np.abs(ref).max()
+        assert err <= 1e-13 * max(kap, 10.0), (j, err, kap)
+    assert np.all(W[:, -1] == 0.0)
+    s.close()
