@@ -2,16 +2,18 @@
 // operator).  The (col, val) stream is read from HBM once; every stored entry
 // then needs one row of W (ncols * s contiguous bytes), gathered through L2.
 // For the banded workloads the W window stays in L2 (hit rate ~90 %, HBM
-// traffic within 1 % of the algorithmic bytes).  Two kernels:
-//   * k_spmm_rows (2 fp64 / 4 fp32 columns per lane, 16-byte loads; each wave
-//     stages its rows' (col, val) range in LDS): the fewest instructions and
-//     wave slots per gathered row, used from 5 (fp64) or 9 (fp32) columns;
+// traffic within 1 % of the algorithmic bytes).  Three kernels:
+//   * k_spmm_block and k_spmm_rows (2 fp64 / 4 fp32 columns per lane, 16-byte
+//     loads; a workgroup, or each wave for itself, stages its rows' (col, val)
+//     range in LDS): the fewest instructions and wave slots per gathered row,
+//     used from 5 (fp64) or 9 (fp32) columns;
 //   * k_spmm_csr (one column per lane, (col, val) broadcast by shuffles):
 //     narrow blocks.
 // Row blocks are remapped so that each XCD (hardware dispatches block b to
 // XCD b % 8) walks one contiguous range of rows: a banded matrix then keeps
 // its W window inside that XCD's L2.
 #include <algorithm>
+#include <type_traits>
 
 #include "internal.h"
 
@@ -137,56 +139,151 @@ template <typename TW> struct Entry;
 template <> struct alignas(16) Entry<double> { uint32_t at; uint32_t pad; double v; };
 template <> struct alignas(8) Entry<float> { uint32_t at; float v; };
 
-// A wave takes 64 / G rows at once, G lanes to a row; lane l holds columns
-// c .. c + CPL - 1, c = min(l CPL, ncols - CPL) (the last lanes may repeat
-// columns, so that every load is whole), and gathers them with one 16-byte
-// load per stored entry.  The rows are consecutive, so their stored entries
-// form one range: a wave copies it to its own part of LDS (coalesced,
-// non-temporal) as entries of W offset and value, and each row's lanes read
-// theirs from there.  Everything is private to the wave (no barrier), waves
-// walk on through their XCD's rows, and while a wave gathers for one group
-// of rows its loads of the next group's entries and of the row pointers
-// after that are in flight.  A group whose entries do not fit (rows much
-// longer than kRowCap on average) is taken kRowCap entries of each row at a
-// time.  Entries are accumulated in CSR order, four gathers in flight per
-// lane.
+// Sum of m staged entries times their W rows, added to acc in order, four
+// gathers in flight; only what is stored is gathered or multiplied.
+template <int CPL, typename TW, typename VT, class Gather>
+__device__ __forceinline__ void add_entries(const Entry<TW>* x, int m, VT& acc, Gather&& gather) {
+  constexpr int UN = 4;
+  int t = 0;
+  for (; t + UN <= m; t += UN) {
+    VT w[UN];
+    TW v[UN];
+#pragma unroll
+    for (int u = 0; u < UN; ++u) {
+      const Entry<TW> en = x[t + u];
+      v[u] = en.v;
+      w[u] = gather(en);
+    }
+#pragma unroll
+    for (int u = 0; u < UN; ++u)
+#pragma unroll
+      for (int q = 0; q < CPL; ++q) acc[q] += v[u] * w[u][q];
+  }
+  if (t < m) {
+    VT w[UN - 1];
+    TW v[UN - 1];
+#pragma unroll
+    for (int u = 0; u < UN - 1; ++u) {
+#pragma unroll
+      for (int q = 0; q < CPL; ++q) w[u][q] = TW(0);
+      v[u] = TW(0);
+      if (t + u < m) {
+        const Entry<TW> en = x[t + u];
+        v[u] = en.v;
+        w[u] = gather(en);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < UN - 1; ++u)
+      if (t + u < m) {
+#pragma unroll
+        for (int q = 0; q < CPL; ++q) acc[q] += v[u] * w[u][q];
+      }
+  }
+}
+template <bool NT, typename T>
+__device__ __forceinline__ T stream_load(const T* p) {
+  return NT ? __builtin_nontemporal_load(p) : *p;
+}
+
+// In both kernels G lanes take a row; lane l of them holds columns c .. c +
+// CPL - 1, c = min(l CPL, ncols - CPL) (the last lanes may repeat columns, so
+// that every load is whole), and gathers them with one 16-byte load per stored
+// entry.  Entries are accumulated in CSR order.
 // BIG: W spans 4 GB or more, LDS holds the column and the address is formed in
 // 64 bits; else it holds the byte offset, added to a scalar base by the load.
-// A matrix of up to kCachedBytes is read through the caches, so that the next
-// product finds it in the memory-side one (256 MB); a larger one would only
-// evict W and itself, and is read with the non-temporal hint (n = 3e5, fp32
-// of 98 MB: 64 against 80 us; n = 1e6, fp64 of 492 MB: 373 against 350 us).
-// What bounds it: a 16-byte load of 64 lanes takes the L1 16 cycles, hit or
+// NT: the matrix is read with the non-temporal hint (see spmm_stream_launch).
+// What bounds them: a 16-byte load of 64 lanes takes the L1 16 cycles, hit or
 // not, so every gather that is issued for a lane group whose row has ended is
 // lost (rows of 41 +- 4.5 entries, eight to a wave: 55 issued with eight in
 // flight, 49 with four), and loads return in order, so the gathers behind a
 // fetch of entries wait for HBM.  Gathers alone take 160 us for the n = 1e6,
-// 41 entries per row, 16-column product, the entries alone 125 us, both
-// together without rows or sums 230 to 270 us; the product takes 345 to 355
-// (380 with the block's entries staged between barriers, two LDS reads, two
-// selects and a 64-bit address per gather, 256 threads a row block).  Rows
-// one after the other without a common end (fewer gathers, more work per
-// entry) took 415 to 480 us, larger fetches with fewer waves 420 us.
-constexpr int kRowCap = 48;  // entries per row that a wave's LDS holds
+// 41 entries per row, 16-column fp64 product, the entries alone 125 us, both
+// together without rows or sums 230 to 270 us; the product takes 355.
+
+// k_spmm_block: a workgroup takes 256 / G consecutive rows and copies their
+// range of entries to LDS (coalesced), kBlockLds bytes at a time, between
+// barriers; nothing is in flight across them, but eight workgroups share a CU
+// (with 32 KB four to five do: n = 1e6, 3 to 50 fp64 entries per row 93 to 360
+// us, so 66 to 343).
+constexpr int kBlockLds = 16 * 1024;
+template <typename TV, typename TW, int G, int CPL, bool BIG, bool NT>
+__global__ __launch_bounds__(256) void k_spmm_block(const int32_t* __restrict__ rp,
+                                                    const int32_t* __restrict__ ci,
+                                                    const TV* __restrict__ val,
+                                                    const TW* __restrict__ W, int64_t ldw,
+                                                    TW* __restrict__ Y, int64_t ldy, int ncols,
+                                                    int64_t n, int per_xcd) {
+  typedef typename Vec16<TW, CPL>::type VT;
+  constexpr int RPB = 256 / G;
+  constexpr unsigned CAP = kBlockLds / sizeof(Entry<TW>);
+  __shared__ Entry<TW> E[CAP];
+  const int b = blockIdx.x;
+  const int lb = (b & 7) * per_xcd + (b >> 3);
+  const int64_t r0 = (int64_t)lb * RPB;
+  if (r0 >= n) return;  // whole block
+  const int l = threadIdx.x % G;
+  const int64_t row = r0 + threadIdx.x / G;
+  const int c = min(l * CPL, ncols - CPL);
+  const uint32_t rowb = (uint32_t)(ldw * sizeof(TW)), cb = (uint32_t)(c * sizeof(TW));
+  const TW* Wc = W + c;
+  const int B0 = rp[r0];
+  const unsigned total = (unsigned)(rp[min(r0 + RPB, n)] - B0);
+  const unsigned e0 = (unsigned)(rp[min(row, n)] - B0), e1 = (unsigned)(rp[min(row + 1, n)] - B0);
+  auto gather = [&](const Entry<TW>& x) {
+    if (BIG) return *reinterpret_cast<const VT*>(Wc + (int64_t)x.at * ldw);
+    return *reinterpret_cast<const VT*>(reinterpret_cast<const char*>(W) + (x.at + cb));
+  };
+  VT acc;
+#pragma unroll
+  for (int q = 0; q < CPL; ++q) acc[q] = TW(0);
+  for (unsigned p = 0; p < total; p += CAP) {
+    const unsigned cnt = min(CAP, total - p);
+    const int32_t* cp = ci + B0 + (int64_t)p;
+    const TV* vp = val + B0 + (int64_t)p;
+    __syncthreads();  // the previous pass is consumed
+    for (unsigned i = threadIdx.x; i < cnt; i += 256) {
+      const uint32_t col = (uint32_t)stream_load<NT>(cp + i);
+      Entry<TW> x;
+      x.at = BIG ? col : col * rowb;
+      x.v = (TW)stream_load<NT>(vp + i);
+      E[i] = x;
+    }
+    __syncthreads();
+    const unsigned a = max(e0, p), z = min(e1, p + cnt);
+    if (a < z) add_entries<CPL>(E + (a - p), (int)(z - a), acc, gather);
+  }
+  if (row < n && l * CPL < ncols) *reinterpret_cast<VT*>(Y + row * ldy + c) = acc;
+}
+
+// k_spmm_rows: a wave takes 64 / G consecutive rows at a time and copies their
+// range of entries (coalesced) to its own part of LDS.  Everything is private
+// to the wave (no barrier), waves walk on through their XCD's rows, and while a
+// wave gathers for one group of rows its loads of the next group's entries and
+// of the row pointers after that are in flight.  The groups whose entries do not
+// fit (kRowCap per row on average) are passed over and taken by themselves after
+// every 64 groups, in passes of up to kRowPass entries of every row, each pass's
+// loads in flight during the one before it.  (With both kinds in one loop the
+// compiler waits for the loads of one where it goes on with the other: rows that
+// all fit took 3 to 15 % longer.)
+constexpr int kRowCap = 48, kRowPass = 44;
 constexpr int64_t kCachedBytes = 160ll << 20;
-template <typename TV, typename TW, int G, int CPL, bool BIG>
-__global__ __launch_bounds__(256) void k_spmm_rows(const int32_t* __restrict__ rp,
-                                                   const int32_t* __restrict__ ci,
-                                                   const TV* __restrict__ val,
-                                                   const TW* __restrict__ W, int64_t ldw,
-                                                   TW* __restrict__ Y, int64_t ldy, int ncols,
-                                                   int64_t n, int per_xcd) {
+constexpr int kRowsWaves(int G) { return G == 4 ? 3 : 4; }  // workgroups per CU: their registers and LDS
+template <typename TV, typename TW, int G, int CPL, bool BIG, bool NT>
+__global__ __launch_bounds__(256)
+void k_spmm_rows(const int32_t* __restrict__ rp, const int32_t* __restrict__ ci,
+                 const TV* __restrict__ val, const TW* __restrict__ W, int64_t ldw,
+                 TW* __restrict__ Y, int64_t ldy, int ncols, int64_t n, int per_xcd) {
   typedef typename Vec16<TW, CPL>::type VT;
   constexpr int NR = 64 / G;             // rows per wave and step
   constexpr int CAP = kRowCap * NR;      // entries in the wave's LDS
   constexpr int NL = CAP / 64;           // entries per lane and copy
-  constexpr int UN = 4;
+  constexpr int NQ = (kRowPass + G - 1) / G;  // ... and pass by rows
   __shared__ Entry<TW> lds[4][CAP];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   Entry<TW>* E = lds[wave];
   const int r = lane / G, l = lane % G;
   const int c = min(l * CPL, ncols - CPL);
-  const bool store = l * CPL < ncols;
   const uint32_t rowb = (uint32_t)(ldw * sizeof(TW)), cb = (uint32_t)(c * sizeof(TW));
   const TW* Wc = W + c;
   // this wave's groups of rows: first, first + step, ... below last
@@ -203,148 +300,207 @@ __global__ __launch_bounds__(256) void k_spmm_rows(const int32_t* __restrict__ r
   // the group's range of entries: the first row's start, the last row's end
   auto lo_of = [&](int e0) { return __builtin_amdgcn_readlane(e0, 0); };
   auto hi_of = [&](int e1) { return __builtin_amdgcn_readlane(e1, 63); };
-  int32_t pc[NL];
-  TV pv[NL];
-  const bool cached = (int64_t)rp[n] * (int)(sizeof(TV) + 4) <= kCachedBytes;
-  auto fetch = [&](int b0, int cnt) {
-    const int32_t* cp = ci + b0;
-    const TV* vp = val + b0;
-    if (cached) {
+  // entries first + stride k below cnt, counted from cp and vp, into registers
+  auto fetch = [&](auto& pc, auto& pv, const int32_t* cp, const TV* vp, int first, auto stride, int cnt) {
 #pragma unroll
-      for (int k = 0; k < NL; ++k) {
-        const int i = 64 * k + lane;
-        if (i < cnt) {
-          pc[k] = cp[i];
-          pv[k] = vp[i];
-        }
-      }
-    } else {
-#pragma unroll
-      for (int k = 0; k < NL; ++k) {
-        const int i = 64 * k + lane;
-        if (i < cnt) {
-          pc[k] = __builtin_nontemporal_load(cp + i);
-          pv[k] = __builtin_nontemporal_load(vp + i);
-        }
+    for (int k = 0; k < (int)(sizeof(pc) / sizeof(pc[0])); ++k) {
+      const int i = first + stride() * k;
+      if (i < cnt) {
+        pc[k] = stream_load<NT>(cp + i);
+        pv[k] = stream_load<NT>(vp + i);
       }
     }
   };
-  auto entry = [&](int32_t col, TV v) {
-    Entry<TW> x;
-    x.at = BIG ? (uint32_t)col : (uint32_t)col * rowb;
-    x.v = (TW)v;
-    return x;
+  // and from there to x
+  auto stage = [&](const auto& pc, const auto& pv, Entry<TW>* x, int first, auto stride, int cnt) {
+#pragma unroll
+    for (int k = 0; k < (int)(sizeof(pc) / sizeof(pc[0])); ++k) {
+      const int i = first + stride() * k;
+      if (i < cnt) {
+        Entry<TW> en;
+        en.at = BIG ? (uint32_t)pc[k] : (uint32_t)pc[k] * rowb;
+        en.v = (TW)pv[k];
+        x[i] = en;
+      }
+    }
   };
+  auto lds_ready = [&]() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  };
+  const std::integral_constant<int, 64> flat{};
+  const std::integral_constant<int, G> by_row{};
   auto gather = [&](const Entry<TW>& x) {
     if (BIG) return *reinterpret_cast<const VT*>(Wc + (int64_t)x.at * ldw);
     return *reinterpret_cast<const VT*>(reinterpret_cast<const char*>(W) + (x.at + cb));
   };
-  int e0, e1, f0, f1;  // row pointers of this group and the next
-  load_rp(first, e0, e1);
-  load_rp(first + step, f0, f1);
-  int b0 = lo_of(e0), b1 = hi_of(e1);
-  fetch(b0, min(b1 - b0, CAP));
-  for (int64_t g = first; g < last; g += step) {
-    VT acc;
+  auto zero = [&]() {
+    VT a;
 #pragma unroll
-    for (int q = 0; q < CPL; ++q) acc[q] = TW(0);
-    const bool fits = b1 - b0 <= CAP;
-    // (the previous group's gathers have returned: their LDS reads are done)
-    if (fits) {
-#pragma unroll
-      for (int k = 0; k < NL; ++k)
-        if (64 * k + lane < b1 - b0) E[64 * k + lane] = entry(pc[k], pv[k]);
-    }
-    // the next group's entries and the row pointers of the one after it
-    const int nb0 = lo_of(f0), nb1 = hi_of(f1);
-    if (g + step < last) fetch(nb0, min(nb1 - nb0, CAP));
-    int g0, g1;
-    load_rp(g + 2 * step, g0, g1);
-    auto rows = [&](const Entry<TW>* x, int m) {
-      int t = 0;
-      for (; t + UN <= m; t += UN) {
-        VT w[UN];
-        TW v[UN];
-#pragma unroll
-        for (int u = 0; u < UN; ++u) {
-          const Entry<TW> en = x[t + u];
-          v[u] = en.v;
-          w[u] = gather(en);
-        }
-#pragma unroll
-        for (int u = 0; u < UN; ++u)
-#pragma unroll
-          for (int q = 0; q < CPL; ++q) acc[q] += v[u] * w[u][q];
-      }
-      if (t < m) {
-        VT w[UN - 1];
-        TW v[UN - 1];
-#pragma unroll
-        for (int u = 0; u < UN - 1; ++u) {
-#pragma unroll
-          for (int q = 0; q < CPL; ++q) w[u][q] = TW(0);
-          v[u] = TW(0);
-          if (t + u < m) {
-            const Entry<TW> en = x[t + u];
-            v[u] = en.v;
-            w[u] = gather(en);
-          }
-        }
-#pragma unroll
-        for (int u = 0; u < UN - 1; ++u)
-          if (t + u < m) {
-#pragma unroll
-            for (int q = 0; q < CPL; ++q) acc[q] += v[u] * w[u][q];
-          }
-      }
-    };
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    if (fits) {
-      rows(E + (e0 - b0), e1 - e0);
-    } else {
-      // kRowCap entries of every row at a time
-      for (int p = 0; __ballot(p < e1 - e0) != 0; p += kRowCap) {
-        for (int k = l; k < kRowCap; k += G)
-          if (k < e1 - e0 - p) E[r * kRowCap + k] = entry(ci[e0 + p + k], val[e0 + p + k]);
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        rows(E + r * kRowCap, min(kRowCap, e1 - e0 - p));
-      }
-    }
+    for (int q = 0; q < CPL; ++q) a[q] = TW(0);
+    return a;
+  };
+  auto store = [&](int64_t g, const VT& acc) {
     const int64_t row = g * NR + r;
-    if (row < n && store) *reinterpret_cast<VT*>(Y + row * ldy + c) = acc;
-    e0 = f0;
-    e1 = f1;
-    f0 = g0;
-    f1 = g1;
-    b0 = nb0;
-    b1 = nb1;
+    if (row < n && l * CPL < ncols) *reinterpret_cast<VT*>(Y + row * ldy + c) = acc;
+  };
+  for (int64_t base = first; base < last; base += (int64_t)64 * step) {
+    const int64_t stop = min(last, base + (int64_t)64 * step);
+    uint64_t rest = 0;  // the groups that do not fit
+    int e0, e1, f0, f1;  // row pointers of this group and the next
+    {
+      load_rp(base, e0, e1);
+      load_rp(base + step, f0, f1);
+      int b0 = lo_of(e0), cnt = hi_of(e1) - b0;
+      int32_t pc[NL];
+      TV pv[NL];
+      if (cnt <= CAP) fetch(pc, pv, ci + b0, val + b0, lane, flat, cnt);
+      uint64_t bit = 1;
+      for (int64_t g = base; g < stop; g += step, bit <<= 1) {
+        const bool fits = cnt <= CAP;
+        // (the previous group's gathers have returned: their LDS reads are done)
+        if (fits) stage(pc, pv, E, lane, flat, cnt);
+        // the next group's entries and the row pointers of the one after it
+        const int nb0 = lo_of(f0), ncnt = hi_of(f1) - nb0;
+        if (g + step < stop && ncnt <= CAP) fetch(pc, pv, ci + nb0, val + nb0, lane, flat, ncnt);
+        int g0, g1;
+        load_rp(g + 2 * step, g0, g1);
+        // vmcnt(0): loads return in order, so the gathers would wait for these in
+        // any case, with fewer of the waves' gathers in each other's way so (fp32,
+        // 16 columns: 246 -> 233 us; fp64, 8: 253 -> 244, 16: 322 -> 315)
+        __builtin_amdgcn_s_waitcnt(0x0F70);
+        if (fits) {
+          VT acc = zero();
+          lds_ready();
+          add_entries<CPL>(E + (e0 - b0), e1 - e0, acc, gather);
+          store(g, acc);
+        } else {
+          rest |= bit;
+        }
+        e0 = f0;
+        e1 = f1;
+        f0 = g0;
+        f1 = g1;
+        b0 = nb0;
+        cnt = ncnt;
+      }
+    }
+    if (rest == 0) continue;
+    auto take = [&]() {  // the next of them, or -1
+      if (rest == 0) return (int64_t)-1;
+      const int64_t g = base + (int64_t)(__ffsll((unsigned long long)rest) - 1) * step;
+      rest &= rest - 1;
+      return g;
+    };
+    // entries of a row per pass: passes as even as whole batches of gathers allow
+    auto pass_len = [&](int m) {
+#pragma unroll
+      for (int o = G; o < 64; o *= 2) m = max(m, __shfl_xor(m, o));
+      m = __builtin_amdgcn_readfirstlane(m);  // the longest row, above kRowCap
+      const int passes = (m - 1) / kRowPass + 1;
+      return min(kRowPass, ((m - 1) / passes + 4) & ~3);
+    };
+    // (one entry more between the rows' parts: they start on different banks)
+    static_assert(kRowPass < kRowCap && kRowPass % 4 == 0, "the rows' parts fit");
+    Entry<TW>* x = E + r * (kRowPass + 1);
+    int64_t g = take(), h = take();  // this group and the next
+    load_rp(g, e0, e1);
+    load_rp(h < 0 ? g : h, f0, f1);
+    int32_t pc[NQ];
+    TV pv[NQ];
+    const int32_t* cp = ci + e0;
+    const TV* vp = val + e0;
+    int left = e1 - e0, len = pass_len(left);  // of the row (below 0 past its end), of the pass
+    fetch(pc, pv, cp, vp, l, by_row, min(left, len));
+    VT acc = zero();
+    for (;;) {
+      const int m = min(left, len);
+      stage(pc, pv, x, l, by_row, m);
+      const bool more = __ballot(left > len) != 0;
+      if (more) {
+        left -= len;
+        cp += len;
+        vp += len;
+      } else {
+        left = f1 - f0;
+        len = pass_len(left);
+        cp = ci + f0;
+        vp = val + f0;
+      }
+      if (more || h >= 0) fetch(pc, pv, cp, vp, l, by_row, min(left, len));
+      lds_ready();
+      add_entries<CPL>(x, m, acc, gather);
+      if (!more) {
+        store(g, acc);
+        if (h < 0) break;
+        acc = zero();
+        g = h;
+        h = take();
+        load_rp(h < 0 ? g : h, f0, f1);
+      }
+    }
   }
 }
 
+// The two kernels above, G lanes to a row, by the mean number of entries per row
+// (the matrices measured have 4e7 entries or 1e6 rows, lengths +- 11 %; us,
+// k_spmm_block : k_spmm_rows).
+//   * Rows that mostly fit kRowCap: k_spmm_rows, whose loads overlap its gathers
+//     (fp64, 16 columns: 27 entries 233 : 229, 41 343 : 315, 45 343 : 330, 47
+//     341 : 404; 8 columns: 16 entries 127 : 115, 41 297 : 244; fp32, 16
+//     columns: 16 entries 84 : 100, 20 137 : 126, 41 269 : 233), but not with 16
+//     lanes per row (fp64, 32 columns, 41 entries: 547 : 605) or 8 in fp32 (292 :
+//     308), where four to eight rows per wave are too little work per step.
+//   * Short rows, and rows that do not fit: k_spmm_block, by more rows in flight
+//     (fp64, 16 columns: 3 entries 74 : 87, 50 340 : 428, 64 327 : 412; rows of
+//     random length, mean 41: 543 : 640).
+//   * Rows so long that a block's take many passes, each as long as its longest
+//     part of a row: k_spmm_rows (fp64, 16 columns: 128 entries 367 : 390, 144
+//     437 : 400; 8: 160 398 : 430, 192 486 : 430; 32: 160 549 : 570, 192 577 :
+//     562; fp32, 16: 224 390 : 408, 256 432 : 409; 32: 256 366 : 384, 512 659 :
+//     380).
+//   * Products that the waves on the chip take in one step (nothing to balance,
+//     all latency; n = 20000, 16 fp64 columns, 41 entries 11 : 9, 96 30 : 20),
+//     and of longer rows also those that the cache holds (n = 80000, 96 entries
+//     82 : 60), which do not wait for HBM.
 template <typename TV, typename TW, int G>
-static hipError_t spmm_rows_launch(const int32_t* rp, const int32_t* ci, const TV* val, const TW* W,
-                                   int64_t ldw, TW* Y, int64_t ldy, int ncols, int64_t n,
-                                   hipStream_t s) {
+static hipError_t spmm_stream_launch(const int32_t* rp, const int32_t* ci, const TV* val, const TW* W,
+                                     int64_t ldw, TW* Y, int64_t ldy, int ncols, int64_t n,
+                                     int64_t nnz, hipStream_t s) {
   constexpr int CPL = 16 / (int)sizeof(TW);
-  constexpr int NR = 64 / G;
-  // a persistent grid, a multiple of the 8 XCDs: four workgroups per CU, three
-  // where a wave takes 16 rows (n = 1e6: 16 fp64 columns 350, 350, 379, 403 us
-  // with 3, 4, 5, 6; 16 fp32 columns 258, 275, 310, 305 us)
+  constexpr int NR = 64 / G, RPB = 256 / G;
+  constexpr bool F64 = sizeof(TW) == 8;
   const int64_t groups = (n + NR - 1) / NR;
-  const int64_t nb = std::min<int64_t>((groups + 3) / 4, 256 * (G == 4 ? 3 : 4));
-  const unsigned grid = (unsigned)((nb + 7) / 8 * 8);
-  const int per = (int)((groups + 7) / 8);
-  if ((uint64_t)n * (uint64_t)ldw * sizeof(TW) >= (1ull << 32))
-    hipLaunchKernelGGL((k_spmm_rows<TV, TW, G, CPL, true>), dim3(grid), dim3(256), 0, s, rp, ci, val, W, ldw, Y,
-                       ldy, ncols, n, per);
-  else
-    hipLaunchKernelGGL((k_spmm_rows<TV, TW, G, CPL, false>), dim3(grid), dim3(256), 0, s, rp, ci, val, W, ldw, Y,
-                       ldy, ncols, n, per);
-  return hipGetLastError();
+  const double mean = (double)nnz / (double)n;
+  const bool big = (uint64_t)n * (uint64_t)ldw * sizeof(TW) >= (1ull << 32);
+  // A matrix of up to kCachedBytes is read through the caches, so that the next
+  // product finds it in the memory-side one (256 MB); a larger one would only
+  // evict W and itself, and is read with the non-temporal hint (n = 3e5, fp32 of
+  // 98 MB: 64 against 80 us; n = 1e6, fp64 of 492 MB: 373 against 350 us).
+  const bool nt = big || nnz * (int64_t)(sizeof(TV) + 4) > kCachedBytes;
+  constexpr int lo = G == 4 ? (F64 ? 14 : 18) : (F64 && G == 8) ? 30 : INT_MAX;
+  constexpr int hi = F64 ? (G == 8 ? 138 : 176) : (G == 4 ? 240 : 288);
+  const bool waves = (groups <= 16 * 256 && mean >= 14) || (mean >= lo && mean <= 45.5) ||
+                     (F64 && G <= 8 && mean > 56 && !nt) || mean > hi;
+  auto launch = [&](auto kernel, int64_t nb, int64_t units) {
+    const unsigned grid = (unsigned)((nb + 7) / 8 * 8);
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, s, rp, ci, val, W, ldw, Y, ldy, ncols, n,
+                       (int)((units + 7) / 8));
+    return hipGetLastError();
+  };
+  if (waves) {
+    // a persistent grid, a multiple of the 8 XCDs: four workgroups per CU, three
+    // where a wave takes 16 rows (their registers and LDS)
+    const int64_t nb = std::min<int64_t>((groups + 3) / 4, 256 * kRowsWaves(G));
+    if (big) return launch(k_spmm_rows<TV, TW, G, CPL, true, true>, nb, groups);
+    if (nt) return launch(k_spmm_rows<TV, TW, G, CPL, false, true>, nb, groups);
+    return launch(k_spmm_rows<TV, TW, G, CPL, false, false>, nb, groups);
+  }
+  const int64_t nb = (n + RPB - 1) / RPB;
+  if (big) return launch(k_spmm_block<TV, TW, G, CPL, true, true>, nb, nb);
+  if (nt) return launch(k_spmm_block<TV, TW, G, CPL, false, true>, nb, nb);
+  return launch(k_spmm_block<TV, TW, G, CPL, false, false>, nb, nb);
 }
 
 // ---- banded matrices: W staged in LDS, slab by slab ----
@@ -489,8 +645,8 @@ __global__ __launch_bounds__(256) void k_csr_windows(const int32_t* __restrict__
 
 template <typename TV, typename TW>
 static hipError_t spmm_any(const int32_t* rp, const int32_t* ci, const TV* val, const TW* W,
-                           int64_t ldw, TW* Y, int64_t ldy, int ncols, int64_t n, const int2* win,
-                           hipStream_t s) {
+                           int64_t ldw, TW* Y, int64_t ldy, int ncols, int64_t n, int64_t nnz,
+                           const int2* win, hipStream_t s) {
   if (n < 1 || ncols < 1) return hipErrorInvalidValue;
   if (win != nullptr) {
     for (int c0 = 0; c0 < ncols; c0 += 16) {
@@ -501,24 +657,24 @@ static hipError_t spmm_any(const int32_t* rp, const int32_t* ci, const TV* val, 
     return hipSuccess;
   }
   constexpr int CPL = 16 / (int)sizeof(TW);
-  // the row kernel is used from 5 (fp64) / 9 (fp32) columns, below which the
-  // one-column-per-lane kernel is as fast, up to 16 lanes per row.  Five to
+  // the 16-byte kernels are used from 5 (fp64) / 9 (fp32) columns, below which
+  // the one-column-per-lane kernel is as fast, up to 16 lanes per row.  Five to
   // eight fp64 columns that are not aligned to 16 bytes stay with the latter,
   // which adds the entries of a row in two sums: a solve that has not
   // converged amplifies rounding, so each product keeps its order of addition.
   const bool odd = CPL == 2 && ((reinterpret_cast<uintptr_t>(W) % 16) != 0 || ldw % CPL != 0);
-  const int rows_min = (CPL == 2) ? (odd ? 9 : 5) : 9;
+  const int wide_min = (CPL == 2) ? (odd ? 9 : 5) : 9;
   constexpr int slice = 16 * CPL;
   for (int c0 = 0; c0 < ncols; c0 += slice) {
     const int nc = std::min(slice, ncols - c0);
     const TW* Wc = W + c0;
     TW* Yc = Y + c0;
     hipError_t e;
-    if (nc >= rows_min) {
+    if (nc >= wide_min) {
       const int lanes = (nc + CPL - 1) / CPL;
-      if (lanes <= 4) e = spmm_rows_launch<TV, TW, 4>(rp, ci, val, Wc, ldw, Yc, ldy, nc, n, s);
-      else if (lanes <= 8) e = spmm_rows_launch<TV, TW, 8>(rp, ci, val, Wc, ldw, Yc, ldy, nc, n, s);
-      else e = spmm_rows_launch<TV, TW, 16>(rp, ci, val, Wc, ldw, Yc, ldy, nc, n, s);
+      if (lanes <= 4) e = spmm_stream_launch<TV, TW, 4>(rp, ci, val, Wc, ldw, Yc, ldy, nc, n, nnz, s);
+      else if (lanes <= 8) e = spmm_stream_launch<TV, TW, 8>(rp, ci, val, Wc, ldw, Yc, ldy, nc, n, nnz, s);
+      else e = spmm_stream_launch<TV, TW, 16>(rp, ci, val, Wc, ldw, Yc, ldy, nc, n, nnz, s);
     } else if (nc <= 1) e = spmm_launch<TV, TW, 1>(rp, ci, val, Wc, ldw, Yc, ldy, nc, n, s);
     else if (nc <= 2) e = spmm_launch<TV, TW, 2>(rp, ci, val, Wc, ldw, Yc, ldy, nc, n, s);
     else if (nc <= 4) e = spmm_launch<TV, TW, 4>(rp, ci, val, Wc, ldw, Yc, ldy, nc, n, s);
@@ -529,14 +685,14 @@ static hipError_t spmm_any(const int32_t* rp, const int32_t* ci, const TV* val, 
 }
 
 hipError_t spmm_csr_f64(const int32_t* rp, const int32_t* ci, const double* val, const double* W,
-                        int64_t ldw, double* Y, int64_t ldy, int ncols, int64_t n, const int2* win,
-                        hipStream_t s) {
-  return spmm_any<double, double>(rp, ci, val, W, ldw, Y, ldy, ncols, n, win, s);
+                        int64_t ldw, double* Y, int64_t ldy, int ncols, int64_t n, int64_t nnz,
+                        const int2* win, hipStream_t s) {
+  return spmm_any<double, double>(rp, ci, val, W, ldw, Y, ldy, ncols, n, nnz, win, s);
 }
 hipError_t spmm_csr_f32(const int32_t* rp, const int32_t* ci, const float* val, const float* W,
-                        int64_t ldw, float* Y, int64_t ldy, int ncols, int64_t n, const int2* win,
-                        hipStream_t s) {
-  return spmm_any<float, float>(rp, ci, val, W, ldw, Y, ldy, ncols, n, win, s);
+                        int64_t ldw, float* Y, int64_t ldy, int ncols, int64_t n, int64_t nnz,
+                        const int2* win, hipStream_t s) {
+  return spmm_any<float, float>(rp, ci, val, W, ldw, Y, ldy, ncols, n, nnz, win, s);
 }
 hipError_t csr_windows(const int32_t* rp, const int32_t* ci, int64_t n, int2* win, int* unsorted,
                        hipStream_t s) {

@@ -166,7 +166,7 @@ const int2* lobpcg_ctx::csr_slab_windows() {
 int lobpcg_ctx::apply_op(const double* W, int64_t ldw, int nc, double* Y, int64_t ldy) {
   hipError_t e = hipSuccess;
   switch (op) {
-    case kOpCsr: e = spmm_csr_f64(rp, ci, val, W, ldw, Y, ldy, nc, n, csr_slab_windows(), stream); break;
+    case kOpCsr: e = spmm_csr_f64(rp, ci, val, W, ldw, Y, ldy, nc, n, nnz, csr_slab_windows(), stream); break;
     case kOpDense:
       e = dense_apply_f64(A, lda, W, ldw, Y, ldy, nc, n, stream);
       break;
@@ -187,7 +187,7 @@ int lobpcg_ctx::apply_op(const float* W, int64_t ldw, int nc, float* Y, int64_t 
   const float* o32 = reinterpret_cast<const float*>(ws + lay.op32);
   hipError_t e = hipSuccess;
   switch (op) {
-    case kOpCsr: e = spmm_csr_f32(rp, ci, o32, W, ldw, Y, ldy, nc, n, csr_slab_windows(), stream); break;
+    case kOpCsr: e = spmm_csr_f32(rp, ci, o32, W, ldw, Y, ldy, nc, n, nnz, csr_slab_windows(), stream); break;
     case kOpDense:
       e = dense_apply_f32(o32, n, W, ldw, Y, ldy, nc, n, stream);
       break;
@@ -929,7 +929,7 @@ int lobpcg_ctx::run_davidson(int k, double tol, int& iter, PhaseOut& out) {
 int lobpcg_ctx::apply_b(const double* W, int64_t ldw, int nc, double* Y, int64_t ldy) {
   hipError_t e = hipSuccess;
   switch (bop) {
-    case kOpCsr: e = spmm_csr_f64(brp, bci, bval, W, ldw, Y, ldy, nc, n, nullptr, stream); break;
+    case kOpCsr: e = spmm_csr_f64(brp, bci, bval, W, ldw, Y, ldy, nc, n, bnnz, nullptr, stream); break;
     case kOpDense:
       e = dense_apply_f64(Bd, ldb, W, ldw, Y, ldy, nc, n, stream);
       break;
