@@ -37,7 +37,7 @@ def matrix(n, mean, kind, seed, tail=False):
         lens = (-mean * torch.log(torch.rand(n, generator=g, device="cuda").clamp(min=1e-4))).floor()
     else:  # "few": most rows short, some very long, some empty
         lens = (mean * 0.5 * torch.rand(n, generator=g, device="cuda")).floor()
-        lens[::997] = 250.0 * mean
+        lens[::997] = min(250.0 * mean, 4000.0)
     lens = lens.clamp(min=0).long()
     rp = torch.zeros(n + 1, dtype=torch.int64, device="cuda")
     rp[1:] = lens.cumsum(0)
