@@ -144,12 +144,14 @@ struct lobpcg_ctx {
   Layout plan(int m, int prec) const;
   size_t op32_elems() const;
   int ensure_layout(int m);
-  int apply_op(const double* W, int64_t ldw, int nc, double* Y, int64_t ldy);
+  // between: bytes that pass through the caches between this product and the
+  // next one with the same matrix (0: a caller's product by itself)
+  int apply_op(const double* W, int64_t ldw, int nc, double* Y, int64_t ldy, int64_t between = 0);
   // brings `bytes` (a multiple of 4, at most kPostBytes) of device memory
   // at src to the host once the work queued before it has run; *out points
   // at the host copy until the next read-back
   int readback(const void* src, size_t bytes, const void** out);
-  int apply_op(const float* W, int64_t ldw, int nc, float* Y, int64_t ldy);
+  int apply_op(const float* W, int64_t ldw, int nc, float* Y, int64_t ldy, int64_t between = 0);
   template <typename T>
   int ortho_run(T* base, int64_t ld, int ny, int nw, lobpcg_ortho_info* info, bool fold = false,
                 double tau_run = -1.0);
@@ -176,7 +178,7 @@ struct lobpcg_ctx {
     return d < lobpcg::kMaxP ? d : lobpcg::kMaxP;
   }
   int run_davidson(int k, double tol, int& iter, PhaseOut& out);
-  int apply_b(const double* W, int64_t ldw, int nc, double* Y, int64_t ldy);
+  int apply_b(const double* W, int64_t ldw, int nc, double* Y, int64_t ldy, int64_t between = 0);
   int ensure_bdiag();
   int b_orthonormalize(double* X, double* BX, int64_t ld, int nc);
   int run_generalized(int k, double tol, int& iter, PhaseOut& out);

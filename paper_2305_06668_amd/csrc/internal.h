@@ -140,12 +140,15 @@ constexpr int kSlabBlockRows = 2048;
 constexpr int kSlabThreads = 1024;
 constexpr int kSlabUnits = kSlabBlockRows * 4 / kSlabThreads;  // rows per thread
 constexpr int kSlabLds = 128 * 1024;                            // bytes of W per slab
+// Y (n x ncols) = A W; nnz stored entries; between: bytes that pass through the
+// caches between this product and the next one with the same matrix, if more
+// than W and Y
 hipError_t spmm_csr_f64(const int32_t* rp, const int32_t* ci, const double* val, const double* W,
                         int64_t ldw, double* Y, int64_t ldy, int ncols, int64_t n, int64_t nnz,
-                        const int2* win, hipStream_t s);
+                        int64_t between, const int2* win, hipStream_t s);
 hipError_t spmm_csr_f32(const int32_t* rp, const int32_t* ci, const float* val, const float* W,
                         int64_t ldw, float* Y, int64_t ldy, int ncols, int64_t n, int64_t nnz,
-                        const int2* win, hipStream_t s);
+                        int64_t between, const int2* win, hipStream_t s);
 hipError_t csr_windows(const int32_t* rp, const int32_t* ci, int64_t n, int2* win, int* unsorted,
                        hipStream_t s);
 // pack (optional, n x 8 values): scratch for a compact copy of W when W is

@@ -267,7 +267,7 @@ __global__ __launch_bounds__(256) void k_spmm_block(const int32_t* __restrict__ 
 // compiler waits for the loads of one where it goes on with the other: rows that
 // all fit took 3 to 15 % longer.)
 constexpr int kRowCap = 48, kRowPass = 44;
-constexpr int64_t kCachedBytes = 160ll << 20;
+constexpr int64_t kCacheBytes = 256ll << 20;  // the memory-side cache
 constexpr int kRowsWaves(int G) { return G == 4 ? 3 : 4; }  // workgroups per CU: their registers and LDS
 template <typename TV, typename TW, int G, int CPL, bool BIG, bool NT>
 __global__ __launch_bounds__(256)
@@ -467,18 +467,25 @@ void k_spmm_rows(const int32_t* __restrict__ rp, const int32_t* __restrict__ ci,
 template <typename TV, typename TW, int G>
 static hipError_t spmm_stream_launch(const int32_t* rp, const int32_t* ci, const TV* val, const TW* W,
                                      int64_t ldw, TW* Y, int64_t ldy, int ncols, int64_t n,
-                                     int64_t nnz, hipStream_t s) {
+                                     int64_t nnz, int64_t between, hipStream_t s) {
   constexpr int CPL = 16 / (int)sizeof(TW);
   constexpr int NR = 64 / G, RPB = 256 / G;
   constexpr bool F64 = sizeof(TW) == 8;
   const int64_t groups = (n + NR - 1) / NR;
   const double mean = (double)nnz / (double)n;
   const bool big = (uint64_t)n * (uint64_t)ldw * sizeof(TW) >= (1ull << 32);
-  // A matrix of up to kCachedBytes is read through the caches, so that the next
-  // product finds it in the memory-side one (256 MB); a larger one would only
-  // evict W and itself, and is read with the non-temporal hint (n = 3e5, fp32 of
-  // 98 MB: 64 against 80 us; n = 1e6, fp64 of 492 MB: 373 against 350 us).
-  const bool nt = big || nnz * (int64_t)(sizeof(TV) + 4) > kCachedBytes;
+  // A matrix that the memory-side cache still holds at the next product is read
+  // through the caches; a larger one, or one with too much between two products,
+  // would only evict W and itself, and is read with the non-temporal hint.  What
+  // passes: the matrix, W and Y, or what the caller names.  (One product after
+  // another, 16 columns, with : without the hint: n = 1e6, 8 fp64 entries per row,
+  // 356 MB 102 : 111 us; fp32 the same 192 MB 68 : 51, 16 entries 260 MB 114 : 84,
+  // 20 entries 292 MB 136 : 138.  Whole fp64 solves of 41 entries per row, 12
+  // columns: n = 1e5, 164 MB with the bases 9.50 : 9.40 ms; 2e5, 328 MB 14.04 :
+  // 14.52; 3e5 29.6 : 30.0.)
+  const int64_t product = 2 * n * ncols * (int64_t)sizeof(TW);
+  const bool nt = big || nnz * (int64_t)(sizeof(TV) + 4) + std::max(product, between) > kCacheBytes;
+  // (mean entries per row)
   constexpr int lo = G == 4 ? (F64 ? 14 : 18) : (F64 && G == 8) ? 30 : INT_MAX;
   constexpr int hi = F64 ? (G == 8 ? 138 : 176) : (G == 4 ? 240 : 288);
   const bool waves = (groups <= 16 * 256 && mean >= 14) || (mean >= lo && mean <= 45.5) ||
@@ -646,7 +653,7 @@ __global__ __launch_bounds__(256) void k_csr_windows(const int32_t* __restrict__
 template <typename TV, typename TW>
 static hipError_t spmm_any(const int32_t* rp, const int32_t* ci, const TV* val, const TW* W,
                            int64_t ldw, TW* Y, int64_t ldy, int ncols, int64_t n, int64_t nnz,
-                           const int2* win, hipStream_t s) {
+                           int64_t between, const int2* win, hipStream_t s) {
   if (n < 1 || ncols < 1) return hipErrorInvalidValue;
   if (win != nullptr) {
     for (int c0 = 0; c0 < ncols; c0 += 16) {
@@ -672,9 +679,9 @@ static hipError_t spmm_any(const int32_t* rp, const int32_t* ci, const TV* val, 
     hipError_t e;
     if (nc >= wide_min) {
       const int lanes = (nc + CPL - 1) / CPL;
-      if (lanes <= 4) e = spmm_stream_launch<TV, TW, 4>(rp, ci, val, Wc, ldw, Yc, ldy, nc, n, nnz, s);
-      else if (lanes <= 8) e = spmm_stream_launch<TV, TW, 8>(rp, ci, val, Wc, ldw, Yc, ldy, nc, n, nnz, s);
-      else e = spmm_stream_launch<TV, TW, 16>(rp, ci, val, Wc, ldw, Yc, ldy, nc, n, nnz, s);
+      if (lanes <= 4) e = spmm_stream_launch<TV, TW, 4>(rp, ci, val, Wc, ldw, Yc, ldy, nc, n, nnz, between, s);
+      else if (lanes <= 8) e = spmm_stream_launch<TV, TW, 8>(rp, ci, val, Wc, ldw, Yc, ldy, nc, n, nnz, between, s);
+      else e = spmm_stream_launch<TV, TW, 16>(rp, ci, val, Wc, ldw, Yc, ldy, nc, n, nnz, between, s);
     } else if (nc <= 1) e = spmm_launch<TV, TW, 1>(rp, ci, val, Wc, ldw, Yc, ldy, nc, n, s);
     else if (nc <= 2) e = spmm_launch<TV, TW, 2>(rp, ci, val, Wc, ldw, Yc, ldy, nc, n, s);
     else if (nc <= 4) e = spmm_launch<TV, TW, 4>(rp, ci, val, Wc, ldw, Yc, ldy, nc, n, s);
@@ -686,13 +693,13 @@ static hipError_t spmm_any(const int32_t* rp, const int32_t* ci, const TV* val, 
 
 hipError_t spmm_csr_f64(const int32_t* rp, const int32_t* ci, const double* val, const double* W,
                         int64_t ldw, double* Y, int64_t ldy, int ncols, int64_t n, int64_t nnz,
-                        const int2* win, hipStream_t s) {
-  return spmm_any<double, double>(rp, ci, val, W, ldw, Y, ldy, ncols, n, nnz, win, s);
+                        int64_t between, const int2* win, hipStream_t s) {
+  return spmm_any<double, double>(rp, ci, val, W, ldw, Y, ldy, ncols, n, nnz, between, win, s);
 }
 hipError_t spmm_csr_f32(const int32_t* rp, const int32_t* ci, const float* val, const float* W,
                         int64_t ldw, float* Y, int64_t ldy, int ncols, int64_t n, int64_t nnz,
-                        const int2* win, hipStream_t s) {
-  return spmm_any<float, float>(rp, ci, val, W, ldw, Y, ldy, ncols, n, nnz, win, s);
+                        int64_t between, const int2* win, hipStream_t s) {
+  return spmm_any<float, float>(rp, ci, val, W, ldw, Y, ldy, ncols, n, nnz, between, win, s);
 }
 hipError_t csr_windows(const int32_t* rp, const int32_t* ci, int64_t n, int2* win, int* unsorted,
                        hipStream_t s) {

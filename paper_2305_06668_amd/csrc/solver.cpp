@@ -163,10 +163,10 @@ const int2* lobpcg_ctx::csr_slab_windows() {
   return slab_ok ? win : nullptr;
 }
 
-int lobpcg_ctx::apply_op(const double* W, int64_t ldw, int nc, double* Y, int64_t ldy) {
+int lobpcg_ctx::apply_op(const double* W, int64_t ldw, int nc, double* Y, int64_t ldy, int64_t between) {
   hipError_t e = hipSuccess;
   switch (op) {
-    case kOpCsr: e = spmm_csr_f64(rp, ci, val, W, ldw, Y, ldy, nc, n, nnz, csr_slab_windows(), stream); break;
+    case kOpCsr: e = spmm_csr_f64(rp, ci, val, W, ldw, Y, ldy, nc, n, nnz, between, csr_slab_windows(), stream); break;
     case kOpDense:
       e = dense_apply_f64(A, lda, W, ldw, Y, ldy, nc, n, stream);
       break;
@@ -183,11 +183,11 @@ int lobpcg_ctx::apply_op(const double* W, int64_t ldw, int nc, double* Y, int64_
 }
 
 // fp32 operator (mixed-precision phase): copies made by ensure_op32
-int lobpcg_ctx::apply_op(const float* W, int64_t ldw, int nc, float* Y, int64_t ldy) {
+int lobpcg_ctx::apply_op(const float* W, int64_t ldw, int nc, float* Y, int64_t ldy, int64_t between) {
   const float* o32 = reinterpret_cast<const float*>(ws + lay.op32);
   hipError_t e = hipSuccess;
   switch (op) {
-    case kOpCsr: e = spmm_csr_f32(rp, ci, o32, W, ldw, Y, ldy, nc, n, nnz, csr_slab_windows(), stream); break;
+    case kOpCsr: e = spmm_csr_f32(rp, ci, o32, W, ldw, Y, ldy, nc, n, nnz, between, csr_slab_windows(), stream); break;
     case kOpDense:
       e = dense_apply_f32(o32, n, W, ldw, Y, ldy, nc, n, stream);
       break;
@@ -762,7 +762,8 @@ int lobpcg_ctx::run_phase(T* V0, T* V1, T* AV0, T* AV1, int k, double tol, bool 
     if (rc) return rc;
     pend_valid = true;
     pend_woff = q;
-    rc = apply_op(V[1 - c] + q, ldo, nact, AV[1 - c] + q, ldo);
+    // (between two products an iteration goes through both bases and their products)
+    rc = apply_op(V[1 - c] + q, ldo, nact, AV[1 - c] + q, ldo, n * 12 * m * (int64_t)sizeof(T));
     if (rc) return rc;
     c = 1 - c;
     L = ldo;
@@ -913,7 +914,7 @@ int lobpcg_ctx::run_davidson(int k, double tol, int& iter, PhaseOut& out) {
                             stream));
     rc = ortho_run<double>(V, md, p, nact, nullptr, false, tau);
     if (rc) return rc;
-    rc = apply_op(V + p, md, nact, AV + p, md);
+    rc = apply_op(V + p, md, nact, AV + p, md, n * 2 * md * (int64_t)sd);
     if (rc) return rc;
     p += nact;
     stats.max_basis = std::max(stats.max_basis, p);
@@ -926,10 +927,10 @@ int lobpcg_ctx::run_davidson(int k, double tol, int& iter, PhaseOut& out) {
 
 // ---- the generalized problem A x = lambda B x (Sec. 3.3) ----------------
 
-int lobpcg_ctx::apply_b(const double* W, int64_t ldw, int nc, double* Y, int64_t ldy) {
+int lobpcg_ctx::apply_b(const double* W, int64_t ldw, int nc, double* Y, int64_t ldy, int64_t between) {
   hipError_t e = hipSuccess;
   switch (bop) {
-    case kOpCsr: e = spmm_csr_f64(brp, bci, bval, W, ldw, Y, ldy, nc, n, bnnz, nullptr, stream); break;
+    case kOpCsr: e = spmm_csr_f64(brp, bci, bval, W, ldw, Y, ldy, nc, n, bnnz, between, nullptr, stream); break;
     case kOpDense:
       e = dense_apply_f64(Bd, ldb, W, ldw, Y, ldy, nc, n, stream);
       break;
@@ -998,6 +999,7 @@ int lobpcg_ctx::run_generalized(int k, double tol, int& iter, PhaseOut& out) {
   double* coef = small_ptr<double>(lay.coef);
   double* cols = small_ptr<double>(lay.cols);
   const size_t sd = sizeof(double);
+  const int64_t traffic = n * 18 * m * (int64_t)sd;  // the bases and their products, between two products
   const int gp = (pkind == LOBPCG_PRECOND_NONE) ? 0 : (pkind == LOBPCG_PRECOND_DIAG_SIGNED ? 2 : 1);
 
   // X0: Euclidean Alg. 2, then B-orthonormalised with one B application
@@ -1159,11 +1161,11 @@ int lobpcg_ctx::run_generalized(int k, double tol, int& iter, PhaseOut& out) {
     }
     if (!(cmax <= tau)) stats.ortho_stalled++;
     // one application of B, one B-Cholesky reusing it, then A W
-    rc = apply_b(W, ldo, nact, BVn + q, ldo);
+    rc = apply_b(W, ldo, nact, BVn + q, ldo, traffic);
     if (rc) return rc;
     rc = b_orthonormalize(W, BVn + q, ldo, nact);
     if (rc) return rc;
-    rc = apply_op(W, ldo, nact, AV[1 - c] + q, ldo);
+    rc = apply_op(W, ldo, nact, AV[1 - c] + q, ldo, traffic);
     if (rc) return rc;
     c = 1 - c;
     L = ldo;
