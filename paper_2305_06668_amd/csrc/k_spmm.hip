@@ -667,17 +667,23 @@ static hipError_t spmm_any(const int32_t* rp, const int32_t* ci, const TV* val, 
   // the 16-byte kernels are used from 5 (fp64) / 9 (fp32) columns, below which
   // the one-column-per-lane kernel is as fast, up to 16 lanes per row.  Five to
   // eight fp64 columns that are not aligned to 16 bytes stay with the latter,
-  // which adds the entries of a row in two sums: a solve that has not
+  // which adds the entries of a row in two sums, and where these are the end of
+  // 33 to 40 they go to the former, which add in order: a solve that has not
   // converged amplifies rounding, so each product keeps its order of addition.
   const bool odd = CPL == 2 && ((reinterpret_cast<uintptr_t>(W) % 16) != 0 || ldw % CPL != 0);
   const int wide_min = (CPL == 2) ? (odd ? 9 : 5) : 9;
   constexpr int slice = 16 * CPL;
   for (int c0 = 0; c0 < ncols; c0 += slice) {
-    const int nc = std::min(slice, ncols - c0);
-    const TW* Wc = W + c0;
-    TW* Yc = Y + c0;
+    int nc = std::min(slice, ncols - c0), c = c0;
+    const bool tail = odd && c0 > 0;
+    if (tail && nc == 1) {  // with its neighbour, which takes the same value again
+      nc = 2;
+      c = c0 - 1;
+    }
+    const TW* Wc = W + c;
+    TW* Yc = Y + c;
     hipError_t e;
-    if (nc >= wide_min) {
+    if (nc >= wide_min || tail) {
       const int lanes = (nc + CPL - 1) / CPL;
       if (lanes <= 4) e = spmm_stream_launch<TV, TW, 4>(rp, ci, val, Wc, ldw, Yc, ldy, nc, n, nnz, between, s);
       else if (lanes <= 8) e = spmm_stream_launch<TV, TW, 8>(rp, ci, val, Wc, ldw, Yc, ldy, nc, n, nnz, between, s);

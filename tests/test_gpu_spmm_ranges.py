@@ -124,3 +124,25 @@ def test_csr_large_w(P, n, mean, kind):
     a = ldw - m
     Y = product(P, rp, ci, val, W, a, m, False)
     check(rp, ci, val, W[:, a:], Y, 2.0**-53)
+
+
+@pytest.mark.parametrize("m", [33, 34, 36, 40, 41, 64])
+def test_csr_misaligned_tail_bits(P, m):
+    """More than 32 fp64 columns at an odd leading dimension add a row's entries
+    in order, as a block aligned to 16 bytes does, also the last one to eight: the
+    same bits."""
+    n = 5003
+    print("csr misaligned tail", m, flush=True)
+    rp, ci, val = matrix(n, 41, "even", 3)
+    W = torch.randn(n, m | 1, generator=gen(m), device="cuda", dtype=torch.float64)
+    Y = torch.full_like(W, 5.0)
+    s = P.Solver(n)
+    s.set_operator_csr(rp, ci, val)
+    P.lobpcg_apply_operator(s.h, W[:, :m], Y[:, :m])
+    torch.cuda.synchronize()
+    s.close()
+    for a in list(range(0, m - 15, 16)) + [m - 16]:
+        Z = product(P, rp, ci, val, W[:, a : a + 16].contiguous(), 0, 16, False)
+        assert torch.equal(Y[:, a : a + 16], Z), (m, a)
+    check(rp, ci, val, W[:, :m], Y[:, :m], 2.0**-53)
+    assert bool((Y[:, m:] == 5.0).all())
