@@ -53,3 +53,29 @@ def test_kron_edges(P, na, m, ldw, q, prec):
         assert np.all(np.abs(out[:, b].reshape(na, na) - ref) <= bound)
     assert np.all(out[:, :q] == 5.0) and np.all(out[:, q + m :] == 5.0)  # other columns untouched
     s.close()
+
+
+@pytest.mark.parametrize("m,ldw,q", [(8, 8, 0), (8, 11, 3), (16, 18, 2), (16, 19, 1), (24, 24, 0), (3, 3, 0), (9, 11, 1)])
+@pytest.mark.parametrize("na", [1, 2, 16, 17, 33, 65, 257, 289])
+def test_kron_no_workspace(P, na, m, ldw, q):
+    """Without a workspace there is no packed copy: the kernel reads the caller's
+    block itself, at its leading dimension, alignment and number of columns, eight
+    columns to a row of the grid."""
+    print("kron no workspace", na, m, ldw, q, flush=True)
+    g = synth.rng(11 * na + m)
+    n = na * na
+    B = g.standard_normal((na, na))
+    A, V = 0.5 * (B + B.T), g.standard_normal((na, na))
+    s = P.Solver(n)
+    s.set_operator_kronsum(torch.from_numpy(A).cuda(), torch.from_numpy(V).cuda())
+    W = g.standard_normal((n, ldw))
+    Y = torch.full((n, ldw), 5.0, dtype=torch.float64, device="cuda")
+    P.lobpcg_apply_operator(s.h, torch.from_numpy(W).cuda()[:, q : q + m], Y[:, q : q + m])
+    out = Y.cpu().numpy()
+    for b in range(q, q + m):
+        Wb = W[:, b].reshape(na, na)
+        ref = A @ Wb + Wb @ A + V * Wb
+        bound = (2 * na + 3) * 2.0**-53 * (abs(A) @ abs(Wb) + abs(Wb) @ abs(A) + abs(V) * abs(Wb))
+        assert np.all(np.abs(out[:, b].reshape(na, na) - ref) <= bound)
+    assert np.all(out[:, :q] == 5.0) and np.all(out[:, q + m :] == 5.0)  # other columns untouched
+    s.close()
