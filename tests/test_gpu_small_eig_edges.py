@@ -69,3 +69,25 @@ def test_small_eigh_edges(P, p, kind):
     assert np.abs(a @ Uh - Uh * lam).max() <= 1e-13 * nrm
     assert np.all(np.diag(Uh) >= 0)
     s.close()
+
+
+@pytest.mark.parametrize("p", [3, 33, 64, 65, 96])
+def test_small_eigh_fallback(P, p):
+    """Entries whose squares are near the end of the exponent range: the reflectors'
+    scale overflows, and the matrix is read again and goes through the Jacobi
+    sweeps, as when a Cholesky factorisation breaks down.  The same bounds."""
+    print("small_eigh fallback", p, flush=True)
+    a = 1e-158 * synth.random_symmetric(p, p)
+    s = P.Solver(300)
+    ev = torch.zeros(p, dtype=torch.float64, device="cuda")
+    U = torch.zeros((p, p), dtype=torch.float64, device="cuda")
+    P.lobpcg_small_eigh(s.h, torch.from_numpy(a).cuda(), ev, U)
+    lam, Uh = ev.cpu().numpy() * 2.0**500, U.cpu().numpy()
+    a = a * 2.0**500  # (the checks' own squares)
+    nrm = np.linalg.norm(a, 2)
+    assert np.all(np.abs(lam - np.linalg.eigvalsh(a)) <= 1e-13 * nrm)
+    assert np.all(np.diff(lam) >= 0)
+    assert np.abs(Uh.T @ Uh - np.eye(p)).max() <= 1e-13
+    assert np.abs(a @ Uh - Uh * lam).max() <= 1e-13 * nrm
+    assert np.all(np.diag(Uh) >= 0)
+    s.close()
