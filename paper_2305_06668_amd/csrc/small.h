@@ -38,14 +38,11 @@ __device__ __forceinline__ double dpp_f64(double v) {
   return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xF, 0xF, true),
                           __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xF, 0xF, true));
 }
-// the 64-bit DPP move (row_newbcast is the one control it takes)
-extern "C" __device__ long lobpcg_update_dpp_i64(long old, long src, int ctrl, int row_mask, int bank_mask,
-                                                 bool bound_ctrl) __asm("llvm.amdgcn.update.dpp.i64");
-// lane L of each row of 16 to the whole row
+// lane L of each row of 16 to the whole row (row_newbcast, the one control that
+// the 64-bit DPP move takes)
 template <int L>
 __device__ __forceinline__ double row_bcast(double v) {
-  const long x = __double_as_longlong(v);
-  return __longlong_as_double(lobpcg_update_dpp_i64(x, x, 0x150 + L, 0xF, 0xF, true));
+  return __builtin_amdgcn_update_dpp(v, v, 0x150 + L, 0xF, 0xF, true);
 }
 // f(integral constant I) for I = B .. E-1
 template <int B, int E, class F>
