@@ -11,6 +11,8 @@
 
 namespace lobpcg {
 
+namespace {  // (k_small.hip has helpers of the same names, in its own order of operations)
+
 // 1 / q and 1 / sqrt(x) to 1 ulp: the hardware estimate (2^-23 or better)
 // and two Newton steps.  q, x finite and not 0, x > 0.
 __device__ __forceinline__ double rcp2(double q) {
@@ -768,6 +770,8 @@ __device__ __forceinline__ bool blk_tri_eigh(const double* __restrict__ a, int p
   }
   return true;
 }
+
+}  // namespace
 
 __global__ __launch_bounds__(kEigThreads) void k_small_eigh(const double* __restrict__ a, int p,
                                                             double* __restrict__ evals,

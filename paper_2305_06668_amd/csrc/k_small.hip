@@ -15,6 +15,8 @@
 
 namespace lobpcg {
 
+namespace {
+
 constexpr double kShiftAlpha0 = 100.0;
 constexpr double kShiftGrowth = 10.0;
 constexpr int kShiftRetries = 20;
@@ -1366,6 +1368,8 @@ __device__ __forceinline__ void load_rr_matrix(const double* a, int p, double* A
   __syncthreads();
 }
 
+}  // namespace
+
 // Rayleigh-Ritz step.  The order of every sum is part of what it computes: an
 // iteration that has not converged amplifies rounding (on a banded matrix of
 // order 1e5, one unit in the last place of the starting block moves the
@@ -1610,6 +1614,8 @@ hipError_t small_cholesky(const double* M, int p, double* L, int* info, hipStrea
 //          coef = [-C; I] (scaled by the pending D) -> BEGIN
 //   FINAL  a pending diagonal scaling was applied: finished.
 
+namespace {
+
 enum { kPhFinal = 5, kPhYCheck = 6 };
 
 // The ortho controller is one workgroup between two passes over the vectors, so
@@ -1675,6 +1681,8 @@ __device__ __forceinline__ double blk_inv_bound(const double* L, int ldl, const 
   *e_out = e;
   return (e < 0.5) ? 1.0 / (1.0 - e) : sqrt(si);
 }
+
+}  // namespace
 
 __global__ __launch_bounds__(kCtlThreads) void k_ortho_ctl(const double* __restrict__ G,
                                                    OrthoState* __restrict__ gst,
