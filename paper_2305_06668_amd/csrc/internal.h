@@ -151,8 +151,6 @@ hipError_t spmm_csr_f32(const int32_t* rp, const int32_t* ci, const float* val, 
                         int64_t between, const int2* win, hipStream_t s);
 hipError_t csr_windows(const int32_t* rp, const int32_t* ci, int64_t n, int2* win, int* unsorted,
                        hipStream_t s);
-// pack (optional, n x 8 values): scratch for a compact copy of W when W is
-// not a compact 8-column block
 hipError_t dense_apply_f64(const double* A, int64_t lda, const double* W, int64_t ldw, double* Y,
                            int64_t ldy, int ncols, int64_t n, hipStream_t s);
 hipError_t dense_apply_f32(const float* A, int64_t lda, const float* W, int64_t ldw, float* Y,

@@ -88,30 +88,30 @@ struct JacobiLds {
   int flags[8];
 };
 
-// sym(a) into A (stride lda), scaled by ds[i] ds[j] from both sides
-__device__ __forceinline__ void load_sym(const double* a, int p, const double* ds, double* A, int lda) {
+// sym(a) into A (stride lda)
+__device__ __forceinline__ void load_sym(const double* a, int p, double* A, int lda) {
   for (int idx = threadIdx.x; idx < p * p; idx += blockDim.x) {
     const int i = idx / p, j = idx - i * p;
-    A[i * lda + j] = 0.5 * (a[i * p + j] + a[j * p + i]) * (ds[i] * ds[j]);
+    A[i * lda + j] = 0.5 * (a[i * p + j] + a[j * p + i]);
   }
   __syncthreads();
 }
 
 // ---------------------------------------------------------------------------
-// Lowest nev eigenpairs of a symmetric p x p matrix by the tridiagonal
+// Eigenpairs of a symmetric p x p matrix by the tridiagonal
 // route (as the Rayleigh-Ritz solve of Alg. 1, for which the paper calls
 // LAPACK, Sec. 3.1), by one workgroup of four waves:
 //   1. Householder reduction A = Q T Q^T: reflector k,
 //      H_k = I - beta_k v_k v_k^T, maps column k below the diagonal to
 //      alpha_k e_{k+1} (Q = H_0 H_1 ... H_{p-2}, the last one I);
-//   2. the nev lowest eigenvalues of T by multisection on Sturm counts,
+//   2. the eigenvalues of T by multisection on Sturm counts,
 //      G points per eigenvalue and round;
 //   3. their vectors by block inverse iteration: a solve with the
 //      partial-pivoting LU of T - lambda_j I from a SplitMix64 start
 //      (pivots below eps ||T|| raised to eps ||T||, one thread per vector),
-//      Cholesky-QR of the nev vectors, a second solve;
+//      Cholesky-QR of the vectors, a second solve;
 //   4. back-transformation u = Q z, 16 lanes per vector;
-//   5. Cholesky-QR, twice, of the nev vectors.
+//   5. Cholesky-QR, twice, of the vectors.
 // Inverse iteration returns the vectors of a cluster of close or repeated
 // eigenvalues as independent mixtures of the cluster's eigenvectors, which
 // drift towards each other with further solves; orthonormalising them in
@@ -133,43 +133,38 @@ constexpr int kEigThreads = 256;
 
 typedef double dd2 __attribute__((ext_vector_type(2)));
 
-// LDS layout of the tridiagonal path, in doubles.  `work` is where a caller
-// may lay its own data over everything but Z and ev once the vectors are
-// done.  The reduction's vectors and the LU of the inverse iteration share
-// `lu`.  Z and the LU have rows for p rounded up to 8.
+// LDS layout of the tridiagonal path, in doubles.  The reduction's vectors and
+// the LU of the inverse iteration share `lu`.  Z and the LU have rows for p
+// rounded up to 8.
 struct TriLayout {
   int ldz, nb;
-  int Z, ev, d, e, beta, work, de, vref, orth, lu, total;
+  int Z, ev, d, e, beta, de, vref, orth, lu;
 };
 constexpr int kTrans = 16 * 17;  // one wave's 16 x 16 transpose
 constexpr int kRedScratch = 128 + 4 * 128;
 // reflectors: rows of 64 up to p = 64 (zeros in front and behind), packed above
 __host__ __device__ inline int ref_doubles(int p) { return p <= 64 ? 64 * p : p * (p - 1) / 2; }
-__host__ __device__ inline TriLayout tri_layout(int p, int nev) {
+__host__ __device__ inline TriLayout tri_layout(int p) {
   TriLayout t;
   const int p8 = (p + 7) & ~7;
-  t.ldz = nev | 1;
+  t.ldz = p | 1;
   int o = 0;
   t.Z = o; o += p8 * t.ldz;
-  t.ev = o; o += nev;
+  t.ev = o; o += p;
   t.d = o; o += p8 + 1;
   t.e = o; o += p8 + 1;
   t.beta = o; o += p;
   o += o & 1;
-  t.work = o;
   t.de = o; o += 2 * (p + 16);
   t.vref = o; o += ref_doubles(p);
-  t.orth = o; o += 4 * kTrans + (nev > 16 ? (nev - 1) / 16 * 16 * 17 : 0);
+  t.orth = o; o += 4 * kTrans + (p > 16 ? (p - 1) / 16 * 16 * 17 : 0);
   t.lu = o;
   const int avail = kEigLdsBytes / 8 - o;
-  int nb = avail / (3 * p8);  // U0^-1, U1, multipliers
-  if (nb > nev) nb = nev;
-  t.nb = nb;
-  const int lu = 3 * p8 * nb;
-  t.total = o + (lu > kRedScratch ? lu : kRedScratch);
+  t.nb = avail / (3 * p8);  // U0^-1, U1, multipliers
+  if (t.nb > p) t.nb = p;
   return t;
 }
-// the path runs for every p the kernels take, also with all vectors wanted
+// the path runs for every p the kernel takes
 static_assert(kEigLdsBytes / 8 > 96 * 97 + 4 * 98 + 2 * 112 + 96 * 95 / 2 + 4 * kTrans + 80 * 17 + kRedScratch &&
                   kEigLdsBytes / 8 > 64 * 65 + 4 * 66 + 2 * 80 + 64 * 64 + 4 * kTrans + 48 * 17 + kRedScratch,
               "LDS of the largest eigensolves");
@@ -177,7 +172,7 @@ static_assert(kEigLdsBytes / 8 > 96 * 97 + 4 * 98 + 2 * 112 + 96 * 95 / 2 + 4 * 
 // offset of reflector k (its entries k+1 .. p-1) in the packed store
 __device__ __forceinline__ int ref_off(int p, int k) { return k * (p - 1) - k * (k - 1) / 2; }
 
-// Householder reduction of sym(a) scaled by ds from both sides.  Lane l of
+// Householder reduction of sym(a).  Lane l of
 // wave w keeps, in registers, rows l (and l + 64: H = 2) of the columns
 // c = w (mod 4), slot by slot; every four steps each wave takes its next slot
 // out as `cur`, the pivot of one of those steps, and moves the rest down.
@@ -193,7 +188,7 @@ __device__ __forceinline__ int ref_off(int p, int k) { return k * (p - 1) - k * 
 // two barriers and about 2100 cycles, where the trailing matrix in LDS under 16 waves took
 // three barriers and 3500 (p = 48: 67 us, now 42).
 template <int H, int NJ>
-__device__ __forceinline__ void reg_tridiag(const double* __restrict__ a, int p, const double* ds, double* d,
+__device__ __forceinline__ void reg_tridiag(const double* __restrict__ a, int p, double* d,
                                             double* e, double* beta, double* vref, double* scr) {
   double* vlin = scr;         // 64 H (H = 2; else the reflector's row of vref)
   double* part = vlin + 128;  // [wave][128]
@@ -205,7 +200,7 @@ __device__ __forceinline__ void reg_tridiag(const double* __restrict__ a, int p,
 #pragma unroll
     for (int jj = 0; jj < NJ; ++jj) {
       const int i = lane + 64 * h, c = 4 * jj + wave;
-      A[h][jj] = (i < p && c < p) ? 0.5 * (a[i * p + c] + a[c * p + i]) * (ds[i] * ds[c]) : 0.0;
+      A[h][jj] = (i < p && c < p) ? 0.5 * (a[i * p + c] + a[c * p + i]) : 0.0;
     }
   __syncthreads();
   const int nslot = (p + 3) >> 2;
@@ -368,22 +363,22 @@ __device__ __forceinline__ int sturm_count(const dd2* __restrict__ de, int p, do
   return (int)c;
 }
 
-// Eigenvalues 0 .. nev-1 (ascending) of T into ev, G lanes to each: the
+// Eigenvalues 0 .. p-1 (ascending) of T into ev, G lanes to each: the
 // largest power of two (64 at most) with one point per thread.  More points
 // per thread shorten the search by less than they add to the count loop,
 // which one wave per SIMD runs at its instruction rate.  Every thread calls
 // it.
-__device__ __forceinline__ void blk_multisection(const dd2* de, int p, int nev, double gl, double gu, double tnorm,
+__device__ __forceinline__ void blk_multisection(const dd2* de, int p, double gl, double gu, double tnorm,
                                                  double* ev) {
   int G = 64;
-  while (G > 1 && G * nev > kEigThreads) G >>= 1;
+  while (G > 1 && G * p > kEigThreads) G >>= 1;
   const int lane = threadIdx.x & 63;
   const int t = lane & (G - 1), gi = (int)threadIdx.x / G;
   const uint64_t gmask = (G == 64) ? ~0ull : (((1ull << G) - 1ull) << (lane & ~(G - 1)));
   const double inv = 1.0 / (double)(G + 1), tp = (double)(t + 1);
-  for (int j0 = 0; j0 < nev; j0 += kEigThreads / G) {
+  for (int j0 = 0; j0 < p; j0 += kEigThreads / G) {
     const int j = j0 + gi;
-    bool act = j < nev;
+    bool act = j < p;
     double lo = gl, hi = gu;
     for (int round = 0; round < 256; ++round) {
       const double w = hi - lo;
@@ -400,7 +395,7 @@ __device__ __forceinline__ void blk_multisection(const dd2* de, int p, int nev, 
         hi = nhi;
       }
     }
-    if (t == 0 && j < nev) ev[j] = lo + 0.5 * (hi - lo);
+    if (t == 0 && j < p) ev[j] = lo + 0.5 * (hi - lo);
   }
 }
 
@@ -614,16 +609,16 @@ __device__ __forceinline__ bool blk_cholqr(double* Z, int ldz, int p, int n, dou
 // rows per lane, four vectors per wave; reflector k - 1 is loaded while
 // reflector k is applied (PACK: from the packed store)
 template <int NT, bool PACK>
-__device__ __forceinline__ void blk_backtransform(double* Z, int ldz, int p, int nev, const double* vref,
+__device__ __forceinline__ void blk_backtransform(double* Z, int ldz, int p, const double* vref,
                                                   const double* beta) {
   const int lane = threadIdx.x & 63, s = lane & 15;
-  for (int jb = 0; jb < nev; jb += 16) {
+  for (int jb = 0; jb < p; jb += 16) {
     const int j = jb + 4 * wave_id() + (lane >> 4);
     double z[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
       const int i = s + 16 * t;
-      z[t] = (i < p && j < nev) ? Z[i * ldz + j] : 0.0;
+      z[t] = (i < p && j < p) ? Z[i * ldz + j] : 0.0;
     }
     double v[NT], b = 0.0;
     auto load = [&](int k) {
@@ -652,17 +647,16 @@ __device__ __forceinline__ void blk_backtransform(double* Z, int ldz, int p, int
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
       const int i = s + 16 * t;
-      if (i < p && j < nev) Z[i * ldz + j] = z[t];
+      if (i < p && j < p) Z[i * ldz + j] = z[t];
     }
   }
   __syncthreads();
 }
 
-// The whole path (1-5) on a (device, p x p) scaled by ds (LDS) from both
-// sides; base: LDS laid out by tri_layout(p, nev), whose ev and Z receive the
-// result.  Every thread of a kEigThreads workgroup calls it; the return value
-// is uniform.
-__device__ __forceinline__ bool blk_tri_eigh(const double* __restrict__ a, int p, int nev, const double* ds, double* base,
+// The whole path (1-5) on a (device, p x p); base: LDS laid out by
+// tri_layout(p), whose ev and Z receive the result.  Every thread of a
+// kEigThreads workgroup calls it; the return value is uniform.
+__device__ __forceinline__ bool blk_tri_eigh(const double* __restrict__ a, int p, double* base,
                              const TriLayout& L) {
   double* d = base + L.d;
   double* e = base + L.e;
@@ -673,9 +667,9 @@ __device__ __forceinline__ bool blk_tri_eigh(const double* __restrict__ a, int p
   dd2* de = reinterpret_cast<dd2*>(base + L.de);
   const int ldz = L.ldz;
   const int lane = threadIdx.x & 63;
-  if (p <= 48) reg_tridiag<1, 12>(a, p, ds, d, e, beta, vref, base + L.lu);
-  else if (p <= 64) reg_tridiag<1, 16>(a, p, ds, d, e, beta, vref, base + L.lu);
-  else reg_tridiag<2, 24>(a, p, ds, d, e, beta, vref, base + L.lu);
+  if (p <= 48) reg_tridiag<1, 12>(a, p, d, e, beta, vref, base + L.lu);
+  else if (p <= 64) reg_tridiag<1, 16>(a, p, d, e, beta, vref, base + L.lu);
+  else reg_tridiag<2, 24>(a, p, d, e, beta, vref, base + L.lu);
   // Gershgorin interval and ||T||, by every wave
   double gl = -INFINITY, gu = -INFINITY;  // (gl holds -min)
   bool bad = false;
@@ -694,11 +688,11 @@ __device__ __forceinline__ bool blk_tri_eigh(const double* __restrict__ a, int p
   gu = wave_max(gu);
   double tnorm = fmax(fabs(gl), fabs(gu));
   if (tnorm == 0.0) {  // the zero matrix
-    for (int idx = threadIdx.x; idx < p * nev; idx += kEigThreads) {
-      const int i = idx / nev, j = idx - i * nev;
+    for (int idx = threadIdx.x; idx < p * p; idx += kEigThreads) {
+      const int i = idx / p, j = idx - i * p;
       Z[i * ldz + j] = (i == j) ? 1.0 : 0.0;
     }
-    for (int j = threadIdx.x; j < nev; j += kEigThreads) ev[j] = 0.0;
+    for (int j = threadIdx.x; j < p; j += kEigThreads) ev[j] = 0.0;
     __syncthreads();
     return true;
   }
@@ -728,8 +722,8 @@ __device__ __forceinline__ bool blk_tri_eigh(const double* __restrict__ a, int p
     if (i < p + 16) de[i] = (i < p) ? dd2{di, fmax(em * em, 0x1.0p-120)} : dd2{4.0, 0x1.0p-120};
   }
   // start vectors
-  for (int idx = threadIdx.x; idx < p8 * nev; idx += kEigThreads) {
-    const int i = idx / nev, j = idx - i * nev;
+  for (int idx = threadIdx.x; idx < p8 * p; idx += kEigThreads) {
+    const int i = idx / p, j = idx - i * p;
     if (i >= p) {
       Z[i * ldz + j] = 0.0;
       continue;
@@ -738,7 +732,7 @@ __device__ __forceinline__ bool blk_tri_eigh(const double* __restrict__ a, int p
     Z[i * ldz + j] = (double)(z >> 11) * 0x1.0p-52 - 1.0;
   }
   __syncthreads();
-  blk_multisection(de, p, nev, gl, gu, tnorm, ev);
+  blk_multisection(de, p, gl, gu, tnorm, ev);
   __syncthreads();
   // two solves with a Cholesky-QR between them (block inverse iteration;
   // with several batches the LU is rebuilt for the second solve), the
@@ -750,23 +744,23 @@ __device__ __forceinline__ bool blk_tri_eigh(const double* __restrict__ a, int p
   uint64_t sw0 = 0, sw1 = 0;
   for (int stage = 0; stage < 3; ++stage) {
     if (stage < 2) {
-      for (int j0 = 0; j0 < nev; j0 += nb) {
+      for (int j0 = 0; j0 < p; j0 += nb) {
         const int t = threadIdx.x, j = j0 + t;
-        if (t < nb && j < nev) {
+        if (t < nb && j < p) {
           double *u0 = lu + t, *u1 = u0 + p8 * nb, *lm = u1 + p8 * nb;
-          if (stage == 0 || nb < nev) tri_invit_solve<true>(d, e, p, ev[j], tol, Z, ldz, j, u0, u1, lm, nb, sw0, sw1);
+          if (stage == 0 || nb < p) tri_invit_solve<true>(d, e, p, ev[j], tol, Z, ldz, j, u0, u1, lm, nb, sw0, sw1);
           else tri_invit_solve<false>(d, e, p, ev[j], tol, Z, ldz, j, u0, u1, lm, nb, sw0, sw1);
         }
         __syncthreads();
       }
     }
     if (stage == 1) {
-      if (p <= 48) blk_backtransform<3, false>(Z, ldz, p, nev, vref, beta);
-      else if (p <= 64) blk_backtransform<4, false>(Z, ldz, p, nev, vref, beta);
-      else blk_backtransform<6, true>(Z, ldz, p, nev, vref, beta);
-      for (int j = threadIdx.x; j < nev; j += kEigThreads) ev[j] = __builtin_amdgcn_ldexp(ev[j], -ex);
+      if (p <= 48) blk_backtransform<3, false>(Z, ldz, p, vref, beta);
+      else if (p <= 64) blk_backtransform<4, false>(Z, ldz, p, vref, beta);
+      else blk_backtransform<6, true>(Z, ldz, p, vref, beta);
+      for (int j = threadIdx.x; j < p; j += kEigThreads) ev[j] = __builtin_amdgcn_ldexp(ev[j], -ex);
     }
-    if (!blk_cholqr(Z, ldz, p, nev, base + L.orth)) return false;
+    if (!blk_cholqr(Z, ldz, p, p, base + L.orth)) return false;
   }
   return true;
 }
@@ -778,11 +772,8 @@ __global__ __launch_bounds__(kEigThreads) void k_small_eigh(const double* __rest
                                                             double* __restrict__ evecs, int* sweeps) {
   extern __shared__ __attribute__((aligned(16))) double smem[];
   __shared__ JacobiLds J;
-  __shared__ double ds[kMaxP];
-  for (int i = threadIdx.x; i < p; i += kEigThreads) ds[i] = 1.0;
-  __syncthreads();
-  const TriLayout T = tri_layout(p, p);
-  if (blk_tri_eigh(a, p, p, ds, smem, T)) {
+  const TriLayout T = tri_layout(p);
+  if (blk_tri_eigh(a, p, smem, T)) {
     for (int idx = threadIdx.x; idx < p * p; idx += kEigThreads) {
       const int i = idx / p, j = idx - i * p;
       const double sg = (smem[T.Z + j * T.ldz + j] < 0.0) ? -1.0 : 1.0;
@@ -796,7 +787,7 @@ __global__ __launch_bounds__(kEigThreads) void k_small_eigh(const double* __rest
   const int ld = p + 1;
   double* A = smem;
   double* V = smem + p * ld;
-  load_sym(a, p, ds, A, ld);
+  load_sym(a, p, A, ld);
   const int sw = blk_jacobi<kEigThreads>(A, ld, V, ld, p, J.cs, J.pr, J.flags, J.scratch);
   blk_sort_evals(A, ld, p, J.perm);
   for (int idx = threadIdx.x; idx < p * p; idx += kEigThreads) {

@@ -21,39 +21,43 @@ constexpr double kShiftAlpha0 = 100.0;
 constexpr double kShiftGrowth = 10.0;
 constexpr int kShiftRetries = 20;
 
-// Cholesky of an n x n symmetric matrix (n <= 16) held by one wave in
-// registers: lane l keeps column c = l & 15, rows r = (l >> 4) + 4 t
-// (t = 0..3), in g[t]; only r >= c is read, and rows or columns from n to 15
-// are those of the identity.  Right-looking, column by column: the pivot is
-// read from its lane, column k of L is formed in its four lanes and handed
-// to the others by lane shuffles, then the trailing entries are updated.
-// Every entry takes the same operations in the same order as the LDS
-// factorizations: G[r][k] / l_kk (KDIV) or G[r][k] * (1 / l_kk), and
-// G[r][c] - L[r][k] L[c][k] as one fused multiply-add.  On return g holds L
-// (diagonal included).  False, uniform over the wave, when a pivot is not
-// > 0 (or, with CHECKINF, not finite); linv (LDS, may be null) receives
-// 1 / l_kk when !KDIV.
-template <bool KDIV, bool CHECKINF>
-__device__ __forceinline__ bool reg_chol16(double (&g)[4], int n, double* linv) {
+// L = chol(S + shift I) for the n x n (n <= 16) matrix S in LDS by one wave (all
+// 64 lanes), written to L in LDS with zeros above the diagonal.  Lane l keeps
+// column c = l & 15, rows r = (l >> 4) + 4 t (t = 0..3), in g[t]; only r >= c is
+// read, and rows or columns from n to 15 are those of the identity.
+// Right-looking, column by column: the pivot is read from its lane, column k of L
+// is formed in its four lanes and handed to the others by lane shuffles, then the
+// trailing entries are updated.  Every entry takes the operations of the LDS
+// factorization in its order: G[r][k] / l_kk, and G[r][c] - L[r][k] L[c][k] as one
+// fused multiply-add.  False (uniform) on a pivot that is not > 0.
+__device__ __forceinline__ bool wave_chol16(const double* S, int lds_, int n, double shift, double* L, int ldl) {
   const int l = threadIdx.x & 63, c = l & 15, rb = l >> 4;
+  double g[4];
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    const int r = rb + 4 * t;
+    g[t] = (r < n && c < n) ? ((r >= c) ? S[r * lds_ + c] + (r == c ? shift : 0.0) : 0.0)
+                            : (r == c ? 1.0 : 0.0);
+  }
+  bool ok = true;
   for (int k = 0; k < n; ++k) {
     // register k >> 2 of lane k + 16 (k & 3) (a select: no indexed registers)
     const int tk = k >> 2;
     const double gk = (tk == 0) ? g[0] : (tk == 1) ? g[1] : (tk == 2) ? g[2] : g[3];
     const double gkk = readlane_f64(gk, k + 16 * (k & 3));
-    if (!(gkk > 0.0)) return false;
-    if (CHECKINF && !(gkk < INFINITY)) return false;
+    if (!(gkk > 0.0)) {
+      ok = false;
+      break;
+    }
     const double lkk = sqrt(gkk);
-    const double inv = KDIV ? 0.0 : 1.0 / lkk;
     if (c == k) {
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
         const int r = rb + 4 * t;
-        if (r > k) g[t] = KDIV ? g[t] / lkk : g[t] * inv;
+        if (r > k) g[t] = g[t] / lkk;
         else if (r == k) g[t] = lkk;
       }
     }
-    if (!KDIV && linv != nullptr && l == 0) linv[k] = inv;
     // lr[t] = L[rb + 4t][k] (lane k + 16 rb, register t); lc[t] from lane
     // k + 16 (c & 3): L[c][k] is its register c >> 2
     double lr[4], lc[4];
@@ -70,36 +74,10 @@ __device__ __forceinline__ bool reg_chol16(double (&g)[4], int n, double* linv) 
         if (rb + 4 * t >= c) g[t] = fma(-lr[t], lck, g[t]);
     }
   }
-  return true;
-}
-
-// One wave (all 64 lanes): L = chol(S + shift I) for the n x n (n <= 16)
-// matrix S in LDS (lower triangle read), written to L in LDS (lower
-// triangle; the strict upper one zeroed when ZUP).  wave_chol16_lds is the
-// out-of-line form, so that the large single-workgroup kernels keep their
-// own register budgets.  Returns false (uniform) on a pivot that is not > 0
-// (or, CHECKINF, not finite).
-template <bool KDIV, bool CHECKINF, bool ZUP>
-__device__ __forceinline__ bool wave_chol16_body(const double* S, int lds_, int n, double shift,
-                                                 double* L, int ldl, double* linv) {
-  const int l = threadIdx.x & 63, c = l & 15, rb = l >> 4;
-  double g[4];
 #pragma unroll
   for (int t = 0; t < 4; ++t) {
     const int r = rb + 4 * t;
-    g[t] = (r < n && c < n) ? ((r >= c) ? S[r * lds_ + c] + (r == c ? shift : 0.0) : 0.0)
-                            : (r == c ? 1.0 : 0.0);
-  }
-  const bool ok = reg_chol16<KDIV, CHECKINF>(g, n, linv);
-  if (ok || ZUP) {
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const int r = rb + 4 * t;
-      if (r < n && c < n) {
-        if (r >= c) L[r * ldl + c] = g[t];
-        else if (ZUP) L[r * ldl + c] = 0.0;
-      }
-    }
+    if (r < n && c < n) L[r * ldl + c] = (r >= c) ? g[t] : 0.0;
   }
   return ok;
 }
@@ -108,7 +86,7 @@ __device__ __forceinline__ bool wave_chol16_body(const double* S, int lds_, int 
 // lower triangle is read; rows and columns from n to N - 1 are those of the
 // identity).  The pivot is handed on by DPP, so a column costs a root, a
 // division, a product and an update in sequence (220 cycles; by lane shuffles
-// through LDS 1100).  Every entry takes the operations of reg_chol16 in its
+// through LDS 1100).  Every entry takes the operations of wave_chol16 in its
 // order: G[r][k] / l_kk (KDIV) or G[r][k] * (1 / l_kk), and
 // G[r][c] - L[r][k] L[c][k] as one fused multiply-add.  On return g holds L
 // and inv the reciprocals of its diagonal (!KDIV).  False, uniform, when a
@@ -332,19 +310,17 @@ __device__ __forceinline__ void blk_normalize(double* X, int ldx, int n, int q, 
 // Cholesky L L^T = M + shift I (lower, n x n); returns true on success.
 // Breaks down when a pivot is not > 0 (NaN included), like LAPACK potrf.
 // Every thread calls it and M must be complete on entry.  Wave 0 alone
-// factors (REG != 0 and n <= 16: in registers, by an out-of-line call in
-// the Rayleigh-Ritz kernel, whose register budget is full, inline in the
-// ortho controller; otherwise column by column in LDS with wave-level
-// syncs) while the other
-// waves wait at the closing barriers: two workgroup barriers per
-// factorization.  Each entry takes the same operations in the same order as
-// a column-parallel factorization by the whole workgroup.
-// REG: 0 column by column in LDS, 1 registers (out of line), 2 registers (inline)
+// factors (REG and n <= 16: in registers, in the ortho controller and the
+// Rayleigh-Ritz kernel with the Jacobi option; otherwise column by column in
+// LDS with wave-level syncs) while the other waves wait at the closing
+// barriers: two workgroup barriers per factorization.  Each entry takes the
+// same operations in the same order as a column-parallel factorization by the
+// whole workgroup.
 template <bool REG>
 __device__ __forceinline__ bool blk_chol(const double* M, int ldm, int n, double shift, double* L, int ldl,
                          int* flag) {
   if (REG && threadIdx.x < 64 && n <= 16) {
-    const bool ok = wave_chol16_body<true, false, true>(M, ldm, n, shift, L, ldl, nullptr);
+    const bool ok = wave_chol16(M, ldm, n, shift, L, ldl);
     if (threadIdx.x == 0) *flag = ok ? 0 : 1;
   } else if (threadIdx.x < 64) {
     const int l = threadIdx.x;
@@ -388,7 +364,7 @@ struct ShiftCount {
 // caller has tried the plain one, and failed.
 template <bool REG>
 __device__ __forceinline__ bool blk_shifted_chol(const double* M, int ldm, int n, double* L, int ldl, int* flag,
-                                 ShiftCount* c, double* scratch, int retries = kShiftRetries, bool plain = true) {
+                                 ShiftCount* c, int retries = kShiftRetries, bool plain = true) {
   if (threadIdx.x == 0) c->factorizations++;
   if (plain && blk_chol<REG>(M, ldm, n, 0.0, L, ldl, flag)) return true;
   if (threadIdx.x == 0) c->failed++;
@@ -465,13 +441,6 @@ __device__ __forceinline__ EigLds eig_lds(double* smem, int p, int m) {
   L.perm = L.pr + 2 * 64;         // 128
   L.flags = L.perm + 128;         // 8
   return L;
-}
-__device__ __forceinline__ void load_sym(const double* a, int p, double* A, int lda) {
-  for (int idx = threadIdx.x; idx < p * p; idx += blockDim.x) {
-    const int i = idx / p, j = idx - i * p;
-    A[i * lda + j] = 0.5 * (a[i * p + j] + a[j * p + i]);
-  }
-  __syncthreads();
 }
 
 // ---------------------------------------------------------------------------
@@ -1484,7 +1453,7 @@ __global__ __launch_bounds__(JAC ? 1024 : kRrThreads) void k_small_rr(const doub
           __syncthreads();
         }
         if (ok) {
-        } else if (blk_shifted_chol<JAC>(M, na, na, Lc, na, L.flags, &cnt, L.scratch, kShiftRetries, JAC || na > 16)) {
+        } else if (blk_shifted_chol<JAC>(M, na, na, Lc, na, L.flags, &cnt, kShiftRetries, JAC || na > 16)) {
           blk_trsm_rt(X, ldx, p, na, Lc, na);
         } else {
           if (threadIdx.x == 0) cnt.svqb++;
@@ -1567,7 +1536,6 @@ __global__ __launch_bounds__(256) void k_small_chol(const double* __restrict__ M
                                                     double* __restrict__ Lout, int* info) {
   __shared__ double Ms[64 * 65];
   __shared__ double Ls[64 * 65];
-  __shared__ double scratch[16];
   __shared__ int flag;
   __shared__ ShiftCount cnt;
   if (threadIdx.x == 0) cnt.factorizations = cnt.failed = cnt.shifted = cnt.svqb = 0;
@@ -1576,7 +1544,7 @@ __global__ __launch_bounds__(256) void k_small_chol(const double* __restrict__ M
     Ms[i * 65 + j] = 0.5 * (M[i * p + j] + M[j * p + i]);
   }
   __syncthreads();
-  const bool ok = blk_shifted_chol<false>(Ms, 65, p, Ls, 65, &flag, &cnt, scratch);
+  const bool ok = blk_shifted_chol<false>(Ms, 65, p, Ls, 65, &flag, &cnt);
   for (int idx = threadIdx.x; idx < p * p; idx += blockDim.x) {
     const int i = idx / p, j = idx - i * p;
     Lout[idx] = ok ? Ls[i * 65 + j] : 0.0;
@@ -1836,7 +1804,7 @@ __global__ __launch_bounds__(kCtlThreads) void k_ortho_ctl(const double* __restr
       __syncthreads();
     }
     if (!ok) {
-      ok = blk_shifted_chol<true>(Ms, ldm, nw, Ls, ldm, &flag, &cnt, scratch, st.shift_retries, nw > 16);
+      ok = blk_shifted_chol<true>(Ms, ldm, nw, Ls, ldm, &flag, &cnt, st.shift_retries, nw > 16);
       if (ok) blk_tri_inv(Ls, ldm, nw, Li, ldm);
     }
     if (ok) {

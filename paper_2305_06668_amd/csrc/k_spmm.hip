@@ -19,12 +19,12 @@
 
 namespace lobpcg {
 
-// G = lanes per stored entry (next power of two >= ncols); a row is owned by a
-// group of GS = max(G, 16) lanes, which holds NP = GS / G "slots" that take
-// stored entries in turn.  The group loads its row's (col, val) pairs in
-// chunks of GS (one per lane, coalesced), four chunks up front, broadcasts
-// them with __shfl, and issues all gathers of a chunk before accumulating.
-// Slot partial sums are combined with xor shuffles at the end.
+// G = lanes per stored entry (1, 2, 4 or 8 >= ncols); a row is owned by a group
+// of 16 lanes, which holds NP = 16 / G "slots" that take stored entries in turn.
+// The group loads its row's (col, val) pairs in chunks of 16 (one per lane,
+// coalesced), two or four chunks up front, broadcasts them with __shfl, and issues
+// all gathers of a pass (G = 8: of a chunk) before accumulating.  Slot partial
+// sums are combined with xor shuffles at the end.
 template <typename TV, typename TW, int G>
 __global__ __launch_bounds__(256) void k_spmm_csr(const int32_t* __restrict__ rp,
                                                   const int32_t* __restrict__ ci,
@@ -32,7 +32,7 @@ __global__ __launch_bounds__(256) void k_spmm_csr(const int32_t* __restrict__ rp
                                                   const TW* __restrict__ W, int64_t ldw,
                                                   TW* __restrict__ Y, int64_t ldy, int ncols,
                                                   int64_t n, int per_xcd) {
-  constexpr int GS = (G < 16) ? 16 : G;
+  constexpr int GS = 16;
   constexpr int NP = GS / G;
   constexpr int RPB = 256 / GS;
   // narrow blocks (G <= 2) take four chunks per pass: a row's entries then
@@ -85,21 +85,17 @@ __global__ __launch_bounds__(256) void k_spmm_csr(const int32_t* __restrict__ rp
     for (int k = 0; k < NCH; ++k) {
       const int base_e = e + k * GS;
       if (base_e >= e1) break;
-      constexpr int UB = (G < 8) ? G : 8;  // gathers in flight per batch
+      TW w[G];
+      TV vv[G];
 #pragma unroll
-      for (int u0 = 0; u0 < G; u0 += UB) {
-        TW w[UB];
-        TV vv[UB];
-#pragma unroll
-        for (int u = 0; u < UB; ++u) {
-          const int t = slot + NP * (u0 + u);
-          const int cidx = __shfl(colr[k], gbase + t, 64);
-          vv[u] = __shfl(vr[k], gbase + t, 64);
-          w[u] = (active && base_e + t < e1) ? W[(int64_t)cidx * ldw + c] : TW(0);
-        }
-#pragma unroll
-        for (int u = 0; u < UB; ++u) acc += (TW)vv[u] * w[u];
+      for (int u = 0; u < G; ++u) {
+        const int t = slot + NP * u;
+        const int cidx = __shfl(colr[k], gbase + t, 64);
+        vv[u] = __shfl(vr[k], gbase + t, 64);
+        w[u] = (active && base_e + t < e1) ? W[(int64_t)cidx * ldw + c] : TW(0);
       }
+#pragma unroll
+      for (int u = 0; u < G; ++u) acc += (TW)vv[u] * w[u];
     }
   }
 #pragma unroll
@@ -111,8 +107,7 @@ template <typename TV, typename TW, int G>
 static hipError_t spmm_launch(const int32_t* rp, const int32_t* ci, const TV* val, const TW* W,
                               int64_t ldw, TW* Y, int64_t ldy, int ncols, int64_t n,
                               hipStream_t s) {
-  constexpr int GS = (G < 16) ? 16 : G;
-  constexpr int RPB = 256 / GS;
+  constexpr int RPB = 256 / 16;
   const int64_t nb = (n + RPB - 1) / RPB;
   const int64_t nbp = (nb + 7) / 8 * 8;
   hipLaunchKernelGGL((k_spmm_csr<TV, TW, G>), dim3((unsigned)nbp), dim3(256), 0, s, rp, ci, val,
