@@ -31,8 +31,8 @@ struct Layout {
   size_t kpack = 0;  // Kronecker operator: n x 8 packed copy of a W block
   size_t cwin = 0;   // CSR operator: column window per block of the banded path (+ a flag)
   size_t dscr = 0;   // block Davidson: n x m scratch for the explicit product A X
-  // tridiagonal preconditioner: off-diagonal, row off-sums, forward factors,
-  // chunk boundary data
+  // tridiagonal preconditioner: off-diagonal, row off-sums, the interfaces of
+  // the groups of rows (scr: of more groups than the others hold)
   size_t tri_e = 0, tri_off = 0, tri_scr = 0, tri_bnd = 0, tri_xb = 0;
   // generalized problem: B V (double-buffered like V) and diag(B)
   size_t BV[2] = {0, 0}, bdiag = 0;

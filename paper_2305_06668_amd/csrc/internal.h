@@ -205,11 +205,15 @@ hipError_t vec_max_abs(const double* x, int64_t len, double* part, double* out, 
 
 // ---- tridiagonal preconditioner (k_tri.hip) ------------------------------
 constexpr int kTriMaxChunks = 1024;  // groups of rows whose interfaces bnd and xb hold
+// doubles of scr, which holds those of more groups (8 per column and group of at
+// least 256 rows)
+inline size_t tri_scratch(int64_t n, int nact) {
+  return n > (int64_t)kTriMaxChunks * 256 ? (size_t)(n / 256 + 1) * 8 * nact : 0;
+}
 // In place: R[:, 0:nact] (ld) <- T_j^-1 R[:, j], T_j = tridiag(e, t, e) with
 // t_i = max(|d_i - theta_j|, off_i + delta_j).  e: n values (e[n-1] = 0),
 // off_i = |e_{i-1}| + |e_i|; bnd: 6 kTriMaxChunks nact doubles, xb: 2
-// kTriMaxChunks nact doubles; scr: n nact doubles (used for n beyond
-// 256 kTriMaxChunks).
+// kTriMaxChunks nact doubles; scr: tri_scratch(n, nact) doubles.
 hipError_t tri_apply_f64(double* R, int64_t ld, int nact, int64_t n, const double* theta,
                          const double* d, const double* e, const double* off, double* bnd,
                          double* xb, double* scr, hipStream_t s);

@@ -379,11 +379,9 @@ hipError_t tri_apply_any(T* R, int64_t ld, int nact, int64_t n, const double* th
                          const double* e, const double* off, double* bnd, double* xb, double* scr,
                          hipStream_t s) {
   if (n < 1 || nact < 1 || nact > 64 || ld < nact) return hipErrorInvalidValue;
-  // the interfaces of more groups than bnd and xb hold go to scr (n nact
-  // doubles against 8 nact per group of at least 256 rows)
-  if (n > (int64_t)kTriMaxChunks * 256) {
+  if (tri_scratch(n, nact) > 0) {
     bnd = scr;
-    xb = scr + n / 256 * 6 * nact + 6 * nact;
+    xb = scr + (n / 256 + 1) * 6 * nact;
   }
   if (nact <= 4) return tri_rows<T, 4>(R, ld, nact, n, theta, d, e, off, bnd, xb, s);
   if (nact <= 8) return tri_rows<T, 8>(R, ld, nact, n, theta, d, e, off, bnd, xb, s);

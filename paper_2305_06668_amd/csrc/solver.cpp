@@ -70,9 +70,9 @@ Layout lobpcg_ctx::plan(int m, int prec) const {
   if (pkind == LOBPCG_PRECOND_TRIDIAG) {
     L.tri_e = take((size_t)n * sizeof(double));
     L.tri_off = take((size_t)n * sizeof(double));
-    L.tri_scr = take((size_t)n * std::max(m, 1) * sizeof(double));
+    L.tri_scr = take(tri_scratch(n, std::max(m, 1)) * sizeof(double));
     L.tri_bnd = take((size_t)kTriMaxChunks * kMaxBlock * 6 * sizeof(double));
-    L.tri_xb = take((size_t)kTriMaxChunks * kMaxBlock * 6 * sizeof(double));
+    L.tri_xb = take((size_t)kTriMaxChunks * kMaxBlock * 2 * sizeof(double));
   }
   L.ltiles = take((size_t)ltiles_cap() * sizeof(int));
   if (op == kOpKron) L.kpack = take((size_t)n * 8 * sizeof(double));
