@@ -204,6 +204,118 @@ __global__ __launch_bounds__(256) void k_dense(const T* __restrict__ A, int64_t 
   }
 }
 
+// Two or four fp64 columns of a compact block (W rows of 16 bytes, aligned as
+// A's are): a wave owns eight rows, a lane two adjacent columns of A per step,
+// so that a W row fetched serves eight rows of A.  A is read with the
+// non-temporal hint: past the 256 MB of the memory-side cache a part of it is
+// then found there by the next product (n = 8192, 4 columns: 86 us, 117
+// without; 10000: 196, 215).
+template <int MC>
+__global__ __launch_bounds__(256) void k_dense_vec(const double* __restrict__ A, int64_t lda,
+                                                   const double* __restrict__ W, int64_t ldw,
+                                                   double* __restrict__ Y, int64_t ldy, int64_t n) {
+  constexpr int R = 8;
+  typedef double __attribute__((ext_vector_type(2))) V;
+  const int lane = threadIdx.x & 63;
+  const int64_t r0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * R;
+  if (r0 >= n) return;
+  double acc[R][MC];
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+#pragma unroll
+    for (int j = 0; j < MC; ++j) acc[r][j] = 0.0;
+  const double* arow[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) arow[r] = A + min(r0 + r, n - 1) * lda;
+  const int64_t nfull = n & ~(int64_t)127;
+#pragma unroll 1
+  for (int64_t c = 2 * lane; c < nfull; c += 128) {
+    V a[R], w[2][MC / 2];
+#pragma unroll
+    for (int r = 0; r < R; ++r) a[r] = __builtin_nontemporal_load(reinterpret_cast<const V*>(arow[r] + c));
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+#pragma unroll
+      for (int q = 0; q < MC / 2; ++q) w[e][q] = *reinterpret_cast<const V*>(W + (c + e) * ldw + 2 * q);
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+      for (int e = 0; e < 2; ++e)
+#pragma unroll
+        for (int j = 0; j < MC; ++j) acc[r][j] += a[r][e] * w[e][j / 2][j % 2];
+  }
+  for (int64_t c = nfull + lane; c < n; c += 64) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const double a = arow[r][c];
+#pragma unroll
+      for (int j = 0; j < MC; ++j) acc[r][j] += a * W[c * ldw + j];
+    }
+  }
+  double mine = 0.0;
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+#pragma unroll
+    for (int j = 0; j < MC; ++j) {
+      double v = acc[r][j];
+#pragma unroll
+      for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off);
+      if (lane == r * MC + j) mine = v;
+    }
+  const int r = lane / MC, j = lane % MC;
+  if (r < R && r0 + r < n) Y[(r0 + r) * ldy + j] = mine;
+}
+
+template <typename T, int R, int MC>
+static void dense_scalar(const T* A, int64_t lda, const T* W, int64_t ldw, T* Y, int64_t ldy, int nc, int64_t n,
+                         hipStream_t s) {
+  hipLaunchKernelGGL((k_dense<T, R, MC>), dim3(cdiv(cdiv(n, R), 4)), dim3(256), 0, s, A, lda, W, ldw, Y, ldy, nc, n);
+}
+
+// Up to four fp64 columns whose rows lie close together (ldw <= 4): the MFMA
+// kernel multiplies 16 columns whatever their number, and its workgroups of 32
+// rows are more than one but fewer than two to a CU between n = 8192 and
+// 16384.  False: no launch, the MFMA kernel is the faster one.  us at n, as
+// launched here and by the MFMA kernel:
+//   1 column    1500: 8.2, 11.0   5000: 35, 52   9000: 126, 185   12000: 192, 259   20000: 547, 622
+//   2 columns   1500: 8.2, 11.2   5000: 48, 52   9000: 146, 185   12000: 200, 259   20000: 518, 623
+//   3 columns   1500: 8.1, 11.1   5000: 40, 52   9000: 156, 186   14000: 287, 305   (7000: 89, 81)
+//   4 columns   1500: 8.8, 11.1   5000: 47, 52   9000: 180, 186   16000: 344, 360   8192: 86, 117
+static bool dense_few(const double* A, int64_t lda, const double* W, int64_t ldw, double* Y, int64_t ldy, int nc,
+                      int64_t n, hipStream_t s) {
+  if (n < 1800) {  // two rows to a wave: enough waves
+    if (nc == 1) dense_scalar<double, 2, 1>(A, lda, W, ldw, Y, ldy, nc, n, s);
+    else if (nc == 2) dense_scalar<double, 2, 2>(A, lda, W, ldw, Y, ldy, nc, n, s);
+    else if (nc == 3) dense_scalar<double, 2, 3>(A, lda, W, ldw, Y, ldy, nc, n, s);
+    else dense_scalar<double, 2, 4>(A, lda, W, ldw, Y, ldy, nc, n, s);
+    return true;
+  }
+  if (n < 16 * 256) return false;
+  const bool vec = lda % 2 == 0 && ldw % 2 == 0 && reinterpret_cast<uintptr_t>(A) % 16 == 0 &&
+                   reinterpret_cast<uintptr_t>(W) % 16 == 0;
+  const int grid8 = cdiv(cdiv(n, 8), 4);
+  if (vec && nc == 4)
+    hipLaunchKernelGGL(k_dense_vec<4>, dim3(grid8), dim3(256), 0, s, A, lda, W, ldw, Y, ldy, n);
+  else if (vec && nc == 2)
+    hipLaunchKernelGGL(k_dense_vec<2>, dim3(grid8), dim3(256), 0, s, A, lda, W, ldw, Y, ldy, n);
+  else if (nc == 1 && n < 12500)
+    dense_scalar<double, 4, 1>(A, lda, W, ldw, Y, ldy, nc, n, s);
+  else if (nc == 1)  // (fewer waves in flight keep more of W in L2: 1 column by <4, 1> at 20000 602 us)
+    dense_scalar<double, 4, 4>(A, lda, W, ldw, Y, ldy, nc, n, s);
+  else if (nc == 2 && n < 12500)
+    dense_scalar<double, 4, 2>(A, lda, W, ldw, Y, ldy, nc, n, s);
+  else if (nc == 3 && (n < 5800 || (n > 8192 && n < 12500)))
+    dense_scalar<double, 4, 3>(A, lda, W, ldw, Y, ldy, nc, n, s);
+  else if (nc == 3 && n >= 12500 && n <= 16384)
+    dense_scalar<double, 8, 3>(A, lda, W, ldw, Y, ldy, nc, n, s);
+  else
+    return false;
+  return true;
+}
+static bool dense_few(const float*, int64_t, const float*, int64_t, float*, int64_t, int, int64_t, hipStream_t) {
+  return false;  // (1500: 8.7 us by the MFMA kernel and 8.1 by scalar products, 12000: 108 and 125)
+}
+
 template <typename T>
 static hipError_t dense_any(const T* A, int64_t lda, const T* W, int64_t ldw, T* Y, int64_t ldy,
                             int ncols, int64_t n, hipStream_t s) {
@@ -218,7 +330,9 @@ static hipError_t dense_any(const T* A, int64_t lda, const T* W, int64_t ldw, T*
   const bool odd = sizeof(T) == 8 && (lda % 2 != 0 || reinterpret_cast<uintptr_t>(A) % 16 != 0);
   for (int c0 = 0; c0 < ncols; c0 += 16) {
     const int nc = std::min(16, ncols - c0);
-    if (odd && nc <= 4 && n >= 16 * 256)
+    if (nc <= 4 && ldw <= 4 && dense_few(A, lda, W + c0, ldw, Y + c0, ldy, nc, n, s))
+      ;
+    else if (odd && nc <= 4 && n >= 16 * 256)
       hipLaunchKernelGGL((k_dense<T, 4, 4>), dim3(cdiv(cdiv(n, 4), 4)), dim3(256), 0, s, A, lda, W + c0, ldw, Y + c0,
                          ldy, nc, n);
     else if (n < 16 * 256)

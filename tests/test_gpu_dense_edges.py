@@ -49,3 +49,27 @@ def test_dense_edges(P, n, pad, m, ldw, q, prec):
     assert bool(((Y[:, q : q + m].double() - Ad @ Wd).abs() <= bound).all())
     assert bool((Y[:, :q] == 5.0).all()) and bool((Y[:, q + m :] == 5.0).all())  # other columns untouched
     s.close()
+
+
+@pytest.mark.parametrize("n,pad", [(1, 0), (2, 1), (7, 0), (127, 1), (128, 0), (1799, 0), (1800, 0), (4095, 1), (4096, 0), (4099, 1), (5799, 0), (8193, 1), (8194, 0), (12499, 1), (12502, 0), (16386, 0)])
+def test_dense_few_columns(P, n, pad):
+    """Up to four columns of a block whose rows lie close together: the sizes,
+    row alignments, widths and offsets between which the kernel changes."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    A = torch.randn((n, n + pad), generator=g, device="cuda", dtype=torch.float64)
+    Ad = A[:, :n].contiguous()
+    Aa = Ad.abs()
+    s = P.Solver(n)
+    s.set_operator_dense(A[:, :n])
+    for m, ldw, q in [(1, 1, 0), (1, 4, 3), (2, 2, 0), (2, 3, 1), (2, 4, 1), (2, 4, 2), (3, 3, 0), (3, 4, 1), (4, 4, 0), (4, 5, 1)]:
+        print("dense few", n, pad, m, ldw, q, flush=True)
+        W = torch.randn((n, ldw), generator=g, device="cuda", dtype=torch.float64)
+        Y = torch.full((n, ldw + 1), 5.0, dtype=torch.float64, device="cuda")
+        P.lobpcg_apply_operator(s.h, W[:, q : q + m], Y[:, q : q + m])
+        Wd = W[:, q : q + m].contiguous()
+        bound = (n + 1) * 2.0**-53 * (Aa @ Wd.abs())
+        # (the oracle's own products round too: as much again)
+        assert bool(((Y[:, q : q + m] - Ad @ Wd).abs() <= 2 * bound).all())
+        assert bool((Y[:, :q] == 5.0).all()) and bool((Y[:, q + m :] == 5.0).all())  # other columns untouched
+    s.close()
