@@ -27,6 +27,10 @@ static inline int cdiv(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 // lane (g, c) is W[k][c] of the same k, columns past ncols being copies of the
 // last one that are not stored.  The next chunk is loaded while the current
 // one is multiplied.  Loads need element alignment only.
+// SPREAD: workgroup b begins 37 b strides of the workgroup further along its
+// rows (and wraps at their end), so that the workgroups, which run in step, do
+// not all read the same columns at a time: rows of 64 KB lie on the same
+// memory channels then.  A sum's additions are as many, in another order.
 // What bounds it: the read of A, once for up to 16 columns (n = 2e4 fp64: 630
 // us = 5.1 TB/s, where a plain sum reads 6.0; 8 columns at a time by scalar
 // products, eight rows per wave: 664 us for 8, 1330 for 16); at small n the
@@ -57,7 +61,7 @@ __device__ __forceinline__ T tree_sum(T (&v)[N]) {
   return v[0];
 }
 
-template <typename T, int RT, int NW, int NA>
+template <typename T, int RT, int NW, int NA, bool SPREAD>
 __global__ __launch_bounds__(64 * NW) void k_dense_mfma(const T* __restrict__ A, int64_t lda,
                                                         const T* __restrict__ W, int64_t ldw,
                                                         T* __restrict__ Y, int64_t ldy, int ncols,
@@ -84,7 +88,14 @@ __global__ __launch_bounds__(64 * NW) void k_dense_mfma(const T* __restrict__ A,
     Vec a[RT][NI];
     T w[NI][VE];
   };
+  const int64_t nfull = n & ~(int64_t)(KC - 1);
+  constexpr int64_t step = KC * NW;
+  const int64_t first = SPREAD ? (int64_t)(blockIdx.x * 37 % (uint32_t)(nfull / step)) * step : 0;
   auto load = [&](Chunk& c, int64_t k0) {
+    if (SPREAD) {
+      k0 += first;
+      if (k0 >= nfull) k0 -= nfull;
+    }
 #pragma unroll
     for (int t = 0; t < RT; ++t)
 #pragma unroll
@@ -111,8 +122,6 @@ __global__ __launch_bounds__(64 * NW) void k_dense_mfma(const T* __restrict__ A,
         sum[t][e] += tree_sum(v);
       }
   };
-  const int64_t nfull = n & ~(int64_t)(KC - 1);
-  constexpr int64_t step = KC * NW;
   int64_t k = KC * wave;
   Chunk c0, c1;
   if (k < nfull) load(c0, k);
@@ -328,6 +337,11 @@ static hipError_t dense_any(const T* A, int64_t lda, const T* W, int64_t ldw, T*
   // load 8 bytes per lane, are faster then (n = 9001, 1 column: 135 against
   // 199 us, 4: 177 and 200, 8: 316 and 203; n = 777, 1 column: 9.4 and 8.9).
   const bool odd = sizeof(T) == 8 && (lda % 2 != 0 || reinterpret_cast<uintptr_t>(A) % 16 != 0);
+  // Workgroups apart: fp64 6016 rows, 16 columns 65 us, 67 in step; 8192: 98 and
+  // 108, compact 8 columns 96 and 114; 16320: 371 and 411; 20000: 657 and 644.
+  // fp32, 9000: 107 and 97; 14000: 174 and 203; 16320, 8 of 24 columns: 211 and
+  // 287; 20000, compact 8 columns: 320 and 315.
+  const bool spread = n >= (sizeof(T) == 8 ? 6000 : 13000) && n < 17000;
   for (int c0 = 0; c0 < ncols; c0 += 16) {
     const int nc = std::min(16, ncols - c0);
     if (nc <= 4 && ldw <= 4 && dense_few(A, lda, W + c0, ldw, Y + c0, ldy, nc, n, s))
@@ -336,14 +350,20 @@ static hipError_t dense_any(const T* A, int64_t lda, const T* W, int64_t ldw, T*
       hipLaunchKernelGGL((k_dense<T, 4, 4>), dim3(cdiv(cdiv(n, 4), 4)), dim3(256), 0, s, A, lda, W + c0, ldw, Y + c0,
                          ldy, nc, n);
     else if (n < 16 * 256)
-      hipLaunchKernelGGL((k_dense_mfma<T, 1, 8, 8>), dim3(cdiv(n, 16)), dim3(512), 0, s, A, lda, W + c0, ldw, Y + c0,
+      hipLaunchKernelGGL((k_dense_mfma<T, 1, 8, 8, false>), dim3(cdiv(n, 16)), dim3(512), 0, s, A, lda, W + c0, ldw, Y + c0,
                          ldy, nc, n);
+    else if (sizeof(T) == 8 && spread)
+      hipLaunchKernelGGL((k_dense_mfma<T, 2, 4, 2, true>), dim3(cdiv(n, 32)), dim3(256), 0, s, A, lda, W + c0, ldw,
+                         Y + c0, ldy, nc, n);
     else if (sizeof(T) == 8 && n >= 6000)
-      hipLaunchKernelGGL((k_dense_mfma<T, 2, 4, 2>), dim3(cdiv(n, 32)), dim3(256), 0, s, A, lda, W + c0, ldw, Y + c0,
-                         ldy, nc, n);
+      hipLaunchKernelGGL((k_dense_mfma<T, 2, 4, 2, false>), dim3(cdiv(n, 32)), dim3(256), 0, s, A, lda, W + c0, ldw,
+                         Y + c0, ldy, nc, n);
+    else if (spread)
+      hipLaunchKernelGGL((k_dense_mfma<T, 1, 4, 4, true>), dim3(cdiv(n, 16)), dim3(256), 0, s, A, lda, W + c0, ldw,
+                         Y + c0, ldy, nc, n);
     else
-      hipLaunchKernelGGL((k_dense_mfma<T, 1, 4, 4>), dim3(cdiv(n, 16)), dim3(256), 0, s, A, lda, W + c0, ldw, Y + c0,
-                         ldy, nc, n);
+      hipLaunchKernelGGL((k_dense_mfma<T, 1, 4, 4, false>), dim3(cdiv(n, 16)), dim3(256), 0, s, A, lda, W + c0, ldw,
+                         Y + c0, ldy, nc, n);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

@@ -73,3 +73,30 @@ def test_dense_few_columns(P, n, pad):
         assert bool(((Y[:, q : q + m] - Ad @ Wd).abs() <= 2 * bound).all())
         assert bool((Y[:, :q] == 5.0).all()) and bool((Y[:, q + m :] == 5.0).all())  # other columns untouched
     s.close()
+
+
+@pytest.mark.parametrize("prec,n,pad", [("f64", 6001, 0), ("f64", 6047, 1), ("f64", 8192, 0), ("f64", 16999, 0), ("f64", 17000, 0), ("f32", 12999, 0), ("f32", 13000, 0), ("f32", 13023, 1), ("f32", 16999, 0)])
+def test_dense_workgroups_apart(P, prec, n, pad):
+    """Sizes at which the workgroups begin at different columns of their rows."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    f32 = prec == "f32"
+    dt, u = (torch.float32, 2.0**-24) if f32 else (torch.float64, 2.0**-53)
+    A = torch.randn((n, n + pad), generator=g, device="cuda", dtype=torch.float64)
+    s = P.Solver(n)
+    s.set_operator_dense(A[:, :n])
+    if f32:
+        s.set_option(P.OPT_PRECISION, P.PREC_FP32)
+        s.ensure_workspace(1)
+    Ad = A[:, :n].to(dt).double().contiguous()
+    Aa = Ad.abs()
+    for m, ldw, q in [(5, 5, 0), (8, 24, 16), (17, 17, 0)]:
+        print("dense apart", prec, n, pad, m, ldw, q, flush=True)
+        W = torch.randn((n, ldw), generator=g, device="cuda", dtype=torch.float64).to(dt)
+        Y = torch.full((n, ldw + 1), 5.0, dtype=dt, device="cuda")
+        (P.lobpcg_apply_operator_f32 if f32 else P.lobpcg_apply_operator)(s.h, W[:, q : q + m], Y[:, q : q + m])
+        Wd = W[:, q : q + m].double().contiguous()
+        bound = (n + 1) * u * (Aa @ Wd.abs())
+        assert bool(((Y[:, q : q + m].double() - Ad @ Wd).abs() <= 2 * bound).all())
+        assert bool((Y[:, :q] == 5.0).all()) and bool((Y[:, q + m :] == 5.0).all())  # other columns untouched
+    s.close()
