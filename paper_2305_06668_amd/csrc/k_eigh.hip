@@ -765,13 +765,65 @@ __device__ __forceinline__ bool blk_tri_eigh(const double* __restrict__ a, int p
   return true;
 }
 
+// The same by Jacobi sweeps on all NT threads.
+template <int NT>
+__device__ __forceinline__ int jacobi_eigh(const double* __restrict__ a, int p, double* smem, JacobiLds& J,
+                                           double* __restrict__ evals, double* __restrict__ evecs) {
+  const int ld = p + 1;
+  double* A = smem;
+  double* V = smem + p * ld;
+  load_sym(a, p, A, ld);
+  const int sw = blk_jacobi<NT>(A, ld, V, ld, p, J.cs, J.pr, J.flags, J.scratch);
+  blk_sort_evals(A, ld, p, J.perm);
+  for (int idx = threadIdx.x; idx < p * p; idx += NT) {
+    const int i = idx / p, j = idx - i * p;
+    const double sg = (V[j * ld + J.perm[j]] < 0.0) ? -1.0 : 1.0;
+    evecs[i * p + j] = sg * V[i * ld + J.perm[j]];
+  }
+  for (int j = threadIdx.x; j < p; j += NT) evals[j] = A[J.perm[j] * ld + J.perm[j]];
+  return sw;
+}
+
 }  // namespace
 
+// By rotations alone: matrices of order 1 and 2 (6 us, 15 to 19 by the
+// tridiagonal path), and large ones that are diagonal up to rotations by 2^-25,
+// whose squares are then below rounding: one sweep and a look.  A sweep of 16
+// waves at p = 96 takes 80 us and the tridiagonal path 1160: p = 96, diagonal
+// 93 us, off-diagonal parts of 1e-8 340; p = 80 76 and 267 (580).  With larger
+// rotations two and three sweeps would still be the faster way, but the
+// cosines' rounding adds up in the vectors (orthonormal to 2e-14, by the
+// tridiagonal path to 6e-16).  What is left to that path is marked by a NaN in
+// evals[0], which no result here is.
+constexpr int kNearMinP = 77;
+__global__ __launch_bounds__(1024) void k_small_eigh_near(const double* __restrict__ a, int p,
+                                                          double* __restrict__ evals,
+                                                          double* __restrict__ evecs, int* sweeps) {
+  extern __shared__ __attribute__((aligned(16))) double smem[];
+  __shared__ JacobiLds J;
+  bool far = false;
+  for (int idx = threadIdx.x; p > 2 && idx < p * p; idx += 1024) {
+    const int i = idx / p, j = idx - i * p;
+    if (j <= i) continue;
+    const double s = 0.5 * fabs(a[i * p + j] + a[j * p + i]), di = a[i * p + i], dj = a[j * p + j];
+    far |= !(s <= 0x1.0p-25 * fabs(di - dj) || s <= 0x1.0p-53 * fmin(fabs(di), fabs(dj)));
+  }
+  if (__syncthreads_or(far)) {
+    if (threadIdx.x == 0) evals[0] = NAN;
+    return;
+  }
+  const int sw = jacobi_eigh<1024>(a, p, smem, J, evals, evecs);
+  if (threadIdx.x == 0 && sweeps != nullptr) *sweeps = sw;
+}
+
+// NEAR: after k_small_eigh_near, on what that one left
+template <bool NEAR>
 __global__ __launch_bounds__(kEigThreads) void k_small_eigh(const double* __restrict__ a, int p,
                                                             double* __restrict__ evals,
                                                             double* __restrict__ evecs, int* sweeps) {
   extern __shared__ __attribute__((aligned(16))) double smem[];
   __shared__ JacobiLds J;
+  if (NEAR && evals[0] == evals[0]) return;
   const TriLayout T = tri_layout(p);
   if (blk_tri_eigh(a, p, smem, T)) {
     for (int idx = threadIdx.x; idx < p * p; idx += kEigThreads) {
@@ -784,18 +836,7 @@ __global__ __launch_bounds__(kEigThreads) void k_small_eigh(const double* __rest
     return;
   }
   __syncthreads();
-  const int ld = p + 1;
-  double* A = smem;
-  double* V = smem + p * ld;
-  load_sym(a, p, A, ld);
-  const int sw = blk_jacobi<kEigThreads>(A, ld, V, ld, p, J.cs, J.pr, J.flags, J.scratch);
-  blk_sort_evals(A, ld, p, J.perm);
-  for (int idx = threadIdx.x; idx < p * p; idx += kEigThreads) {
-    const int i = idx / p, j = idx - i * p;
-    const double sg = (V[j * ld + J.perm[j]] < 0.0) ? -1.0 : 1.0;
-    evecs[i * p + j] = sg * V[i * ld + J.perm[j]];
-  }
-  for (int j = threadIdx.x; j < p; j += kEigThreads) evals[j] = A[J.perm[j] * ld + J.perm[j]];
+  const int sw = jacobi_eigh<kEigThreads>(a, p, smem, J, evals, evecs);
   if (threadIdx.x == 0 && sweeps != nullptr) *sweeps = sw;
 }
 
@@ -804,12 +845,20 @@ hipError_t small_eigh(const double* a, int p, double* evals, double* evecs, int*
   if (p < 1 || p > kMaxP) return hipErrorInvalidValue;
   static bool attr = false;
   if (!attr) {
-    (void)hipFuncSetAttribute((const void*)k_small_eigh, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              kEigLdsBytes);
+    for (const void* f : {(const void*)k_small_eigh<false>, (const void*)k_small_eigh<true>, (const void*)k_small_eigh_near})
+      (void)hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kEigLdsBytes);
     (void)hipGetLastError();
     attr = true;
   }
-  hipLaunchKernelGGL(k_small_eigh, dim3(1), dim3(kEigThreads), kEigLdsBytes, s, a, p, evals, evecs, sweeps);
+  // (a result written over the matrix would leave the second kernel none)
+  auto apart = [&](const double* x, int len) { return x + len <= a || a + p * p <= x; };
+  const bool near = p >= kNearMinP && apart(evals, p) && apart(evecs, p * p);
+  if (near || p <= 2)
+    hipLaunchKernelGGL(k_small_eigh_near, dim3(1), dim3(1024), kEigLdsBytes, s, a, p, evals, evecs, sweeps);
+  if (near)
+    hipLaunchKernelGGL(k_small_eigh<true>, dim3(1), dim3(kEigThreads), kEigLdsBytes, s, a, p, evals, evecs, sweeps);
+  else if (p > 2)
+    hipLaunchKernelGGL(k_small_eigh<false>, dim3(1), dim3(kEigThreads), kEigLdsBytes, s, a, p, evals, evecs, sweeps);
   return hipGetLastError();
 }
 

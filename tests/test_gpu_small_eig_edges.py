@@ -91,3 +91,28 @@ def test_small_eigh_fallback(P, p):
     assert np.abs(a @ Uh - Uh * lam).max() <= 1e-13 * nrm
     assert np.all(np.diag(Uh) >= 0)
     s.close()
+
+
+@pytest.mark.parametrize("off", [0.0, 1e-17, 1e-9, 1e-5, 1e-3, 0.02, 0.5])
+@pytest.mark.parametrize("p", [1, 2, 76, 77, 83, 84, 90, 96])
+def test_small_eigh_nearly_diagonal(P, p, off):
+    """Off-diagonal entries small against the distances on the diagonal, which
+    large matrices solve by rotations, on both sides of the choice; also in
+    place, where they do not.  The same bounds."""
+    print("small_eigh nearly diagonal", p, off, flush=True)
+    g = synth.rng(p)
+    a = np.diag(g.permutation(np.arange(p, dtype=float))) + off * synth.random_symmetric(p, p)
+    s = P.Solver(300)
+    for inplace in (False, True):
+        A = torch.from_numpy(a).cuda()
+        ev = torch.zeros(p, dtype=torch.float64, device="cuda")
+        U = A if inplace else torch.zeros((p, p), dtype=torch.float64, device="cuda")
+        P.lobpcg_small_eigh(s.h, A, ev, U)
+        lam, Uh = ev.cpu().numpy(), U.cpu().numpy()
+        nrm = np.linalg.norm(a, 2)
+        assert np.all(np.abs(lam - np.linalg.eigvalsh(a)) <= 1e-13 * nrm)
+        assert np.all(np.diff(lam) >= 0)
+        assert np.abs(Uh.T @ Uh - np.eye(p)).max() <= 1e-13
+        assert np.abs(a @ Uh - Uh * lam).max() <= 1e-13 * nrm
+        assert np.all(np.diag(Uh) >= 0)
+    s.close()
