@@ -245,8 +245,10 @@ __device__ __forceinline__ void screen_groups(float* L, int64_t gr, int64_t step
   constexpr int Q = 4;  // groups whose operands are under way together
   const int lane = threadIdx.x & 63, w = wave_id();
   const bool small = total < (int64_t)INT32_MAX;
+  // groups past the end: none active, and no pass for four of them
+  if (lane < kScreen && gr + lane * step >= ngroups) reinterpret_cast<int*>(L + gAct)[lane * kGroup + w] = 0;
 #pragma unroll 1
-  for (int b = 0; b < kScreen; b += Q) {
+  for (int b = 0; b < kScreen && gr + b * step < ngroups; b += Q) {
     int64_t row[Q];
     int col[Q];
     double dm[Q], th[Q], rr[Q];

@@ -57,3 +57,10 @@ def test_learned_apply_sizes(P, n, m):
         assert np.all(np.abs(W[~near, j] - ref[~near]) <= 1e-14 * np.abs(ref[~near])), j
         ref, _ = M.precondition(p, R[near, j], d[near], theta[j], rho[near], s_)
         assert np.all(np.abs(W[near, j] - ref) <= 1e-4 * np.abs(ref)), j
+
+
+@pytest.mark.parametrize("n,m", [(512 * 256, 1), (512 * 256 + 1, 1), (512 * 256 * 4, 1), (512 * 256 * 4 + 1, 1), (512 * 256 * 16 + 700, 1)])
+def test_learned_apply_group_counts(P, n, m):
+    """One group for every workgroup and one more, four and one more (the groups of
+    a pass), sixteen (all that are screened at once) and two more."""
+    test_learned_apply_sizes(P, n, m)
