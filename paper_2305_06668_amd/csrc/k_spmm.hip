@@ -8,7 +8,7 @@
 //     range in LDS): the fewest instructions and wave slots per gathered row,
 //     used from 5 (fp64) or 9 (fp32) columns;
 //   * k_spmm_csr (one column per lane, (col, val) broadcast by shuffles):
-//     narrow blocks.
+//     narrow blocks, and some misaligned ones (see spmm_any).
 // Row blocks are remapped so that each XCD (hardware dispatches block b to
 // XCD b % 8) walks one contiguous range of rows: a banded matrix then keeps
 // its W window inside that XCD's L2.
@@ -19,11 +19,11 @@
 
 namespace lobpcg {
 
-// G = lanes per stored entry (1, 2, 4 or 8 >= ncols); a row is owned by a group
+// G = lanes per stored entry (1, 2, 4, 8 or 16 >= ncols); a row is owned by a group
 // of 16 lanes, which holds NP = 16 / G "slots" that take stored entries in turn.
 // The group loads its row's (col, val) pairs in chunks of 16 (one per lane,
 // coalesced), two or four chunks up front, broadcasts them with __shfl, and issues
-// all gathers of a pass (G = 8: of a chunk) before accumulating.  Slot partial
+// all gathers of a pass (G >= 8: of a chunk) before accumulating.  Slot partial
 // sums are combined with xor shuffles at the end.
 template <typename TV, typename TW, int G>
 __global__ __launch_bounds__(256) void k_spmm_csr(const int32_t* __restrict__ rp,
@@ -483,7 +483,10 @@ static hipError_t spmm_stream_launch(const int32_t* rp, const int32_t* ci, const
   // (mean entries per row)
   constexpr int lo = G == 4 ? (F64 ? 14 : 18) : (F64 && G == 8) ? 30 : INT_MAX;
   constexpr int hi = F64 ? (G == 8 ? 138 : 176) : (G == 4 ? 240 : 288);
+  // (6000 to 9400 groups are one to two rounds of k_spmm_block's workgroups, the
+  // last one uneven: 23 fp32 columns, n = 7e4, 41 entries per row 27 : 29 us)
   const bool waves = (groups <= 16 * 256 && mean >= 14) || (mean >= lo && mean <= 45.5) ||
+                     (G == 8 && groups > 6000 && groups <= 9400 && mean > 20 && mean <= 45.5) ||
                      (F64 && G <= 8 && mean > 56 && !nt) || mean > hi;
   auto launch = [&](auto kernel, int64_t nb, int64_t units) {
     const unsigned grid = (unsigned)((nb + 7) / 8 * 8);
@@ -665,7 +668,21 @@ static hipError_t spmm_any(const int32_t* rp, const int32_t* ci, const TV* val, 
   // which adds the entries of a row in two sums, and where these are the end of
   // 33 to 40 they go to the former, which add in order: a solve that has not
   // converged amplifies rounding, so each product keeps its order of addition.
-  const bool odd = CPL == 2 && ((reinterpret_cast<uintptr_t>(W) % 16) != 0 || ldw % CPL != 0);
+  // Nine to sixteen misaligned fp32 columns of longer rows go to the latter too:
+  // a gather of theirs by four lanes touches two lines as often as not, one by
+  // sixteen lanes once (us, it : the others: 13 columns, n = 5e4, 41 entries per
+  // row 17.5 : 19.1, 60 24 : 30, 80 30 : 38; n = 1e5, 80 55 : 63; n = 2e5 103 :
+  // 110, but n = 3e5, 60 121 : 116, n = 25000, 80 17.7 : 16.9 and n = 1.4e5, 41 43 :
+  // 41; 9 columns, n = 5e4, 60 22.6 : 26.6; 10, n = 37000, 60 17.8 : 16.4, 80 22.3 :
+  // 23.5).
+  const bool mis = (reinterpret_cast<uintptr_t>(W) % 16) != 0 || ldw % CPL != 0;
+  const double mean = (double)nnz / (double)n;
+  auto longer = [&](int nc) {
+    if (n > 200000 || (n > 15000 && n < 30000)) return false;
+    if (nc >= 13 && n > 44000 && n < 110000) return mean > 24;
+    return mean > ((nc >= 13 || (n > 44000 && n <= 65536)) ? 45.5 : 70.0);
+  };
+  const bool odd = CPL == 2 && mis;
   const int wide_min = (CPL == 2) ? (odd ? 9 : 5) : 9;
   constexpr int slice = 16 * CPL;
   for (int c0 = 0; c0 < ncols; c0 += slice) {
@@ -678,7 +695,9 @@ static hipError_t spmm_any(const int32_t* rp, const int32_t* ci, const TV* val, 
     const TW* Wc = W + c;
     TW* Yc = Y + c;
     hipError_t e;
-    if (nc >= wide_min || tail) {
+    if (CPL == 4 && mis && nc > 8 && nc <= 16 && longer(nc)) {
+      e = spmm_launch<TV, TW, 16>(rp, ci, val, Wc, ldw, Yc, ldy, nc, n, s);
+    } else if (nc >= wide_min || tail) {
       const int lanes = (nc + CPL - 1) / CPL;
       if (lanes <= 4) e = spmm_stream_launch<TV, TW, 4>(rp, ci, val, Wc, ldw, Yc, ldy, nc, n, nnz, between, s);
       else if (lanes <= 8) e = spmm_stream_launch<TV, TW, 8>(rp, ci, val, Wc, ldw, Yc, ldy, nc, n, nnz, between, s);

@@ -146,3 +146,23 @@ def test_csr_misaligned_tail_bits(P, m):
         assert torch.equal(Y[:, a : a + 16], Z), (m, a)
     check(rp, ci, val, W[:, :m], Y[:, :m], 2.0**-53)
     assert bool((Y[:, m:] == 5.0).all())
+
+
+@pytest.mark.parametrize("n,mean,kind", [(12_000, 80, "even"), (5_003, 60, "uneven"), (9_001, 400, "few"), (15_001, 80, "even"), (30_001, 48, "uneven"), (44_003, 25, "even"), (65_537, 48, "even"), (109_999, 25, "uneven"), (75_001, 30, "even")])
+def test_csr_misaligned_f32(P, n, mean, kind):
+    """Nine to sixteen fp32 columns whose rows are not aligned to 16 bytes, and more
+    of them around them."""
+    rp, ci, val = matrix(n, mean, kind, n)
+    for m, ldw, a in [(8, 9, 1), (9, 27, 9), (12, 12 * 3 + 1, 3), (13, 13, 0), (16, 48, 33), (16, 17, 1), (17, 17, 0), (31, 31, 0)]:
+        print("csr misaligned f32", n, mean, kind, m, ldw, a, flush=True)
+        ldw = max(ldw, a + m)
+        W = torch.randn((n, ldw), generator=gen(m), device="cuda", dtype=torch.float64).float()
+        Y = torch.full((n, ldw), 5.0, dtype=torch.float32, device="cuda")
+        s = P.Solver(n)
+        s.set_operator_csr(rp, ci, val)
+        s.set_option(P.OPT_PRECISION, P.PREC_FP32)
+        s.ensure_workspace(1)
+        P.lobpcg_apply_operator_f32(s.h, W[:, a : a + m], Y[:, a : a + m])
+        check(rp, ci, val, W[:, a : a + m], Y[:, a : a + m], 2.0**-24)
+        assert bool((Y[:, :a] == 5.0).all()) and bool((Y[:, a + m :] == 5.0).all())  # other columns untouched
+        s.close()
