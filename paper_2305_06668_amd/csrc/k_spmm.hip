@@ -13,6 +13,7 @@
 // XCD b % 8) walks one contiguous range of rows: a banded matrix then keeps
 // its W window inside that XCD's L2.
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 #include "internal.h"
@@ -197,22 +198,20 @@ __device__ __forceinline__ T stream_load(const T* p) {
 // together without rows or sums 230 to 270 us; the product takes 355.
 
 // k_spmm_block: a workgroup takes 256 / G consecutive rows and copies their
-// range of entries to LDS (coalesced), kBlockLds bytes at a time, between
-// barriers; nothing is in flight across them, but eight workgroups share a CU
-// (with 32 KB four to five do: n = 1e6, 3 to 50 fp64 entries per row 93 to 360
-// us, so 66 to 343).
-constexpr int kBlockLds = 16 * 1024;
+// range of entries to LDS (coalesced), `cap` entries at a time (block_lds),
+// between barriers; nothing is in flight across them, but six to eight
+// workgroups share a CU.
 template <typename TV, typename TW, int G, int CPL, bool BIG, bool NT>
 __global__ __launch_bounds__(256) void k_spmm_block(const int32_t* __restrict__ rp,
                                                     const int32_t* __restrict__ ci,
                                                     const TV* __restrict__ val,
                                                     const TW* __restrict__ W, int64_t ldw,
                                                     TW* __restrict__ Y, int64_t ldy, int ncols,
-                                                    int64_t n, int per_xcd) {
+                                                    int64_t n, int per_xcd, unsigned cap) {
   typedef typename Vec16<TW, CPL>::type VT;
   constexpr int RPB = 256 / G;
-  constexpr unsigned CAP = kBlockLds / sizeof(Entry<TW>);
-  __shared__ Entry<TW> E[CAP];
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  Entry<TW>* E = reinterpret_cast<Entry<TW>*>(lds);
   const int b = blockIdx.x;
   const int lb = (b & 7) * per_xcd + (b >> 3);
   const int64_t r0 = (int64_t)lb * RPB;
@@ -232,8 +231,8 @@ __global__ __launch_bounds__(256) void k_spmm_block(const int32_t* __restrict__ 
   VT acc;
 #pragma unroll
   for (int q = 0; q < CPL; ++q) acc[q] = TW(0);
-  for (unsigned p = 0; p < total; p += CAP) {
-    const unsigned cnt = min(CAP, total - p);
+  for (unsigned p = 0; p < total; p += cap) {
+    const unsigned cnt = min(cap, total - p);
     const int32_t* cp = ci + B0 + (int64_t)p;
     const TV* vp = val + B0 + (int64_t)p;
     __syncthreads();  // the previous pass is consumed
@@ -262,7 +261,7 @@ __global__ __launch_bounds__(256) void k_spmm_block(const int32_t* __restrict__ 
 // compiler waits for the loads of one where it goes on with the other: rows that
 // all fit took 3 to 15 % longer.)
 constexpr int kRowCap = 48, kRowPass = 44;
-constexpr int64_t kCacheBytes = 256ll << 20;  // the memory-side cache
+constexpr int64_t kCacheBytes = 280000000;  // the memory-side cache, 268, and a little that passes
 constexpr int kRowsWaves(int G) { return G == 4 ? 3 : 4; }  // workgroups per CU: their registers and LDS
 template <typename TV, typename TW, int G, int CPL, bool BIG, bool NT>
 __global__ __launch_bounds__(256)
@@ -458,7 +457,26 @@ void k_spmm_rows(const int32_t* __restrict__ rp, const int32_t* __restrict__ ci,
 //   * Products that the waves on the chip take in one step (nothing to balance,
 //     all latency; n = 20000, 16 fp64 columns, 41 entries 11 : 9, 96 30 : 20),
 //     and of longer rows also those that the cache holds (n = 80000, 96 entries
-//     82 : 60), which do not wait for HBM.
+//     82 : 60; 32 columns, n = 1e5, 100 entries 107 : 111, 140 160 : 151; 32 fp32
+//     columns, n = 6e4, 150 62 : 62, 170 84 : 69), which do not wait for HBM.
+
+// LDS of a workgroup of k_spmm_block, of `blocks`, whose rows have `entries`
+// entries of `size` bytes on average: 20 KB, with which eight workgroups just
+// share a CU; 26 where that saves a pass and the grid is many rounds or one; 16
+// where the passes are as many and it is one, or they are nearly full, or the
+// grid is two rounds (fp64, n = 3e5 or 4e5, 16 / 20 / 26 KB: 24 columns, 70
+// entries per row 368 / 311 / 328 us, 80 403 / 344 / 354, 90 338 / 341 / 304, 110
+// 416 / 381 / 392; 16 columns, 64 185 / 196 / 201, 80 256 / 212 / 244, 100 268 /
+// 240 / 222; n = 6e4, 50 27 / 29; 32 fp32 columns, n = 1e6, 3 72 / 78).
+static unsigned block_lds(double entries, int size, int64_t blocks) {
+  auto passes = [&](int kb) { return std::ceil(entries * size / (kb * 1024.0)); };
+  const bool few = blocks <= 12 * 256;
+  if ((!few || blocks <= 6 * 256) && passes(26) < passes(20)) return 26 * 1024;
+  if (passes(16) == passes(20) && (few || passes(16) <= 1 || entries * size > 0.9 * 16384 * passes(16)))
+    return 16 * 1024;
+  return 20 * 1024;
+}
+
 template <typename TV, typename TW, int G>
 static hipError_t spmm_stream_launch(const int32_t* rp, const int32_t* ci, const TV* val, const TW* W,
                                      int64_t ldw, TW* Y, int64_t ldy, int ncols, int64_t n,
@@ -475,7 +493,8 @@ static hipError_t spmm_stream_launch(const int32_t* rp, const int32_t* ci, const
   // passes: the matrix, W and Y, or what the caller names.  (One product after
   // another, 16 columns, with : without the hint: n = 1e6, 8 fp64 entries per row,
   // 356 MB 102 : 111 us; fp32 the same 192 MB 68 : 51, 16 entries 260 MB 114 : 84,
-  // 20 entries 292 MB 136 : 138.  Whole fp64 solves of 41 entries per row, 12
+  // 20 entries 292 MB 136 : 138; n = 2e5, 80 fp64 entries, 24 columns 269 MB 169 :
+  // 203, 32 columns 294 MB 212 : 205.  Whole fp64 solves of 41 entries per row, 12
   // columns: n = 1e5, 164 MB with the bases 9.50 : 9.40 ms; 2e5, 328 MB 14.04 :
   // 14.52; 3e5 29.6 : 30.0.)
   const int64_t product = 2 * n * ncols * (int64_t)sizeof(TW);
@@ -487,25 +506,28 @@ static hipError_t spmm_stream_launch(const int32_t* rp, const int32_t* ci, const
   // last one uneven: 23 fp32 columns, n = 7e4, 41 entries per row 27 : 29 us)
   const bool waves = (groups <= 16 * 256 && mean >= 14) || (mean >= lo && mean <= 45.5) ||
                      (G == 8 && groups > 6000 && groups <= 9400 && mean > 20 && mean <= 45.5) ||
-                     (F64 && G <= 8 && mean > 56 && !nt) || mean > hi;
-  auto launch = [&](auto kernel, int64_t nb, int64_t units) {
+                     (!nt && ((F64 && mean > (G <= 8 ? 56 : groups <= 9400 ? 75 : 105)) || (G == 8 && mean > 155) ||
+                              (groups <= 9400 && mean > 160))) ||
+                     mean > hi;
+  auto launch = [&](auto kernel, int64_t nb, int64_t units, unsigned lds, auto... more) {
     const unsigned grid = (unsigned)((nb + 7) / 8 * 8);
-    hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, s, rp, ci, val, W, ldw, Y, ldy, ncols, n,
-                       (int)((units + 7) / 8));
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), lds, s, rp, ci, val, W, ldw, Y, ldy, ncols, n,
+                       (int)((units + 7) / 8), more...);
     return hipGetLastError();
   };
   if (waves) {
     // a persistent grid, a multiple of the 8 XCDs: four workgroups per CU, three
     // where a wave takes 16 rows (their registers and LDS)
     const int64_t nb = std::min<int64_t>((groups + 3) / 4, 256 * kRowsWaves(G));
-    if (big) return launch(k_spmm_rows<TV, TW, G, CPL, true, true>, nb, groups);
-    if (nt) return launch(k_spmm_rows<TV, TW, G, CPL, false, true>, nb, groups);
-    return launch(k_spmm_rows<TV, TW, G, CPL, false, false>, nb, groups);
+    if (big) return launch(k_spmm_rows<TV, TW, G, CPL, true, true>, nb, groups, 0);
+    if (nt) return launch(k_spmm_rows<TV, TW, G, CPL, false, true>, nb, groups, 0);
+    return launch(k_spmm_rows<TV, TW, G, CPL, false, false>, nb, groups, 0);
   }
   const int64_t nb = (n + RPB - 1) / RPB;
-  if (big) return launch(k_spmm_block<TV, TW, G, CPL, true, true>, nb, nb);
-  if (nt) return launch(k_spmm_block<TV, TW, G, CPL, false, true>, nb, nb);
-  return launch(k_spmm_block<TV, TW, G, CPL, false, false>, nb, nb);
+  const unsigned lds = block_lds(mean * RPB, sizeof(Entry<TW>), nb), cap = lds / (unsigned)sizeof(Entry<TW>);
+  if (big) return launch(k_spmm_block<TV, TW, G, CPL, true, true>, nb, nb, lds, cap);
+  if (nt) return launch(k_spmm_block<TV, TW, G, CPL, false, true>, nb, nb, lds, cap);
+  return launch(k_spmm_block<TV, TW, G, CPL, false, false>, nb, nb, lds, cap);
 }
 
 // ---- banded matrices: W staged in LDS, slab by slab ----

@@ -166,3 +166,24 @@ def test_csr_misaligned_f32(P, n, mean, kind):
         check(rp, ci, val, W[:, a : a + m], Y[:, a : a + m], 2.0**-24)
         assert bool((Y[:, :a] == 5.0).all()) and bool((Y[:, a + m :] == 5.0).all())  # other columns untouched
         s.close()
+
+
+@pytest.mark.parametrize("f32", [False, True])
+@pytest.mark.parametrize("n,mean,kind", [(60_000, 3, "even"), (50_000, 50, "even"), (200_003, 52, "uneven"), (30_001, 80, "even"), (100_003, 64, "even"), (100_003, 100, "few"), (30_001, 300, "even")])
+def test_csr_passes(P, n, mean, kind, f32):
+    """Each size of the workgroups' LDS, one pass and several, and longer rows of
+    products that the cache holds."""
+    rp, ci, val = matrix(n, mean, kind, n)
+    for m in (6, 12, 16, 32, 64):
+        print("csr passes", n, mean, kind, f32, m, flush=True)
+        W = torch.randn((n, m), generator=gen(m), device="cuda", dtype=torch.float64)
+        W = W.float() if f32 else W
+        Y = torch.full((n, m), 5.0, dtype=W.dtype, device="cuda")
+        s = P.Solver(n)
+        s.set_operator_csr(rp, ci, val)
+        if f32:
+            s.set_option(P.OPT_PRECISION, P.PREC_FP32)
+        s.ensure_workspace(1)
+        (P.lobpcg_apply_operator_f32 if f32 else P.lobpcg_apply_operator)(s.h, W, Y)
+        check(rp, ci, val, W, Y, 2.0**-24 if f32 else 2.0**-53)
+        s.close()
