@@ -6,7 +6,7 @@
 // place of the starting block moves the eigenvalues in the first digit after
 // five iterations), so its operations keep their order, and what a few
 // iterations give, and what is trained on it, stays as it was, bit for bit.
-// 48 x 48 with all vectors: 550 us by k_small_rr's steps, 150 us here.
+// 48 x 48 with all vectors: 550 us by k_small_rr's steps, 147 us here.
 #include "small.h"
 
 namespace lobpcg {

@@ -34,7 +34,7 @@ static inline int cdiv(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 // What bounds it: the read of A, once for up to 16 columns (n = 2e4 fp64: 630
 // us = 5.1 TB/s, where a plain sum reads 6.0; 8 columns at a time by scalar
 // products, eight rows per wave: 664 us for 8, 1330 for 16); at small n the
-// latency of a wave's few chunks (n = 2000, 13 columns: 14 us; 70 before, as
+// latency of a wave's few chunks (n = 2000, 13 columns: 15 us; 65 before, as
 // 63 workgroups and a packing pass for each 8 columns).  Chunks of 64 columns,
 // a contiguous range per wave and the non-temporal hint were all slower (the
 // hint 790 against 656 us, and A of up to 256 MB is read again from the

@@ -438,8 +438,8 @@ void k_spmm_rows(const int32_t* __restrict__ rp, const int32_t* __restrict__ ci,
 }
 
 // The two kernels above, G lanes to a row, by the mean number of entries per row
-// (the matrices measured have 4e7 entries or 1e6 rows, lengths +- 11 %; us,
-// k_spmm_block : k_spmm_rows).
+// (the matrices measured have 4e7 entries or 1e6 rows, lengths +- 11 %; us, with
+// 16 KB of LDS k_spmm_block : k_spmm_rows).
 //   * Rows that mostly fit kRowCap: k_spmm_rows, whose loads overlap its gathers
 //     (fp64, 16 columns: 27 entries 233 : 229, 41 343 : 315, 45 343 : 330, 47
 //     341 : 404; 8 columns: 16 entries 127 : 115, 41 297 : 244; fp32, 16
